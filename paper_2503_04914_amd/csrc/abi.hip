@@ -164,10 +164,15 @@ mskm_status mskm_create(int32_t device, void* hip_stream, mskm_ctx** out) {
     }
     c->own_stream = true;
   }
+  int ncu = 0;
+  if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) ncu = 0;
+  c->ncu = std::min(ncu, 256);
   if (hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->ev1) != hipSuccess ||
+      hipEventCreateWithFlags(&c->ev_grid, hipEventDisableTiming) != hipSuccess ||
       hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) != hipSuccess) {
     if (c->ev0) (void)hipEventDestroy(c->ev0);
     if (c->ev1) (void)hipEventDestroy(c->ev1);
+    if (c->ev_grid) (void)hipEventDestroy(c->ev_grid);
     mskm::ctx_trim(c);
   if (c->own_stream) (void)hipStreamDestroy(c->stream);
     delete c;
@@ -188,6 +193,8 @@ mskm_status mskm_destroy(mskm_ctx* c) {
   c->batch_cache.clear();
   (void)hipEventDestroy(c->ev0);
   (void)hipEventDestroy(c->ev1);
+  mskm::cg_grid_forget(c);
+  (void)hipEventDestroy(c->ev_grid);
   if (c->side) {
     (void)hipStreamSynchronize(c->side);
     (void)hipStreamDestroy(c->side);
@@ -363,6 +370,7 @@ mskm_status mskm_hier_destroy(mskm_hier* h) {
       (void)hipEventDestroy(e);
     }
   if (h->solve_ws_free) h->solve_ws_free(h->solve_ws);
+  if (h->cg_grid_free) h->cg_grid_free(h->cg_grid);
   for (mskm_trunc* t : h->truncs) t->h = nullptr;  // they keep their own memory until destroyed
   for (size_t i = 0; i < h->allocs.size(); ++i) mskm::ctx_release(h->ctx, h->allocs[i], h->alloc_bytes[i]);
   for (size_t i = 0; i < h->stage_blocks.size(); ++i)

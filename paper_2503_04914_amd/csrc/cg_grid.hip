@@ -1,0 +1,651 @@
+// CG on one or more middle-sized levels in one launch (x0 = 0): textbook
+// conjugate gradients (Theorem cg), plain or with the cell block-Jacobi
+// preconditioner, with every workgroup of the levels on the GPU at once and
+// every matrix entry, inverse entry and vector of its rows held on its CU.
+//
+// What bounds a level of 10^3 .. 10^5 rows is not its bytes but the chain of
+// dependent steps of an iteration: as separate launches it took two to five
+// kernels of 3-6 us each (the preconditioned FP32 form 12 us, the textbook
+// FP64 form 17 us an iteration on 16,384 rows). Here an iteration is two
+// exchanges between the level's workgroups, about 1.5 us each, plus the work
+// on rows that never leave the CU.
+//
+// Exchange without a barrier or a cache flush: every workgroup stores its
+// partial sums into a slot of its own with device-coherent (agent scope)
+// stores, and every workgroup polls all slots of its level with
+// device-coherent loads until each holds something other than kEmptySlot, a
+// bit pattern that no stored value has. The polled words carry the data, so
+// nothing has to be ordered before them. Direction entries a workgroup needs
+// from its neighbours travel the same way: each publishes z of its rows and
+// polls the entries of z it needs (its halo). Agent-scope fences, which write
+// back and invalidate a whole XCD's L2, are not used. Measured: 1.4 / 1.5 /
+// 2.0 us an exchange for 64 / 128 / 256 workgroups with slots 64 bytes apart
+// (2.3 / 2.8 / 3.3 us with adjacent slots; a counter barrier with fences 3.4 /
+// 5.5 / 10.4 us).
+//
+// Reuse of the buffers: exchanges alternate A (r.r, r.z, with the halo of z)
+// and B (p.q); each kind has two buffers used in turn. Words of A's buffer n
+// are emptied after B(n) was received (everybody has left A(n)), words of B's
+// buffer n after A(n+1) was received, a z buffer after B(n) was received. All
+// stores of a workgroup are waited for before it publishes the next B, so
+// whoever has received that B sees the emptied words, and polls that buffer
+// again only later.
+//
+// Waiting: every poll loop ends after `spin` polls. A workgroup that gives up
+// sets *aborted and leaves, the others then give up the same way, and the
+// caller solves the levels by the launched kernels instead. All workgroups of
+// a launch must be on the GPU together: at most one per CU is launched, and
+// launches of this kernel from different streams of the process are ordered
+// one after the other (another kernel only delays the start).
+#include <algorithm>
+#include <mutex>
+#include <vector>
+
+#include "cg_state.h"
+#include "device_common.h"
+
+namespace mskm {
+
+constexpr int kGridThreads = 512;
+constexpr int kGridE = 64;          // matrix entries per lane kept in registers (at most)
+constexpr int kGridLocal = 4096;    // direction entries per workgroup: its rows and its halo
+constexpr int kGridSlot = 8;        // 64-byte slots
+constexpr int64_t kGridLevelRows = 131072;  // column bitmap of the plan: 16 KiB of LDS
+
+__device__ constexpr uint64_t kEmptySlot = 0x7ff4deadbeef0001ull;  // signalling NaN patterns: arithmetic never
+__device__ constexpr uint32_t kEmptyWord = 0x7fa4beefu;            // produces them (results are quieted)
+
+// Levels that can be solved this way with 512 / lanes rows per workgroup:
+// workgroup w of level l takes `per` consecutive blocks of the level's
+// work table (64-row blocks, or the preconditioner's workgroups of whole blocks).
+struct CgGridDev {
+  int32_t nwg = 0;
+  int32_t* wg0 = nullptr;           // device [L + 1]
+  int32_t* lev = nullptr;           // [nwg]
+  int32_t* row0 = nullptr;          // [nwg] first row
+  int32_t* nrow = nullptr;          // [nwg]
+  int32_t* nhalo = nullptr;         // [nwg]
+  int32_t* halo = nullptr;          // [nwg][kGridLocal] rows of the halo, ascending
+  uint16_t* lidx = nullptr;         // [nwg][kGridE][kGridThreads] position of each entry's column
+  int32_t* stats = nullptr;         // [2 L] h_local, h_row
+  uint64_t* slots = nullptr;        // [4][nwg][kGridSlot]: A and B, two buffers each
+};
+struct CgGridPlan {
+  bool built = false;
+  std::vector<int32_t> h_wg0;       // [L + 1] first workgroup of each level
+  std::vector<int32_t> h_local;     // [L] most direction entries of one of its workgroups
+  std::vector<int32_t> h_row;       // [L] longest row
+  CgGridDev d;
+};
+
+struct CgGrid {
+  CgGridPlan plan[2][2];  // [block-Jacobi][lanes per row 2, 1]
+};
+
+static void cg_grid_free(void* p) { delete static_cast<CgGrid*>(p); }
+
+// --------------------------------------------------------------------- plan
+
+// One workgroup per planned workgroup: its halo (columns of
+// its rows outside its rows, ascending) by a bitmap over the level, and each
+// entry's position in the workgroup's direction vector (own rows first, then
+// the halo), laid out by the registers that will hold the entries.
+__global__ void __launch_bounds__(kGridThreads)
+    k_grid_plan(const CgGridDev P, int L, int lanes, int per, const DevLevel* __restrict__ lev, const WorkTable wt,
+                const int64_t* __restrict__ rp, const int32_t* __restrict__ col) {
+  constexpr int kWords = (int)(kGridLevelRows / 32);
+  constexpr int kPer = kWords / kGridThreads;  // bitmap words per thread in the scan
+  __shared__ uint32_t bits[kWords];
+  __shared__ uint32_t rank[kWords];
+  __shared__ uint32_t ws[kGridThreads / kWave];
+  __shared__ int maxlen;
+  const int wg = blockIdx.x, t = threadIdx.x;
+  const int l = P.lev[wg];
+  const int64_t off = lev[l].off;
+  const int b0 = wt.lev_begin[l] + (wg - P.wg0[l]) * per;
+  const int b1 = min(b0 + per, wt.lev_begin[l + 1]);
+  const int64_t r0 = wt.row0[b0];
+  const int nr = (int)(wt.row1[b1 - 1] - r0);
+  for (int w = t; w < kWords; w += kGridThreads) bits[w] = 0;
+  if (t == 0) maxlen = 0;
+  __syncthreads();
+  const int64_t e0 = rp[r0], e1 = rp[r0 + nr];
+  for (int64_t k = e0 + t; k < e1; k += kGridThreads) {
+    const int64_t c = col[k];
+    if (c < r0 || c >= r0 + nr) atomicOr(&bits[(c - off) >> 5], 1u << ((c - off) & 31));
+  }
+  __syncthreads();
+  // rank[w] = set bits before word w
+  uint32_t sum = 0;
+  for (int q = 0; q < kPer; ++q) sum += __popc(bits[t * kPer + q]);
+  uint32_t inc = sum;
+  for (int o = 1; o < kWave; o <<= 1) {
+    const uint32_t v = __shfl_up(inc, o, kWave);
+    if (t % kWave >= o) inc += v;
+  }
+  if (t % kWave == kWave - 1) ws[t / kWave] = inc;
+  __syncthreads();
+  uint32_t base = inc - sum, total = 0;
+  for (int w = 0; w < kGridThreads / kWave; ++w) {
+    if (w < t / kWave) base += ws[w];
+    total += ws[w];
+  }
+  for (int q = 0; q < kPer; ++q) {
+    const int w = t * kPer + q;
+    rank[w] = base;
+    base += __popc(bits[w]);
+  }
+  __syncthreads();
+  for (int w = t; w < kWords; w += kGridThreads) {
+    uint32_t m = bits[w];
+    int pos = (int)rank[w];
+    while (m) {
+      const int b = __ffs(m) - 1;
+      m &= m - 1;
+      if (pos < kGridLocal) P.halo[(size_t)wg * kGridLocal + pos] = (int32_t)(off + 32 * w + b);
+      ++pos;
+    }
+  }
+  const int i = t / lanes, g = t % lanes;
+  int len = 0;
+  if (i < nr) {
+    const int64_t s = rp[r0 + i], e = rp[r0 + i + 1];
+    len = (int)min<int64_t>(e - s, INT32_MAX);
+    for (int k = 0; k < kGridE; ++k) {
+      const int64_t q = s + g + (int64_t)k * lanes;
+      if (q >= e) break;
+      const int64_t c = col[q];
+      int p;
+      if (c >= r0 && c < r0 + nr) {
+        p = (int)(c - r0);
+      } else {
+        const int64_t d = c - off;
+        p = nr + (int)(rank[d >> 5] + __popc(bits[d >> 5] & ((1u << (d & 31)) - 1u)));
+      }
+      P.lidx[((size_t)wg * kGridE + k) * kGridThreads + t] = (uint16_t)min(p, kGridLocal - 1);
+    }
+  }
+  atomicMax(&maxlen, len);
+  __syncthreads();
+  if (t == 0) {
+    P.row0[wg] = (int32_t)r0;
+    P.nrow[wg] = nr;
+    P.nhalo[wg] = (int32_t)min(total, (uint32_t)kGridLocal);
+    atomicMax(&P.stats[l], nr + (int)total);
+    atomicMax(&P.stats[L + l], maxlen);
+  }
+}
+
+static mskm_status build_plan(mskm_hier* h, CgGridPlan& P, bool bj, int lanes) {
+  const int L = h->L;
+  const WorkTable& wt = bj ? h->bj.wt : h->wt_spmv;
+  // the preconditioner's workgroups hold at most 256 rows on levels of up to kGridLevelRows
+  const int per = bj ? (lanes == 2 ? 1 : 2) : kGridThreads / lanes / 64;
+  CgGridDev& D = P.d;
+  P.h_wg0.assign(L + 1, 0);
+  P.h_local.assign(L, 0);
+  P.h_row.assign(L, 0);
+  std::vector<int32_t> lev;
+  const int nd = (int)h->h_depth_begin.size() - 1;
+  for (int d = 0; d < nd; ++d) {  // depths whose levels fit the GPU together
+    const int l0 = h->h_depth_begin[d], l1 = h->h_depth_begin[d + 1];
+    int64_t tot = 0, rows = 0;
+    for (int l = l0; l < l1; ++l) {
+      tot += (wt.h_lev_begin[l + 1] - wt.h_lev_begin[l] + per - 1) / per;
+      rows = std::max<int64_t>(rows, h->h_lev[l].n);
+    }
+    const bool in = tot <= h->ctx->ncu && rows <= kGridLevelRows;
+    for (int l = l0; l < l1; ++l) {
+      P.h_wg0[l] = (int32_t)lev.size();
+      const int nw = (wt.h_lev_begin[l + 1] - wt.h_lev_begin[l] + per - 1) / per;
+      for (int w = 0; in && w < nw; ++w) lev.push_back(l);
+    }
+  }
+  P.h_wg0[L] = (int32_t)lev.size();
+  const size_t n = lev.size();
+  if (n == 0) return MSKM_OK;
+  MSKM_TRY(halloc(h, &D.wg0, (size_t)L + 1));
+  MSKM_TRY(halloc(h, &D.lev, n));
+  MSKM_TRY(halloc(h, &D.row0, n));
+  MSKM_TRY(halloc(h, &D.nrow, n));
+  MSKM_TRY(halloc(h, &D.nhalo, n));
+  MSKM_TRY(halloc(h, &D.halo, n * kGridLocal));
+  MSKM_TRY(halloc(h, &D.lidx, n * kGridE * kGridThreads));
+  MSKM_TRY(halloc(h, &D.stats, 2 * (size_t)L));
+  MSKM_TRY(halloc(h, &D.slots, 4 * n * kGridSlot));
+  hipStream_t s = h->ctx->stream;
+  MSKM_TRY(upload_async(h, D.wg0, P.h_wg0.data(), P.h_wg0.size() * 4));
+  MSKM_TRY(upload_async(h, D.lev, lev.data(), n * 4));
+  MSKM_HIP_TRY(hipMemsetAsync(D.stats, 0, 2 * (size_t)L * 4, s));
+  D.nwg = (int32_t)n;
+  hipLaunchKernelGGL(k_grid_plan, dim3(D.nwg), dim3(kGridThreads), 0, s, D, L, lanes, per, h->d_lev, wt,
+                     h->diag.rowptr, h->diag.col);
+  std::vector<int32_t> st(2 * (size_t)L);
+  MSKM_HIP_TRY(hipMemcpyAsync(st.data(), D.stats, st.size() * 4, hipMemcpyDeviceToHost, s));
+  MSKM_HIP_TRY(hipStreamSynchronize(s));
+  P.h_local.assign(st.begin(), st.begin() + L);
+  P.h_row.assign(st.begin() + L, st.end());
+  return MSKM_OK;
+}
+
+// Workgroups of levels lo..hi in this plan, 0 when one of them cannot be
+// solved this way (not planned, a row or a halo too long) or they do not fit
+// the GPU together.
+static int plan_workgroups(const mskm_hier* h, const CgGridPlan& P, int lanes, int lo, int hi) {
+  for (int l = lo; l <= hi; ++l)
+    if (P.h_wg0[l + 1] == P.h_wg0[l] || P.h_row[l] > lanes * kGridE || P.h_local[l] > kGridLocal) return 0;
+  const int n = P.h_wg0[hi + 1] - P.h_wg0[lo];
+  return n <= h->ctx->ncu ? n : 0;
+}
+
+mskm_status cg_grid_ready(mskm_hier* h, int lo, int hi, bool bj, int* lanes) {
+  *lanes = 0;
+  if (h->N >= INT32_MAX) return MSKM_OK;
+  for (int l = lo; l <= hi; ++l)
+    if (h->h_lev[l].n > kGridLevelRows || h->h_lev[l].n <= 0) return MSKM_OK;
+  if (!h->cg_grid) {
+    auto* g = new (std::nothrow) CgGrid();
+    if (!g) return MSKM_OK;
+    h->cg_grid = g;
+    h->cg_grid_free = cg_grid_free;
+  }
+  CgGrid& g = *static_cast<CgGrid*>(h->cg_grid);
+  // 256 rows per workgroup, two lanes a row, as long as the workgroups are at
+  // most one per CU; else 512 rows, one lane a row
+  for (int k = 0; k < 2; ++k) {
+    CgGridPlan& P = g.plan[bj ? 1 : 0][k];
+    const int ln = k == 0 ? 2 : 1;
+    if (!P.built) {
+      P.built = true;
+      const mskm_status st = build_plan(h, P, bj, ln);
+      if (st == MSKM_ENOMEM) {  // no room for the plan: these levels stay launched
+        P.h_wg0.assign(h->L + 1, 0);
+      } else if (st < 0) {
+        return st;
+      }
+    }
+    if (plan_workgroups(h, P, ln, lo, hi) > 0) {
+      *lanes = ln;
+      return MSKM_OK;
+    }
+  }
+  return MSKM_OK;
+}
+
+// -------------------------------------------------------------------- solve
+
+// lane-crossing moves within 16 lanes
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;                 // quad permutations
+constexpr int kDppHalfMirror = 0x141, kDppMirror = 0x140;       // within 8 and 16 lanes
+template <int G, typename T>
+__device__ __forceinline__ T lanes_sum(T v) {  // over G (a power of two, at most 16) neighbouring lanes
+  if constexpr (G >= 2) v += dpp<kDppXor1>(v);
+  if constexpr (G >= 4) v += dpp<kDppXor2>(v);
+  if constexpr (G >= 8) v += dpp<kDppHalfMirror>(v);
+  if constexpr (G >= 16) v += dpp<kDppMirror>(v);
+  return v;
+}
+__device__ __forceinline__ double readlane_f64(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+__device__ __forceinline__ double wave64_sum(double v) {
+  v = lanes_sum<16>(v);
+  return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
+}
+
+// Device-coherent words. A value whose bits are the empty pattern (it can
+// only be a signalling NaN from the caller's data) is published quieted.
+__device__ __forceinline__ uint32_t word_of(float v) {
+  const uint32_t b = __float_as_uint(v);
+  return b == kEmptyWord ? b | 0x00400000u : b;
+}
+__device__ __forceinline__ uint64_t word_of(double v) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  return b == kEmptySlot ? b | 0x0008000000000000ull : b;
+}
+__device__ __forceinline__ float value_of(uint32_t b) { return __uint_as_float(b); }
+__device__ __forceinline__ double value_of(uint64_t b) { return __longlong_as_double((long long)b); }
+template <typename T>
+struct GridWord;
+template <>
+struct GridWord<float> {
+  using type = uint32_t;
+  static constexpr uint32_t empty = kEmptyWord;
+};
+template <>
+struct GridWord<double> {
+  using type = uint64_t;
+  static constexpr uint64_t empty = kEmptySlot;
+};
+template <typename W>
+__device__ __forceinline__ void put(W* p, W v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename W>
+__device__ __forceinline__ W get(const W* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The word at p once it is there; *bad after `spin` further polls.
+template <typename W>
+__device__ __forceinline__ W poll(const W* p, W empty, int spin, int* bad) {
+  W u = get(p);
+  for (int k = 0; u == empty && k < spin; ++k) u = get(p);
+  if (u == empty) *bad = 1;
+  return u;
+}
+
+// The row's z = M^-1 r from rs: this lane's share of the inverse row, in
+// registers (N of them) or read through the caches (N = 1).
+template <int G, int N, typename TX>
+__device__ __forceinline__ TX grid_precond(const TX (&iv)[N], const TX* Mi, int bm, const TX* rb, int g) {
+  TX a = 0;
+  if constexpr (N > 1) {
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      if (g + k * G < bm) a += iv[k] * rb[g + k * G];
+  } else {
+    for (int j = g; j < bm; j += G) a += Mi[j] * rb[j];
+  }
+  return lanes_sum<G>(a);
+}
+
+// Empties z0, z1 on the rows [r0, r0 + n) and every slot of the plan.
+template <typename TX>
+__global__ void __launch_bounds__(kBlock)
+    k_grid_empty(typename GridWord<TX>::type* __restrict__ z0, typename GridWord<TX>::type* __restrict__ z1,
+                 int64_t r0, int64_t n, uint64_t* __restrict__ slots, int64_t ns, int32_t* __restrict__ aborted) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i < n) {
+    z0[r0 + i] = GridWord<TX>::empty;
+    z1[r0 + i] = GridWord<TX>::empty;
+  }
+  if (i < ns) slots[i] = kEmptySlot;
+  if (i == 0) *aborted = 0;
+}
+
+// G lanes per row, 512 / G rows per workgroup, at most E matrix entries per
+// lane. Thread t holds entries g, g + G, ... of row t / G (g = t % G) and the
+// row's share of its block inverse; all G lanes of a row hold its x, r, p, z.
+template <typename TX, bool PC, int G, int E>
+__global__ void __launch_bounds__(kGridThreads)
+    k_cg_grid(const CgGridDev P, int wgb, const DevLevel* __restrict__ lev, const int64_t* __restrict__ rp,
+              const TX* __restrict__ val, const TX* __restrict__ b, TX* __restrict__ x,
+              typename GridWord<TX>::type* z0, typename GridWord<TX>::type* z1, CgLevel* __restrict__ st,
+              int32_t* aborted, double rtol2, int maxit, int spin, const PcArgs<TX> pc) {
+  using W = typename GridWord<TX>::type;
+  constexpr int RW = kGridThreads / G;
+  constexpr int kWaves = kGridThreads / kWave;
+  constexpr int kH = kGridLocal / kGridThreads;  // halo entries per thread
+  constexpr bool kInvRegs = PC && sizeof(TX) == 4;
+  constexpr int kI = kInvRegs ? kBjMax / G : 1;
+  __shared__ TX pw[kGridLocal];    // direction: own rows, then the halo
+  __shared__ int32_t hrow[kGridLocal];  // rows of the halo
+  __shared__ TX rs[PC ? RW : 1];   // residual of the own rows
+  __shared__ double sm[2][kWaves], sp[kWaves];
+  __shared__ int bad;
+  const int wg = wgb + blockIdx.x, t = threadIdx.x, w = t / kWave, lane = t % kWave;
+  const int l = P.lev[wg], w0 = P.wg0[l], nw = P.wg0[l + 1] - w0;
+  const int r0 = P.row0[wg], nr = P.nrow[wg], nh = P.nhalo[wg];
+  const int i = t / G, g = t % G;
+  const bool mine = i < nr, first = mine && g == 0;
+  const int64_t row = r0 + (mine ? i : 0);
+  // slot of workgroup wg0 + q of the level in buffer k: slot + (k * nslot + q) * kGridSlot
+  uint64_t* const slotA = P.slots + (size_t)w0 * kGridSlot;
+  uint64_t* const slotB = slotA + (size_t)2 * P.nwg * kGridSlot;
+  const int me = wg - w0, nslot = P.nwg;
+
+  // matrix entries (past the row's end: value 0 at position 0)
+  TX v[E];
+  uint32_t ci[E / 2];
+  int len;
+  {
+    const int64_t s = rp[row], e = rp[row + 1];
+    len = mine ? (int)(e - s) : 0;
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+      const int q = g + k * G;
+      v[k] = q < len ? val[s + q] : (TX)0;
+      const uint32_t c = q < len ? P.lidx[((size_t)wg * kGridE + k) * kGridThreads + t] : 0u;
+      if (k & 1)
+        ci[k / 2] |= c << 16;
+      else
+        ci[k / 2] = c;
+    }
+  }
+  int kmax = (len + G - 1) / G;  // entries per lane of the wave's longest row
+  for (int o = 32; o > 0; o >>= 1) kmax = max(kmax, __shfl_xor(kmax, o, kWave));
+  kmax = __builtin_amdgcn_readfirstlane(kmax);
+  // block inverse: entries g, g + G, ... of the row
+  int ba = 0, bm = 0;
+  const TX* Mi = nullptr;
+  TX iv[kI];
+  if constexpr (PC) {
+    if (mine) {
+      const int32_t bk = pc.of_row[row];
+      const int64_t a = pc.start[bk];
+      bm = (int)(pc.start[bk + 1] - a);
+      ba = (int)(a - r0);
+      Mi = pc.inv + pc.off[bk] + (row - a) * bm;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < kI; ++k) iv[k] = kInvRegs && g + k * G < bm ? Mi[g + k * G] : (TX)0;
+
+  TX xi = 0, ri = mine ? b[row] : (TX)0, pi = 0, zi;
+  for (int q = t; q < nr + nh; q += kGridThreads) pw[q] = (TX)0;
+  if (t == 0) bad = 0;
+  if constexpr (PC) {
+    if (first) rs[i] = ri;
+    __syncthreads();
+    zi = grid_precond<G, kI, TX>(iv, Mi, bm, rs + ba, g);
+  } else {
+    zi = ri;
+  }
+  // halo entries t, t + kGridThreads, ... are the thread's; their rows stay in LDS
+  for (int q = t; q < nh; q += kGridThreads) hrow[q] = P.halo[(size_t)wg * kGridLocal + q];
+
+  double rzold = 0.0, bb = 0.0, rr = 0.0;
+  int n = 0, capped = 0;
+  for (;; ++n) {
+    W* const zc = n & 1 ? z1 : z0;
+    W* const zp = n & 1 ? z0 : z1;
+    // publish z, then (exchange A) r.r and r.z
+    if (first) {
+      put(&zc[row], word_of(zi));
+      if (n > 0) put(&zp[row], GridWord<TX>::empty);
+    }
+    double a = first ? (double)ri * (double)ri : 0.0, c = first ? (double)ri * (double)zi : 0.0;
+    a = wave64_sum(a);
+    c = wave64_sum(c);
+    if (lane == 0) {
+      sm[0][w] = a;
+      sm[1][w] = c;
+    }
+    __syncthreads();
+    if (w < 2) {
+      const double s = lanes_sum<kWaves>(sm[w][lane % kWaves]);
+      if (lane == 0) put(slotA + ((n & 1) * nslot + me) * kGridSlot + w, word_of(s));
+    }
+    // the halo of z and the level's sums, whichever comes first
+    W hz[kH];
+#pragma unroll
+    for (int q = 0; q < kH; ++q) hz[q] = t + q * kGridThreads < nh ? get(&zc[hrow[t + q * kGridThreads]]) : (W)0;
+    a = 0.0;
+    if (t % 256 < nw)
+      a = value_of(poll(slotA + ((n & 1) * nslot + t % 256) * kGridSlot + t / 256, kEmptySlot, spin, &bad));
+#pragma unroll
+    for (int q = 0; q < kH; ++q)
+      if (hz[q] == GridWord<TX>::empty) hz[q] = poll(&zc[hrow[t + q * kGridThreads]], GridWord<TX>::empty, spin, &bad);
+    a = wave64_sum(a);
+    if (lane == 0) sp[w] = a;
+    __syncthreads();
+    if (bad) break;
+    if (t == 0 && n > 0) put(slotB + (((n + 1) & 1) * nslot + me) * kGridSlot, kEmptySlot);
+    rr = (sp[0] + sp[1]) + (sp[2] + sp[3]);
+    const double rz = (sp[4] + sp[5]) + (sp[6] + sp[7]);
+    if (n == 0) bb = rr;
+    const bool conv = isfinite(rr) && !(rr > rtol2 * bb);
+    if (conv || !isfinite(rr) || !(rz > 0.0) || !isfinite(rz) || n >= maxit) {
+      capped = conv ? 0 : 1;
+      break;
+    }
+    // direction on the own rows and the halo
+    const TX beta = n == 0 ? (TX)0 : (TX)(rz / rzold);
+    rzold = rz;
+    pi = zi + beta * pi;
+    if (first) pw[i] = pi;
+#pragma unroll
+    for (int q = 0; q < kH; ++q)
+      if (t + q * kGridThreads < nh) {
+        const int at = nr + t + q * kGridThreads;
+        pw[at] = value_of(hz[q]) + beta * pw[at];
+      }
+    __syncthreads();
+    TX q = 0;
+#pragma unroll
+    for (int k0 = 0; k0 < E; k0 += 8)
+      if (k0 < kmax) {
+#pragma unroll
+        for (int k = k0; k < k0 + 8; ++k) q += v[k] * pw[k & 1 ? ci[k / 2] >> 16 : ci[k / 2] & 0xffffu];
+      }
+    q = lanes_sum<G>(q);
+    // exchange B: p.q (every earlier store of this workgroup is waited for first)
+    a = wave64_sum(first ? (double)pi * (double)q : 0.0);
+    if (lane == 0) sm[0][w] = a;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (w == 0) {
+      const double s = lanes_sum<kWaves>(sm[0][lane % kWaves]);
+      if (lane == 0) put(slotB + ((n & 1) * nslot + me) * kGridSlot, word_of(s));
+    }
+    a = 0.0;
+    if (t < 256 && t < nw) a = value_of(poll(slotB + ((n & 1) * nslot + t) * kGridSlot, kEmptySlot, spin, &bad));
+    if (w < 4) {
+      a = wave64_sum(a);
+      if (lane == 0) sp[w] = a;
+    }
+    __syncthreads();
+    if (bad) break;
+    const double pq = (sp[0] + sp[1]) + (sp[2] + sp[3]);
+    if (!(pq > 0.0) || !isfinite(pq)) {  // cannot happen for SPD A and p != 0
+      capped = !(rr <= rtol2 * bb);
+      break;
+    }
+    if (w < 2 && lane == 0) put(slotA + ((n & 1) * nslot + me) * kGridSlot + w, kEmptySlot);
+    const double alpha = rz / pq;
+    xi = (TX)((double)xi + alpha * (double)pi);
+    ri = (TX)((double)ri - alpha * (double)q);
+    if constexpr (PC) {
+      if (first) rs[i] = ri;
+      __syncthreads();
+      zi = grid_precond<G, kI, TX>(iv, Mi, bm, rs + ba, g);
+    } else {
+      zi = ri;
+    }
+  }
+  if (bad) {
+    if (t == 0) atomicOr(aborted, 1);
+    return;
+  }
+  if (first) x[row] = xi;
+  if (t == 0 && wg == w0) {
+    CgLevel* const o = st + l;
+    o->rtol2 = rtol2;
+    o->bb = bb;
+    o->rr = rr;
+    o->maxit = maxit;
+    o->on = 1;
+    o->iters = n;
+    o->done = 1;
+    o->capped = capped;
+    o->fallback = 0;
+  }
+}
+
+// Launches of the persistent kernel on one device run one after the other:
+// two of them partly resident at the same time would wait for workgroups
+// that cannot start. `ev` is the event of the context that launched last.
+namespace {
+struct GridOrder {
+  std::mutex mu;
+  mskm_ctx* last = nullptr;
+};
+constexpr int kGridDevices = 64;
+GridOrder g_order[kGridDevices];
+}  // namespace
+
+void cg_grid_forget(mskm_ctx* c) {
+  if (c->device < 0 || c->device >= kGridDevices) return;
+  GridOrder& o = g_order[c->device];
+  std::lock_guard<std::mutex> lock(o.mu);
+  if (o.last == c) o.last = nullptr;
+}
+
+void cg_grid_set_spin(mskm_ctx* c, int spin) { c->grid_spin = spin; }
+
+template <typename TX>
+mskm_status cg_grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, const TX* val, const TX* b, TX* x,
+                           TX* z0, TX* z1, CgLevel* st, int32_t* aborted, double rtol2, int maxit,
+                           const PcArgs<TX>& pc) {
+  using W = typename GridWord<TX>::type;
+  CgGridPlan& P = static_cast<CgGrid*>(h->cg_grid)->plan[bj ? 1 : 0][lanes == 2 ? 0 : 1];
+  mskm_ctx* c = h->ctx;
+  hipStream_t s = c->stream;
+  const int w0 = P.h_wg0[lo], nw = P.h_wg0[hi + 1] - w0;
+  int longest = 0;
+  for (int l = lo; l <= hi; ++l) longest = std::max(longest, P.h_row[l]);
+  const int64_t r0 = h->h_off[lo], n = h->h_off[hi + 1] - r0, ns = (int64_t)4 * P.d.nwg * kGridSlot;
+  hipLaunchKernelGGL(k_grid_empty<TX>, dim3((unsigned)((std::max(n, ns) + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
+                     (W*)z0, (W*)z1, r0, n, P.d.slots, ns, aborted);
+  if (c->device < 0 || c->device >= kGridDevices) return fail(MSKM_ELIMIT, "device index beyond 63");
+  GridOrder& o = g_order[c->device];
+  std::lock_guard<std::mutex> lock(o.mu);
+  if (o.last && o.last != c) MSKM_HIP_TRY(hipStreamWaitEvent(s, o.last->ev_grid, 0));
+#define MSKM_GRID_LAUNCH(PCF, GG, EE)                                                                              \
+  hipLaunchKernelGGL((k_cg_grid<TX, PCF, GG, EE>), dim3(nw), dim3(kGridThreads), 0, s, P.d, w0, h->d_lev,          \
+                     h->diag.rowptr, val, b, x, (W*)z0, (W*)z1, st, aborted, rtol2, maxit, c->grid_spin, pc)
+  if (lanes == 2 && longest <= 64) {
+    if (bj)
+      MSKM_GRID_LAUNCH(true, 2, 32);
+    else
+      MSKM_GRID_LAUNCH(false, 2, 32);
+  } else if (lanes == 2) {
+    if (bj)
+      MSKM_GRID_LAUNCH(true, 2, 64);
+    else
+      MSKM_GRID_LAUNCH(false, 2, 64);
+  } else if (longest <= 48) {
+    if (bj)
+      MSKM_GRID_LAUNCH(true, 1, 48);
+    else
+      MSKM_GRID_LAUNCH(false, 1, 48);
+  } else {
+    if (bj)
+      MSKM_GRID_LAUNCH(true, 1, 64);
+    else
+      MSKM_GRID_LAUNCH(false, 1, 64);
+  }
+#undef MSKM_GRID_LAUNCH
+  MSKM_HIP_TRY(hipGetLastError());
+  MSKM_HIP_TRY(hipEventRecord(c->ev_grid, s));
+  o.last = c;
+  return MSKM_OK;
+}
+template mskm_status cg_grid_launch<float>(mskm_hier*, int, int, bool, int, const float*, const float*, float*, float*,
+                                           float*, CgLevel*, int32_t*, double, int, const PcArgs<float>&);
+template mskm_status cg_grid_launch<double>(mskm_hier*, int, int, bool, int, const double*, const double*, double*,
+                                            double*, double*, CgLevel*, int32_t*, double, int, const PcArgs<double>&);
+
+}  // namespace mskm

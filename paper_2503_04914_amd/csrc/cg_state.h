@@ -1,0 +1,51 @@
+// State and arguments shared by the CG kernels (solve.hip, cg_grid.hip).
+#pragma once
+
+#include <cstdint>
+
+#include "mskm_internal.h"
+
+namespace mskm {
+
+// Per-level solve control and state (one struct per level).
+struct CgLevel {
+  double rtol2;   // rtol^2 (host)
+  double bb;      // b.b
+  double rr;      // r.r of the current iterate
+  double alpha;   // step of the current iteration
+  double beta;    // direction coefficient for the next spmv
+  int32_t maxit;  // iteration cap (host)
+  int32_t on;     // participates (host)
+  int32_t iters;  // iterations done
+  int32_t done;   // stopped (converged, capped or broken down)
+  int32_t capped; // stopped by the cap or by non-finite data
+  int32_t fallback; // flexible CG: 0 network in use, 2 just dropped (restart), 1 dropped
+  double rr_prev;   // single-reduction form: r.r and step of the previous iteration
+  double alpha_prev;
+};
+
+// Preconditioner arguments (block-Jacobi forms).
+template <typename TX>
+struct PcArgs {
+  const int64_t* start;
+  const int32_t* of_row;
+  const int64_t* off;
+  const TX* inv;
+  TX* z;  // z = M^-1 r
+};
+
+// cg_grid.hip: the whole CG of levels lo..hi in one launch, their workgroups
+// all on the GPU at once. cg_grid_ready decides (building the plan at its
+// first use) whether these levels can take it, and with how many lanes per
+// row (0: they cannot).
+mskm_status cg_grid_ready(mskm_hier* h, int lo, int hi, bool bj, int* lanes);
+// Queues the solve A_l x_l = b_l (x0 = 0) of levels lo..hi; z0, z1: two
+// vectors of the hierarchy's length, scratch. st[l] receives the final
+// states. *aborted (device) is set, and x and st are unusable, when a
+// workgroup's wait ran out.
+template <typename TX>
+mskm_status cg_grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, const TX* val, const TX* b, TX* x,
+                           TX* z0, TX* z1, CgLevel* st, int32_t* aborted, double rtol2, int maxit,
+                           const PcArgs<TX>& pc);
+
+}  // namespace mskm

@@ -193,6 +193,9 @@ struct mskm_ctx {
   // hierarchy's finest levels are formed there while the main stream solves
   // the coarser levels
   hipStream_t side = nullptr;
+  int32_t ncu = 0;              // compute units, at most 256 (workgroups of one persistent CG launch)
+  int32_t grid_spin = 1 << 15;  // polls before a wait of that kernel is given up (about 30 ms)
+  hipEvent_t ev_grid = nullptr; // after this context's last persistent CG launch
   // device blocks of destroyed hierarchies, kept for the next allocation of
   // the same size (a hierarchy rebuilt with the same shape reuses all of
   // them without hipMalloc); at most kBlockCacheCap bytes, freed by
@@ -281,6 +284,8 @@ struct mskm_hier {
   size_t stage_used = 0;                // bytes taken from the last staging block
   int32_t* knn = nullptr;               // [N][16] same-level nearest neighbours (learned warm start)
   std::vector<mskm_trunc*> truncs;      // thresholded blocks built on this hierarchy (detached at destroy)
+  void* cg_grid = nullptr;              // plans of the persistent CG (cg_grid.hip), created at its first use
+  void (*cg_grid_free)(void*) = nullptr;
   void* solve_ws = nullptr;             // solver workspace (solve.hip), created on first solve
   void (*solve_ws_free)(void*) = nullptr;
 };
@@ -421,6 +426,12 @@ mskm_status bj_wait(mskm_hier* h, int hi);
 mskm_status bj_start_side(mskm_hier* h);
 template <typename TX>
 void launch_bj_apply(mskm_hier* h, int lo, int hi, const TX* r, TX* u);
+
+// cg_grid.hip: no later launch waits for this context's (called before its event goes)
+void cg_grid_forget(mskm_ctx* c);
+// Polls before a wait of this context's persistent launches is given up (0:
+// at the first look; for tests of the way back to the launched kernels).
+void cg_grid_set_spin(mskm_ctx* c, int spin);
 
 // solve.hip
 mskm_status apply_op(mskm_hier* h, int op, int prec, const double* x_in, int nrhs, double* y_in, bool io_dev);

@@ -14,6 +14,7 @@
 #include <cstring>
 #include <type_traits>
 
+#include "cg_state.h"
 #include "device_common.h"
 
 namespace mskm {
@@ -485,23 +486,6 @@ __global__ void __launch_bounds__(kBlock)
 // big kernels of the next phase; the kernel boundaries order and publish them.
 // Partial sums are reduced in block order: the result is deterministic.
 
-// Per-level solve control and state (one struct per level).
-struct CgLevel {
-  double rtol2;   // rtol^2 (host)
-  double bb;      // b.b
-  double rr;      // r.r of the current iterate
-  double alpha;   // step of the current iteration
-  double beta;    // direction coefficient for the next spmv
-  int32_t maxit;  // iteration cap (host)
-  int32_t on;     // participates (host)
-  int32_t iters;  // iterations done
-  int32_t done;   // stopped (converged, capped or broken down)
-  int32_t capped; // stopped by the cap or by non-finite data
-  int32_t fallback; // flexible CG: 0 network in use, 2 just dropped (restart), 1 dropped
-  double rr_prev;   // single-reduction form: r.r and step of the previous iteration
-  double alpha_prev;
-};
-
 constexpr int kRedBlock = 1024;  // threads of the per-level reduce kernels
 
 // Fixed-order block sum of part[a..e), result in thread 0.
@@ -866,16 +850,6 @@ __global__ void __launch_bounds__(kRedBlock) k_cg1_red(int lev0, const int32_t* 
   if (threadIdx.x == 0) cg1_decide(st[l], gamma, delta, rr);
 }
 
-// Preconditioner arguments of the single-reduction update (PC form).
-template <typename TX>
-struct PcArgs {
-  const int64_t* start;
-  const int32_t* of_row;
-  const int64_t* off;
-  const TX* inv;
-  TX* z;  // z = M^-1 r
-};
-
 // Single-reduction update on the block's rows: p = z + beta p; s = q + beta s
 // (= A p); x += alpha p; r -= alpha s; then (PC) z = M^-1 r for the block's
 // rows, the block being a workgroup of whole preconditioner blocks.
@@ -1194,6 +1168,10 @@ struct SolveWS {
   CgLevel* h_chk[2] = {nullptr, nullptr};  // pinned state copies of the two chunks in flight
   CgLevel* h_defer = nullptr;  // pinned final states of levels solved by one workgroup, read at the next flush
   std::vector<char> deferred;  // levels whose final state waits in h_defer
+  int32_t* aborted = nullptr;    // device: a persistent CG launch gave up (cg_grid.hip)
+  int32_t* h_aborted = nullptr;  // pinned copies of it, one per level (its lowest)
+  bool grid_failed = false;      // one of them was set: the solve is run again without these launches
+  bool grid_off = false;         // no persistent launches (that second run)
   hipEvent_t ev_defer = nullptr;  // after the last copy into h_defer
   hipEvent_t ev_chk[2] = {nullptr, nullptr};
   hipEvent_t pending = nullptr;  // copy of a speculative chunk still in flight (null: none)
@@ -1252,6 +1230,7 @@ static mskm_status get_ws(mskm_hier* h, SolveWS** out) {
     carve(&w->part_v, (size_t)h->wt_vec.nblocks, base);
     carve(&w->part_res, 2 * (size_t)h->wt_spmv.nblocks, base);
     carve(&w->st, 2 * (size_t)h->L, base);  // two parities (fused single-reduction form)
+    carve(&w->aborted, 1, base);
   };
   layout(nullptr);
   w->ctx = h->ctx;
@@ -1265,7 +1244,7 @@ static mskm_status get_ws(mskm_hier* h, SolveWS** out) {
     layout(static_cast<char*>(base));
   }
   const size_t pin_states = 4 * (size_t)h->L * sizeof(CgLevel);  // a multiple of 8 bytes
-  const size_t pin_bytes = pin_states + 2 * (size_t)h->wt_spmv.nblocks * sizeof(double);
+  const size_t pin_bytes = pin_states + 2 * (size_t)h->wt_spmv.nblocks * sizeof(double) + 4 * (size_t)h->L;
   if (st == MSKM_OK) st = mskm::ctx_host_alloc(h->ctx, pin_bytes, &w->pinned);
   if (st == MSKM_OK) w->pinned_bytes = pin_bytes;
   if (st == MSKM_OK) {
@@ -1275,6 +1254,8 @@ static mskm_status get_ws(mskm_hier* h, SolveWS** out) {
     w->h_chk[1] = ps + 2 * h->L;
     w->h_defer = ps + 3 * h->L;
     w->h_part_res = reinterpret_cast<double*>(static_cast<char*>(w->pinned) + pin_states);
+    w->h_aborted = reinterpret_cast<int32_t*>(w->h_part_res + 2 * (size_t)h->wt_spmv.nblocks);
+    std::memset(w->h_aborted, 0, 4 * (size_t)h->L);
     w->deferred.assign(h->L, 0);
   }
   for (hipEvent_t* e : {&w->ev_chk[0], &w->ev_chk[1], &w->ev_defer})
@@ -1445,8 +1426,8 @@ static mskm_status chunk_graph(mskm_hier* h, SolveWS& W, const TV* dval, int lo,
   return MSKM_OK;
 }
 
-// Adds the final states of the levels solved by one workgroup (copied into
-// h_defer behind their launch) to the statistics; waits for that copy.
+// Adds the final states of the levels solved in one launch (copied into
+// h_defer behind it) to the statistics; waits for that copy.
 static mskm_status flush_deferred(mskm_hier* h, SolveWS& W, CgStats* cs) {
   bool any = false;
   for (char d : W.deferred) any = any || d != 0;
@@ -1455,6 +1436,10 @@ static mskm_status flush_deferred(mskm_hier* h, SolveWS& W, CgStats* cs) {
   for (int l = 0; l < h->L; ++l) {
     if (!W.deferred[l]) continue;
     W.deferred[l] = 0;
+    if (W.h_aborted[l]) {
+      W.h_aborted[l] = 0;
+      W.grid_failed = true;
+    }
     const CgLevel& o = W.h_defer[l];
     cs->iters_total += o.iters;
     if (l < kMaxLevels) cs->last_iters[l] = o.iters;
@@ -1486,6 +1471,23 @@ static mskm_status cg_run(mskm_hier* h, SolveWS& W, const TV* dval, const std::v
     bool ok = form != kCgTextbook && !mlp && !warm;
     for (int l = a; l <= e && ok; ++l) ok = m[l] && h->h_lev[l].n <= kWgSolveRows;
     return ok;
+  };
+  // captures the next levels' chunk (when they are chunked) while queued work runs
+  auto capture_next = [&]() -> mskm_status {
+    if (!next_on) return MSKM_OK;
+    int nlo = 0, nhi = h->L - 1;
+    while (nlo < h->L && !(*next_on)[nlo]) ++nlo;
+    while (nhi >= 0 && !(*next_on)[nhi]) --nhi;
+    if (nlo > nhi || all_small(*next_on, nlo, nhi)) return MSKM_OK;
+    if (!mlp && !W.grid_off) {
+      int lanes = 0;
+      MSKM_TRY(cg_grid_ready(h, nlo, nhi, bj, &lanes));
+      if (lanes > 0) return MSKM_OK;
+    }
+    int Gn = h->spmv_g[MSKM_OP_DIAG][sizeof(TX) == 4 ? 1 : 0];
+    if (Gn >= 2 * kVecFlag && Gn < 3 * kVecFlag) Gn -= kVecFlag;
+    hipGraphExec_t next_exec = nullptr;
+    return chunk_graph<TV, TX>(h, W, dval, nlo, nhi, x, K, Gn, form, &next_exec);
   };
   if (all_small(on, lo, hi)) {  // one workgroup per level, all iterations in one launch, no host check
     for (int l = lo; l <= hi; ++l)
@@ -1520,20 +1522,37 @@ static mskm_status cg_run(mskm_hier* h, SolveWS& W, const TV* dval, const std::v
     MSKM_HIP_TRY(hipMemcpyAsync(W.h_defer + lo, W.st + lo, (hi - lo + 1) * sizeof(CgLevel), hipMemcpyDeviceToHost, s));
     MSKM_HIP_TRY(hipEventRecord(W.ev_defer, s));
     for (int l = lo; l <= hi; ++l) W.deferred[l] = 1;
-    // capture the next levels' chunk while the workgroups run (when they are chunked)
-    if (next_on) {
-      int nlo = 0, nhi = h->L - 1;
-      while (nlo < h->L && !(*next_on)[nlo]) ++nlo;
-      while (nhi >= 0 && !(*next_on)[nhi]) --nhi;
-      if (nlo <= nhi && !all_small(*next_on, nlo, nhi)) {
-        int Gn = h->spmv_g[MSKM_OP_DIAG][sizeof(TX) == 4 ? 1 : 0];
-        if (Gn >= 2 * kVecFlag && Gn < 3 * kVecFlag) Gn -= kVecFlag;
-        hipGraphExec_t next_exec = nullptr;
-        MSKM_TRY((chunk_graph<TV, TX>(h, W, dval, nlo, nhi, x, K, Gn, form, &next_exec)));
-      }
-    }
-    return MSKM_OK;
+    return capture_next();
   }
+  // middle levels: the whole solve in one launch of workgroups that are all
+  // on the GPU at once (cg_grid.hip)
+  if (!mlp && !warm && !W.grid_off) {
+    int lanes = 0;
+    bool all_on = true;
+    for (int l = lo; l <= hi; ++l) all_on = all_on && on[l];
+    if (all_on) MSKM_TRY(cg_grid_ready(h, lo, hi, bj, &lanes));
+    if (lanes > 0) {
+      for (int l = lo; l <= hi; ++l)
+        if (W.deferred[l]) {
+          MSKM_TRY(flush_deferred(h, W, cs));
+          break;
+        }
+      if (bj) MSKM_TRY(bj_start_side(h));
+      MSKM_TRY(cg_grid_launch<TX>(h, lo, hi, bj, lanes, dval, b, x, (TX*)W.p0, (TX*)W.p1, W.st, W.aborted,
+                                  rtol * rtol, maxit, pc_args<TX>(h, W)));
+      MSKM_HIP_TRY(
+          hipMemcpyAsync(W.h_defer + lo, W.st + lo, (hi - lo + 1) * sizeof(CgLevel), hipMemcpyDeviceToHost, s));
+      MSKM_HIP_TRY(hipMemcpyAsync(W.h_aborted + lo, W.aborted, 4, hipMemcpyDeviceToHost, s));
+      MSKM_HIP_TRY(hipEventRecord(W.ev_defer, s));
+      for (int l = lo; l <= hi; ++l) W.deferred[l] = 1;
+      return capture_next();
+    }
+  }
+  for (int l = lo; l <= hi; ++l)
+    if (on[l] && W.deferred[l]) {  // a state of this level still waits in h_defer
+      MSKM_TRY(flush_deferred(h, W, cs));
+      break;
+    }
   // the first chunked level starts the side-stream inversion of the finest
   // depth's blocks (its few-block launches leave most of the GPU free)
   if (bj) MSKM_TRY(bj_start_side(h));
@@ -1611,12 +1630,7 @@ static mskm_status cg_run(mskm_hier* h, SolveWS& W, const TV* dval, const std::v
     if (launched < max_chunks) MSKM_TRY(launch());
     if (!prepared) {  // capture the next levels' chunk while this one's two chunks run
       prepared = true;
-      int nlo = 0, nhi = h->L - 1;
-      while (nlo < h->L && !(*next_on)[nlo]) ++nlo;
-      while (nhi >= 0 && !(*next_on)[nhi]) --nhi;
-      hipGraphExec_t next_exec = nullptr;
-      if (nlo <= nhi && !all_small(*next_on, nlo, nhi))
-        MSKM_TRY((chunk_graph<TV, TX>(h, W, dval, nlo, nhi, x, K, G, form, &next_exec)));
+      MSKM_TRY(capture_next());
     }
     MSKM_HIP_TRY(hipEventSynchronize(W.ev_chk[checked & 1]));
     const CgLevel* c = W.h_chk[checked & 1];
@@ -1941,8 +1955,8 @@ static void lower_update(mskm_hier* h, const TV* lval, const TX* t, const TX* f,
 // CG on the levels below the top, then CG on D) or sequential (block forward
 // substitution, one CG per level).
 template <typename TV, typename TX>
-static mskm_status solve_internal(mskm_hier* h, SolveWS& W, const TV* dval, const TV* lval, const TX* f, TX* alpha,
-                                  const mskm_solve_opts* o, int* sweeps_done, CgStats* cs) {
+static mskm_status solve_pass(mskm_hier* h, SolveWS& W, const TV* dval, const TV* lval, const TX* f, TX* alpha,
+                              const mskm_solve_opts* o, int* sweeps_done, CgStats* cs) {
   hipStream_t s = h->ctx->stream;
   const int64_t N = h->N;
   const int L = h->L;
@@ -1998,6 +2012,22 @@ static mskm_status solve_internal(mskm_hier* h, SolveWS& W, const TV* dval, cons
   std::fill(on.begin(), on.end(), 1);
   MSKM_TRY((cg_run<TV, TX>(h, W, dval, on, beta, alpha, o->cg_rtol, maxit, prev, K, cs, prev ? nullptr : mlp, bj)));
   return flush_deferred(h, W, cs);
+}
+
+// The same, run again with launched kernels only when a persistent launch
+// gave up (its workgroups did not all get onto the GPU in time).
+template <typename TV, typename TX>
+static mskm_status solve_internal(mskm_hier* h, SolveWS& W, const TV* dval, const TV* lval, const TX* f, TX* alpha,
+                                  const mskm_solve_opts* o, int* sweeps_done, CgStats* cs) {
+  const CgStats before = *cs;
+  MSKM_TRY((solve_pass<TV, TX>(h, W, dval, lval, f, alpha, o, sweeps_done, cs)));
+  if (!W.grid_failed) return MSKM_OK;
+  W.grid_failed = false;
+  W.grid_off = true;
+  *cs = before;
+  const mskm_status st = solve_pass<TV, TX>(h, W, dval, lval, f, alpha, o, sweeps_done, cs);
+  W.grid_off = false;
+  return st;
 }
 
 // ------------------------------------------------------------- residual
@@ -2633,8 +2663,19 @@ mskm_status trunc_solve(mskm_hier* h, const Csr& X, const double* f_in, const ms
     }
     double rtol = o->cg_rtol;
     if (refine_on && rounds > 0) rtol = std::min(0.1, std::max(o->cg_rtol, 0.5 * o->target_rel_residual / rel));
+    const CgStats before = cs;
     MSKM_TRY((cg_run<double, double>(h, W, h->diag.val, on, b, nb, rtol, maxit, false, K, &cs, nullptr, bj)));
     MSKM_TRY(flush_deferred(h, W, &cs));
+    if (W.grid_failed) {  // a persistent launch gave up: the launched kernels instead
+      W.grid_failed = false;
+      W.grid_off = true;
+      cs = before;
+      const mskm_status again =
+          cg_run<double, double>(h, W, h->diag.val, on, b, nb, rtol, maxit, false, K, &cs, nullptr, bj);
+      W.grid_off = false;
+      MSKM_TRY(again);
+      MSKM_TRY(flush_deferred(h, W, &cs));
+    }
     hipLaunchKernelGGL(k_axpy64, dim3(nblk(N)), dim3(kBlock), 0, s, (const double*)nb, W.ai, N);
     ++rounds;
     MSKM_TRY(residual_internal(h, W, W.ai, W.fi, &rel, W.res));
