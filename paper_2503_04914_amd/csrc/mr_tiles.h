@@ -1,0 +1,55 @@
+// Tiles of the many-right-hand-side products (mr_tiles.hip).
+#pragma once
+
+#include <cstdint>
+
+#include "mskm_internal.h"
+
+namespace mskm {
+
+// Rows of one tile and columns of one segment of a tile's entries.
+constexpr int kTileRows = 16;
+constexpr int kTileSeg = 64;
+
+// One CSR matrix in tiles of 16 rows: tile 4 b + w holds rows 16 w .. of block
+// b of the 64-row SpMV work table. A tile lists the distinct columns of its
+// rows, ascending, padded to a multiple of 16 with its last column; its
+// entries are grouped by segments of 64 listed columns, each with its row and
+// position in the list.
+struct MrTiles {
+  int64_t ntile = 0, nseg = 0, ncol = 0, nnz = 0;
+  int64_t* cptr = nullptr;   // [ntile + 1] first listed column
+  int32_t* cols = nullptr;   // [ncol]
+  int64_t* sptr = nullptr;   // [ntile + 1] first segment
+  int64_t* eptr = nullptr;   // [nseg + 1] first entry of each segment
+  uint16_t* code = nullptr;  // [nnz] row << 7 | position % 128
+  double* val = nullptr;     // [nnz] values in tile order, as stored by the hierarchy
+  float* val32 = nullptr;
+  float* lo = nullptr;
+};
+
+// The tiles of a hierarchy's blocks, built at the first call that needs them;
+// *out is null where they are not available (a tile with more than 65536
+// columns, or no memory): the caller takes the general products.
+mskm_status mr_tiles(mskm_hier* h, bool lower, const MrTiles** out);
+
+// Right-hand sides are padded to a width that the tiles' products take: 16,
+// or a multiple of 32 (the padding solves zero systems, which stop at once).
+inline int mr_width(int nrhs) { return nrhs <= 16 ? 16 : (nrhs + 31) / 32 * 32; }
+
+// q = A p on the blocks [b0, b0 + nb) of the SpMV work table with partials p.q
+// part[block][ldr], A the diagonal blocks' tiles, p and q [N][ldr]; levels
+// with lev_done set are skipped. The right-hand sides go in slices of `chunk`
+// (the slowest launch dimension; a multiple of 64 dividing ldr, or ldr).
+template <typename TX>
+void mr_tile_cg(mskm_hier* h, const MrTiles& D, int ldr, int chunk, int b0, int nb, const TX* p, TX* q,
+                const int32_t* lev_done, double* part);
+// y = f - L x on blocks [b0, b0 + nb), L the lower blocks' tiles.
+template <typename TX>
+void mr_tile_lower(mskm_hier* h, const MrTiles& Lw, int ldr, int b0, int nb, const TX* x, const TX* f, TX* y);
+// r = f - (L + D) a in FP64 over the whole work table, partials r.r and f.f
+// [block][ldr]; rout nullable.
+void mr_tile_residual(mskm_hier* h, const MrTiles& D, const MrTiles& Lw, int ldr, const double* a, const double* f,
+                      double* rout, double* rrp, double* ffp);
+
+}  // namespace mskm

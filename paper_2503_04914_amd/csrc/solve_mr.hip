@@ -15,6 +15,7 @@
 #include <string>
 
 #include "device_common.h"
+#include "mr_tiles.h"
 
 namespace mskm {
 
@@ -41,23 +42,26 @@ static unsigned mr_nblk(int64_t n, int per) {
   return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + per - 1) / per, 1 << 30));
 }
 
-// out[i*R + r] = in[perm[i]*R + r] (input -> internal), or the inverse.
+// Caller's vectors [n][nrhs] in input order into internal order [n][R], R >=
+// nrhs (columns past nrhs are zero), and back.
 template <typename TO>
 __global__ void __launch_bounds__(kBlock) k_mr_to_internal(const double* __restrict__ in, const int32_t* __restrict__ perm,
-                                                           TO* __restrict__ out, int64_t n, int R) {
+                                                           TO* __restrict__ out, int64_t n, int nrhs, int R) {
   const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (e >= n * R) return;
-  const int64_t i = e / R, r = e % R;
-  out[e] = (TO)in[(int64_t)perm[i] * R + r];
+  const int64_t i = e / R;
+  const int r = (int)(e - i * R);
+  out[e] = r < nrhs ? (TO)in[(int64_t)perm[i] * nrhs + r] : (TO)0;
 }
 
 template <typename TI>
 __global__ void __launch_bounds__(kBlock) k_mr_to_input(const TI* __restrict__ in, const int32_t* __restrict__ perm,
-                                                        double* __restrict__ out, int64_t n, int R) {
+                                                        double* __restrict__ out, int64_t n, int nrhs, int R) {
   const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (e >= n * R) return;
-  const int64_t i = e / R, r = e % R;
-  out[(int64_t)perm[i] * R + r] = (double)in[e];
+  if (e >= n * nrhs) return;
+  const int64_t i = e / nrhs;
+  const int r = (int)(e - i * nrhs);
+  out[(int64_t)perm[i] * nrhs + r] = (double)in[i * R + r];
 }
 
 // Y[i][:] = b[i][:] + sign * (A X)[i][:] for rows [r0, r1) (b nullable).
@@ -111,21 +115,8 @@ __device__ __forceinline__ void mr_block_partial(const double* acc, const MrCfg&
 
 constexpr int kMrLds = kBlock * kMaxRPerLane;  // doubles of LDS for block partials
 
-// ---------------------------------------------------------------- wave rows
-// Fast path for R a multiple of 64: one wave per row, lane gl owns RM
-// consecutive right-hand sides gl RM .. gl RM + RM - 1 of a chunk, so a
-// gathered row of X is one RM-wide load per lane. A row's entries are read
-// 64 at a time by the lanes and broadcast with readlane, and gathered in
-// batches of eight, two batches in flight (mr_row_acc), instead of one
-// dependent chain of index load -> gather per entry. The CG product takes
-// the right-hand sides in chunks (blockIdx.y, the slowest launch dimension):
-// in chunks of 64 the rows of X the running workgroups gather are 256 bytes
-// (FP32) wide, a working set the L2 holds better. On the 1M-row Halton level,
-// 256 right-hand sides, it takes 2.70 ms in chunks of 64, 3.14 ms in chunks
-// of 128 and 3.22 ms unchunked. The lower products and the
-// residual read rows with entries in every coarser level, whose re-reading
-// per chunk costs more than the narrower gathers save (the top level's lower
-// product 1.6 ms unchunked, 2.3 ms in chunks of 64): one chunk of all R.
+// One wave per row for R a multiple of 64: lane gl owns RM consecutive
+// right-hand sides, one RM-wide load per row (block-Jacobi apply).
 inline bool mr_wave_rows(const MrCfg& c) { return c.LR == 64 && c.R == 64 * c.RM; }
 
 template <int RM, typename T>
@@ -151,60 +142,6 @@ template <>
 __device__ __forceinline__ void st_rm<1, float>(float* __restrict__ p, const float (&v)[1]) { *p = v[0]; }
 template <>
 __device__ __forceinline__ void st_rm<1, double>(double* __restrict__ p, const double (&v)[1]) { *p = v[0]; }
-
-__device__ __forceinline__ int32_t lane_bcast(int32_t v, int l) { return __builtin_amdgcn_readlane(v, l); }
-__device__ __forceinline__ float lane_bcast(float v, int l) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
-__device__ __forceinline__ double lane_bcast(double v, int l) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
-  return __hiloint2double(hi, lo);
-}
-
-// acc[m] += sum over the entries k in [s, e) of value(k) * X[col[k]][gl RM + m],
-// in entry order. value(k) returns the entry's value in the accumulation type TA.
-// The entries of a 64-entry run are taken in batches of eight gathers; the
-// next batch's gathers are issued before the current batch's products, so
-// two batches are in flight. Entry j of the run is lane j's: lanes past the
-// run's end hold value 0 and the run's last column, so no batch needs a
-// bounds branch (a batch starts below the run's end and ends at lane 63 at
-// most).
-template <int RM, typename TA, typename TX>
-__device__ __forceinline__ void mr_gather8(const TX* __restrict__ x, int64_t ldx, int gl, int32_t cl, int u,
-                                           TX (&xv)[8][RM]) {
-#pragma unroll
-  for (int q = 0; q < 8; ++q) ld_rm<RM>(x + (int64_t)lane_bcast(cl, u + q) * ldx + gl * RM, xv[q]);
-}
-template <int RM, typename TA, typename TX>
-__device__ __forceinline__ void mr_fma8(TA vl, int u, const TX (&xv)[8][RM], TA (&acc)[RM]) {
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const TA v = lane_bcast(vl, u + q);
-#pragma unroll
-    for (int m = 0; m < RM; ++m) acc[m] += v * (TA)xv[q][m];
-  }
-}
-template <int RM, typename TA, typename TX, typename ValueOf>
-__device__ __forceinline__ void mr_row_acc(int64_t s, int64_t e, const int32_t* __restrict__ col, ValueOf value,
-                                           const TX* __restrict__ x, int64_t ldx, int gl, TA (&acc)[RM]) {
-  const int lane = threadIdx.x % 64;
-  for (int64_t k0 = s; k0 < e; k0 += 64) {
-    const int n = (int)min<int64_t>(64, e - k0);
-    const int64_t k = k0 + min(lane, n - 1);
-    const int32_t cl = col[k];
-    const TA vl = lane < n ? value(k) : (TA)0;
-    const int nb = (n + 7) / 8;
-    TX xa[8][RM], xb[8][RM];
-    mr_gather8<RM, TA, TX>(x, ldx, gl, cl, 0, xa);
-    for (int b = 0; b < nb; b += 2) {
-      if (b + 1 < nb) mr_gather8<RM, TA, TX>(x, ldx, gl, cl, 8 * (b + 1), xb);
-      mr_fma8<RM, TA, TX>(vl, 8 * b, xa, acc);
-      if (b + 2 < nb) mr_gather8<RM, TA, TX>(x, ldx, gl, cl, 8 * (b + 2), xa);
-      if (b + 1 < nb) mr_fma8<RM, TA, TX>(vl, 8 * (b + 1), xb, acc);
-    }
-  }
-}
 
 // Block partials for the wave-row mapping: acc[m] belongs to rhs c0 + gl RM
 // + m of the chunk of 64 RM right-hand sides starting at c0; part[blk][ldr].
@@ -521,114 +458,6 @@ __global__ void __launch_bounds__(kBlock)
   }
 }
 
-// Wave-row forms of the CG product, the SpMM and the FP64 residual (R = 64 RM).
-// The CG product takes the right-hand sides in chunks of 64 RM (blockIdx.y,
-// the slowest launch dimension): the rows of P that the running workgroups
-// gather are then 64 RM wide, a working set the L2 holds.
-template <int RM, typename TV, typename TX>
-__global__ void __launch_bounds__(kBlock)
-    k_mr_cg_spmm_w(const WorkTable wt, int base, const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
-                   const TV* __restrict__ val, const TX* __restrict__ p, TX* __restrict__ q,
-                   const int32_t* __restrict__ lev_done, double* __restrict__ pqp, int ldr) {
-  __shared__ double sm[kMrLds];
-  const int blk = base + xcd_block_id(gridDim.x);
-  const int l = wt.lev[blk];
-  if (lev_done[l]) return;
-  const int gl = threadIdx.x % 64;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-  const int c0 = (int)blockIdx.y * 64 * RM;
-  double part[RM];
-#pragma unroll
-  for (int m = 0; m < RM; ++m) part[m] = 0.0;
-  for (int64_t i = wt.row0[blk] + w; i < wt.row1[blk]; i += kBlock / 64) {
-    TX acc[RM];
-#pragma unroll
-    for (int m = 0; m < RM; ++m) acc[m] = 0;
-    mr_row_acc<RM, TX, TX>(rp[i], rp[i + 1], col, [&](int64_t k) { return (TX)val[k]; }, p + c0, ldr, gl, acc);
-    TX pi[RM];
-    ld_rm<RM>(p + i * ldr + c0 + gl * RM, pi);
-    st_rm<RM>(q + i * ldr + c0 + gl * RM, acc);
-#pragma unroll
-    for (int m = 0; m < RM; ++m) part[m] += (double)pi[m] * (double)acc[m];
-  }
-  mr_block_partial_w<RM>(part, sm, pqp, blk, ldr, c0);
-}
-
-// Y[i][:] = b[i][:] + sign (A X)[i][:] for rows [r0, r1) (b nullable), one
-// wave per row, the right-hand sides in chunks of 64 RM (blockIdx.y; the
-// caller launches one chunk of all R).
-template <int RM, typename TV, typename TX>
-__global__ void __launch_bounds__(kBlock)
-    k_mr_spmm_w(const int64_t* __restrict__ rp, const int32_t* __restrict__ col, const TV* __restrict__ val,
-                const TX* __restrict__ x, const TX* __restrict__ b, TX* __restrict__ y, TX sign, int64_t r0,
-                int64_t r1, int ldr) {
-  const int gl = threadIdx.x % 64;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-  const int c0 = (int)blockIdx.y * 64 * RM;
-  const int64_t waves = (int64_t)gridDim.x * (kBlock / 64);
-  for (int64_t i = r0 + (int64_t)blockIdx.x * (kBlock / 64) + w; i < r1; i += waves) {
-    TX acc[RM];
-#pragma unroll
-    for (int m = 0; m < RM; ++m) acc[m] = 0;
-    mr_row_acc<RM, TX, TX>(rp[i], rp[i + 1], col, [&](int64_t k) { return (TX)val[k]; }, x + c0, ldr, gl, acc);
-    const int64_t o = i * ldr + c0 + gl * RM;
-    TX bi[RM];
-    if (b) ld_rm<RM>(b + o, bi);
-#pragma unroll
-    for (int m = 0; m < RM; ++m) acc[m] = (b ? bi[m] : (TX)0) + sign * acc[m];
-    st_rm<RM>(y + o, acc);
-  }
-}
-
-// FP64 residual, one wave per row, the right-hand sides in chunks of 64 RM
-// (blockIdx.y): values stored FP64, else FP32 plus the FP32 remainder;
-// partials rr[blk][r], ff[blk][r].
-template <int RM>
-__global__ void __launch_bounds__(kBlock)
-    k_mr_residual_w(const WorkTable wt, const int64_t* __restrict__ drp, const int32_t* __restrict__ dc,
-                    const double* __restrict__ dv, const int64_t* __restrict__ lrp, const int32_t* __restrict__ lc,
-                    const double* __restrict__ lv, const float* __restrict__ dh, const float* __restrict__ dl,
-                    const float* __restrict__ lh, const float* __restrict__ ll, const double* __restrict__ a,
-                    const double* __restrict__ f, double* __restrict__ rout, double* __restrict__ rrp,
-                    double* __restrict__ ffp, int ldr) {
-  __shared__ double sm[kMrLds];
-  const int blk = xcd_block_id(gridDim.x);
-  const int gl = threadIdx.x % 64;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-  const int c0 = (int)blockIdx.y * 64 * RM;
-  double prr[RM], pff[RM];
-#pragma unroll
-  for (int m = 0; m < RM; ++m) prr[m] = pff[m] = 0.0;
-  for (int64_t i = wt.row0[blk] + w; i < wt.row1[blk]; i += kBlock / 64) {
-    double acc[RM];
-#pragma unroll
-    for (int m = 0; m < RM; ++m) acc[m] = 0.0;
-    const double* ac = a + c0;
-    if (dv)
-      mr_row_acc<RM, double, double>(drp[i], drp[i + 1], dc, [&](int64_t k) { return dv[k]; }, ac, ldr, gl, acc);
-    else
-      mr_row_acc<RM, double, double>(drp[i], drp[i + 1], dc,
-                                     [&](int64_t k) { return (double)dh[k] + (double)dl[k]; }, ac, ldr, gl, acc);
-    if (lv)
-      mr_row_acc<RM, double, double>(lrp[i], lrp[i + 1], lc, [&](int64_t k) { return lv[k]; }, ac, ldr, gl, acc);
-    else
-      mr_row_acc<RM, double, double>(lrp[i], lrp[i + 1], lc,
-                                     [&](int64_t k) { return (double)lh[k] + (double)ll[k]; }, ac, ldr, gl, acc);
-    const int64_t o = i * ldr + c0 + gl * RM;
-    double fi[RM];
-    ld_rm<RM>(f + o, fi);
-#pragma unroll
-    for (int m = 0; m < RM; ++m) {
-      acc[m] = fi[m] - acc[m];
-      prr[m] += acc[m] * acc[m];
-      pff[m] += fi[m] * fi[m];
-    }
-    if (rout) st_rm<RM>(rout + o, acc);
-  }
-  mr_block_partial_w<RM>(prr, sm, rrp, blk, ldr, c0);
-  mr_block_partial_w<RM>(pff, sm, ffp, blk, ldr, c0);
-}
-
 // Per-level sums of block partials part[b][R] -> out[l][R] (grid: levels x
 // chunks of 64 right-hand sides; fixed order).
 __global__ void __launch_bounds__(kMrRedThreads) k_mr_level_sums(const int32_t* __restrict__ lev_begin,
@@ -823,6 +652,7 @@ namespace {
 
 struct MrWS {
   MrCfg c{};
+  const MrTiles *D = nullptr, *Lw = nullptr;  // tiles of the blocks (null: row by row)
   size_t NR = 0;
   double *fi = nullptr, *ai = nullptr, *res = nullptr;
   void *beta = nullptr, *t = nullptr, *r = nullptr, *p = nullptr, *q = nullptr, *f32 = nullptr, *a32 = nullptr;
@@ -853,49 +683,28 @@ __global__ void __launch_bounds__(kBlock) k_mr_fill(T* __restrict__ v, int64_t n
 }
 
 // q = A p with the partials p.q per (block, rhs) over the blocks [b0, b0 + nb)
-// of the SpMV work table (the CG product of every running level). For R a
-// multiple of 64 the right-hand sides go in chunks of `chunk` (64, 128, 256
-// or 512, dividing R).
+// of the SpMV work table (the CG product of every running level): on the
+// diagonal blocks' tiles D, the right-hand sides in chunks of `chunk` where
+// that divides R; without tiles row by row.
 template <typename TV, typename TX>
-static void launch_mr_cg_product(mskm_hier* h, const MrCfg& c, int chunk, int b0, int nb, const TV* dval,
-                                 const TX* p, TX* q, const int32_t* lev_done, double* part) {
-  hipStream_t s = h->ctx->stream;
-  const WorkTable& ws = h->wt_spmv;
-  const int64_t* drp = h->diag.rowptr;
-  const int32_t* dcl = h->diag.col;
-  if (!mr_wave_rows(c)) {
-    hipLaunchKernelGGL((k_mr_cg_spmm<TV, TX>), dim3(nb), dim3(kBlock), 0, s, ws, b0, drp, dcl, dval, p, q, lev_done,
-                       part, c);
-    return;
-  }
-  const dim3 grid(nb, c.R / chunk);
-  switch (chunk / 64) {
-#define MSKM_MR_CGP_W(RMV)                                                                                      \
-  case RMV:                                                                                                    \
-    hipLaunchKernelGGL((k_mr_cg_spmm_w<RMV, TV, TX>), grid, dim3(kBlock), 0, s, ws, b0, drp, dcl, dval, p, q,  \
-                       lev_done, part, c.R);                                                                   \
-    break;
-    MSKM_MR_CGP_W(2)
-    MSKM_MR_CGP_W(4)
-    MSKM_MR_CGP_W(8)
-#undef MSKM_MR_CGP_W
-    default:
-      hipLaunchKernelGGL((k_mr_cg_spmm_w<1, TV, TX>), dim3(nb, c.R / 64), dim3(kBlock), 0, s, ws, b0, drp, dcl, dval,
-                         p, q, lev_done, part, c.R);
-  }
+static void launch_mr_cg_product(mskm_hier* h, const MrTiles* D, const MrCfg& c, int chunk, int b0, int nb,
+                                 const TV* dval, const TX* p, TX* q, const int32_t* lev_done, double* part) {
+  if (nb <= 0) return;
+  if (D)
+    mr_tile_cg<TX>(h, *D, c.R, chunk, b0, nb, p, q, lev_done, part);
+  else
+    hipLaunchKernelGGL((k_mr_cg_spmm<TV, TX>), dim3(nb), dim3(kBlock), 0, h->ctx->stream, h->wt_spmv, b0,
+                       h->diag.rowptr, h->diag.col, dval, p, q, lev_done, part, c);
 }
 
 // Chunk width of the CG product for this R: the fastest of the candidates
 // (64, 128, 256, 512 dividing R) timed once per hierarchy, R and precision on
 // its largest level, then kept (the timing overwrites q and the partials,
-// which the solve rewrites). Staging each 64-row block's distinct columns of
-// P in LDS instead (sorted lists, one byte per entry for its position) ran
-// at half the speed of the chunked gathers: the 48-64 KB of LDS per
-// workgroup leave two or three workgroups per CU.
+// which the solve rewrites).
 template <typename TV, typename TX>
-static int mr_chunk_for(mskm_hier* h, const MrCfg& c, const TV* dval, const TX* p, TX* q, double* part,
-                        const int32_t* zeros) {
-  if (!mr_wave_rows(c) || c.R / 64 > 8) return 64;
+static int mr_chunk_for(mskm_hier* h, const MrTiles* D, const MrCfg& c, const TV* dval, const TX* p, TX* q,
+                        double* part, const int32_t* zeros) {
+  if (!D || c.R % 64) return c.R;
   int32_t& slot = h->mr_chunk[c.R / 64 - 1][sizeof(TX) == 4 ? 1 : 0];
   if (slot > 0) return slot;
   int big = 0;  // the largest level (a solve's first call may run only the coarsest)
@@ -908,10 +717,10 @@ static int mr_chunk_for(mskm_hier* h, const MrCfg& c, const TV* dval, const TX* 
   float best_ms = 0.f;
   for (int ch = 64; ch <= std::min(c.R, 512); ch *= 2) {
     if (c.R % ch) continue;
-    launch_mr_cg_product<TV, TX>(h, c, ch, b0, nb, dval, p, q, zeros, part);  // warm
+    launch_mr_cg_product<TV, TX>(h, D, c, ch, b0, nb, dval, p, q, zeros, part);  // warm
     float ms = 0.f;
     if (hipEventRecord(h->ctx->ev0, s) != hipSuccess) return 64;
-    for (int k = 0; k < 2; ++k) launch_mr_cg_product<TV, TX>(h, c, ch, b0, nb, dval, p, q, zeros, part);
+    for (int k = 0; k < 2; ++k) launch_mr_cg_product<TV, TX>(h, D, c, ch, b0, nb, dval, p, q, zeros, part);
     if (hipEventRecord(h->ctx->ev1, s) != hipSuccess || hipEventSynchronize(h->ctx->ev1) != hipSuccess ||
         hipEventElapsedTime(&ms, h->ctx->ev0, h->ctx->ev1) != hipSuccess)
       return 64;
@@ -995,7 +804,7 @@ mskm_status mr_cg(mskm_hier* h, MrWS& W, const TV* dval, const std::vector<char>
   double* rzp = pc ? W.part_z : nullptr;
   // chunk width of the product (timed at the first solve with this R; levels all running)
   hipLaunchKernelGGL(k_mr_fill<int32_t>, dim3(mr_nblk(h->L, kBlock)), dim3(kBlock), 0, s, W.lev_done, (int64_t)h->L, 0);
-  const int chunk = mr_chunk_for<TV, TX>(h, c, dval, p, q, W.part_s, W.lev_done);
+  const int chunk = mr_chunk_for<TV, TX>(h, W.D, c, dval, p, q, W.part_s, W.lev_done);
   if (vbn > 0)
     hipLaunchKernelGGL(k_mr_init<TX>, dim3(vbn), dim3(kBlock), 0, s, wv, vb0, b, x, r, p, W.st, W.part_v, c);
   if (pc) bj_apply(nullptr);
@@ -1010,7 +819,7 @@ mskm_status mr_cg(mskm_hier* h, MrWS& W, const TV* dval, const std::vector<char>
       if (vbn > 0)
         hipLaunchKernelGGL(k_mr_dir<TX>, dim3(vbn), dim3(kBlock), 0, s, wv, vb0, pc ? (const TX*)z : (const TX*)r, p,
                            W.st, W.lev_done, c);
-      if (sbn > 0) launch_mr_cg_product<TV, TX>(h, c, chunk, sb0, sbn, dval, p, q, W.lev_done, W.part_s);
+      if (sbn > 0) launch_mr_cg_product<TV, TX>(h, W.D, c, chunk, sb0, sbn, dval, p, q, W.lev_done, W.part_s);
       hipLaunchKernelGGL(k_mr_red_a, rgrid, dim3(kMrRedThreads), 0, s, lo, ws.lev_begin, W.part_s, W.st, W.lev_done,
                          c);
       if (vbn > 0)
@@ -1060,36 +869,24 @@ mskm_status mr_cg(mskm_hier* h, MrWS& W, const TV* dval, const std::vector<char>
   return MSKM_OK;
 }
 
+// y = f - (T - D) t on the levels l0 .. l1 - 1.
 template <typename TV, typename TX>
-void mr_lower(mskm_hier* h, const TV* lval, const TX* t, const TX* f, TX* y, int64_t r0, int64_t r1, const MrCfg& c) {
+void mr_lower(mskm_hier* h, const MrWS& W, const TV* lval, const TX* t, const TX* f, TX* y, int l0, int l1) {
+  const int64_t r0 = h->h_off[l0], r1 = h->h_off[l1];
   if (r1 <= r0) return;
-  const dim3 grid(mr_nblk(r1 - r0, kBlock / c.LR));
-  hipStream_t s = h->ctx->stream;
-  const int64_t* rp = h->lower.rowptr;
-  const int32_t* cl = h->lower.col;
-  // all right-hand sides in one chunk: the lower rows are long (all coarser
-  // levels), and re-reading them per chunk of 64 costs more than it saves
-  switch (mr_wave_rows(c) && c.RM <= 8 && (c.RM & (c.RM - 1)) == 0 ? c.RM : 0) {
-#define MSKM_MR_SPMM_W(RMV)                                                                                       \
-  case RMV:                                                                                                      \
-    hipLaunchKernelGGL((k_mr_spmm_w<RMV, TV, TX>), grid, dim3(kBlock), 0, s, rp, cl, lval, t, f, y, (TX)-1, r0, r1, \
-                       c.R);                                                                                     \
-    break;
-    MSKM_MR_SPMM_W(1)
-    MSKM_MR_SPMM_W(2)
-    MSKM_MR_SPMM_W(4)
-    MSKM_MR_SPMM_W(8)
-#undef MSKM_MR_SPMM_W
-    default:
-      hipLaunchKernelGGL((k_mr_spmm<TV, TX>), grid, dim3(kBlock), 0, s, rp, cl, lval, t, f, y, (TX)-1, r0, r1, c);
+  if (W.Lw) {
+    const std::vector<int32_t>& lb = h->wt_spmv.h_lev_begin;
+    mr_tile_lower<TX>(h, *W.Lw, W.c.R, lb[l0], lb[l1] - lb[l0], t, f, y);
+    return;
   }
+  hipLaunchKernelGGL((k_mr_spmm<TV, TX>), dim3(mr_nblk(r1 - r0, kBlock / W.c.LR)), dim3(kBlock), 0, h->ctx->stream,
+                     h->lower.rowptr, h->lower.col, lval, t, f, y, (TX)-1, r0, r1, W.c);
 }
 
 template <typename TV, typename TX>
 mskm_status mr_solve_internal(mskm_hier* h, MrWS& W, const TV* dval, const TV* lval, const TX* f, TX* alpha,
                               const mskm_solve_opts* o, int* sweeps_done, MrStats* ms) {
   hipStream_t s = h->ctx->stream;
-  const MrCfg c = W.c;
   const int L = h->L;
   TX* beta = (TX*)W.beta;
   TX* t = (TX*)W.t;
@@ -1102,7 +899,7 @@ mskm_status mr_solve_internal(mskm_hier* h, MrWS& W, const TV* dval, const TV* l
     const int D = (int)h->h_depth_begin.size() - 1;
     for (int d = 0; d < D; ++d) {
       const int l0 = h->h_depth_begin[d], l1 = h->h_depth_begin[d + 1];
-      mr_lower<TV, TX>(h, lval, alpha, f, beta, h->h_off[l0], h->h_off[l1], c);
+      mr_lower<TV, TX>(h, W, lval, alpha, f, beta, l0, l1);
       std::fill(on.begin(), on.end(), 0);
       for (int l = l0; l < l1; ++l) on[l] = 1;
       MSKM_TRY((mr_cg<TV, TX>(h, W, dval, on, beta, alpha, o->cg_rtol, maxit, K, ms)));
@@ -1117,7 +914,7 @@ mskm_status mr_solve_internal(mskm_hier* h, MrWS& W, const TV* dval, const TV* l
   for (int l = 0; l < L; ++l) on[l] = h->h_next[l] >= 0;
   for (int sw = 0; sw < S && Lmax > 1; ++sw) {
     MSKM_TRY((mr_cg<TV, TX>(h, W, dval, on, beta, t, o->cg_rtol, maxit, K, ms)));
-    mr_lower<TV, TX>(h, lval, t, f, beta, 0, h->N, c);
+    mr_lower<TV, TX>(h, W, lval, t, f, beta, 0, L);
     *sweeps_done = sw + 1;
   }
   std::fill(on.begin(), on.end(), 1);
@@ -1136,23 +933,11 @@ mskm_status mr_residual(mskm_hier* h, MrWS& W, const double* a, const double* f,
   if (a_zero) {
     hipLaunchKernelGGL(k_mr_residual_zero, grid, dim3(kBlock), 0, s, wt, f, rout, W.part_s, W.part_v2, c);
   } else {
-    // one chunk (the rows span every level; see mr_lower)
-    switch (mr_wave_rows(c) && c.RM <= 8 && (c.RM & (c.RM - 1)) == 0 ? c.RM : 0) {
-#define MSKM_MR_RES_W(RMV)                                                                                          \
-  case RMV:                                                                                                        \
-    hipLaunchKernelGGL(k_mr_residual_w<RMV>, grid, dim3(kBlock), 0, s, wt, D.rowptr, D.col, D.val, Lw.rowptr,      \
-                       Lw.col, Lw.val, D.val32, D.val32lo, Lw.val32, Lw.val32lo, a, f, rout, W.part_s, W.part_v2,  \
-                       c.R);                                                                                       \
-    break;
-      MSKM_MR_RES_W(1)
-      MSKM_MR_RES_W(2)
-      MSKM_MR_RES_W(4)
-      MSKM_MR_RES_W(8)
-#undef MSKM_MR_RES_W
-      default:
-        hipLaunchKernelGGL(k_mr_residual, grid, dim3(kBlock), 0, s, wt, D.rowptr, D.col, D.val, Lw.rowptr, Lw.col,
-                           Lw.val, D.val32, D.val32lo, Lw.val32, Lw.val32lo, a, f, rout, W.part_s, W.part_v2, c);
-    }
+    if (W.D && W.Lw)
+      mr_tile_residual(h, *W.D, *W.Lw, c.R, a, f, rout, W.part_s, W.part_v2);
+    else
+      hipLaunchKernelGGL(k_mr_residual, grid, dim3(kBlock), 0, s, wt, D.rowptr, D.col, D.val, Lw.rowptr, Lw.col,
+                         Lw.val, D.val32, D.val32lo, Lw.val32, Lw.val32lo, a, f, rout, W.part_s, W.part_v2, c);
   }
   // per-level sums on the device (part_v holds 2 L R doubles), then per group on the host
   const size_t LR = (size_t)h->L * c.R;
@@ -1196,7 +981,10 @@ mskm_status set_mr_chunk(mskm_hier* h, int R, int prec, int chunk) {
 template <typename TV, typename TX>
 static mskm_status time_mr_product_t(mskm_hier* h, const TV* dval, int level, int R, int repeats, float* avg_ms) {
   hipStream_t s = h->ctx->stream;
-  const MrCfg c = mr_cfg(R);
+  const MrCfg c = mr_cfg(mr_width(R));
+  R = c.R;
+  const MrTiles* D = nullptr;
+  MSKM_TRY(mr_tiles(h, false, &D));
   const WorkTable& ws = h->wt_spmv;
   const int b0 = ws.h_lev_begin[level], nb = ws.h_lev_begin[level + 1] - b0;
   const size_t NR = (size_t)h->N * R;
@@ -1210,11 +998,11 @@ static mskm_status time_mr_product_t(mskm_hier* h, const TV* dval, int level, in
   if (st == MSKM_OK) {
     hipLaunchKernelGGL(k_mr_fill<TX>, dim3(mr_nblk((int64_t)NR, kBlock)), dim3(kBlock), 0, s, p, (int64_t)NR, (TX)1);
     hipLaunchKernelGGL(k_mr_fill<int32_t>, dim3(mr_nblk(h->L, kBlock)), dim3(kBlock), 0, s, done, (int64_t)h->L, 0);
-    const int chunk = mr_chunk_for<TV, TX>(h, c, dval, (const TX*)p, q, part, done);
+    const int chunk = mr_chunk_for<TV, TX>(h, D, c, dval, (const TX*)p, q, part, done);
     float ms = 0.f;
     if (hipEventRecord(h->ctx->ev0, s) != hipSuccess) st = fail(MSKM_EDEVICE, "event record");
     for (int k = 0; st == MSKM_OK && k < repeats; ++k)
-      if (nb > 0) launch_mr_cg_product<TV, TX>(h, c, chunk, b0, nb, dval, p, q, done, part);
+      if (nb > 0) launch_mr_cg_product<TV, TX>(h, D, c, chunk, b0, nb, dval, p, q, done, part);
     if (st == MSKM_OK && (hipEventRecord(h->ctx->ev1, s) != hipSuccess || hipEventSynchronize(h->ctx->ev1) != hipSuccess ||
                           hipEventElapsedTime(&ms, h->ctx->ev0, h->ctx->ev1) != hipSuccess))
       st = fail(MSKM_EDEVICE, "event timing");
@@ -1251,10 +1039,12 @@ mskm_status lagrange_columns(mskm_hier* h, int l, int64_t n0, int R, double rtol
   hipStream_t s = h->ctx->stream;
   const int64_t nl = h->h_off[l + 1] - h->h_off[l];
   const int nr = (int)std::max<int64_t>(0, std::min<int64_t>(R, nl - n0));
+  if (R != mr_width(R)) return fail(MSKM_EINVAL, "lagrange_columns: R must be 16 or a multiple of 32");
   MrWS W;
   W.c = mr_cfg(R);
   W.NR = (size_t)h->N * R;
   const size_t NR = W.NR;
+  MSKM_TRY(mr_tiles(h, false, &W.D));
   MSKM_TRY(dalloc(&W.fi, NR));
   for (void** v : {&W.r, &W.p, &W.q}) MSKM_TRY(dalloc(reinterpret_cast<char**>(v), NR * 8));
   const size_t nbp = (size_t)std::max(h->wt_spmv.nblocks, h->wt_vec.nblocks) * R;
@@ -1286,9 +1076,12 @@ mskm_status solve_multi(mskm_hier* h, const double* f_in, int nrhs, const mskm_s
   const bool mixed = o->precision == MSKM_PREC_FP32;
   if (mixed ? !h->diag.val32 : !h->diag.val) return fail(MSKM_ESTATE, "requested precision's values are not stored");
   MrWS W;
-  W.c = mr_cfg(nrhs);
-  W.NR = (size_t)h->N * nrhs;
-  const size_t NR = W.NR;
+  W.c = mr_cfg(mr_width(nrhs));
+  const int R = W.c.R;  // right-hand sides with padding
+  W.NR = (size_t)h->N * R;
+  const size_t NR = W.NR, NU = (size_t)h->N * nrhs;  // internal vectors, the caller's
+  MSKM_TRY(mr_tiles(h, false, &W.D));
+  MSKM_TRY(mr_tiles(h, true, &W.Lw));
   for (double** v : {&W.fi, &W.ai}) MSKM_TRY(dalloc(v, NR));
   if (mixed) MSKM_TRY(dalloc(&W.res, NR));
   const size_t xs = mixed ? 4 : 8;
@@ -1303,19 +1096,19 @@ mskm_status solve_multi(mskm_hier* h, const double* f_in, int nrhs, const mskm_s
     MSKM_TRY(dalloc(reinterpret_cast<float**>(&W.f32), NR));
     MSKM_TRY(dalloc(reinterpret_cast<float**>(&W.a32), NR));
   }
-  const size_t nbp = (size_t)std::max(h->wt_spmv.nblocks, h->wt_vec.nblocks) * nrhs;
+  const size_t nbp = (size_t)std::max(h->wt_spmv.nblocks, h->wt_vec.nblocks) * R;
   MSKM_TRY(dalloc(&W.part_s, nbp));
-  MSKM_TRY(dalloc(&W.part_v, std::max(nbp, (size_t)2 * h->L * nrhs)));  // also the residual's level sums
+  MSKM_TRY(dalloc(&W.part_v, std::max(nbp, (size_t)2 * h->L * R)));  // also the residual's level sums
   MSKM_TRY(dalloc(&W.part_v2, nbp));
-  if (W.pc) MSKM_TRY(dalloc(&W.part_z, (size_t)std::max(h->bj.wt.nblocks, 1) * nrhs));
-  MSKM_TRY(dalloc(&W.st, (size_t)h->L * nrhs));
+  if (W.pc) MSKM_TRY(dalloc(&W.part_z, (size_t)std::max(h->bj.wt.nblocks, 1) * R));
+  MSKM_TRY(dalloc(&W.st, (size_t)h->L * R));
   MSKM_TRY(dalloc(&W.lev_done, h->L));
   MSKM_HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&W.h_lev_done), h->L * 4, hipHostMallocDefault));
   const double* fdev = f_in;
   double* fstage = nullptr;
   if (!io_dev) {
-    MSKM_TRY(dalloc(&fstage, NR));
-    MSKM_HIP_TRY(hipMemcpyAsync(fstage, f_in, NR * 8, hipMemcpyHostToDevice, s));
+    MSKM_TRY(dalloc(&fstage, NU));
+    MSKM_HIP_TRY(hipMemcpyAsync(fstage, f_in, NU * 8, hipMemcpyHostToDevice, s));
     fdev = fstage;
   }
   MrStats ms;
@@ -1324,7 +1117,7 @@ mskm_status solve_multi(mskm_hier* h, const double* f_in, int nrhs, const mskm_s
   std::vector<double> rel;
   MSKM_HIP_TRY(hipEventRecord(h->ctx->ev0, s));
   hipLaunchKernelGGL(k_mr_to_internal<double>, dim3(mr_nblk(NR, kBlock)), dim3(kBlock), 0, s, fdev, h->perm, W.fi, h->N,
-                     nrhs);
+                     nrhs, R);
   mskm_status st = MSKM_OK;
   if (!mixed) {
     st = mr_solve_internal<double, double>(h, W, h->diag.val, h->lower.val, W.fi, W.ai, o, &sweeps_done, &ms);
@@ -1351,13 +1144,13 @@ mskm_status solve_multi(mskm_hier* h, const double* f_in, int nrhs, const mskm_s
   if (st == MSKM_OK) {
     double* adev = alpha_out;
     double* astage = nullptr;
-    if (!io_dev) st = dalloc(&astage, NR), adev = astage;
+    if (!io_dev) st = dalloc(&astage, NU), adev = astage;
     if (st == MSKM_OK) {
-      hipLaunchKernelGGL(k_mr_to_input<double>, dim3(mr_nblk(NR, kBlock)), dim3(kBlock), 0, s, (const double*)W.ai,
-                         h->perm, adev, h->N, nrhs);
+      hipLaunchKernelGGL(k_mr_to_input<double>, dim3(mr_nblk(NU, kBlock)), dim3(kBlock), 0, s, (const double*)W.ai,
+                         h->perm, adev, h->N, nrhs, R);
       if (hipEventRecord(h->ctx->ev1, s) != hipSuccess) st = fail(MSKM_EDEVICE, "event");
       if (st == MSKM_OK && !io_dev &&
-          hipMemcpyAsync(alpha_out, astage, NR * 8, hipMemcpyDeviceToHost, s) != hipSuccess)
+          hipMemcpyAsync(alpha_out, astage, NU * 8, hipMemcpyDeviceToHost, s) != hipSuccess)
         st = fail(MSKM_EDEVICE, "alpha copy");
       if (st == MSKM_OK && hipStreamSynchronize(s) != hipSuccess) st = fail(MSKM_EDEVICE, "sync");
     }

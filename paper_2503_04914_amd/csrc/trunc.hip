@@ -27,6 +27,7 @@
 #include <limits>
 
 #include "device_common.h"
+#include "mr_tiles.h"
 
 namespace mskm {
 
@@ -304,7 +305,7 @@ mskm_status trunc_build(mskm_hier* h, double T, double cg_rtol, mskm_trunc* tr) 
       if (h->h_next[l] >= 0) m = std::max(m, h->h_off[l + 1] - h->h_off[l]);
     return m;
   }();
-  const int R = (int)std::max<int64_t>(1, std::min<int64_t>(kChunk, maxn));
+  const int R = mr_width((int)std::max<int64_t>(1, std::min<int64_t>(kChunk, maxn)));
   if (nnz > 0 && maxn > 0) MSKM_TRY(sc.get(&Z, (size_t)N * R));
   tr->cg_iters = 0;
   tr->capped = false;
