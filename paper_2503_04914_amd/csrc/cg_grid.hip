@@ -257,8 +257,10 @@ mskm_status cg_grid_ready(mskm_hier* h, int lo, int hi, bool bj, int* lanes) {
     const int ln = k == 0 ? 2 : 1;
     if (!P.built) {
       P.built = true;
+      const size_t mark = h->allocs.size();
       const mskm_status st = build_plan(h, P, bj, ln);
       if (st == MSKM_ENOMEM) {  // no room for the plan: these levels stay launched
+        halloc_undo(h, mark);
         P.h_wg0.assign(h->L + 1, 0);
       } else if (st < 0) {
         return st;

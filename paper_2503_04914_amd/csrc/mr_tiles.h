@@ -3,6 +3,8 @@
 
 #include <cstdint>
 
+#include <hip/hip_runtime.h>
+
 #include "mskm_internal.h"
 
 namespace mskm {
@@ -39,17 +41,82 @@ inline int mr_width(int nrhs) { return nrhs <= 16 ? 16 : (nrhs + 31) / 32 * 32; 
 
 // q = A p on the blocks [b0, b0 + nb) of the SpMV work table with partials p.q
 // part[block][ldr], A the diagonal blocks' tiles, p and q [N][ldr]; levels
-// with lev_done set are skipped. The right-hand sides go in slices of `chunk`
+// with running[l] = 0 are skipped. The right-hand sides go in slices of `chunk`
 // (the slowest launch dimension; a multiple of 64 dividing ldr, or ldr).
 template <typename TX>
 void mr_tile_cg(mskm_hier* h, const MrTiles& D, int ldr, int chunk, int b0, int nb, const TX* p, TX* q,
-                const int32_t* lev_done, double* part);
+                const int32_t* running, double* part);
 // y = f - L x on blocks [b0, b0 + nb), L the lower blocks' tiles.
 template <typename TX>
 void mr_tile_lower(mskm_hier* h, const MrTiles& Lw, int ldr, int b0, int nb, const TX* x, const TX* f, TX* y);
 // r = f - (L + D) a in FP64 over the whole work table, partials r.r and f.f
-// [block][ldr]; rout nullable.
+// [block][ldr]; rout (nullable) receives r rounded to FP32.
 void mr_tile_residual(mskm_hier* h, const MrTiles& D, const MrTiles& Lw, int ldr, const double* a, const double* f,
-                      double* rout, double* rrp, double* ffp);
+                      float* rout, double* rrp, double* ffp);
+
+// Right-hand sides per lane of the many-right-hand-side kernels: 16 bytes, as
+// far as the width is a multiple of 16 lanes' worth.
+template <typename TX>
+inline int mr_lane_rhs(int ldr) {
+  if (sizeof(TX) == 4 && ldr % 64 == 0) return 4;
+  return ldr % 32 == 0 ? 2 : 1;
+}
+
+// ------------------------------------------------------------ device helpers
+
+typedef float mf4 __attribute__((ext_vector_type(4)));
+typedef double md4 __attribute__((ext_vector_type(4)));
+typedef int mi4 __attribute__((ext_vector_type(4)));
+
+template <typename T>
+struct Mma;
+template <>
+struct Mma<float> {
+  using acc = mf4;
+  static constexpr int kCols = 128, kStride = kCols + 4;  // columns of the tile in LDS, row stride
+  static __device__ __forceinline__ acc mul(float a, float b, acc c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int k, int i) { return 4 * k + i; }  // of accumulator element i
+};
+template <>
+struct Mma<double> {
+  using acc = md4;
+  static constexpr int kCols = 64, kStride = kCols + 2;
+  static __device__ __forceinline__ acc mul(double a, double b, acc c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int k, int i) { return k + 4 * i; }
+};
+
+template <typename T, int NT>
+struct VecN {
+  typedef T type __attribute__((ext_vector_type(NT)));
+};
+template <typename T>
+struct VecN<T, 1> {
+  typedef T type;
+};
+template <int NT, typename T>
+__device__ __forceinline__ void load_nt(const T* p, T (&v)[NT]) {
+  const typename VecN<T, NT>::type u = *reinterpret_cast<const typename VecN<T, NT>::type*>(p);
+  if constexpr (NT == 1) {
+    v[0] = u;
+  } else {
+#pragma unroll
+    for (int q = 0; q < NT; ++q) v[q] = u[q];
+  }
+}
+template <int NT, typename T>
+__device__ __forceinline__ void store_nt(T* p, const T (&v)[NT]) {
+  typename VecN<T, NT>::type u;
+  if constexpr (NT == 1) {
+    u = v[0];
+  } else {
+#pragma unroll
+    for (int q = 0; q < NT; ++q) u[q] = v[q];
+  }
+  *reinterpret_cast<typename VecN<T, NT>::type*>(p) = u;
+}
 
 }  // namespace mskm

@@ -246,7 +246,9 @@ mskm_status mr_tiles(mskm_hier* h, bool lower, const MrTiles** out) {
   const int k = lower ? 1 : 0;
   if (!S.tried[k]) {
     S.tried[k] = true;
+    const size_t mark = h->allocs.size();
     const mskm_status st = build_tiles(h, lower ? h->lower : h->diag, S.t[k], &S.ok[k]);
+    if (!S.ok[k]) halloc_undo(h, mark);
     if (st < 0 && st != MSKM_ENOMEM) return st;
   }
   if (S.ok[k]) *out = &S.t[k];
@@ -254,61 +256,6 @@ mskm_status mr_tiles(mskm_hier* h, bool lower, const MrTiles** out) {
 }
 
 // ------------------------------------------------------------------ products
-
-typedef float mf4 __attribute__((ext_vector_type(4)));
-typedef double md4 __attribute__((ext_vector_type(4)));
-typedef int mi4 __attribute__((ext_vector_type(4)));
-
-template <typename T>
-struct Mma;
-template <>
-struct Mma<float> {
-  using acc = mf4;
-  static constexpr int kCols = 128, kStride = kCols + 4;  // columns of the tile in LDS, row stride
-  static __device__ __forceinline__ acc mul(float a, float b, acc c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ int row(int k, int i) { return 4 * k + i; }  // of accumulator element i
-};
-template <>
-struct Mma<double> {
-  using acc = md4;
-  static constexpr int kCols = 64, kStride = kCols + 2;
-  static __device__ __forceinline__ acc mul(double a, double b, acc c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ int row(int k, int i) { return k + 4 * i; }
-};
-
-template <typename T, int NT>
-struct VecN {
-  typedef T type __attribute__((ext_vector_type(NT)));
-};
-template <typename T>
-struct VecN<T, 1> {
-  typedef T type;
-};
-template <int NT, typename T>
-__device__ __forceinline__ void load_nt(const T* p, T (&v)[NT]) {
-  const typename VecN<T, NT>::type u = *reinterpret_cast<const typename VecN<T, NT>::type*>(p);
-  if constexpr (NT == 1) {
-    v[0] = u;
-  } else {
-#pragma unroll
-    for (int q = 0; q < NT; ++q) v[q] = u[q];
-  }
-}
-template <int NT, typename T>
-__device__ __forceinline__ void store_nt(T* p, const T (&v)[NT]) {
-  typename VecN<T, NT>::type u;
-  if constexpr (NT == 1) {
-    u = v[0];
-  } else {
-#pragma unroll
-    for (int q = 0; q < NT; ++q) u[q] = v[q];
-  }
-  *reinterpret_cast<typename VecN<T, NT>::type*>(p) = u;
-}
 
 // Value of entry e in the product's precision.
 template <typename T>
@@ -407,12 +354,12 @@ __device__ __forceinline__ void tile_partial(double (&acc)[NT], double (*sm)[16 
 template <typename TX, int NT>
 __global__ void __launch_bounds__(kBlock)
     k_mrt_cg(const WorkTable wt, int base, int sub, const MrTiles D, const TileVals<TX> val, const TX* __restrict__ p,
-             TX* __restrict__ q, int ldr, const int32_t* __restrict__ lev_done, double* __restrict__ part) {
+             TX* __restrict__ q, int ldr, const int32_t* __restrict__ running, double* __restrict__ part) {
   __shared__ TX As[kBlock / kWave][kTileRows * Mma<TX>::kStride];
   __shared__ double sm[kBlock / kWave][16 * 4];
   const int id = xcd_block_id(gridDim.x);
   const int blk = base + id / sub, c0 = ((int)blockIdx.y * sub + id % sub) * 16 * NT;
-  if (lev_done[wt.lev[blk]]) return;
+  if (running[wt.lev[blk]] == 0) return;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
   const int n = lane % 16, k4 = lane / 16;
   const int64_t r0 = wt.row0[blk] + kTileRows * w, r1 = wt.row1[blk];
@@ -476,7 +423,7 @@ template <int NT>
 __global__ void __launch_bounds__(kBlock)
     k_mrt_residual(const WorkTable wt, int sub, const MrTiles D, const MrTiles Lw, const TileVals<double> dval,
                    const TileVals<double> lval, const double* __restrict__ a, const double* __restrict__ f,
-                   double* __restrict__ rout, double* __restrict__ rrp, double* __restrict__ ffp, int ldr) {
+                   float* __restrict__ rout, double* __restrict__ rrp, double* __restrict__ ffp, int ldr) {
   __shared__ double As[kBlock / kWave][kTileRows * Mma<double>::kStride];
   __shared__ double sm[kBlock / kWave][16 * 4];
   const int id = xcd_block_id(gridDim.x);
@@ -505,7 +452,12 @@ __global__ void __launch_bounds__(kBlock)
           prr[u] += ri[u] * ri[u];
           pff[u] += fi[u] * fi[u];
         }
-        if (rout) store_nt<NT>(rout + row * ldr + c0 + NT * n, ri);
+        if (rout) {
+          float r32[NT];
+#pragma unroll
+          for (int u = 0; u < NT; ++u) r32[u] = (float)ri[u];
+          store_nt<NT>(rout + row * ldr + c0 + NT * n, r32);
+        }
       }
     }
   }
@@ -513,12 +465,6 @@ __global__ void __launch_bounds__(kBlock)
   tile_partial<NT>(pff, sm, ffp, (size_t)blk * ldr + c0);
 }
 
-// Right-hand sides per lane: 16 bytes, as far as the width is a multiple of 16 NT.
-template <typename TX>
-static int lanes_nt(int ldr) {
-  if (sizeof(TX) == 4 && ldr % 64 == 0) return 4;
-  return ldr % 32 == 0 ? 2 : 1;
-}
 template <typename TX>
 static TileVals<TX> tile_vals(const MrTiles& T);
 template <>
@@ -532,16 +478,16 @@ TileVals<double> tile_vals<double>(const MrTiles& T) {
 
 template <typename TX>
 void mr_tile_cg(mskm_hier* h, const MrTiles& D, int ldr, int chunk, int b0, int nb, const TX* p, TX* q,
-                const int32_t* lev_done, double* part) {
+                const int32_t* running, double* part) {
   if (nb <= 0) return;
-  const int nt = lanes_nt<TX>(ldr), width = 16 * nt;
+  const int nt = mr_lane_rhs<TX>(ldr), width = 16 * nt;
   if (chunk % width || ldr % chunk) chunk = ldr;
   const int sub = chunk / width;
   const dim3 grid(nb * sub, ldr / chunk);
   hipStream_t s = h->ctx->stream;
   const TileVals<TX> v = tile_vals<TX>(D);
 #define MSKM_MRT(NTV)                                                                                             \
-  hipLaunchKernelGGL((k_mrt_cg<TX, NTV>), grid, dim3(kBlock), 0, s, h->wt_spmv, b0, sub, D, v, p, q, ldr, lev_done, \
+  hipLaunchKernelGGL((k_mrt_cg<TX, NTV>), grid, dim3(kBlock), 0, s, h->wt_spmv, b0, sub, D, v, p, q, ldr, running, \
                      part)
   if constexpr (sizeof(TX) == 4) {
     if (nt == 4) {
@@ -563,7 +509,7 @@ template void mr_tile_cg<double>(mskm_hier*, const MrTiles&, int, int, int, int,
 template <typename TX>
 void mr_tile_lower(mskm_hier* h, const MrTiles& Lw, int ldr, int b0, int nb, const TX* x, const TX* f, TX* y) {
   if (nb <= 0) return;
-  const int nt = lanes_nt<TX>(ldr), sub = ldr / (16 * nt);
+  const int nt = mr_lane_rhs<TX>(ldr), sub = ldr / (16 * nt);
   const dim3 grid(nb * sub);
   hipStream_t s = h->ctx->stream;
   const TileVals<TX> v = tile_vals<TX>(Lw);
@@ -585,8 +531,8 @@ template void mr_tile_lower<float>(mskm_hier*, const MrTiles&, int, int, int, co
 template void mr_tile_lower<double>(mskm_hier*, const MrTiles&, int, int, int, const double*, const double*, double*);
 
 void mr_tile_residual(mskm_hier* h, const MrTiles& D, const MrTiles& Lw, int ldr, const double* a, const double* f,
-                      double* rout, double* rrp, double* ffp) {
-  const int nt = lanes_nt<double>(ldr), sub = ldr / (16 * nt);
+                      float* rout, double* rrp, double* ffp) {
+  const int nt = mr_lane_rhs<double>(ldr), sub = ldr / (16 * nt);
   const dim3 grid((unsigned)h->wt_spmv.nblocks * sub);
   hipStream_t s = h->ctx->stream;
   const TileVals<double> dv = tile_vals<double>(D), lv = tile_vals<double>(Lw);

@@ -343,6 +343,17 @@ mskm_status halloc(mskm_hier* h, T** p, size_t count) {
   return MSKM_OK;
 }
 
+// Gives back the hierarchy's allocations made after the first `mark` ones (a
+// structure that could not be built for lack of memory).
+inline void halloc_undo(mskm_hier* h, size_t mark) {
+  while (h->allocs.size() > mark) {
+    h->device_bytes -= static_cast<int64_t>(h->alloc_bytes.back());
+    ctx_release(h->ctx, h->allocs.back(), h->alloc_bytes.back());
+    h->allocs.pop_back();
+    h->alloc_bytes.pop_back();
+  }
+}
+
 // scratch allocation owned by the caller (freed with hipFree)
 template <typename T>
 mskm_status dalloc(T** p, size_t count) {
