@@ -34,6 +34,7 @@ struct MrTiles {
 // *out is null where they are not available (a tile with more than 65536
 // columns, or no memory): the caller takes the general products.
 mskm_status mr_tiles(mskm_hier* h, bool lower, const MrTiles** out);
+bool mr_tiles_built(const mskm_hier* h);  // both matrices' tiles are there
 
 // Right-hand sides are padded to a width that the tiles' products take: 16,
 // or a multiple of 32 (the padding solves zero systems, which stop at once).

@@ -255,6 +255,11 @@ mskm_status mr_tiles(mskm_hier* h, bool lower, const MrTiles** out) {
   return MSKM_OK;
 }
 
+bool mr_tiles_built(const mskm_hier* h) {
+  const auto* S = static_cast<const MrTileSet*>(h->mr_tiles);
+  return S && S->ok[0] && S->ok[1];
+}
+
 // ------------------------------------------------------------------ products
 
 // Value of entry e in the product's precision.

@@ -494,6 +494,9 @@ mskm_status lagrange_columns(mskm_hier* h, int l, int64_t n0, int R, double rtol
                              int64_t* iters, bool* capped);
 mskm_status solve_multi(mskm_hier* h, const double* f, int nrhs, const mskm_solve_opts* o, double* alpha,
                         mskm_report* rep);
+// solve_mr.hip: residuals of several right-hand sides at once (device vectors,
+// host rel_out); *done false where the one-by-one form is to be taken.
+mskm_status residual_multi(mskm_hier* h, const double* alpha, const double* f, int nrhs, double* rel_out, bool* done);
 mskm_status residual(mskm_hier* h, const double* alpha, const double* f, int nrhs, double* rel_out, bool io_dev);
 // Allocation-free residual: device vectors in input order, partials in the
 // static scratch array (noalloc_init at context creation), stream-ordered.

@@ -2738,6 +2738,9 @@ mskm_status residual(mskm_hier* h, const double* alpha, const double* f, int nrh
   DevBuf A, F;
   MSKM_TRY(stage_in(s, alpha, (size_t)N * nrhs, io_dev, A));
   MSKM_TRY(stage_in(s, f, (size_t)N * nrhs, io_dev, F));
+  bool done = false;
+  MSKM_TRY(residual_multi(h, A.p, F.p, nrhs, rel_out, &done));
+  if (done) return MSKM_OK;
   SolveWS* Wp = nullptr;  // the solver workspace's internal-order vectors and residual partials
   MSKM_TRY(get_ws(h, &Wp));
   double* ai = Wp->ai;

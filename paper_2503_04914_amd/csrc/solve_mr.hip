@@ -19,16 +19,16 @@
 
 namespace mskm {
 
-// Caller's vectors [n][nrhs] in input order into internal order [n][R], R >=
-// nrhs (columns past nrhs are zero), and back.
+// `cnt` columns of the caller's vectors in[n][stride], input order, into
+// internal order [n][R], R >= cnt (columns past cnt are zero), and back.
 template <typename TO>
 __global__ void __launch_bounds__(kBlock) k_mr_to_internal(const double* __restrict__ in, const int32_t* __restrict__ perm,
-                                                           TO* __restrict__ out, int64_t n, int nrhs, int R) {
+                                                           TO* __restrict__ out, int64_t n, int stride, int cnt, int R) {
   const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (e >= n * R) return;
   const int64_t i = e / R;
   const int r = (int)(e - i * R);
-  out[e] = r < nrhs ? (TO)in[(int64_t)perm[i] * nrhs + r] : (TO)0;
+  out[e] = r < cnt ? (TO)in[(int64_t)perm[i] * stride + r] : (TO)0;
 }
 
 template <typename TI>
@@ -440,7 +440,7 @@ mskm_status solve_multi(mskm_hier* h, const double* f_in, int nrhs, const mskm_s
   std::vector<double> rel;
   MSKM_HIP_TRY(hipEventRecord(h->ctx->ev0, s));
   hipLaunchKernelGGL(k_mr_to_internal<double>, dim3(mr_nblk(NR, kBlock)), dim3(kBlock), 0, s, fdev, h->perm, W.fi, h->N,
-                     nrhs, R);
+                     nrhs, nrhs, R);
   if (!mixed) {
     MSKM_TRY((mr_solve_internal<double, double>(h, W, h->diag.val, h->lower.val, W.fi, W.ai, o, &sweeps_done)));
     MSKM_TRY(mr_residual(h, W, W.ai, W.fi, nullptr, rel));
@@ -488,6 +488,40 @@ mskm_status solve_multi(mskm_hier* h, const double* f_in, int nrhs, const mskm_s
   }
   MSKM_HIP_TRY(hipGetLastError());
   return enoconv ? MSKM_ENOCONV : MSKM_OK;
+}
+
+// mskm_residual for several right-hand sides at once, on the tiles of the
+// blocks: the matrix is read once for up to 512 of them instead of once each
+// (349,504 points, 256 right-hand sides: 3.1 ms against 256 passes of 0.19 ms,
+// each with two permutations and a host wait). The tiles cost about as much
+// as 16 such passes to build, so fewer right-hand sides use them only when a
+// solve has left them. *done stays false where this form does not apply (no
+// tiles, no room for the vectors).
+mskm_status residual_multi(mskm_hier* h, const double* alpha, const double* f, int nrhs, double* rel_out, bool* done) {
+  *done = false;
+  constexpr int kBuildAt = 16, kSlab = 64 * kMaxRPerLane;
+  if (nrhs < 2 || (nrhs < kBuildAt && !mr_tiles_built(h))) return MSKM_OK;
+  hipStream_t s = h->ctx->stream;
+  for (int r0 = 0; r0 < nrhs; r0 += kSlab) {
+    const int cnt = std::min(kSlab, nrhs - r0), R = mr_width(cnt);
+    MrWS W;
+    const mskm_status st = mr_workspace(h, R, 0, false, W);
+    if (st == MSKM_ENOMEM) return MSKM_OK;
+    if (st < 0) return st;
+    MSKM_TRY(mr_tiles(h, false, &W.D));
+    MSKM_TRY(mr_tiles(h, true, &W.Lw));
+    if (!W.D || !W.Lw) return MSKM_OK;
+    const unsigned nb = mr_nblk(h->N * R, kBlock);
+    hipLaunchKernelGGL(k_mr_to_internal<double>, dim3(nb), dim3(kBlock), 0, s, alpha + r0, h->perm, W.ai, h->N, nrhs,
+                       cnt, R);
+    hipLaunchKernelGGL(k_mr_to_internal<double>, dim3(nb), dim3(kBlock), 0, s, f + r0, h->perm, W.fi, h->N, nrhs, cnt,
+                       R);
+    std::vector<double> rel;
+    MSKM_TRY(mr_residual(h, W, W.ai, W.fi, nullptr, rel));
+    std::memcpy(rel_out + (size_t)r0 * h->ngroups, rel.data(), (size_t)cnt * h->ngroups * sizeof(double));
+  }
+  *done = true;
+  return MSKM_OK;
 }
 
 }  // namespace mskm

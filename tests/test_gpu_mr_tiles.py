@@ -52,3 +52,28 @@ def test_far_columns():
     """Lower rows whose columns lie in windows more than 65536 columns apart (FP64: the third level is
     nearly solved by the second, so a per-level bar on its small coefficients needs the tight solve)."""
     _run([40, 70001, 70003], 3, "fp64", [1])
+
+
+@pytest.mark.parametrize("nrhs", [1, 2, 15, 16, 530])
+def test_residuals_at_once(nrhs):
+    """Residuals of several right-hand sides at once against one by one (the
+    same FP64 products in another order: 1e-12 of residuals of order one), before
+    and after a solve has built the tiles; a batch reports per group."""
+    import paper_2503_04914_amd as m
+
+    hs = [synth.halton_hierarchy(sizes=[9, 70, 515]), synth.halton_hierarchy(sizes=[33, 130], start=7001)]
+    N = sum(h.n_total for h in hs)
+    rng = np.random.default_rng(11)
+    A, F = rng.standard_normal((N, nrhs)), rng.standard_normal((N, nrhs))
+    ctx = m.mskm_create(0)
+    hd = m.mskm_hier_create_batch(ctx, [(h.points, h.offsets, h.delta) for h in hs])
+    try:
+        one = np.concatenate([m.mskm_residual(ctx, hd, np.ascontiguousarray(A[:, r]), np.ascontiguousarray(F[:, r]))
+                              for r in range(nrhs)])
+        np.testing.assert_allclose(m.mskm_residual(ctx, hd, A, F, nrhs=nrhs), one, rtol=1e-12)
+        X = np.zeros((N, 3))
+        m.mskm_solve(ctx, hd, np.ascontiguousarray(np.ones((N, 3))), X, m.solve_opts(cg_rtol=1e-6), nrhs=3)
+        np.testing.assert_allclose(m.mskm_residual(ctx, hd, A, F, nrhs=nrhs), one, rtol=1e-12)
+    finally:
+        m.mskm_hier_destroy(hd)
+        m.mskm_destroy(ctx)
