@@ -402,6 +402,11 @@ struct CtxScratch {
   ~CtxScratch();
 };
 inline mskm_status Carve::alloc(mskm_ctx* c, void** base) {
+  // up to a multiple of an eighth of the next lower power of two, so that
+  // calls of similar sizes find each other's blocks
+  size_t g = 256;
+  while (g * 16 <= bytes) g *= 2;
+  bytes = (bytes + g - 1) / g * g;
   MSKM_TRY(ctx_alloc(c, bytes, base));
   place(static_cast<char*>(*base));
   return MSKM_OK;
