@@ -371,6 +371,7 @@ mskm_status mskm_hier_destroy(mskm_hier* h) {
     }
   if (h->solve_ws_free) h->solve_ws_free(h->solve_ws);
   if (h->cg_grid_free) h->cg_grid_free(h->cg_grid);
+  if (h->cg_stream_free) h->cg_stream_free(h->cg_stream);
   if (h->mr_tiles_free) h->mr_tiles_free(h->mr_tiles);
   for (mskm_trunc* t : h->truncs) t->h = nullptr;  // they keep their own memory until destroyed
   for (size_t i = 0; i < h->allocs.size(); ++i) mskm::ctx_release(h->ctx, h->allocs[i], h->alloc_bytes[i]);

@@ -41,19 +41,15 @@
 #include <mutex>
 #include <vector>
 
+#include "cg_grid.h"
 #include "cg_state.h"
 #include "device_common.h"
 
 namespace mskm {
 
-constexpr int kGridThreads = 512;
 constexpr int kGridE = 64;          // matrix entries per lane kept in registers (at most)
 constexpr int kGridLocal = 4096;    // direction entries per workgroup: its rows and its halo
-constexpr int kGridSlot = 8;        // 64-byte slots
 constexpr int64_t kGridLevelRows = 131072;  // column bitmap of the plan: 16 KiB of LDS
-
-__device__ constexpr uint64_t kEmptySlot = 0x7ff4deadbeef0001ull;  // signalling NaN patterns: arithmetic never
-__device__ constexpr uint32_t kEmptyWord = 0x7fa4beefu;            // produces them (results are quieted)
 
 // Levels that can be solved this way with 512 / lanes rows per workgroup:
 // workgroup w of level l takes `per` consecutive blocks of the level's
@@ -276,78 +272,6 @@ mskm_status cg_grid_ready(mskm_hier* h, int lo, int hi, bool bj, int* lanes) {
 
 // -------------------------------------------------------------------- solve
 
-// lane-crossing moves within 16 lanes
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
-  return __hiloint2double(hi, lo);
-}
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;                 // quad permutations
-constexpr int kDppHalfMirror = 0x141, kDppMirror = 0x140;       // within 8 and 16 lanes
-template <int G, typename T>
-__device__ __forceinline__ T lanes_sum(T v) {  // over G (a power of two, at most 16) neighbouring lanes
-  if constexpr (G >= 2) v += dpp<kDppXor1>(v);
-  if constexpr (G >= 4) v += dpp<kDppXor2>(v);
-  if constexpr (G >= 8) v += dpp<kDppHalfMirror>(v);
-  if constexpr (G >= 16) v += dpp<kDppMirror>(v);
-  return v;
-}
-__device__ __forceinline__ double readlane_f64(double v, int l) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
-                          __builtin_amdgcn_readlane(__double2loint(v), l));
-}
-__device__ __forceinline__ double wave64_sum(double v) {
-  v = lanes_sum<16>(v);
-  return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
-}
-
-// Device-coherent words. A value whose bits are the empty pattern (it can
-// only be a signalling NaN from the caller's data) is published quieted.
-__device__ __forceinline__ uint32_t word_of(float v) {
-  const uint32_t b = __float_as_uint(v);
-  return b == kEmptyWord ? b | 0x00400000u : b;
-}
-__device__ __forceinline__ uint64_t word_of(double v) {
-  const uint64_t b = (uint64_t)__double_as_longlong(v);
-  return b == kEmptySlot ? b | 0x0008000000000000ull : b;
-}
-__device__ __forceinline__ float value_of(uint32_t b) { return __uint_as_float(b); }
-__device__ __forceinline__ double value_of(uint64_t b) { return __longlong_as_double((long long)b); }
-template <typename T>
-struct GridWord;
-template <>
-struct GridWord<float> {
-  using type = uint32_t;
-  static constexpr uint32_t empty = kEmptyWord;
-};
-template <>
-struct GridWord<double> {
-  using type = uint64_t;
-  static constexpr uint64_t empty = kEmptySlot;
-};
-template <typename W>
-__device__ __forceinline__ void put(W* p, W v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <typename W>
-__device__ __forceinline__ W get(const W* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// The word at p once it is there; *bad after `spin` further polls.
-template <typename W>
-__device__ __forceinline__ W poll(const W* p, W empty, int spin, int* bad) {
-  W u = get(p);
-  for (int k = 0; u == empty && k < spin; ++k) u = get(p);
-  if (u == empty) *bad = 1;
-  return u;
-}
-
 // The row's z = M^-1 r from rs: this lane's share of the inverse row, in
 // registers (N of them) or read through the caches (N = 1).
 template <int G, int N, typename TX>
@@ -361,20 +285,6 @@ __device__ __forceinline__ TX grid_precond(const TX (&iv)[N], const TX* Mi, int 
     for (int j = g; j < bm; j += G) a += Mi[j] * rb[j];
   }
   return lanes_sum<G>(a);
-}
-
-// Empties z0, z1 on the rows [r0, r0 + n) and every slot of the plan.
-template <typename TX>
-__global__ void __launch_bounds__(kBlock)
-    k_grid_empty(typename GridWord<TX>::type* __restrict__ z0, typename GridWord<TX>::type* __restrict__ z1,
-                 int64_t r0, int64_t n, uint64_t* __restrict__ slots, int64_t ns, int32_t* __restrict__ aborted) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i < n) {
-    z0[r0 + i] = GridWord<TX>::empty;
-    z1[r0 + i] = GridWord<TX>::empty;
-  }
-  if (i < ns) slots[i] = kEmptySlot;
-  if (i == 0) *aborted = 0;
 }
 
 // G lanes per row, 512 / G rows per workgroup, at most E matrix entries per
@@ -576,9 +486,7 @@ __global__ void __launch_bounds__(kGridThreads)
   }
 }
 
-// Launches of the persistent kernel on one device run one after the other:
-// two of them partly resident at the same time would wait for workgroups
-// that cannot start. `ev` is the event of the context that launched last.
+// `last` is the context that launched a persistent kernel last.
 namespace {
 struct GridOrder {
   std::mutex mu;
@@ -595,7 +503,42 @@ void cg_grid_forget(mskm_ctx* c) {
   if (o.last == c) o.last = nullptr;
 }
 
+mskm_status cg_grid_in_turn(mskm_ctx* c, const std::function<void()>& launch) {
+  if (c->device < 0 || c->device >= kGridDevices) return fail(MSKM_ELIMIT, "device index beyond 63");
+  GridOrder& o = g_order[c->device];
+  std::lock_guard<std::mutex> lock(o.mu);
+  if (o.last && o.last != c) MSKM_HIP_TRY(hipStreamWaitEvent(c->stream, o.last->ev_grid, 0));
+  launch();
+  MSKM_HIP_TRY(hipGetLastError());
+  MSKM_HIP_TRY(hipEventRecord(c->ev_grid, c->stream));
+  o.last = c;
+  return MSKM_OK;
+}
+
 void cg_grid_set_spin(mskm_ctx* c, int spin) { c->grid_spin = spin; }
+
+// Empties z0, z1 on the rows [r0, r0 + n) and every slot of the plan.
+template <typename TX>
+__global__ void __launch_bounds__(kBlock)
+    k_grid_empty(typename GridWord<TX>::type* __restrict__ z0, typename GridWord<TX>::type* __restrict__ z1,
+                 int64_t r0, int64_t n, uint64_t* __restrict__ slots, int64_t ns, int32_t* __restrict__ aborted) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i < n) {
+    z0[r0 + i] = GridWord<TX>::empty;
+    z1[r0 + i] = GridWord<TX>::empty;
+  }
+  if (i < ns) slots[i] = kEmptySlot;
+  if (i == 0) *aborted = 0;
+}
+
+template <typename TX>
+void grid_empty(hipStream_t s, TX* z0, TX* z1, int64_t r0, int64_t n, uint64_t* slots, int64_t ns, int32_t* aborted) {
+  using W = typename GridWord<TX>::type;
+  hipLaunchKernelGGL(k_grid_empty<TX>, dim3((unsigned)((std::max(n, ns) + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
+                     (W*)z0, (W*)z1, r0, n, slots, ns, aborted);
+}
+template void grid_empty<float>(hipStream_t, float*, float*, int64_t, int64_t, uint64_t*, int64_t, int32_t*);
+template void grid_empty<double>(hipStream_t, double*, double*, int64_t, int64_t, uint64_t*, int64_t, int32_t*);
 
 template <typename TX>
 mskm_status cg_grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, const TX* val, const TX* b, TX* x,
@@ -609,12 +552,8 @@ mskm_status cg_grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, con
   int longest = 0;
   for (int l = lo; l <= hi; ++l) longest = std::max(longest, P.h_row[l]);
   const int64_t r0 = h->h_off[lo], n = h->h_off[hi + 1] - r0, ns = (int64_t)4 * P.d.nwg * kGridSlot;
-  hipLaunchKernelGGL(k_grid_empty<TX>, dim3((unsigned)((std::max(n, ns) + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
-                     (W*)z0, (W*)z1, r0, n, P.d.slots, ns, aborted);
-  if (c->device < 0 || c->device >= kGridDevices) return fail(MSKM_ELIMIT, "device index beyond 63");
-  GridOrder& o = g_order[c->device];
-  std::lock_guard<std::mutex> lock(o.mu);
-  if (o.last && o.last != c) MSKM_HIP_TRY(hipStreamWaitEvent(s, o.last->ev_grid, 0));
+  grid_empty<TX>(s, z0, z1, r0, n, P.d.slots, ns, aborted);
+  return cg_grid_in_turn(c, [&] {
 #define MSKM_GRID_LAUNCH(PCF, GG, EE)                                                                              \
   hipLaunchKernelGGL((k_cg_grid<TX, PCF, GG, EE>), dim3(nw), dim3(kGridThreads), 0, s, P.d, w0, h->d_lev,          \
                      h->diag.rowptr, val, b, x, (W*)z0, (W*)z1, st, aborted, rtol2, maxit, c->grid_spin, pc)
@@ -640,10 +579,7 @@ mskm_status cg_grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, con
       MSKM_GRID_LAUNCH(false, 1, 64);
   }
 #undef MSKM_GRID_LAUNCH
-  MSKM_HIP_TRY(hipGetLastError());
-  MSKM_HIP_TRY(hipEventRecord(c->ev_grid, s));
-  o.last = c;
-  return MSKM_OK;
+  });
 }
 template mskm_status cg_grid_launch<float>(mskm_hier*, int, int, bool, int, const float*, const float*, float*, float*,
                                            float*, CgLevel*, int32_t*, double, int, const PcArgs<float>&);

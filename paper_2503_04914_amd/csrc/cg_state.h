@@ -48,4 +48,10 @@ mskm_status cg_grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, con
                            TX* z0, TX* z1, CgLevel* st, int32_t* aborted, double rtol2, int maxit,
                            const PcArgs<TX>& pc);
 
+// cg_stream.hip: the same for all levels of one depth, FP32, where they do not
+// fit the registers. cg_stream_ready: *depth is that depth, or -1.
+mskm_status cg_stream_ready(mskm_hier* h, int lo, int hi, bool bj, int* depth);
+mskm_status cg_stream_launch(mskm_hier* h, int depth, bool bj, const float* b, float* x, float* z0, float* z1,
+                             CgLevel* st, int32_t* aborted, double rtol2, int maxit, const PcArgs<float>& pc);
+
 }  // namespace mskm

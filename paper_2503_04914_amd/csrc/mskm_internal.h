@@ -286,6 +286,8 @@ struct mskm_hier {
   std::vector<mskm_trunc*> truncs;      // thresholded blocks built on this hierarchy (detached at destroy)
   void* cg_grid = nullptr;              // plans of the persistent CG (cg_grid.hip), created at its first use
   void (*cg_grid_free)(void*) = nullptr;
+  void* cg_stream = nullptr;            // plans of the persistent CG of large levels (cg_stream.hip)
+  void (*cg_stream_free)(void*) = nullptr;
   void* mr_tiles = nullptr;             // tiles of the many-rhs products (mr_tiles.hip), created at their first use
   void (*mr_tiles_free)(void*) = nullptr;
   void* solve_ws = nullptr;             // solver workspace (solve.hip), created on first solve

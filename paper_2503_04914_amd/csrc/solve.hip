@@ -1483,6 +1483,9 @@ static mskm_status cg_run(mskm_hier* h, SolveWS& W, const TV* dval, const std::v
       int lanes = 0;
       MSKM_TRY(cg_grid_ready(h, nlo, nhi, bj, &lanes));
       if (lanes > 0) return MSKM_OK;
+      int depth = -1;
+      if (sizeof(TX) == 4) MSKM_TRY(cg_stream_ready(h, nlo, nhi, bj, &depth));
+      if (depth >= 0) return MSKM_OK;
     }
     int Gn = h->spmv_g[MSKM_OP_DIAG][sizeof(TX) == 4 ? 1 : 0];
     if (Gn >= 2 * kVecFlag && Gn < 3 * kVecFlag) Gn -= kVecFlag;
@@ -1524,22 +1527,29 @@ static mskm_status cg_run(mskm_hier* h, SolveWS& W, const TV* dval, const std::v
     for (int l = lo; l <= hi; ++l) W.deferred[l] = 1;
     return capture_next();
   }
-  // middle levels: the whole solve in one launch of workgroups that are all
-  // on the GPU at once (cg_grid.hip)
+  // middle levels, and a depth of large ones in FP32: the whole solve in one
+  // launch of workgroups that are all on the GPU at once (cg_grid.hip,
+  // cg_stream.hip)
   if (!mlp && !warm && !W.grid_off) {
-    int lanes = 0;
+    int lanes = 0, depth = -1;
     bool all_on = true;
     for (int l = lo; l <= hi; ++l) all_on = all_on && on[l];
     if (all_on) MSKM_TRY(cg_grid_ready(h, lo, hi, bj, &lanes));
-    if (lanes > 0) {
+    if (all_on && lanes == 0 && sizeof(TX) == 4) MSKM_TRY(cg_stream_ready(h, lo, hi, bj, &depth));
+    if (lanes > 0 || depth >= 0) {
       for (int l = lo; l <= hi; ++l)
         if (W.deferred[l]) {
           MSKM_TRY(flush_deferred(h, W, cs));
           break;
         }
       if (bj) MSKM_TRY(bj_start_side(h));
-      MSKM_TRY(cg_grid_launch<TX>(h, lo, hi, bj, lanes, dval, b, x, (TX*)W.p0, (TX*)W.p1, W.st, W.aborted,
-                                  rtol * rtol, maxit, pc_args<TX>(h, W)));
+      if (lanes > 0) {
+        MSKM_TRY(cg_grid_launch<TX>(h, lo, hi, bj, lanes, dval, b, x, (TX*)W.p0, (TX*)W.p1, W.st, W.aborted,
+                                    rtol * rtol, maxit, pc_args<TX>(h, W)));
+      } else if constexpr (sizeof(TX) == 4) {
+        MSKM_TRY(cg_stream_launch(h, depth, bj, b, x, (TX*)W.p0, (TX*)W.p1, W.st, W.aborted, rtol * rtol, maxit,
+                                  pc_args<TX>(h, W)));
+      }
       MSKM_HIP_TRY(
           hipMemcpyAsync(W.h_defer + lo, W.st + lo, (hi - lo + 1) * sizeof(CgLevel), hipMemcpyDeviceToHost, s));
       MSKM_HIP_TRY(hipMemcpyAsync(W.h_aborted + lo, W.aborted, 4, hipMemcpyDeviceToHost, s));

@@ -105,3 +105,45 @@ def test_all_level_kinds_agree(algorithm):
     finally:
         m.mskm_hier_destroy(hd)
         m.mskm_destroy(ctx)
+
+
+@pytest.mark.parametrize("bj", [False, True])
+@pytest.mark.parametrize("case", ["one slot past a multiple of 512 rows", "uneven levels of one depth", "3-D", "wide rows"])
+def test_large_fp32_levels(case, bj):
+    """The FP32 form for levels past the registers: its coefficients (refined to 1e-13) equal to those of
+    the launched kernels (spin limit 0), and repeats bit for bit."""
+    import paper_2503_04914_amd as m
+
+    if case == "3-D":
+        h = synth.uniform3d_hierarchy(2, n0=20000)  # 20,000 and 160,000 points
+        hs = [h]
+    elif case == "uneven levels of one depth":
+        hs = [synth.halton_hierarchy(sizes=s, start=1 + 500000 * k)
+              for k, s in enumerate(([50, 150001], [1200, 3001], [400, 90007]))]
+    elif case == "wide rows":
+        hs = [synth.halton_hierarchy(sizes=[5000, 140001], nu=5.4)]  # about 92 entries a row
+    else:
+        hs = [synth.halton_hierarchy(sizes=[1000, 256 * 1024 + 77])]
+    set_spin = getattr(m.lib(), "_ZN4mskm16cg_grid_set_spinEP8mskm_ctxi")
+    set_spin.argtypes, set_spin.restype = [ctypes.c_void_p, ctypes.c_int], None
+    f = np.concatenate([synth.fourier_target(1400 + k, h.dim)(h.points) for k, h in enumerate(hs)])
+    ctx = m.mskm_create(0)
+    hd = m.mskm_hier_create_batch(ctx, [(h.points, h.offsets, h.delta) for h in hs], fp64=False, fp32=True)
+    o = m.solve_opts(precision=m.MSKM_PREC_FP32, algorithm=m.MSKM_ALG_SEQUENTIAL, cg_rtol=1e-5, max_refine=20,
+                     target_rel_residual=1e-13,
+                     precond=m.MSKM_PRECOND_BLOCK_JACOBI if bj else m.MSKM_PRECOND_NONE)
+    try:
+        out = []
+        for spin in (1 << 15, 0, 1 << 15):
+            print(f"[stream] spin limit {spin}", flush=True)
+            set_spin(ctx, spin)
+            a = np.zeros_like(f)
+            r = m.mskm_solve(ctx, hd, f, a, o)
+            assert r.status == m.MSKM_OK, r.report
+            out.append(a)
+        assert np.array_equal(out[0], out[2])
+        # both within the repository's bar for refined mixed coefficients (1e-8)
+        assert np.linalg.norm(out[1] - out[0]) <= 2e-8 * np.linalg.norm(out[0])
+    finally:
+        m.mskm_hier_destroy(hd)
+        m.mskm_destroy(ctx)
