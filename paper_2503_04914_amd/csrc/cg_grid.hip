@@ -247,10 +247,14 @@ mskm_status cg_grid_ready(mskm_hier* h, int lo, int hi, bool bj, int* lanes) {
   }
   CgGrid& g = *static_cast<CgGrid*>(h->cg_grid);
   // 256 rows per workgroup, two lanes a row, as long as the workgroups are at
-  // most one per CU; else 512 rows, one lane a row
-  for (int k = 0; k < 2; ++k) {
-    CgGridPlan& P = g.plan[bj ? 1 : 0][k];
-    const int ln = k == 0 ? 2 : 1;
+  // most one per CU; else 512 rows, one lane a row. The latter first for levels
+  // of up to 512 rows that it solves with one workgroup each: a solve of 341 rows
+  // takes 87 us without exchanges, one of 1,365 rows in five workgroups 157 us
+  // (k_cg_level_wg, which reads the matrix in every iteration: 259 us for 341).
+  int64_t most = 0;
+  for (int l = lo; l <= hi; ++l) most = std::max<int64_t>(most, h->h_lev[l].n);
+  auto fits = [&](int ln, int* nw) -> mskm_status {
+    CgGridPlan& P = g.plan[bj ? 1 : 0][ln == 2 ? 0 : 1];
     if (!P.built) {
       P.built = true;
       const size_t mark = h->allocs.size();
@@ -262,10 +266,20 @@ mskm_status cg_grid_ready(mskm_hier* h, int lo, int hi, bool bj, int* lanes) {
         return st;
       }
     }
-    if (plan_workgroups(h, P, ln, lo, hi) > 0) {
-      *lanes = ln;
+    *nw = plan_workgroups(h, P, ln, lo, hi);
+    return MSKM_OK;
+  };
+  int nw = 0;
+  if (most > kGridThreads / 2 && most <= kGridThreads) {
+    MSKM_TRY(fits(1, &nw));
+    if (nw == hi - lo + 1) {
+      *lanes = 1;
       return MSKM_OK;
     }
+  }
+  for (int ln = 2; ln >= 1 && *lanes == 0; --ln) {
+    MSKM_TRY(fits(ln, &nw));
+    if (nw > 0) *lanes = ln;
   }
   return MSKM_OK;
 }
@@ -290,7 +304,9 @@ __device__ __forceinline__ TX grid_precond(const TX (&iv)[N], const TX* Mi, int 
 // G lanes per row, 512 / G rows per workgroup, at most E matrix entries per
 // lane. Thread t holds entries g, g + G, ... of row t / G (g = t % G) and the
 // row's share of its block inverse; all G lanes of a row hold its x, r, p, z.
-template <typename TX, bool PC, int G, int E>
+// SOLO: every level has one workgroup, which exchanges nothing and takes the
+// sums from LDS.
+template <typename TX, bool PC, int G, int E, bool SOLO>
 __global__ void __launch_bounds__(kGridThreads)
     k_cg_grid(const CgGridDev P, int wgb, const DevLevel* __restrict__ lev, const int64_t* __restrict__ rp,
               const TX* __restrict__ val, const TX* __restrict__ b, TX* __restrict__ x,
@@ -303,9 +319,9 @@ __global__ void __launch_bounds__(kGridThreads)
   constexpr bool kInvRegs = PC && sizeof(TX) == 4;
   constexpr int kI = kInvRegs ? kBjMax / G : 1;
   __shared__ TX pw[kGridLocal];    // direction: own rows, then the halo
-  __shared__ int32_t hrow[kGridLocal];  // rows of the halo
+  __shared__ int32_t hrow[SOLO ? 1 : kGridLocal];  // rows of the halo
   __shared__ TX rs[PC ? RW : 1];   // residual of the own rows
-  __shared__ double sm[2][kWaves], sp[kWaves];
+  __shared__ double sm[2][kWaves], sb[kWaves], sp[kWaves];
   __shared__ int bad;
   const int wg = wgb + blockIdx.x, t = threadIdx.x, w = t / kWave, lane = t % kWave;
   const int l = P.lev[wg], w0 = P.wg0[l], nw = P.wg0[l + 1] - w0;
@@ -317,6 +333,7 @@ __global__ void __launch_bounds__(kGridThreads)
   uint64_t* const slotA = P.slots + (size_t)w0 * kGridSlot;
   uint64_t* const slotB = slotA + (size_t)2 * P.nwg * kGridSlot;
   const int me = wg - w0, nslot = P.nwg;
+  if (SOLO && blockIdx.x == 0 && t == 0) *aborted = 0;
 
   // matrix entries (past the row's end: value 0 at position 0)
   TX v[E];
@@ -366,7 +383,7 @@ __global__ void __launch_bounds__(kGridThreads)
     zi = ri;
   }
   // halo entries t, t + kGridThreads, ... are the thread's; their rows stay in LDS
-  for (int q = t; q < nh; q += kGridThreads) hrow[q] = P.halo[(size_t)wg * kGridLocal + q];
+  for (int q = t; !SOLO && q < nh; q += kGridThreads) hrow[q] = P.halo[(size_t)wg * kGridLocal + q];
 
   double rzold = 0.0, bb = 0.0, rr = 0.0;
   int n = 0, capped = 0;
@@ -374,7 +391,7 @@ __global__ void __launch_bounds__(kGridThreads)
     W* const zc = n & 1 ? z1 : z0;
     W* const zp = n & 1 ? z0 : z1;
     // publish z, then (exchange A) r.r and r.z
-    if (first) {
+    if (first && !SOLO) {
       put(&zc[row], word_of(zi));
       if (n > 0) put(&zp[row], GridWord<TX>::empty);
     }
@@ -386,27 +403,34 @@ __global__ void __launch_bounds__(kGridThreads)
       sm[1][w] = c;
     }
     __syncthreads();
-    if (w < 2) {
-      const double s = lanes_sum<kWaves>(sm[w][lane % kWaves]);
-      if (lane == 0) put(slotA + ((n & 1) * nslot + me) * kGridSlot + w, word_of(s));
+    double rz;
+    W hz[SOLO ? 1 : kH];
+    if constexpr (SOLO) {
+      rr = lanes_sum<kWaves>(sm[0][lane % kWaves]);
+      rz = lanes_sum<kWaves>(sm[1][lane % kWaves]);
+    } else {
+      if (w < 2) {
+        const double s = lanes_sum<kWaves>(sm[w][lane % kWaves]);
+        if (lane == 0) put(slotA + ((n & 1) * nslot + me) * kGridSlot + w, word_of(s));
+      }
+      // the halo of z and the level's sums, whichever comes first
+#pragma unroll
+      for (int q = 0; q < kH; ++q) hz[q] = t + q * kGridThreads < nh ? get(&zc[hrow[t + q * kGridThreads]]) : (W)0;
+      a = 0.0;
+      if (t % 256 < nw)
+        a = value_of(poll(slotA + ((n & 1) * nslot + t % 256) * kGridSlot + t / 256, kEmptySlot, spin, &bad));
+#pragma unroll
+      for (int q = 0; q < kH; ++q)
+        if (hz[q] == GridWord<TX>::empty)
+          hz[q] = poll(&zc[hrow[t + q * kGridThreads]], GridWord<TX>::empty, spin, &bad);
+      a = wave64_sum(a);
+      if (lane == 0) sp[w] = a;
+      __syncthreads();
+      if (bad) break;
+      if (t == 0 && n > 0) put(slotB + (((n + 1) & 1) * nslot + me) * kGridSlot, kEmptySlot);
+      rr = (sp[0] + sp[1]) + (sp[2] + sp[3]);
+      rz = (sp[4] + sp[5]) + (sp[6] + sp[7]);
     }
-    // the halo of z and the level's sums, whichever comes first
-    W hz[kH];
-#pragma unroll
-    for (int q = 0; q < kH; ++q) hz[q] = t + q * kGridThreads < nh ? get(&zc[hrow[t + q * kGridThreads]]) : (W)0;
-    a = 0.0;
-    if (t % 256 < nw)
-      a = value_of(poll(slotA + ((n & 1) * nslot + t % 256) * kGridSlot + t / 256, kEmptySlot, spin, &bad));
-#pragma unroll
-    for (int q = 0; q < kH; ++q)
-      if (hz[q] == GridWord<TX>::empty) hz[q] = poll(&zc[hrow[t + q * kGridThreads]], GridWord<TX>::empty, spin, &bad);
-    a = wave64_sum(a);
-    if (lane == 0) sp[w] = a;
-    __syncthreads();
-    if (bad) break;
-    if (t == 0 && n > 0) put(slotB + (((n + 1) & 1) * nslot + me) * kGridSlot, kEmptySlot);
-    rr = (sp[0] + sp[1]) + (sp[2] + sp[3]);
-    const double rz = (sp[4] + sp[5]) + (sp[6] + sp[7]);
     if (n == 0) bb = rr;
     const bool conv = isfinite(rr) && !(rr > rtol2 * bb);
     if (conv || !isfinite(rr) || !(rz > 0.0) || !isfinite(rz) || n >= maxit) {
@@ -418,12 +442,14 @@ __global__ void __launch_bounds__(kGridThreads)
     rzold = rz;
     pi = zi + beta * pi;
     if (first) pw[i] = pi;
+    if constexpr (!SOLO) {
 #pragma unroll
-    for (int q = 0; q < kH; ++q)
-      if (t + q * kGridThreads < nh) {
-        const int at = nr + t + q * kGridThreads;
-        pw[at] = value_of(hz[q]) + beta * pw[at];
-      }
+      for (int q = 0; q < kH; ++q)
+        if (t + q * kGridThreads < nh) {
+          const int at = nr + t + q * kGridThreads;
+          pw[at] = value_of(hz[q]) + beta * pw[at];
+        }
+    }
     __syncthreads();
     TX q = 0;
 #pragma unroll
@@ -435,27 +461,33 @@ __global__ void __launch_bounds__(kGridThreads)
     q = lanes_sum<G>(q);
     // exchange B: p.q (every earlier store of this workgroup is waited for first)
     a = wave64_sum(first ? (double)pi * (double)q : 0.0);
-    if (lane == 0) sm[0][w] = a;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (w == 0) {
-      const double s = lanes_sum<kWaves>(sm[0][lane % kWaves]);
-      if (lane == 0) put(slotB + ((n & 1) * nslot + me) * kGridSlot, word_of(s));
+    if (lane == 0) sb[w] = a;
+    double pq;
+    if constexpr (SOLO) {
+      __syncthreads();
+      pq = lanes_sum<kWaves>(sb[lane % kWaves]);
+    } else {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      if (w == 0) {
+        const double s = lanes_sum<kWaves>(sb[lane % kWaves]);
+        if (lane == 0) put(slotB + ((n & 1) * nslot + me) * kGridSlot, word_of(s));
+      }
+      a = 0.0;
+      if (t < 256 && t < nw) a = value_of(poll(slotB + ((n & 1) * nslot + t) * kGridSlot, kEmptySlot, spin, &bad));
+      if (w < 4) {
+        a = wave64_sum(a);
+        if (lane == 0) sp[w] = a;
+      }
+      __syncthreads();
+      if (bad) break;
+      pq = (sp[0] + sp[1]) + (sp[2] + sp[3]);
     }
-    a = 0.0;
-    if (t < 256 && t < nw) a = value_of(poll(slotB + ((n & 1) * nslot + t) * kGridSlot, kEmptySlot, spin, &bad));
-    if (w < 4) {
-      a = wave64_sum(a);
-      if (lane == 0) sp[w] = a;
-    }
-    __syncthreads();
-    if (bad) break;
-    const double pq = (sp[0] + sp[1]) + (sp[2] + sp[3]);
     if (!(pq > 0.0) || !isfinite(pq)) {  // cannot happen for SPD A and p != 0
       capped = !(rr <= rtol2 * bb);
       break;
     }
-    if (w < 2 && lane == 0) put(slotA + ((n & 1) * nslot + me) * kGridSlot + w, kEmptySlot);
+    if (!SOLO && w < 2 && lane == 0) put(slotA + ((n & 1) * nslot + me) * kGridSlot + w, kEmptySlot);
     const double alpha = rz / pq;
     xi = (TX)((double)xi + alpha * (double)pi);
     ri = (TX)((double)ri - alpha * (double)q);
@@ -552,34 +584,39 @@ mskm_status cg_grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, con
   int longest = 0;
   for (int l = lo; l <= hi; ++l) longest = std::max(longest, P.h_row[l]);
   const int64_t r0 = h->h_off[lo], n = h->h_off[hi + 1] - r0, ns = (int64_t)4 * P.d.nwg * kGridSlot;
-  grid_empty<TX>(s, z0, z1, r0, n, P.d.slots, ns, aborted);
-  return cg_grid_in_turn(c, [&] {
-#define MSKM_GRID_LAUNCH(PCF, GG, EE)                                                                              \
-  hipLaunchKernelGGL((k_cg_grid<TX, PCF, GG, EE>), dim3(nw), dim3(kGridThreads), 0, s, P.d, w0, h->d_lev,          \
+  // one workgroup per level: no words to empty, no launch to wait for
+  const bool solo = nw == hi - lo + 1;
+  if (!solo) grid_empty<TX>(s, z0, z1, r0, n, P.d.slots, ns, aborted);
+  auto launch = [&] {
+#define MSKM_GRID_LAUNCH(PCF, GG, EE, SS)                                                                          \
+  hipLaunchKernelGGL((k_cg_grid<TX, PCF, GG, EE, SS>), dim3(nw), dim3(kGridThreads), 0, s, P.d, w0, h->d_lev,      \
                      h->diag.rowptr, val, b, x, (W*)z0, (W*)z1, st, aborted, rtol2, maxit, c->grid_spin, pc)
-  if (lanes == 2 && longest <= 64) {
-    if (bj)
-      MSKM_GRID_LAUNCH(true, 2, 32);
+#define MSKM_GRID_FORM(GG, EE)               \
+  do {                                       \
+    if (solo && bj)                          \
+      MSKM_GRID_LAUNCH(true, GG, EE, true);  \
+    else if (solo)                           \
+      MSKM_GRID_LAUNCH(false, GG, EE, true); \
+    else if (bj)                             \
+      MSKM_GRID_LAUNCH(true, GG, EE, false); \
+    else                                     \
+      MSKM_GRID_LAUNCH(false, GG, EE, false); \
+  } while (0)
+    if (lanes == 2 && longest <= 64)
+      MSKM_GRID_FORM(2, 32);
+    else if (lanes == 2)
+      MSKM_GRID_FORM(2, 64);
+    else if (longest <= 48)
+      MSKM_GRID_FORM(1, 48);
     else
-      MSKM_GRID_LAUNCH(false, 2, 32);
-  } else if (lanes == 2) {
-    if (bj)
-      MSKM_GRID_LAUNCH(true, 2, 64);
-    else
-      MSKM_GRID_LAUNCH(false, 2, 64);
-  } else if (longest <= 48) {
-    if (bj)
-      MSKM_GRID_LAUNCH(true, 1, 48);
-    else
-      MSKM_GRID_LAUNCH(false, 1, 48);
-  } else {
-    if (bj)
-      MSKM_GRID_LAUNCH(true, 1, 64);
-    else
-      MSKM_GRID_LAUNCH(false, 1, 64);
-  }
+      MSKM_GRID_FORM(1, 64);
+#undef MSKM_GRID_FORM
 #undef MSKM_GRID_LAUNCH
-  });
+  };
+  if (!solo) return cg_grid_in_turn(c, launch);
+  launch();
+  MSKM_HIP_TRY(hipGetLastError());
+  return MSKM_OK;
 }
 template mskm_status cg_grid_launch<float>(mskm_hier*, int, int, bool, int, const float*, const float*, float*, float*,
                                            float*, CgLevel*, int32_t*, double, int, const PcArgs<float>&);

@@ -927,7 +927,8 @@ __global__ void __launch_bounds__(kBlock)
   cg1_rows<TX, PC>(wt.row0[blk], wt.row1[blk], coef[0], (TX)coef[1], x, r, p, sv, q, pc, rs);
 }
 
-// Small levels: the whole CG solve of a level in one workgroup (one
+// Small levels whose rows are too long for the registers of cg_grid.hip, or of
+// depths with more levels than CUs: the whole CG solve of a level in one workgroup (one
 // workgroup per level, levels lev0 + blockIdx.x), in the single-reduction
 // form and with the decision rule of the kernels above (cg1_decide), so a
 // level stops after the same test. The phases are separated by workgroup
@@ -1492,6 +1493,37 @@ static mskm_status cg_run(mskm_hier* h, SolveWS& W, const TV* dval, const std::v
     hipGraphExec_t next_exec = nullptr;
     return chunk_graph<TV, TX>(h, W, dval, nlo, nhi, x, K, Gn, form, &next_exec);
   };
+  // the whole solve of small and middle levels, and of a depth of large ones in
+  // FP32, in one launch of workgroups that are all on the GPU at once
+  // (cg_grid.hip, cg_stream.hip)
+  if (!mlp && !warm && !W.grid_off) {
+    int lanes = 0, depth = -1;
+    bool all_on = true;
+    for (int l = lo; l <= hi; ++l) all_on = all_on && on[l];
+    if (all_on) MSKM_TRY(cg_grid_ready(h, lo, hi, bj, &lanes));
+    if (all_on && lanes == 0 && sizeof(TX) == 4) MSKM_TRY(cg_stream_ready(h, lo, hi, bj, &depth));
+    if (lanes > 0 || depth >= 0) {
+      for (int l = lo; l <= hi; ++l)
+        if (W.deferred[l]) {
+          MSKM_TRY(flush_deferred(h, W, cs));
+          break;
+        }
+      if (bj) MSKM_TRY(bj_start_side(h));
+      if (lanes > 0) {
+        MSKM_TRY(cg_grid_launch<TX>(h, lo, hi, bj, lanes, dval, b, x, (TX*)W.p0, (TX*)W.p1, W.st, W.aborted,
+                                    rtol * rtol, maxit, pc_args<TX>(h, W)));
+      } else if constexpr (sizeof(TX) == 4) {
+        MSKM_TRY(cg_stream_launch(h, depth, bj, b, x, (TX*)W.p0, (TX*)W.p1, W.st, W.aborted, rtol * rtol, maxit,
+                                  pc_args<TX>(h, W)));
+      }
+      MSKM_HIP_TRY(
+          hipMemcpyAsync(W.h_defer + lo, W.st + lo, (hi - lo + 1) * sizeof(CgLevel), hipMemcpyDeviceToHost, s));
+      MSKM_HIP_TRY(hipMemcpyAsync(W.h_aborted + lo, W.aborted, 4, hipMemcpyDeviceToHost, s));
+      MSKM_HIP_TRY(hipEventRecord(W.ev_defer, s));
+      for (int l = lo; l <= hi; ++l) W.deferred[l] = 1;
+      return capture_next();
+    }
+  }
   if (all_small(on, lo, hi)) {  // one workgroup per level, all iterations in one launch, no host check
     for (int l = lo; l <= hi; ++l)
       if (W.deferred[l]) {  // a state of this level still waits in h_defer
@@ -1526,37 +1558,6 @@ static mskm_status cg_run(mskm_hier* h, SolveWS& W, const TV* dval, const std::v
     MSKM_HIP_TRY(hipEventRecord(W.ev_defer, s));
     for (int l = lo; l <= hi; ++l) W.deferred[l] = 1;
     return capture_next();
-  }
-  // middle levels, and a depth of large ones in FP32: the whole solve in one
-  // launch of workgroups that are all on the GPU at once (cg_grid.hip,
-  // cg_stream.hip)
-  if (!mlp && !warm && !W.grid_off) {
-    int lanes = 0, depth = -1;
-    bool all_on = true;
-    for (int l = lo; l <= hi; ++l) all_on = all_on && on[l];
-    if (all_on) MSKM_TRY(cg_grid_ready(h, lo, hi, bj, &lanes));
-    if (all_on && lanes == 0 && sizeof(TX) == 4) MSKM_TRY(cg_stream_ready(h, lo, hi, bj, &depth));
-    if (lanes > 0 || depth >= 0) {
-      for (int l = lo; l <= hi; ++l)
-        if (W.deferred[l]) {
-          MSKM_TRY(flush_deferred(h, W, cs));
-          break;
-        }
-      if (bj) MSKM_TRY(bj_start_side(h));
-      if (lanes > 0) {
-        MSKM_TRY(cg_grid_launch<TX>(h, lo, hi, bj, lanes, dval, b, x, (TX*)W.p0, (TX*)W.p1, W.st, W.aborted,
-                                    rtol * rtol, maxit, pc_args<TX>(h, W)));
-      } else if constexpr (sizeof(TX) == 4) {
-        MSKM_TRY(cg_stream_launch(h, depth, bj, b, x, (TX*)W.p0, (TX*)W.p1, W.st, W.aborted, rtol * rtol, maxit,
-                                  pc_args<TX>(h, W)));
-      }
-      MSKM_HIP_TRY(
-          hipMemcpyAsync(W.h_defer + lo, W.st + lo, (hi - lo + 1) * sizeof(CgLevel), hipMemcpyDeviceToHost, s));
-      MSKM_HIP_TRY(hipMemcpyAsync(W.h_aborted + lo, W.aborted, 4, hipMemcpyDeviceToHost, s));
-      MSKM_HIP_TRY(hipEventRecord(W.ev_defer, s));
-      for (int l = lo; l <= hi; ++l) W.deferred[l] = 1;
-      return capture_next();
-    }
   }
   for (int l = lo; l <= hi; ++l)
     if (on[l] && W.deferred[l]) {  // a state of this level still waits in h_defer

@@ -60,6 +60,19 @@ def test_level_sizes(top, mixed, bj):
         m.mskm_destroy(ctx)
 
 
+@pytest.mark.parametrize("bj", [False, True])
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("top", [300, 511, 512, 513])
+def test_one_workgroup_levels(top, mixed, bj):
+    import paper_2503_04914_amd as m
+
+    ctx = m.mskm_create(0)
+    try:
+        _check(m, ctx, *_hier(top), mixed, bj)
+    finally:
+        m.mskm_destroy(ctx)
+
+
 @pytest.mark.parametrize("mixed", [False, True])
 @pytest.mark.parametrize("case", ["rows of about 100", "rows past 128", "3-D"])
 def test_row_lengths(case, mixed):
