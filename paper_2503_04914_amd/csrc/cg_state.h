@@ -48,6 +48,17 @@ mskm_status cg_grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, con
                            TX* z0, TX* z1, CgLevel* st, int32_t* aborted, double rtol2, int maxit,
                            const PcArgs<TX>& pc);
 
+// The same for nrhs right-hand sides (b, x: [N][R], R >= nrhs, zeros past them;
+// z0, z1: scratch of that size;
+// states to st[l * R + r]), every column a system of its own. *how: 0 when it
+// takes more launches than are worth it (nothing is queued), 1 queued, 2 queued
+// and *aborted has to be looked at.
+struct MrState;
+template <typename TX>
+mskm_status cg_grid_columns(mskm_hier* h, int lo, int hi, bool bj, const TX* val, const TX* b, TX* x, TX* z0, TX* z1,
+                            int nrhs, int R, MrState* st, int32_t* aborted, double rtol2, int maxit, const PcArgs<TX>& pc,
+                            int* how);
+
 // cg_stream.hip: the same for all levels of one depth, FP32, where they do not
 // fit the registers. cg_stream_ready: *depth is that depth, or -1.
 mskm_status cg_stream_ready(mskm_hier* h, int lo, int hi, bool bj, int* depth);

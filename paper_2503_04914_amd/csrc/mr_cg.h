@@ -34,6 +34,7 @@ struct MrLevStat {
 struct MrWS {
   mskm_ctx* ctx = nullptr;
   MrCfg c{};
+  int nrhs = 0;  // right-hand sides that are not padding
   const MrTiles *D = nullptr, *Lw = nullptr;  // tiles of the blocks (null: row by row)
   double *fi = nullptr, *ai = nullptr;        // FP64 f, alpha [N][R], internal order
   void *beta = nullptr, *t = nullptr, *r = nullptr, *p = nullptr, *q = nullptr, *z = nullptr;
@@ -45,6 +46,8 @@ struct MrWS {
   int32_t* running = nullptr;  // [L] systems of each level still running
   int32_t* on = nullptr;       // [L]
   MrLevStat* stat = nullptr;   // [L]
+  int32_t* aborted = nullptr;  // the persistent form gave up
+  int32_t* h_aborted = nullptr;
   int32_t* h_running[2] = {nullptr, nullptr};  // pinned copies behind the two chunks in flight
   hipEvent_t ev[2] = {nullptr, nullptr};
   void* base = nullptr;
@@ -65,7 +68,7 @@ struct MrWS {
 
 // Vectors a workspace holds: what 0 residual only, 1 FP64 solve, 2 mixed
 // solve, 3 CG only (right-hand side in fi, solution the caller's).
-mskm_status mr_workspace(mskm_hier* h, int R, int what, bool pc, MrWS& W);
+mskm_status mr_workspace(mskm_hier* h, int nrhs, int R, int what, bool pc, MrWS& W);
 
 // CG on A_l X_l = B_l (x0 = 0) for the levels with on[l], all right-hand sides
 // at once. Queues the work; the host waits only to see when every system has

@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <cstring>
 
+#include "cg_state.h"
 #include "device_common.h"
 #include "mr_cg.h"
 
@@ -404,7 +405,8 @@ MrWS::~MrWS() {
   if (pinned) ctx_host_release(ctx, pinned, pinned_bytes);
 }
 
-mskm_status mr_workspace(mskm_hier* h, int R, int what, bool pc, MrWS& W) {
+mskm_status mr_workspace(mskm_hier* h, int nrhs, int R, int what, bool pc, MrWS& W) {
+  W.nrhs = nrhs;
   W.ctx = h->ctx;
   W.pc = pc;
   int LR = 1;
@@ -436,6 +438,7 @@ mskm_status mr_workspace(mskm_hier* h, int R, int what, bool pc, MrWS& W) {
     cv.add(&W.running, L);
     cv.add(&W.on, L);
     cv.add(&W.stat, L);
+    cv.add(&W.aborted, 1);
   }
   MSKM_TRY(cv.alloc(h->ctx, &W.base));
   W.bytes = cv.bytes;
@@ -446,10 +449,11 @@ mskm_status mr_workspace(mskm_hier* h, int R, int what, bool pc, MrWS& W) {
   W.q = q;
   W.z = z;
   if (what == 0) return MSKM_OK;
-  W.pinned_bytes = 2 * L * sizeof(int32_t);
+  W.pinned_bytes = (2 * L + 1) * sizeof(int32_t);
   MSKM_TRY(ctx_host_alloc(h->ctx, W.pinned_bytes, &W.pinned));
   W.h_running[0] = static_cast<int32_t*>(W.pinned);
   W.h_running[1] = W.h_running[0] + L;
+  W.h_aborted = W.h_running[1] + L;
   for (hipEvent_t& e : W.ev) MSKM_HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   MSKM_HIP_TRY(hipMemsetAsync(W.stat, 0, L * sizeof(MrLevStat), h->ctx->stream));
   return MSKM_OK;
@@ -591,13 +595,35 @@ mskm_status mr_cg(mskm_hier* h, MrWS& W, const TV* dval, const std::vector<char>
     else
       inv = h->bj.inv32;
   }
-  // chunk width of the product (timed at the first solve with this R, every level running)
   TX *p = (TX*)W.p, *q = (TX*)W.q;
+  std::vector<int32_t> on32(on.begin(), on.end());
+  MSKM_HIP_TRY(hipMemcpyAsync(W.on, on32.data(), L * 4, hipMemcpyHostToDevice, s));  // pageable: copied before return
+  // small levels: every column solved by workgroups of its own in one launch
+  // (cg_grid.hip). Launched, an iteration is five launches of 3-9 us however
+  // small the level is.
+  bool all_on = dval != nullptr;
+  for (int l = lo; l <= hi; ++l) all_on = all_on && on[l];
+  if (all_on) {
+    int how = 0;
+    const PcArgs<TX> pc{h->bj.start, h->bj.of_row, h->bj.off, inv, nullptr};
+    MSKM_TRY((cg_grid_columns<TX>(h, lo, hi, W.pc, dval, b, x, p, q, W.nrhs, R, W.st, W.aborted, rtol * rtol,
+                                 maxit, pc, &how)));
+    *W.h_aborted = 0;
+    if (how == 2) {
+      MSKM_HIP_TRY(hipMemcpyAsync(W.h_aborted, W.aborted, 4, hipMemcpyDeviceToHost, s));
+      MSKM_HIP_TRY(hipEventRecord(W.ev[0], s));
+      MSKM_HIP_TRY(hipEventSynchronize(W.ev[0]));
+    }
+    if (how > 0 && *W.h_aborted == 0) {
+      hipLaunchKernelGGL(k_mr_stats, dim3(nlev), dim3(kBlock), 0, s, lo, W.st, W.on, W.stat, R);
+      MSKM_HIP_TRY(hipGetLastError());
+      return MSKM_OK;
+    }
+  }
+  // chunk width of the product (timed at the first solve with this R, every level running)
   mr_fill<int32_t>(s, W.running, L, 1);
   const int chunk = mr_chunk_for<TV, TX>(h, W.D, W.c, dval, p, q, W.part_s, W.running);
   const MrRun<TX> run{h, W, lo, hi, chunk, b, x, inv};
-  std::vector<int32_t> on32(on.begin(), on.end());
-  MSKM_HIP_TRY(hipMemcpyAsync(W.on, on32.data(), L * 4, hipMemcpyHostToDevice, s));  // pageable: copied before return
   hipLaunchKernelGGL(k_mr_state, dim3(mr_nblk((int64_t)nlev * R, kBlock)), dim3(kBlock), 0, s, lo, nlev, R,
                      rtol * rtol, maxit, W.st, W.running);
   run.template update<true>();

@@ -389,7 +389,7 @@ mskm_status lagrange_columns(mskm_hier* h, int l, int64_t n0, int R, double rtol
   const int64_t nl = h->h_off[l + 1] - h->h_off[l];
   const int nr = (int)std::max<int64_t>(0, std::min<int64_t>(R, nl - n0));
   MrWS W;
-  MSKM_TRY(mr_workspace(h, R, 3, false, W));
+  MSKM_TRY(mr_workspace(h, R, R, 3, false, W));
   MSKM_TRY(mr_tiles(h, false, &W.D));
   MSKM_HIP_TRY(hipMemsetAsync(W.fi + (size_t)h->h_off[l] * R, 0, (size_t)nl * R * 8, s));
   if (nr > 0)
@@ -420,7 +420,7 @@ mskm_status solve_multi(mskm_hier* h, const double* f_in, int nrhs, const mskm_s
   const int R = mr_width(nrhs);  // right-hand sides with padding
   const int64_t NR = h->N * R, NU = h->N * nrhs;  // internal vectors, the caller's
   MrWS W;
-  MSKM_TRY(mr_workspace(h, R, mixed ? 2 : 1, pc, W));
+  MSKM_TRY(mr_workspace(h, nrhs, R, mixed ? 2 : 1, pc, W));
   MSKM_TRY(mr_tiles(h, false, &W.D));
   MSKM_TRY(mr_tiles(h, true, &W.Lw));
   const double* fdev = f_in;
@@ -505,7 +505,7 @@ mskm_status residual_multi(mskm_hier* h, const double* alpha, const double* f, i
   for (int r0 = 0; r0 < nrhs; r0 += kSlab) {
     const int cnt = std::min(kSlab, nrhs - r0), R = mr_width(cnt);
     MrWS W;
-    const mskm_status st = mr_workspace(h, R, 0, false, W);
+    const mskm_status st = mr_workspace(h, cnt, R, 0, false, W);
     if (st == MSKM_ENOMEM) return MSKM_OK;
     if (st < 0) return st;
     MSKM_TRY(mr_tiles(h, false, &W.D));

@@ -160,3 +160,44 @@ def test_large_fp32_levels(case, bj):
     finally:
         m.mskm_hier_destroy(hd)
         m.mskm_destroy(ctx)
+
+
+@pytest.mark.parametrize("bj", [False, True])
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("R", [3, 33, 300])
+def test_columns(R, mixed, bj):
+    """Many right-hand sides on small levels (in one launch, in several, and too many for it): every column's
+    residual, columns equal to their own solves, and the way back to the launched kernels (spin limit 0)."""
+    import paper_2503_04914_amd as m
+
+    h = synth.halton_hierarchy(sizes=[60, 300, 1200, 4800])
+    F = np.ascontiguousarray(np.stack([synth.fourier_target(1500 + r)(h.points) for r in range(R)], axis=1))
+    F[:, 1] = 0.0
+    set_spin = getattr(m.lib(), "_ZN4mskm16cg_grid_set_spinEP8mskm_ctxi")
+    set_spin.argtypes, set_spin.restype = [ctypes.c_void_p, ctypes.c_int], None
+    kw = dict(algorithm=m.MSKM_ALG_SEQUENTIAL, precond=m.MSKM_PRECOND_BLOCK_JACOBI if bj else m.MSKM_PRECOND_NONE)
+    o = m.solve_opts(precision=m.MSKM_PREC_FP32, cg_rtol=1e-5, target_rel_residual=1e-13, max_refine=20, **kw) \
+        if mixed else m.solve_opts(cg_rtol=1e-13, **kw)
+    bar = 2e-8 if mixed else 2e-10  # two results, each within the repository's bar (1e-8 mixed, 1e-10 FP64)
+    ctx = m.mskm_create(0)
+    hd = m.mskm_hier_create(ctx, h.points, h.offsets, h.delta, fp64=True, fp32=mixed)
+    try:
+        out = []
+        for spin in (1 << 15, 0, 1 << 15):
+            print(f"[columns] spin limit {spin}", flush=True)
+            set_spin(ctx, spin)
+            A = np.zeros_like(F)
+            r = m.mskm_solve(ctx, hd, F, A, o, nrhs=R)
+            assert r.status == m.MSKM_OK, r.report
+            assert m.mskm_residual(ctx, hd, A, F, nrhs=R).max() <= 1e-12
+            assert np.all(A[:, 1] == 0.0)
+            out.append(A)
+        assert np.array_equal(out[0], out[2])
+        assert np.linalg.norm(out[1] - out[0]) <= bar * np.linalg.norm(out[0])
+        for c in {0, R // 2, R - 1}:
+            a = np.zeros(len(F))
+            assert m.mskm_solve(ctx, hd, np.ascontiguousarray(F[:, c]), a, o).status == m.MSKM_OK
+            assert np.linalg.norm(out[0][:, c] - a) <= bar * np.linalg.norm(a)
+    finally:
+        m.mskm_hier_destroy(hd)
+        m.mskm_destroy(ctx)
