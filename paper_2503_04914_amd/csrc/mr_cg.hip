@@ -474,7 +474,7 @@ template void mr_cg_product<double, double>(mskm_hier*, const MrTiles*, const Mr
                                             const double*, double*, const int32_t*, double*);
 
 // Chunk width of the CG product for this R: the fastest of the candidates
-// (64, 128, 256, 512 dividing R) timed once per hierarchy, R and precision on
+// (64, 128, 256, 512, dividing R and not less than a workgroup's) timed once per hierarchy, R and precision on
 // its largest level, then kept (the timing overwrites q and the partials,
 // which the solve rewrites).
 template <typename TV, typename TX>
@@ -489,18 +489,19 @@ int mr_chunk_for(mskm_hier* h, const MrTiles* D, const MrCfg& c, const TV* dval,
   const WorkTable& ws = h->wt_spmv;
   const int b0 = ws.h_lev_begin[big], nb = ws.h_lev_begin[big + 1] - b0;
   hipStream_t s = h->ctx->stream;
-  int best = 64;
+  const int least = std::max(64, mr_cg_width<TX>(c.R));
+  int best = least;
   float best_ms = 0.f;
-  for (int ch = 64; ch <= std::min(c.R, 512); ch *= 2) {
+  for (int ch = least; ch <= std::min(c.R, 512); ch *= 2) {
     if (c.R % ch) continue;
     mr_cg_product<TV, TX>(h, D, c, ch, b0, nb, dval, p, q, running, part);  // warm
     float ms = 0.f;
-    if (hipEventRecord(h->ctx->ev0, s) != hipSuccess) return 64;
+    if (hipEventRecord(h->ctx->ev0, s) != hipSuccess) return least;
     for (int k = 0; k < 2; ++k) mr_cg_product<TV, TX>(h, D, c, ch, b0, nb, dval, p, q, running, part);
     if (hipEventRecord(h->ctx->ev1, s) != hipSuccess || hipEventSynchronize(h->ctx->ev1) != hipSuccess ||
         hipEventElapsedTime(&ms, h->ctx->ev0, h->ctx->ev1) != hipSuccess)
-      return 64;
-    if (ch == 64 || ms < best_ms) {
+      return least;
+    if (ch == least || ms < best_ms) {
       best = ch;
       best_ms = ms;
     }

@@ -43,7 +43,7 @@ inline int mr_width(int nrhs) { return nrhs <= 16 ? 16 : (nrhs + 31) / 32 * 32; 
 // q = A p on the blocks [b0, b0 + nb) of the SpMV work table with partials p.q
 // part[block][ldr], A the diagonal blocks' tiles, p and q [N][ldr]; levels
 // with running[l] = 0 are skipped. The right-hand sides go in slices of `chunk`
-// (the slowest launch dimension; a multiple of 64 dividing ldr, or ldr).
+// (the slowest launch dimension; a multiple of mr_cg_width dividing ldr, or ldr).
 template <typename TX>
 void mr_tile_cg(mskm_hier* h, const MrTiles& D, int ldr, int chunk, int b0, int nb, const TX* p, TX* q,
                 const int32_t* running, double* part);
@@ -61,6 +61,15 @@ template <typename TX>
 inline int mr_lane_rhs(int ldr) {
   if (sizeof(TX) == 4 && ldr % 64 == 0) return 4;
   return ldr % 32 == 0 ? 2 : 1;
+}
+
+// Right-hand sides of one workgroup of mr_tile_cg, which its chunks are
+// multiples of: four waves' slices where the width has whole groups of them
+// (k_mrt_cg4), else one.
+template <typename TX>
+inline int mr_cg_width(int ldr) {
+  const int one = 16 * mr_lane_rhs<TX>(ldr);
+  return one >= 32 && ldr % (4 * one) == 0 ? 4 * one : one;
 }
 
 // ------------------------------------------------------------ device helpers

@@ -262,26 +262,52 @@ bool mr_tiles_built(const mskm_hier* h) {
 
 // ------------------------------------------------------------------ products
 
-// Value of entry e in the product's precision.
+// Values in the product's precision: entries i, i + step, ... from entry e on (past `last`: that one again).
 template <typename T>
 struct TileVals;
 template <>
 struct TileVals<float> {
   const float* v;
-  __device__ __forceinline__ float operator()(int64_t e) const { return v[e]; }
+  template <int N>
+  __device__ __forceinline__ void get(int64_t e, int i, int step, int last, float (&o)[N]) const {
+#pragma unroll
+    for (int u = 0; u < N; ++u) o[u] = (v + e)[(uint32_t)min(i + u * step, last)];
+  }
 };
 template <>
 struct TileVals<double> {
   const double* v;
   const float *hi, *lo;  // without FP64 values: FP32 value + remainder
-  __device__ __forceinline__ double operator()(int64_t e) const { return v ? v[e] : (double)hi[e] + (double)lo[e]; }
+  template <int N>
+  __device__ __forceinline__ void get(int64_t e, int i, int step, int last, double (&o)[N]) const {
+    if (v) {
+#pragma unroll
+      for (int u = 0; u < N; ++u) o[u] = (v + e)[(uint32_t)min(i + u * step, last)];
+    } else {
+      float a[N], b[N];
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        const uint32_t k = (uint32_t)min(i + u * step, last);
+        a[u] = (hi + e)[k];
+        b[u] = (lo + e)[k];
+      }
+#pragma unroll
+      for (int u = 0; u < N; ++u) o[u] = (double)a[u] + (double)b[u];
+    }
+  }
 };
 
-// d += tile * X for right-hand sides c0 + NT n + q; As: the wave's LDS.
+// A wave's LDS: the tile's columns of a pass, and their rows of X.
+template <typename TX>
+struct TileLds {
+  alignas(16) TX a[kTileRows * Mma<TX>::kStride];
+  alignas(16) int32_t c[Mma<TX>::kCols];
+};
+
+// d += tile * X for right-hand sides c0 + NT n + q; S: the wave's LDS.
 template <typename TX, int NT>
-__device__ __forceinline__ void tile_mul(const MrTiles& T, int64_t tile, const TileVals<TX>& val,
-                                         const TX* __restrict__ x, int ldr, int c0, TX* As,
-                                         typename Mma<TX>::acc (&d)[NT]) {
+__device__ __forceinline__ void tile_mul(const MrTiles& T, int64_t tile, const TileVals<TX>& val, const TX* x, int ldr,
+                                         int c0, TileLds<TX>& S, typename Mma<TX>::acc (&d)[NT]) {
   constexpr int CH = Mma<TX>::kCols, ST = Mma<TX>::kStride;
   const int lane = threadIdx.x % kWave, n = lane % 16, k4 = lane / 16;
   const int64_t s0 = T.sptr[tile], s1 = T.sptr[tile + 1], cb = T.cptr[tile];
@@ -289,44 +315,54 @@ __device__ __forceinline__ void tile_mul(const MrTiles& T, int64_t tile, const T
   const TX* xc = x + c0 + NT * n;
   for (int ch = 0; ch * CH < nc; ++ch) {
     const int steps = min(CH, nc - ch * CH) / 16;
-    const int32_t* cl = T.cols + cb + ch * CH + 4 * k4;
-    // rows of X of the first step, columns of the second
-    mi4 c = *reinterpret_cast<const mi4*>(cl);
-    TX b[4][NT];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) load_nt<NT>(xc + (int64_t)c[j] * ldr, b[j]);
-    if (steps > 1) c = *reinterpret_cast<const mi4*>(cl + 16);
-    // the tile's columns of this pass
+    for (int z = lane; z < 16 * steps; z += kWave) S.c[z] = T.cols[cb + ch * CH + z];
     typedef typename VecN<TX, 16 / sizeof(TX)>::type zvec;
-    for (int z = lane; z < kTileRows * ST * (int)sizeof(TX) / 16; z += kWave) reinterpret_cast<zvec*>(As)[z] = (zvec)(TX)0;
+    for (int z = lane; z < kTileRows * ST * (int)sizeof(TX) / 16; z += kWave)
+      reinterpret_cast<zvec*>(S.a)[z] = (zvec)(TX)0;
     __builtin_amdgcn_wave_barrier();
+    // rows of X of the first step; columns of the step after the one asked for
+    mi4 c = *reinterpret_cast<const mi4*>(S.c + 4 * k4);
+    TX b0[4][NT], b1[4][NT];
+    auto rows = [&](int next, TX (&bn)[4][NT]) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) load_nt<NT>(xc + (int64_t)c[j] * ldr, bn[j]);
+      c = *reinterpret_cast<const mi4*>(S.c + 4 * k4 + 16 * min(next, steps - 1));
+      asm volatile("" ::: "memory");
+    };
+    rows(1, b0);
+    // the tile's columns of this pass
     const int64_t ea = T.eptr[s0 + ch * (CH / kTileSeg)];
     const int64_t ee = T.eptr[min(s0 + (ch + 1) * (CH / kTileSeg), s1)];
-    for (int64_t e = ea + lane; e < ee; e += kWave) {
-      const int cd = T.code[e];
-      As[(cd >> 7) * ST + (cd & (CH - 1))] = val(e);
+    const int ne = (int)(ee - ea);
+    for (int e = lane; e < ne; e += 4 * kWave) {
+      int cd[4];
+      TX v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) cd[u] = (T.code + ea)[(uint32_t)min(e + u * kWave, ne - 1)];  // past the end: the last one again
+      val.template get<4>(ea, e, kWave, ne - 1, v);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) S.a[(cd[u] >> 7) * ST + (cd[u] & (CH - 1))] = v[u];
     }
     __builtin_amdgcn_wave_barrier();
-    const TX* Ar = As + n * ST + 4 * k4;
-    for (int s = 0; s < steps; ++s) {
-      TX a[4], bn[4][NT];
+    const TX* Ar = S.a + n * ST + 4 * k4;
+    auto step = [&](int s, TX (&bc)[4][NT]) {
+      TX a[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) a[j] = Ar[16 * s + j];
-      if (s + 1 < steps) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) load_nt<NT>(xc + (int64_t)c[j] * ldr, bn[j]);
-        if (s + 2 < steps) c = *reinterpret_cast<const mi4*>(cl + 16 * (s + 2));
-      }
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int q = 0; q < NT; ++q) d[q] = Mma<TX>::mul(a[j], b[j][q], d[q]);
-      if (s + 1 < steps) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int q = 0; q < NT; ++q) b[j][q] = bn[j][q];
-      }
+        for (int q = 0; q < NT; ++q) d[q] = Mma<TX>::mul(a[j], bc[j][q], d[q]);
+    };
+    // the loads are unconditional (past the end: the last step's rows again)
+    // and held in place by the empty asm statement: under a branch, or sunk to
+    // their use, the products would wait for the ones just issued
+    for (int s = 0; s < steps; ++s) {
+      rows(s + 2, b1);
+      step(s, b0);
+      if (++s >= steps) break;
+      rows(s + 2, b0);
+      step(s, b1);
     }
     __builtin_amdgcn_wave_barrier();
   }
@@ -357,10 +393,10 @@ __device__ __forceinline__ void tile_partial(double (&acc)[NT], double (*sm)[16 
 // waves, one tile each. blockIdx.x = block * sub + slice within the chunk,
 // blockIdx.y the chunk.
 template <typename TX, int NT>
-__global__ void __launch_bounds__(kBlock)
-    k_mrt_cg(const WorkTable wt, int base, int sub, const MrTiles D, const TileVals<TX> val, const TX* __restrict__ p,
+__global__ void __launch_bounds__(kBlock, 4)
+    k_mrt_cg(const WorkTable wt, int base, int sub, const MrTiles D, const TileVals<TX> val, const TX* p,
              TX* __restrict__ q, int ldr, const int32_t* __restrict__ running, double* __restrict__ part) {
-  __shared__ TX As[kBlock / kWave][kTileRows * Mma<TX>::kStride];
+  __shared__ TileLds<TX> As[kBlock / kWave];
   __shared__ double sm[kBlock / kWave][16 * 4];
   const int id = xcd_block_id(gridDim.x);
   const int blk = base + id / sub, c0 = ((int)blockIdx.y * sub + id % sub) * 16 * NT;
@@ -376,16 +412,18 @@ __global__ void __launch_bounds__(kBlock)
 #pragma unroll
     for (int u = 0; u < NT; ++u) d[u] = (typename Mma<TX>::acc)(TX)0;
     tile_mul<TX, NT>(D, 4 * (int64_t)blk + w, val, p, ldr, c0, As[w], d);
+    TX pi[4][NT];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) load_nt<NT>(p + min(r0 + Mma<TX>::row(k4, i), r1 - 1) * ldr + c0 + NT * n, pi[i]);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int64_t row = r0 + Mma<TX>::row(k4, i);
       if (row < r1) {
-        TX pi[NT], qi[NT];
-        load_nt<NT>(p + row * ldr + c0 + NT * n, pi);
+        TX qi[NT];
 #pragma unroll
         for (int u = 0; u < NT; ++u) {
           qi[u] = d[u][i];
-          acc[u] += (double)pi[u] * (double)qi[u];
+          acc[u] += (double)pi[i][u] * (double)qi[u];
         }
         store_nt<NT>(q + row * ldr + c0 + NT * n, qi);
       }
@@ -394,12 +432,170 @@ __global__ void __launch_bounds__(kBlock)
   tile_partial<NT>(acc, sm, part, (size_t)blk * ldr + c0);
 }
 
+// The same for widths of whole groups of four slices: workgroup (block, group
+// of slices), wave w slice w of the group, and four tiles one after the other.
+// The four waves lay a tile's columns out in LDS together, once for four
+// slices, in two buffers in turn, and the next one's entries are on their way
+// in registers while one is multiplied. Sums stay in the wave's lanes over the
+// four tiles: the workgroups of four neighbouring blocks take one tile of the
+// same block at a time, so that the rows of p that an XCD works on (2 MB for
+// 256 right-hand sides) stay in its L2; with a block's tiles in one workgroup
+// 811 MB an iteration came from beyond it instead of 290. Every row has its
+// diagonal entry, so a tile with rows has columns.
+// 262,144 rows with 256 right-hand sides in FP32: 237 us (k_mrt_cg 323 us, or
+// 256 us with its loads in place); the matrix cores are busy for 103 us of it,
+// the vectors' 540 MB take 116 us, and 2.3 GB of rows of p pass from L2 to L1.
+template <typename TX, int NT>
+__global__ void __launch_bounds__(kBlock, 4)
+    k_mrt_cg4(const WorkTable wt, int base, int sub, const MrTiles T, const TileVals<TX> val, const TX* p,
+              TX* __restrict__ q, int ldr, const int32_t* __restrict__ running, double* __restrict__ part) {
+  constexpr int CH = Mma<TX>::kCols, ST = Mma<TX>::kStride, kE = kTileRows * CH / kBlock;
+  constexpr int kVec = kTileRows * ST * (int)sizeof(TX) / 16;  // 16-byte words of a buffer
+  typedef typename VecN<TX, 16 / sizeof(TX)>::type zvec;
+  typedef uint32_t mu4 __attribute__((ext_vector_type(4)));
+  __shared__ __align__(16) TX As[2][kTileRows * ST];
+  __shared__ __align__(16) uint32_t offs[2][CH];  // byte offsets of the columns' rows of p
+  const int id = xcd_block_id(gridDim.x);
+  const int blk = base + id / sub;
+  const int lev = wt.lev[blk];
+  if (running[lev] == 0) return;
+  const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t / kWave), lane = t % kWave;
+  const int n = lane % 16, k4 = lane / 16;
+  const int c0 = (((int)blockIdx.y * sub + id % sub) * (kBlock / kWave) + w) * 16 * NT + NT * n;
+  const uint32_t rowb = (uint32_t)ldr * sizeof(TX), c0b = (uint32_t)c0 * sizeof(TX);
+  // the set's blocks sb .. sb + ns - 1; this workgroup's tiles are j, j + ns, ... of its 4 ns
+  const int lb = wt.lev_begin[lev], sb = lb + (blk - lb) / 4 * 4, ns = min(4, wt.lev_begin[lev + 1] - sb), j = blk - sb;
+  const char* const pb = reinterpret_cast<const char*>(p);
+  auto row_at = [&](uint32_t o) { return reinterpret_cast<const TX*>(pb + (uint32_t)(o + c0b)); };
+  // the pass at hand: the i-th tile (rows r0 ..), its columns ch CH ..
+  int64_t tile = 0, cb = 0, sg = 0, r0 = 0, r1 = 0;
+  int nc = 0, i = -1, ch = 0, ne = 0;
+  auto next_tile = [&] {  // one with rows, if there is one
+    do {
+      ++i;
+      if (i >= 4) return;
+      const int q = j + i * ns, b = sb + q / 4;
+      tile = 4 * (int64_t)b + q % 4;
+      r0 = wt.row0[b] + kTileRows * (q % 4);
+      r1 = wt.row1[b];
+    } while (r0 >= r1);
+    ch = 0;
+    cb = T.cptr[tile];
+    sg = T.sptr[tile];
+    nc = (int)(T.cptr[tile + 1] - cb);
+  };
+  uint32_t cd[kE];
+  TX ev[kE];
+  int32_t col = 0;
+  auto entries = [&] {  // of the pass, to registers
+    const int64_t ea = T.eptr[sg], ee = T.eptr[min(sg + CH / kTileSeg, T.sptr[tile + 1])];
+    ne = (int)(ee - ea);
+    col = T.cols[cb + ch * CH + min(t, min(CH, nc - ch * CH) - 1)];
+    // past the end: the last one again
+#pragma unroll
+    for (int u = 0; u < kE; ++u) cd[u] = (T.code + ea)[(uint32_t)min(u * kBlock + t, ne - 1)];
+    val.template get<kE>(ea, t, kBlock, ne - 1, ev);
+    asm volatile("" ::: "memory");
+  };
+  next_tile();
+  if (i < 4) entries();
+  int buf = 0;
+  for (int z = t; z < kVec; z += kBlock) reinterpret_cast<zvec*>(As[0])[z] = (zvec)(TX)0;
+  double acc[NT];
+  typename Mma<TX>::acc d[NT];
+#pragma unroll
+  for (int u = 0; u < NT; ++u) {
+    acc[u] = 0.0;
+    d[u] = (typename Mma<TX>::acc)(TX)0;
+  }
+  while (i < 4) {
+    __syncthreads();  // the buffer is clear, the other one read
+    const int steps = min(CH, nc - ch * CH) / 16;
+#pragma unroll
+    for (int u = 0; u < kE; ++u)
+      if (u * kBlock + t < ne) As[buf][(cd[u] >> 7) * ST + (cd[u] & (CH - 1))] = ev[u];
+    if (t < 16 * steps) offs[buf][t] = (uint32_t)col * rowb;
+    __syncthreads();
+    const TX* Ar = As[buf] + n * ST + 4 * k4;
+    const uint32_t* Or = offs[buf] + 4 * k4;
+    TX b0[4][NT], b1[4][NT];
+    mu4 o = *reinterpret_cast<const mu4*>(Or);
+    auto rows = [&](int next, TX (&bn)[4][NT]) {  // of the step at o; then o of step `next`
+#pragma unroll
+      for (int j = 0; j < 4; ++j) load_nt<NT>(row_at(o[j]), bn[j]);
+      o = *reinterpret_cast<const mu4*>(Or + 16 * min(next, steps - 1));
+      asm volatile("" ::: "memory");
+    };
+    rows(1, b0);
+    // the next pass
+    const bool last = (ch + 1) * CH >= nc;
+    const int64_t ra = r0, rb = r1;
+    if (last) {
+      next_tile();
+    } else {
+      ++ch;
+      sg += CH / kTileSeg;
+    }
+    buf ^= 1;
+    if (i < 4) {
+      entries();
+      for (int z = t; z < kVec; z += kBlock) reinterpret_cast<zvec*>(As[buf])[z] = (zvec)(TX)0;
+    }
+    auto step = [&](int s, TX (&bc)[4][NT]) {
+      TX a[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) a[j] = Ar[16 * s + j];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int u = 0; u < NT; ++u) d[u] = Mma<TX>::mul(a[j], bc[j][u], d[u]);
+    };
+    for (int s = 0; s < steps; ++s) {
+      rows(s + 2, b1);
+      step(s, b0);
+      if (++s >= steps) break;
+      rows(s + 2, b0);
+      step(s, b1);
+    }
+    if (last) {
+#pragma unroll
+      for (int g = 0; g < 4; g += 2) {
+        TX pi[2][NT];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          load_nt<NT>(row_at((uint32_t)min(ra + Mma<TX>::row(k4, g + h), rb - 1) * rowb), pi[h]);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int64_t row = ra + Mma<TX>::row(k4, g + h);
+          if (row < rb) {
+            TX qi[NT];
+#pragma unroll
+            for (int u = 0; u < NT; ++u) {
+              qi[u] = d[u][g + h];
+              acc[u] += (double)pi[h][u] * (double)qi[u];
+            }
+            store_nt<NT>(q + row * ldr + c0, qi);
+          }
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < NT; ++u) d[u] = (typename Mma<TX>::acc)(TX)0;
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < NT; ++u) {
+    acc[u] += __shfl_xor(acc[u], 16, kWave);
+    acc[u] += __shfl_xor(acc[u], 32, kWave);
+    if (lane < 16) part[(size_t)blk * ldr + c0 + u] = acc[u];
+  }
+}
+
 // y = f - L x.
 template <typename TX, int NT>
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kBlock, 4)
     k_mrt_lower(const WorkTable wt, int base, int sub, const MrTiles Lw, const TileVals<TX> val,
-                const TX* __restrict__ x, const TX* __restrict__ f, TX* __restrict__ y, int ldr) {
-  __shared__ TX As[kBlock / kWave][kTileRows * Mma<TX>::kStride];
+   const TX* x, const TX* __restrict__ f, TX* __restrict__ y, int ldr) {
+  __shared__ TileLds<TX> As[kBlock / kWave];
   const int id = xcd_block_id(gridDim.x);
   const int blk = base + id / sub, c0 = (id % sub) * 16 * NT;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
@@ -410,14 +606,16 @@ __global__ void __launch_bounds__(kBlock)
 #pragma unroll
   for (int u = 0; u < NT; ++u) d[u] = (typename Mma<TX>::acc)(TX)0;
   tile_mul<TX, NT>(Lw, 4 * (int64_t)blk + w, val, x, ldr, c0, As[w], d);
+  TX fi[4][NT];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) load_nt<NT>(f + min(r0 + Mma<TX>::row(k4, i), r1 - 1) * ldr + c0 + NT * n, fi[i]);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int64_t row = r0 + Mma<TX>::row(k4, i);
     if (row < r1) {
-      TX fi[NT], yi[NT];
-      load_nt<NT>(f + row * ldr + c0 + NT * n, fi);
+      TX yi[NT];
 #pragma unroll
-      for (int u = 0; u < NT; ++u) yi[u] = fi[u] - d[u][i];
+      for (int u = 0; u < NT; ++u) yi[u] = fi[i][u] - d[u][i];
       store_nt<NT>(y + row * ldr + c0 + NT * n, yi);
     }
   }
@@ -425,11 +623,11 @@ __global__ void __launch_bounds__(kBlock)
 
 // r = f - (L + D) a in FP64 with partials r.r and f.f.
 template <int NT>
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kBlock, 4)
     k_mrt_residual(const WorkTable wt, int sub, const MrTiles D, const MrTiles Lw, const TileVals<double> dval,
-                   const TileVals<double> lval, const double* __restrict__ a, const double* __restrict__ f,
+                   const TileVals<double> lval, const double* a, const double* __restrict__ f,
                    float* __restrict__ rout, double* __restrict__ rrp, double* __restrict__ ffp, int ldr) {
-  __shared__ double As[kBlock / kWave][kTileRows * Mma<double>::kStride];
+  __shared__ TileLds<double> As[kBlock / kWave];
   __shared__ double sm[kBlock / kWave][16 * 4];
   const int id = xcd_block_id(gridDim.x);
   const int blk = id / sub, c0 = (id % sub) * 16 * NT;
@@ -445,17 +643,19 @@ __global__ void __launch_bounds__(kBlock)
     for (int u = 0; u < NT; ++u) d[u] = (md4)0.0;
     tile_mul<double, NT>(Lw, 4 * (int64_t)blk + w, lval, a, ldr, c0, As[w], d);
     tile_mul<double, NT>(D, 4 * (int64_t)blk + w, dval, a, ldr, c0, As[w], d);
+    double fi[4][NT];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) load_nt<NT>(f + min(r0 + Mma<double>::row(k4, i), r1 - 1) * ldr + c0 + NT * n, fi[i]);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int64_t row = r0 + Mma<double>::row(k4, i);
       if (row < r1) {
-        double fi[NT], ri[NT];
-        load_nt<NT>(f + row * ldr + c0 + NT * n, fi);
+        double ri[NT];
 #pragma unroll
         for (int u = 0; u < NT; ++u) {
-          ri[u] = fi[u] - d[u][i];
+          ri[u] = fi[i][u] - d[u][i];
           prr[u] += ri[u] * ri[u];
-          pff[u] += fi[u] * fi[u];
+          pff[u] += fi[i][u] * fi[i][u];
         }
         if (rout) {
           float r32[NT];
@@ -485,25 +685,37 @@ template <typename TX>
 void mr_tile_cg(mskm_hier* h, const MrTiles& D, int ldr, int chunk, int b0, int nb, const TX* p, TX* q,
                 const int32_t* running, double* part) {
   if (nb <= 0) return;
-  const int nt = mr_lane_rhs<TX>(ldr), width = 16 * nt;
+  const int nt = mr_lane_rhs<TX>(ldr);
+  // k_mrt_cg4 takes a block's tiles one after the other and 32-bit offsets into
+  // p: from kWideBlocks workgroups on
+  // (4,096 of them: 237 us against 256; 1,024: 22.6 against 20.1; 256: 18 against 9)
+  constexpr int kWideBlocks = 2048;
+  const int four = mr_cg_width<TX>(ldr);
+  const bool wide = four > 16 * nt && (int64_t)nb * (ldr / four) >= kWideBlocks &&
+                    (uint64_t)h->N * ldr * sizeof(TX) <= UINT32_MAX;
+  const int width = wide ? four : 16 * nt;
   if (chunk % width || ldr % chunk) chunk = ldr;
   const int sub = chunk / width;
   const dim3 grid(nb * sub, ldr / chunk);
   hipStream_t s = h->ctx->stream;
   const TileVals<TX> v = tile_vals<TX>(D);
-#define MSKM_MRT(NTV)                                                                                             \
-  hipLaunchKernelGGL((k_mrt_cg<TX, NTV>), grid, dim3(kBlock), 0, s, h->wt_spmv, b0, sub, D, v, p, q, ldr, running, \
-                     part)
+#define MSKM_MRT(K, NTV) \
+  hipLaunchKernelGGL((K<TX, NTV>), grid, dim3(kBlock), 0, s, h->wt_spmv, b0, sub, D, v, p, q, ldr, running, part)
   if constexpr (sizeof(TX) == 4) {
     if (nt == 4) {
-      MSKM_MRT(4);
+      if (wide)
+        MSKM_MRT(k_mrt_cg4, 4);
+      else
+        MSKM_MRT(k_mrt_cg, 4);
       return;
     }
   }
-  if (nt == 2)
-    MSKM_MRT(2);
+  if (nt == 2 && wide)
+    MSKM_MRT(k_mrt_cg4, 2);
+  else if (nt == 2)
+    MSKM_MRT(k_mrt_cg, 2);
   else
-    MSKM_MRT(1);
+    MSKM_MRT(k_mrt_cg, 1);
 #undef MSKM_MRT
 }
 template void mr_tile_cg<float>(mskm_hier*, const MrTiles&, int, int, int, int, const float*, float*, const int32_t*,

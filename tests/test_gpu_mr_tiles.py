@@ -77,3 +77,33 @@ def test_residuals_at_once(nrhs):
     finally:
         m.mskm_hier_destroy(hd)
         m.mskm_destroy(ctx)
+
+
+@pytest.mark.parametrize("mode,top", [("fp64", 32900), ("fp32", 65700)])
+def test_wide_groups(mode, top):
+    """Levels of so many blocks that a workgroup takes four slices of right-hand sides (block counts that are
+    no multiple of its sets of four, the last block not full): columns against their own solves."""
+    import paper_2503_04914_amd as m
+
+    R = 512
+    h = synth.halton_hierarchy(sizes=[40, top // 5, top])
+    base = [synth.fourier_target(4300 + r)(h.points) for r in range(4)]
+    F = np.ascontiguousarray(np.stack([base[c % 4] * (1.0 + c) for c in range(R)], axis=1))
+    ctx = m.mskm_create(0)
+    hd = m.mskm_hier_create(ctx, h.points, h.offsets, h.delta, fp64=mode == "fp64", fp32=mode != "fp64")
+    kw = dict(algorithm=m.MSKM_ALG_SEQUENTIAL, precond=m.MSKM_PRECOND_BLOCK_JACOBI)
+    o = m.solve_opts(cg_rtol=1e-13, **kw) if mode == "fp64" else \
+        m.solve_opts(precision=m.MSKM_PREC_FP32, cg_rtol=1e-5, target_rel_residual=1e-13, max_refine=20, **kw)
+    try:
+        A = np.zeros_like(F)
+        r = m.mskm_solve(ctx, hd, F, A, o, nrhs=R)
+        assert r.status == m.MSKM_OK, r.report
+        assert m.mskm_residual(ctx, hd, A, F, nrhs=R).max() <= 1e-12
+        for c in (0, 190, R - 1):
+            a = np.zeros(len(F))
+            assert m.mskm_solve(ctx, hd, np.ascontiguousarray(F[:, c]), a, o).status == m.MSKM_OK
+            # two results, each within the repository's bar (1e-10 FP64, 1e-8 mixed)
+            assert np.linalg.norm(A[:, c] - a) <= (2e-10 if mode == "fp64" else 2e-8) * np.linalg.norm(a)
+    finally:
+        m.mskm_hier_destroy(hd)
+        m.mskm_destroy(ctx)
