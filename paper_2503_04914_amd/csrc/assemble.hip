@@ -157,14 +157,38 @@ __global__ void __launch_bounds__(kBlock) k_bbox_partial(const double* __restric
   }
 }
 
-// Cell key of every point of level l (row-major, axis 0 fastest).
+// Blocks of the launches over the points of all levels: one launch a step
+// instead of one a level, since small levels leave most of the GPU idle: the
+// fill of the 99 levels of sixteen series took 8.4 ms in 99 launches and takes
+// 2.7 ms in one, that of a Halton state of 87,000 sites 0.54 ms and 0.26 ms.
+struct LevelBlocks {
+  int L = 0;
+  const int64_t* in_off = nullptr;  // [L] first input point
+  const int32_t *b64 = nullptr, *b256 = nullptr;  // [L + 1] first block of 64, of kBlock points
+};
+
+// Level of block b (first[l] <= b < first[l + 1]).
+__device__ __forceinline__ int level_of_block(const int32_t* __restrict__ first, int L, int b) {
+  int lo = 0, hi = L - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) / 2;
+    if (first[mid] <= b)
+      lo = mid;
+    else
+      hi = mid - 1;
+  }
+  return lo;
+}
+
+// Cell key of every point (row-major, axis 0 fastest).
 __global__ void __launch_bounds__(kBlock) k_cell_key(const double* __restrict__ pts, int dim,
-                                                     const DevLevel* __restrict__ lev, int l, int64_t off, int64_t n,
+                                                     const DevLevel* __restrict__ lev, const LevelBlocks lb,
                                                      int32_t* __restrict__ key, int32_t* __restrict__ count) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
+  const int l = level_of_block(lb.b256, lb.L, blockIdx.x);
   const DevLevel L = lev[l];
-  const int64_t g = off + i;
+  const int64_t i = (int64_t)(blockIdx.x - lb.b256[l]) * kBlock + threadIdx.x;
+  if (i >= L.n) return;
+  const int64_t g = lb.in_off[l] + i;
   int k = 0, stride = 1;
   for (int d = 0; d < dim; ++d) {
     const int c = cell_coord(pts[g * dim + d], L.lo[d], L.inv_cell, L.nc[d]);
@@ -176,13 +200,14 @@ __global__ void __launch_bounds__(kBlock) k_cell_key(const double* __restrict__ 
 }
 
 // Unordered placement of each point into its cell's slot range.
-__global__ void __launch_bounds__(kBlock) k_cell_scatter(const DevLevel* __restrict__ lev, int l, int64_t off,
-                                                         int64_t n, const int32_t* __restrict__ key,
+__global__ void __launch_bounds__(kBlock) k_cell_scatter(const DevLevel* __restrict__ lev, const LevelBlocks lb,
+                                                         const int32_t* __restrict__ key,
                                                          const int64_t* __restrict__ cs, int32_t* __restrict__ cursor,
                                                          int32_t* __restrict__ tmp) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
-  const int64_t g = off + i;
+  const int l = level_of_block(lb.b256, lb.L, blockIdx.x);
+  const int64_t i = (int64_t)(blockIdx.x - lb.b256[l]) * kBlock + threadIdx.x;
+  if (i >= lev[l].n) return;
+  const int64_t g = lb.in_off[l] + i;
   const int c = lev[l].cs_off + key[g];
   const int pos = atomicAdd(&cursor[c], 1);
   tmp[cs[c] + pos] = (int32_t)g;
@@ -191,14 +216,15 @@ __global__ void __launch_bounds__(kBlock) k_cell_scatter(const DevLevel* __restr
 // Final position = cell start + rank of the input index among the cell's
 // points: the in-cell order is ascending input index, independent of the
 // order in which the scatter's atomics landed.
-__global__ void __launch_bounds__(kBlock) k_cell_rank(const DevLevel* __restrict__ lev, int l, int64_t off,
-                                                      int64_t n, int dim, const double* __restrict__ pts,
+__global__ void __launch_bounds__(kBlock) k_cell_rank(const DevLevel* __restrict__ lev, const LevelBlocks lb, int dim,
+                                                      const double* __restrict__ pts,
                                                       const int32_t* __restrict__ key, const int64_t* __restrict__ cs,
                                                       const int32_t* __restrict__ tmp, int32_t* __restrict__ perm,
                                                       int32_t* __restrict__ iperm, double* __restrict__ xs,
                                                       int64_t N) {
-  const int64_t s = off + (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (s >= off + n) return;
+  const int l = level_of_block(lb.b256, lb.L, blockIdx.x);
+  const int64_t s = lev[l].off + (int64_t)(blockIdx.x - lb.b256[l]) * kBlock + threadIdx.x;
+  if (s >= lev[l].off + lev[l].n) return;
   const int32_t g = tmp[s];
   const int c = lev[l].cs_off + key[g];
   const int64_t a = cs[c], b = cs[c + 1];
@@ -276,15 +302,16 @@ __device__ __forceinline__ T wave_max(T v) {
 
 template <int DIM>
 __global__ void __launch_bounds__(kWave)
-    k_nbr_tile_count(int k, const DevLevel* __restrict__ lev, const int32_t* __restrict__ cs_all,
+    k_nbr_tile_count(const LevelBlocks lb, const DevLevel* __restrict__ lev, const int32_t* __restrict__ cs_all,
                      const double* __restrict__ xs, int64_t N, int64_t* __restrict__ cnt_d,
                      int64_t* __restrict__ cnt_l, int32_t* __restrict__ cnt_lv) {
   __shared__ double sx[kTileCap], sy[kTileCap], sz[DIM == 3 ? kTileCap : 1];
   __shared__ int64_t box_a[kMaxBoxRows];
   __shared__ int32_t box_o[kMaxBoxRows];
+  const int blk = xcd_block_id(gridDim.x), k = level_of_block(lb.b64, lb.L, blk);
   const DevLevel Lk = lev[k];
   const int lane = threadIdx.x;
-  const int64_t r = (int64_t)blockIdx.x * kWave + lane;
+  const int64_t r = (int64_t)(blk - lb.b64[k]) * kWave + lane;
   const bool act = r < Lk.n;
   const int64_t i = Lk.off + (act ? r : 0);
   const double* X = xs;
@@ -413,7 +440,7 @@ __device__ __forceinline__ void wave_lds_sync() {
 
 template <int DIM>
 __global__ void __launch_bounds__(kFillWaves * kWave)
-    k_nbr_tile_fill(int k, const DevLevel* __restrict__ lev, const int32_t* __restrict__ cs_all,
+    k_nbr_tile_fill(const LevelBlocks lb, const DevLevel* __restrict__ lev, const int32_t* __restrict__ cs_all,
                     const double* __restrict__ xs, int64_t N, const int64_t* __restrict__ dptr,
                     int32_t* __restrict__ dcol, double* __restrict__ dval, float* __restrict__ dval32,
                     const int64_t* __restrict__ lptr, int32_t* __restrict__ lcol, double* __restrict__ lval,
@@ -430,11 +457,12 @@ __global__ void __launch_bounds__(kFillWaves * kWave)
   __shared__ int32_t box_cs[kMaxBoxRows * kBoxCols];
   __shared__ int box[8];         // X0, X1, Y0, Y1, Z0, Z1, staged, cell starts staged
   __shared__ int64_t lpos_s[kWave];  // next lower-block position of each row of the tile
+  const int blk = xcd_block_id(gridDim.x), k = level_of_block(lb.b64, lb.L, blk);
   const DevLevel Lk = lev[k];
   const int lane = threadIdx.x % kWave;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
-  const int64_t tile0 = (int64_t)blockIdx.x * kWave;
+  const int64_t tile0 = (int64_t)(blk - lb.b64[k]) * kWave;
   const int nrow_tile = (int)min<int64_t>(kWave, Lk.n - tile0);
   double* const qd = q_d2[w];
   int32_t* const qc = q_col[w];
@@ -728,7 +756,7 @@ __global__ void __launch_bounds__(kBlock) k_point_records(int dim, int L, const 
   reinterpret_cast<double4*>(rec)[i] = r;
 }
 
-static mskm_status build_sell(mskm_hier* h, bool want64, bool want32, bool with_lo);
+static mskm_status build_sell(mskm_hier* h, const LevelBlocks& lb, bool want64, bool want32, bool with_lo);
 
 mskm_status assemble_hierarchy(mskm_hier* h, const double* pts, bool want64, bool want32, bool want_lsell) {
   hipStream_t s = h->ctx->stream;
@@ -820,6 +848,8 @@ mskm_status assemble_hierarchy(mskm_hier* h, const double* pts, bool want64, boo
   //    between kernels would synchronise the device)
   int32_t *key = nullptr, *count = nullptr, *tmp = nullptr;
   int64_t *count64 = nullptr, *cs64 = nullptr, *cnt_d = nullptr, *cnt_l = nullptr, *part = nullptr;
+  int64_t* in_off = nullptr;
+  int32_t *d_b64 = nullptr, *d_b256 = nullptr;
   int32_t* cnt_lv = nullptr;  // [coarser level][N] per-level lower counts (sliced lower copy only)
   int max_depth = 1;
   for (int g = 0; g < h->ngroups; ++g) max_depth = std::max(max_depth, (int)h->h_group_levels[g] - 1);
@@ -836,17 +866,31 @@ mskm_status assemble_hierarchy(mskm_hier* h, const double* pts, bool want64, boo
     cv.add(&cnt_d, N + 1);
     cv.add(&cnt_l, N + 1);
     cv.add(&part, std::max(scan_parts(cs_total), scan_parts(N + 1)));
+    cv.add(&in_off, L);
+    cv.add(&d_b64, (size_t)L + 1);
+    cv.add(&d_b256, (size_t)L + 1);
     MSKM_TRY(cv.alloc(h->ctx, &scratch));
     scratch_bytes = cv.bytes;
   }
   CtxScratch free_scratch{h->ctx, scratch, scratch_bytes};
-  MSKM_HIP_TRY(hipMemsetAsync(count, 0, cs_total * 4, s));
-  for (int l = 0; l < L; ++l) {
-    const int64_t n = h->h_lev[l].n;
-    if (n == 0) continue;
-    hipLaunchKernelGGL(k_cell_key, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, s, pts, dim, h->d_lev, l, h->h_in_off[l],
-                       n, key, count);
+  LevelBlocks lb;
+  int nb64 = 0, nb256 = 0;
+  {
+    std::vector<int32_t> b64(L + 1, 0), b256(L + 1, 0);
+    for (int l = 0; l < L; ++l) {
+      b64[l + 1] = b64[l] + (h->h_lev[l].n + kWave - 1) / kWave;
+      b256[l + 1] = b256[l] + (h->h_lev[l].n + kBlock - 1) / kBlock;
+    }
+    nb64 = b64[L];
+    nb256 = b256[L];
+    MSKM_HIP_TRY(hipMemcpyAsync(in_off, h->h_in_off.data(), (size_t)L * 8, hipMemcpyHostToDevice, s));  // pageable:
+    MSKM_HIP_TRY(hipMemcpyAsync(d_b64, b64.data(), (size_t)(L + 1) * 4, hipMemcpyHostToDevice, s));     // copied before
+    MSKM_HIP_TRY(hipMemcpyAsync(d_b256, b256.data(), (size_t)(L + 1) * 4, hipMemcpyHostToDevice, s));   // return
+    lb = LevelBlocks{L, in_off, d_b64, d_b256};
   }
+  MSKM_HIP_TRY(hipMemsetAsync(count, 0, cs_total * 4, s));
+  if (nb256 > 0)
+    hipLaunchKernelGGL(k_cell_key, dim3(nb256), dim3(kBlock), 0, s, pts, dim, h->d_lev, lb, key, count);
   // widen counts and scan over all levels' tables at once: since every
   // point lands in exactly one cell of its level, the scan value at a
   // level's first cell equals that level's offset, so cs64 holds internal
@@ -859,17 +903,10 @@ mskm_status assemble_hierarchy(mskm_hier* h, const double* pts, bool want64, boo
   MSKM_TRY(halloc(h, &h->perm, N));
   MSKM_TRY(halloc(h, &h->iperm, N));
   MSKM_TRY(halloc(h, &h->xs, (size_t)dim * N));
-  for (int l = 0; l < L; ++l) {
-    const int64_t n = h->h_lev[l].n;
-    if (n == 0) continue;
-    hipLaunchKernelGGL(k_cell_scatter, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, s, h->d_lev, l, h->h_in_off[l], n, key,
-                       cs64, count, tmp);
-  }
-  for (int l = 0; l < L; ++l) {
-    const int64_t n = h->h_lev[l].n;
-    if (n == 0) continue;
-    hipLaunchKernelGGL(k_cell_rank, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, s, h->d_lev, l, h->h_off[l], n, dim, pts,
-                       key, cs64, tmp, h->perm, h->iperm, h->xs, N);
+  if (nb256 > 0) {
+    hipLaunchKernelGGL(k_cell_scatter, dim3(nb256), dim3(kBlock), 0, s, h->d_lev, lb, key, cs64, count, tmp);
+    hipLaunchKernelGGL(k_cell_rank, dim3(nb256), dim3(kBlock), 0, s, h->d_lev, lb, dim, pts, key, cs64, tmp, h->perm,
+                       h->iperm, h->xs, N);
   }
 
   // point records for the SpMV variants that recompute entry values
@@ -880,15 +917,10 @@ mskm_status assemble_hierarchy(mskm_hier* h, const double* pts, bool want64, boo
   // 4. count pass
   MSKM_HIP_TRY(hipMemsetAsync(cnt_d + N, 0, 8, s));
   MSKM_HIP_TRY(hipMemsetAsync(cnt_l + N, 0, 8, s));
-  for (int k = 0; k < L; ++k) {
-    const int64_t n = h->h_lev[k].n;
-    if (n == 0) continue;
-    if (dim == 3)
-      hipLaunchKernelGGL(k_nbr_tile_count<3>, dim3(grid_for(n, kWave)), dim3(kWave), 0, s, k, h->d_lev, h->cell_start,
-                         h->xs, N, cnt_d, cnt_l, cnt_lv);
-    else
-      hipLaunchKernelGGL(k_nbr_tile_count<2>, dim3(grid_for(n, kWave)), dim3(kWave), 0, s, k, h->d_lev, h->cell_start,
-                         h->xs, N, cnt_d, cnt_l, cnt_lv);
+  if (nb64 > 0) {
+    auto* count_k = dim == 3 ? k_nbr_tile_count<3> : k_nbr_tile_count<2>;
+    hipLaunchKernelGGL(count_k, dim3(nb64), dim3(kWave), 0, s, lb, h->d_lev, h->cell_start, h->xs, N, cnt_d, cnt_l,
+                       cnt_lv);
   }
   MSKM_TRY(halloc(h, &h->diag.rowptr, N + 1));
   MSKM_TRY(halloc(h, &h->lower.rowptr, N + 1));
@@ -911,19 +943,13 @@ mskm_status assemble_hierarchy(mskm_hier* h, const double* pts, bool want64, boo
     if (want32) MSKM_HIP_TRY(hipMemsetAsync(c->val32 + c->nnz, 0, kCsrPad * 4, s));
     if (want_lo) MSKM_HIP_TRY(hipMemsetAsync(c->val32lo + c->nnz, 0, kCsrPad * 4, s));
   }
-  for (int k = 0; k < L; ++k) {
-    const int64_t n = h->h_lev[k].n;
-    if (n == 0) continue;
-    if (dim == 3)
-      hipLaunchKernelGGL(k_nbr_tile_fill<3>, dim3(grid_for(n, kWave)), dim3(kFillWaves * kWave), 0, s, k, h->d_lev,
-                         h->cell_start, h->xs, N, h->diag.rowptr, h->diag.col, h->diag.val, h->diag.val32, h->lower.rowptr,
-                         h->lower.col, h->lower.val, h->lower.val32, h->diag.val32lo, h->lower.val32lo);
-    else
-      hipLaunchKernelGGL(k_nbr_tile_fill<2>, dim3(grid_for(n, kWave)), dim3(kFillWaves * kWave), 0, s, k, h->d_lev,
-                         h->cell_start, h->xs, N, h->diag.rowptr, h->diag.col, h->diag.val, h->diag.val32, h->lower.rowptr,
-                         h->lower.col, h->lower.val, h->lower.val32, h->diag.val32lo, h->lower.val32lo);
+  if (nb64 > 0) {
+    auto* fill_k = dim == 3 ? k_nbr_tile_fill<3> : k_nbr_tile_fill<2>;
+    hipLaunchKernelGGL(fill_k, dim3(nb64), dim3(kFillWaves * kWave), 0, s, lb, h->d_lev, h->cell_start, h->xs, N,
+                       h->diag.rowptr, h->diag.col, h->diag.val, h->diag.val32, h->lower.rowptr, h->lower.col,
+                       h->lower.val, h->lower.val32, h->diag.val32lo, h->lower.val32lo);
   }
-  MSKM_TRY(build_sell(h, want64, want32, want_lsell));
+  MSKM_TRY(build_sell(h, lb, want64, want32, want_lsell));
   if (want_lsell) MSKM_TRY(build_lsell(h, want64, want32, cnt_lv));
   MSKM_HIP_TRY(hipEventRecord(h->ev_asm[1], s));
   h->asm_pending = true;  // assemble_ms is read at the first statistics query
@@ -933,13 +959,15 @@ mskm_status assemble_hierarchy(mskm_hier* h, const double* pts, bool want64, boo
 
 // ------------------------------------------------------------------ SELL
 
-// Row of every slot: slot t of the level's slices holds row off + t, or -1
-// past the level's last row.
-__global__ void __launch_bounds__(kBlock) k_sell_rows(int64_t off, int64_t n, int64_t slot0, int64_t nslots,
+// Row of every slot (one wave per slice; a level's slices are its blocks of 64
+// rows): slot t of the level's slices holds row off + t, or -1 past the level's
+// last row.
+static_assert(kSellC == kWave, "a slice is a block of 64 rows");
+__global__ void __launch_bounds__(kSellC) k_sell_rows(const LevelBlocks lb, const DevLevel* __restrict__ lev,
                                                       int32_t* __restrict__ rows) {
-  const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (t >= nslots) return;
-  rows[slot0 + t] = t < n ? (int32_t)(off + t) : -1;
+  const int l = level_of_block(lb.b64, lb.L, blockIdx.x);
+  const int64_t t = (int64_t)(blockIdx.x - lb.b64[l]) * kSellC + threadIdx.x;
+  rows[(int64_t)blockIdx.x * kSellC + threadIdx.x] = t < lev[l].n ? (int32_t)(lev[l].off + t) : -1;
 }
 
 // Width (in entries, w_s * kSellC) of every slice: its longest row rounded
@@ -1053,7 +1081,7 @@ __global__ void __launch_bounds__(kSellC)
   for (int64_t d = sptr[s] + threadIdx.x; d < sptr[s + 1]; d += kSellC) col16[d] = (uint16_t)(scol[d] - b);
 }
 
-static mskm_status build_sell(mskm_hier* h, bool want64, bool want32, bool with_lo) {
+static mskm_status build_sell(mskm_hier* h, const LevelBlocks& lb, bool want64, bool want32, bool with_lo) {
   hipStream_t s = h->ctx->stream;
   Sell& S = h->sell;
   const int L = h->L;
@@ -1063,12 +1091,8 @@ static mskm_status build_sell(mskm_hier* h, bool want64, bool want32, bool with_
   S.nslices = S.h_slice_begin[L];
   MSKM_TRY(halloc(h, &S.rows, (size_t)S.nslices * kSellC));
   MSKM_TRY(halloc(h, &S.sptr, (size_t)S.nslices + 1));
-  for (int l = 0; l < L; ++l) {
-    const int64_t nslots = (S.h_slice_begin[l + 1] - S.h_slice_begin[l]) * kSellC;
-    if (nslots > 0)
-      hipLaunchKernelGGL(k_sell_rows, dim3(grid_for(nslots, kBlock)), dim3(kBlock), 0, s, h->h_off[l],
-                         h->h_off[l + 1] - h->h_off[l], S.h_slice_begin[l] * kSellC, nslots, S.rows);
-  }
+  if (S.nslices > 0)
+    hipLaunchKernelGGL(k_sell_rows, dim3((unsigned)S.nslices), dim3(kSellC), 0, s, lb, h->d_lev, S.rows);
   // scratch: slice widths, scan partials, the wide-slice counter
   int64_t *d_w = nullptr, *part = nullptr;
   int32_t* d_wide = nullptr;

@@ -28,11 +28,11 @@ namespace mskm {
 // coarser levels (columns ascend, coarsest level first); cnt_lv is
 // level-major, cnt_lv[q N + row].
 __global__ void __launch_bounds__(kSellC)
-    k_lsell_count(int64_t s0, int64_t ns, int64_t seg0, int nseg_per_slice, const int32_t* __restrict__ rows,
+    k_lsell_count(const int64_t* __restrict__ slice_seg, const int32_t* __restrict__ rows,
                   const int64_t* __restrict__ rp, const int32_t* __restrict__ col, const int32_t* __restrict__ cnt_lv,
                   int64_t N, int64_t* __restrict__ w, int32_t* __restrict__ base, int32_t* __restrict__ wide) {
-  if (blockIdx.x >= ns) return;
-  const int64_t sl = s0 + blockIdx.x;
+  const int64_t sl = blockIdx.x, seg0 = slice_seg[sl];
+  const int nseg_per_slice = (int)(slice_seg[sl + 1] - seg0);
   const int t = threadIdx.x;
   const int32_t row = rows[sl * kSellC + t];
   int64_t a = row >= 0 ? rp[row] : 0;
@@ -47,7 +47,7 @@ __global__ void __launch_bounds__(kSellC)
       hi = max(hi, __shfl_xor(hi, o, kSellC));
     }
     if (t == 0) {
-      const int64_t sg = seg0 + (int64_t)blockIdx.x * nseg_per_slice + q;
+      const int64_t sg = seg0 + q;
       w[sg] = (cnt + 3) / 4 * 4 * kSellC;
       base[sg] = hi >= 0 ? lo : 0;
       if (hi >= 0 && hi - lo > 65535) atomicAdd(wide, 1);
@@ -68,14 +68,14 @@ constexpr int kLsWaves = 4;
 constexpr int kLsRows = kSellC / kLsWaves;   // slots per wave
 constexpr int kLsGroups = kSellC / kLsRows;  // groups per wave step
 __global__ void __launch_bounds__(kLsWaves * kSellC)
-    k_lsell_fill(int64_t s0, int64_t ns, int64_t seg0, int nseg_per_slice, const int32_t* __restrict__ rows,
+    k_lsell_fill(const int64_t* __restrict__ slice_seg, const int32_t* __restrict__ rows,
                  const int64_t* __restrict__ rp, const int32_t* __restrict__ col, const double* __restrict__ val,
                  const float* __restrict__ val32, const float* __restrict__ lo32, const int32_t* __restrict__ cnt_lv,
                  int64_t N, const int64_t* __restrict__ seg_ptr, const int32_t* __restrict__ base,
                  uint16_t* __restrict__ scol, double* __restrict__ sval, float* __restrict__ sval32,
                  float* __restrict__ slo) {
-  if (blockIdx.x >= ns) return;
-  const int64_t sl = s0 + blockIdx.x;
+  const int64_t sl = blockIdx.x, seg0 = slice_seg[sl];
+  const int nseg_per_slice = (int)(slice_seg[sl + 1] - seg0);
   const int lane = threadIdx.x % kSellC, w = threadIdx.x / kSellC;
   const int t = w * kLsRows + lane % kLsRows, gl = lane / kLsRows;
   const int32_t row = rows[sl * kSellC + t];
@@ -83,7 +83,7 @@ __global__ void __launch_bounds__(kLsWaves * kSellC)
   typedef unsigned short us4 __attribute__((ext_vector_type(4)));
   for (int q = 0; q < nseg_per_slice; ++q) {
     const int64_t n = row >= 0 ? cnt_lv[q * N + row] : 0;
-    const int64_t sg = seg0 + (int64_t)blockIdx.x * nseg_per_slice + q;
+    const int64_t sg = seg0 + q;
     const int64_t e0 = seg_ptr[sg], groups = (seg_ptr[sg + 1] - e0) / (4 * kSellC);
     const int32_t cb = base[sg];
     for (int64_t g = gl; g < groups; g += kLsGroups) {
@@ -167,12 +167,16 @@ mskm_status build_lsell(mskm_hier* h, bool want64, bool want32, const int32_t* c
   } free_base{h->ctx, &base, (size_t)X.nseg * 4};
   MSKM_HIP_TRY(hipMemsetAsync(wide, 0, 4, s));
   MSKM_HIP_TRY(hipMemsetAsync(w + X.nseg, 0, 8, s));
-  for (int l = 0; l < L; ++l) {
-    const int64_t ns = S.h_slice_begin[l + 1] - S.h_slice_begin[l];
-    if (ns == 0 || h->h_depth[l] == 0) continue;
-    hipLaunchKernelGGL(k_lsell_count, dim3((unsigned)ns), dim3(kSellC), 0, s, S.h_slice_begin[l], ns, seg0[l],
-                       h->h_depth[l], S.rows, h->lower.rowptr, h->lower.col, cnt_lv, h->N, w, base, wide);
-  }
+  // the first segment of every slice (host table, then device)
+  std::vector<int64_t> ss((size_t)S.nslices + 1, 0);
+  for (int l = 0; l < L; ++l)
+    for (int64_t sl = S.h_slice_begin[l]; sl < S.h_slice_begin[l + 1]; ++sl)
+      ss[sl] = seg0[l] + (sl - S.h_slice_begin[l]) * h->h_depth[l];
+  ss[S.nslices] = X.nseg;
+  MSKM_TRY(halloc(h, &X.slice_seg, ss.size()));
+  MSKM_TRY(upload_async(h, X.slice_seg, ss.data(), ss.size() * 8));
+  hipLaunchKernelGGL(k_lsell_count, dim3((unsigned)S.nslices), dim3(kSellC), 0, s, X.slice_seg, S.rows, h->lower.rowptr,
+                     h->lower.col, cnt_lv, h->N, w, base, wide);
   int32_t hwide = 0;
   MSKM_HIP_TRY(hipMemcpyAsync(&hwide, wide, 4, hipMemcpyDeviceToHost, s));
   MSKM_HIP_TRY(hipStreamSynchronize(s));
@@ -185,26 +189,14 @@ mskm_status build_lsell(mskm_hier* h, bool want64, bool want32, const int32_t* c
   if (want64) MSKM_TRY(halloc(h, &X.val, (size_t)X.entries));
   if (want32) MSKM_TRY(halloc(h, &X.val32, (size_t)X.entries));
   if (h->lower.val32lo) MSKM_TRY(halloc(h, &X.lo, (size_t)X.entries));
-  for (int l = 0; l < L; ++l) {
-    const int64_t ns = S.h_slice_begin[l + 1] - S.h_slice_begin[l];
-    if (ns == 0 || h->h_depth[l] == 0) continue;
-    hipLaunchKernelGGL(k_lsell_fill, dim3((unsigned)ns), dim3(kLsWaves * kSellC), 0, s, S.h_slice_begin[l], ns, seg0[l],
-                       h->h_depth[l], S.rows, h->lower.rowptr, h->lower.col, h->lower.val, h->lower.val32,
-                       h->lower.val32lo, cnt_lv, h->N, X.seg_ptr, base, X.col16, X.val, X.val32, X.lo);
-  }
+  hipLaunchKernelGGL(k_lsell_fill, dim3((unsigned)S.nslices), dim3(kLsWaves * kSellC), 0, s, X.slice_seg, S.rows,
+                     h->lower.rowptr, h->lower.col, h->lower.val, h->lower.val32, h->lower.val32lo, cnt_lv, h->N,
+                     X.seg_ptr, base, X.col16, X.val, X.val32, X.lo);
   h->allocs.push_back(base);
   h->alloc_bytes.push_back((size_t)X.nseg * 4);
   h->device_bytes += X.nseg * 4;
   X.seg_base = base;
   base = nullptr;
-  // the first segment of every slice (host table, then device)
-  std::vector<int64_t> ss((size_t)S.nslices + 1, 0);
-  for (int l = 0; l < L; ++l)
-    for (int64_t sl = S.h_slice_begin[l]; sl < S.h_slice_begin[l + 1]; ++sl)
-      ss[sl] = seg0[l] + (sl - S.h_slice_begin[l]) * h->h_depth[l];
-  ss[S.nslices] = X.nseg;
-  MSKM_TRY(halloc(h, &X.slice_seg, ss.size()));
-  MSKM_TRY(upload_async(h, X.slice_seg, ss.data(), ss.size() * 8));
   X.built = true;
   MSKM_HIP_TRY(hipGetLastError());
   return MSKM_OK;
