@@ -1,6 +1,7 @@
 // Many-right-hand-side CG (mr_cg.hip) and its workspace.
 #pragma once
 
+#include <memory>
 #include <vector>
 
 #include "mr_tiles.h"
@@ -76,6 +77,21 @@ mskm_status mr_workspace(mskm_hier* h, int nrhs, int R, int what, bool pc, MrWS&
 template <typename TV, typename TX>
 mskm_status mr_cg(mskm_hier* h, MrWS& W, const TV* dval, const std::vector<char>& on, const TX* b, TX* x, double rtol,
                   int maxit, int K);
+
+// Coefficient vectors of Lagrange functions (Section 4; solve_mr.hip): columns
+// of A_l^-1 by CG from zero with unit right-hand sides, `width` at a time. The
+// workspace and the captured iterations serve every call of columns().
+struct LagrangeSolver {
+  mskm_hier* h = nullptr;
+  int R = 0;
+  std::unique_ptr<MrWS> W;
+  mskm_status open(mskm_hier* h, int width);
+  // Columns n0 .. n0 + R - 1 of level l: Z [N][R] FP64 device, internal order,
+  // rows of level l written (columns past the level's end are zero).
+  mskm_status columns(int l, int64_t n0, double rtol, int maxit, double* Z);
+  // CG iterations so far (sum over all systems), and whether a cap stopped one.
+  mskm_status totals(int64_t* iters, bool* capped);
+};
 
 // Row-by-row CG product (solve_mr.hip), where there are no tiles.
 template <typename TV, typename TX>

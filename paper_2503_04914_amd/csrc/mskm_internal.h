@@ -492,13 +492,6 @@ mskm_status train_pairs(mskm_hier* h, const double* f, int nrhs, bool io_dev, do
 
 // solve_mr.hip: many right-hand sides in the same launches (2 <= nrhs <= 512)
 bool mr_supported(int nrhs);
-// Columns n0 .. n0+R-1 of A_l^-1 (the coefficient vectors of level l's
-// Lagrange functions, Section 4) by CG from zero on A_l with unit right-hand
-// sides: Z [N][R] FP64 device, internal order, rows of level l written
-// (columns past the level's end are zero). The CG iterations (sum over the
-// R systems) and whether a cap stopped one are returned.
-mskm_status lagrange_columns(mskm_hier* h, int l, int64_t n0, int R, double rtol, int maxit, double* Z,
-                             int64_t* iters, bool* capped);
 mskm_status solve_multi(mskm_hier* h, const double* f, int nrhs, const mskm_solve_opts* o, double* alpha,
                         mskm_report* rep);
 // solve_mr.hip: residuals of several right-hand sides at once (device vectors,

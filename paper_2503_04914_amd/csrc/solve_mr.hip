@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <new>
 #include <string>
 
 #include "device_common.h"
@@ -380,28 +381,42 @@ __global__ void __launch_bounds__(kBlock) k_mr_unit(double* __restrict__ E, int6
   if (r < nr) E[(off + n0 + r) * R + r] = 1.0;
 }
 
-mskm_status lagrange_columns(mskm_hier* h, int l, int64_t n0, int R, double rtol, int maxit, double* Z,
-                             int64_t* iters, bool* capped) {
+mskm_status LagrangeSolver::open(mskm_hier* hier, int width) {
+  h = hier;
+  R = width;
   if (R < 1 || R > 64 * kMaxRPerLane || R != mr_width(R))
-    return fail(MSKM_EINVAL, "lagrange_columns: R must be 16 or a multiple of 32 up to 512");
-  if (!h->diag.val) return fail(MSKM_ESTATE, "lagrange_columns: FP64 values are not stored");
+    return fail(MSKM_EINVAL, "Lagrange columns: the width must be 16 or a multiple of 32 up to 512");
+  if (!h->diag.val) return fail(MSKM_ESTATE, "Lagrange columns: FP64 values are not stored");
+  W.reset(new (std::nothrow) MrWS());
+  if (!W) return fail(MSKM_ENOMEM, "host memory");
+  MSKM_TRY(mr_workspace(h, R, R, 3, false, *W));
+  return mr_tiles(h, false, &W->D);
+}
+
+mskm_status LagrangeSolver::columns(int l, int64_t n0, double rtol, int maxit, double* Z) {
   hipStream_t s = h->ctx->stream;
   const int64_t nl = h->h_off[l + 1] - h->h_off[l];
   const int nr = (int)std::max<int64_t>(0, std::min<int64_t>(R, nl - n0));
-  MrWS W;
-  MSKM_TRY(mr_workspace(h, R, R, 3, false, W));
-  MSKM_TRY(mr_tiles(h, false, &W.D));
-  MSKM_HIP_TRY(hipMemsetAsync(W.fi + (size_t)h->h_off[l] * R, 0, (size_t)nl * R * 8, s));
+  MSKM_HIP_TRY(hipMemsetAsync(W->fi + (size_t)h->h_off[l] * R, 0, (size_t)nl * R * 8, s));
   if (nr > 0)
-    hipLaunchKernelGGL(k_mr_unit, dim3((nr + kBlock - 1) / kBlock), dim3(kBlock), 0, s, W.fi, h->h_off[l], n0, nr, R);
+    hipLaunchKernelGGL(k_mr_unit, dim3((nr + kBlock - 1) / kBlock), dim3(kBlock), 0, s, W->fi, h->h_off[l], n0, nr, R);
+  W->nrhs = std::max(nr, 1);
   std::vector<char> on(h->L, 0);
   on[l] = 1;
-  MSKM_TRY((mr_cg<double, double>(h, W, h->diag.val, on, W.fi, Z, rtol, maxit, 8)));
-  MrLevStat S;
-  MSKM_HIP_TRY(hipMemcpyAsync(&S, W.stat + l, sizeof(S), hipMemcpyDeviceToHost, s));
+  return mr_cg<double, double>(h, *W, h->diag.val, on, W->fi, Z, rtol, maxit, 8);
+}
+
+mskm_status LagrangeSolver::totals(int64_t* iters, bool* capped) {
+  hipStream_t s = h->ctx->stream;
+  std::vector<MrLevStat> S(h->L);
+  MSKM_HIP_TRY(hipMemcpyAsync(S.data(), W->stat, S.size() * sizeof(MrLevStat), hipMemcpyDeviceToHost, s));
   MSKM_HIP_TRY(hipStreamSynchronize(s));
-  if (iters) *iters = S.iters;
-  if (capped) *capped = S.capped != 0;
+  *iters = 0;
+  *capped = false;
+  for (const MrLevStat& l : S) {
+    *iters += l.iters;
+    *capped |= l.capped != 0;
+  }
   return MSKM_OK;
 }
 

@@ -27,7 +27,7 @@
 #include <limits>
 
 #include "device_common.h"
-#include "mr_tiles.h"
+#include "mr_cg.h"
 
 namespace mskm {
 
@@ -160,12 +160,16 @@ __device__ __forceinline__ int64_t lower_bound_col(const int32_t* __restrict__ c
 //   X[i][n] = sum over the lower CSR's level-j entries (m, b) of row i of
 //             b * Z[m][n - c0],
 // Z [N][R] holding A_j^-1 e_n for the chunk's centres (rows of level j).
+// One wave per row, a lane per kept entry: the row's entries of B are the same
+// words for all lanes and neighbouring lanes read neighbouring columns of Z. (One
+// thread per row left a level of 4,096 rows on 16 workgroups: 190 us a
+// launch, now 13.)
 __global__ void __launch_bounds__(kBlock)
     k_trunc_values(int64_t r0, int64_t r1, int64_t j0, int64_t j1, int64_t c0, int R,
                    const int64_t* __restrict__ lrp, const int32_t* __restrict__ lcol, const double* __restrict__ lval,
                    const double* __restrict__ Z, const int64_t* __restrict__ xrp, const int32_t* __restrict__ xcol,
                    double* __restrict__ xval) {
-  const int64_t i = r0 + (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  const int64_t i = r0 + (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
   if (i >= r1) return;
   // kept entries of row i in the chunk
   const int64_t xa = xrp[i], xe = xrp[i + 1];
@@ -176,10 +180,11 @@ __global__ void __launch_bounds__(kBlock)
   // row i's entries of B_kj in the lower CSR
   const int64_t la = lower_bound_col(lcol, lrp[i], lrp[i + 1], j0);
   const int64_t le = lower_bound_col(lcol, la, lrp[i + 1], j1);
-  for (int64_t e = ea; e < ee; ++e) {
-    const int64_t r = (int64_t)xcol[e] - c0;
+  for (int64_t e = ea + threadIdx.x % kWave; e < ee; e += kWave) {
+    const double* const Zr = Z + ((int64_t)xcol[e] - c0);
     double acc = 0.0;
-    for (int64_t k = la; k < le; ++k) acc += lval[k] * Z[(int64_t)lcol[k] * R + r];
+#pragma unroll 8
+    for (int64_t k = la; k < le; ++k) acc += lval[k] * Zr[(int64_t)lcol[k] * R];
     xval[e] = acc;
   }
 }
@@ -306,28 +311,34 @@ mskm_status trunc_build(mskm_hier* h, double T, double cg_rtol, mskm_trunc* tr) 
     return m;
   }();
   const int R = mr_width((int)std::max<int64_t>(1, std::min<int64_t>(kChunk, maxn)));
-  if (nnz > 0 && maxn > 0) MSKM_TRY(sc.get(&Z, (size_t)N * R));
+  LagrangeSolver lag;  // workspace and captured iterations for all chunks
+  if (nnz > 0 && maxn > 0) {
+    MSKM_TRY(sc.get(&Z, (size_t)N * R));
+    MSKM_TRY(lag.open(h, R));
+  }
   tr->cg_iters = 0;
   tr->capped = false;
   for (int j = 0; j < L && nnz > 0; ++j) {
     if (h->h_next[j] < 0) continue;  // no finer level: no block has centres here
     const int64_t nj = h->h_off[j + 1] - h->h_off[j];
     for (int64_t n0 = 0; n0 < nj; n0 += R) {
-      int64_t it = 0;
-      bool capped = false;
-      MSKM_TRY(lagrange_columns(h, j, n0, R, cg_rtol, 20000, Z, &it, &capped));
-      tr->cg_iters += it;
-      tr->capped |= capped;
+      MSKM_TRY(lag.columns(j, n0, cg_rtol, 20000, Z));
       for (int k = h->h_next[j]; k >= 0; k = h->h_next[k]) {
         const int64_t nk = h->h_off[k + 1] - h->h_off[k];
         if (nk == 0) continue;
-        hipLaunchKernelGGL(k_trunc_values, dim3(grid_rows(nk)), dim3(kBlock), 0, s, h->h_off[k], h->h_off[k + 1],
-                           h->h_off[j], h->h_off[j + 1], h->h_off[j] + n0, R, h->lower.rowptr, h->lower.col,
-                           h->lower.val, Z, tr->X.rowptr, tr->X.col, tr->X.val);
+        const unsigned waves = kBlock / kWave;
+        hipLaunchKernelGGL(k_trunc_values, dim3((unsigned)((nk + waves - 1) / waves)), dim3(kBlock), 0, s, h->h_off[k],
+                           h->h_off[k + 1], h->h_off[j], h->h_off[j + 1], h->h_off[j] + n0, R, h->lower.rowptr,
+                           h->lower.col, h->lower.val, Z, tr->X.rowptr, tr->X.col, tr->X.val);
       }
     }
   }
   MSKM_HIP_TRY(hipEventRecord(h->ctx->ev1, s));
+  if (lag.W) {
+    bool capped = false;
+    MSKM_TRY(lag.totals(&tr->cg_iters, &capped));
+    tr->capped = capped;
+  }
   MSKM_HIP_TRY(hipStreamSynchronize(s));
   float ms = 0.f;
   MSKM_HIP_TRY(hipEventElapsedTime(&ms, h->ctx->ev0, h->ctx->ev1));
