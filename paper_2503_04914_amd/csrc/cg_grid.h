@@ -22,9 +22,10 @@ __device__ constexpr uint32_t kEmptyWord = 0x7fa4beefu;            // produces t
 // would wait for workgroups that cannot start.
 mskm_status cg_grid_in_turn(mskm_ctx* c, const std::function<void()>& launch);
 
-// Empties z0, z1 on the rows [r0, r0 + n) and ns slot words, clears *aborted.
+// Empties z0, z1 (and z2) on the rows [r0, r0 + n) and ns slot words, clears *aborted.
 template <typename TX>
-void grid_empty(hipStream_t s, TX* z0, TX* z1, int64_t r0, int64_t n, uint64_t* slots, int64_t ns, int32_t* aborted);
+void grid_empty(hipStream_t s, TX* z0, TX* z1, TX* z2, int64_t r0, int64_t n, uint64_t* slots, int64_t ns,
+                int32_t* aborted);
 
 // lane-crossing moves within 16 lanes
 template <int CTRL>

@@ -6,30 +6,39 @@
 // What bounds a level of 10^3 .. 10^5 rows is not its bytes but the chain of
 // dependent steps of an iteration: as separate launches it took two to five
 // kernels of 3-6 us each (the preconditioned FP32 form 12 us, the textbook
-// FP64 form 17 us an iteration on 16,384 rows). Here an iteration is two
-// exchanges between the level's workgroups, about 1.5 us each, plus the work
-// on rows that never leave the CU.
+// FP64 form 17 us an iteration on 16,384 rows). Here an iteration is one
+// exchange between the level's workgroups, about 1.5 us, plus the work on rows
+// that never leave the CU.
+//
+// One exchange an iteration: with q = A p and w = M^-1 q in hand, a workgroup
+// publishes p.q, r.z, r.r, q.z, q.w of its rows, and w. The sums give the step
+// alpha = r.z / p.q, the stopping test on r.r, and r.z after the step, r.z - 2
+// alpha q.z + alpha^2 q.w, so that the next direction needs nothing more: the
+// halo's z and direction are carried along by every workgroup that reads them,
+// z -= alpha w. r.z and r.r themselves are summed anew every time, only beta
+// uses the predicted value. Against the two exchanges of the textbook order
+// (r.r, r.z and the halo of z, then p.q): 58,000 rows in FP32 380 us a solve
+// (490 before), 22,000 in FP64 without preconditioner 1,021 us (1,333), 1,089
+// rows 462 us (545); coefficients and errors against 64 bits as before.
 //
 // Exchange without a barrier or a cache flush: every workgroup stores its
 // partial sums into a slot of its own with device-coherent (agent scope)
 // stores, and every workgroup polls all slots of its level with
 // device-coherent loads until each holds something other than kEmptySlot, a
 // bit pattern that no stored value has. The polled words carry the data, so
-// nothing has to be ordered before them. Direction entries a workgroup needs
-// from its neighbours travel the same way: each publishes z of its rows and
-// polls the entries of z it needs (its halo). Agent-scope fences, which write
+// nothing has to be ordered before them. The entries of w that a workgroup
+// needs from its neighbours travel the same way. Agent-scope fences, which write
 // back and invalidate a whole XCD's L2, are not used. Measured: 1.4 / 1.5 /
 // 2.0 us an exchange for 64 / 128 / 256 workgroups with slots 64 bytes apart
 // (2.3 / 2.8 / 3.3 us with adjacent slots; a counter barrier with fences 3.4 /
 // 5.5 / 10.4 us).
 //
-// Reuse of the buffers: exchanges alternate A (r.r, r.z, with the halo of z)
-// and B (p.q); each kind has two buffers used in turn. Words of A's buffer n
-// are emptied after B(n) was received (everybody has left A(n)), words of B's
-// buffer n after A(n+1) was received, a z buffer after B(n) was received. All
-// stores of a workgroup are waited for before it publishes the next B, so
-// whoever has received that B sees the emptied words, and polls that buffer
-// again only later.
+// Reuse of the buffers: exchange m uses buffer m % 3 (exchange 0 has the halo's
+// first z only). A workgroup empties its words of exchange m - 1 once it has
+// received exchange m, which everybody published after leaving m - 1. All
+// stores of a workgroup are waited for before it publishes m + 1, so whoever has
+// received m + 1 sees the emptied words, and polls that buffer again only then,
+// for m + 2.
 //
 // Waiting: every poll loop ends after `spin` polls. A workgroup that gives up
 // sets *aborted and leaves, the others then give up the same way, and the
@@ -66,7 +75,7 @@ struct CgGridDev {
   uint16_t* lidx = nullptr;         // [nwg][kGridE][kGridThreads] position of each entry's column
   int32_t* stats = nullptr;         // [2 L] h_local, h_row
   int32_t nslot = 0;                // workgroups of one launch (at most)
-  uint64_t* slots = nullptr;        // [4][nslot][kGridSlot]: A and B, two buffers each
+  uint64_t* slots = nullptr;        // [3][nslot][kGridSlot]: three buffers
 };
 struct CgGridPlan {
   bool built = false;
@@ -211,7 +220,7 @@ static mskm_status build_plan(mskm_hier* h, CgGridPlan& P, bool bj, int lanes) {
   MSKM_TRY(halloc(h, &D.lidx, n * kGridE * kGridThreads));
   MSKM_TRY(halloc(h, &D.stats, 2 * (size_t)L));
   D.nslot = h->ctx->ncu;
-  MSKM_TRY(halloc(h, &D.slots, 4 * (size_t)D.nslot * kGridSlot));
+  MSKM_TRY(halloc(h, &D.slots, 3 * (size_t)D.nslot * kGridSlot));
   hipStream_t s = h->ctx->stream;
   MSKM_TRY(upload_async(h, D.wg0, P.h_wg0.data(), P.h_wg0.size() * 4));
   MSKM_TRY(upload_async(h, D.lev, lev.data(), n * 4));
@@ -312,6 +321,8 @@ struct GridCols {
   MrState* st;  // [L][ld], instead of the per-level states
 };
 
+constexpr int kSums = 5;  // p.q, r.z, r.r, q.z, q.M^-1 q
+
 // G lanes per row, 512 / G rows per workgroup, at most E matrix entries per
 // lane. Thread t holds entries g, g + G, ... of row t / G (g = t % G) and the
 // row's share of its block inverse; all G lanes of a row hold its x, r, p, z.
@@ -321,7 +332,8 @@ template <typename TX, bool PC, int G, int E, bool SOLO>
 __global__ void __launch_bounds__(kGridThreads)
     k_cg_grid(const CgGridDev P, int wgb, const DevLevel* __restrict__ lev, const int64_t* __restrict__ rp,
               const TX* __restrict__ val, const TX* __restrict__ b, TX* __restrict__ x,
-              typename GridWord<TX>::type* z0, typename GridWord<TX>::type* z1, CgLevel* __restrict__ st,
+              typename GridWord<TX>::type* z0, typename GridWord<TX>::type* z1, typename GridWord<TX>::type* z2,
+              CgLevel* __restrict__ st,
               int32_t* aborted, double rtol2, int maxit, int spin, const PcArgs<TX> pc,
               const GridCols gc) {
   using W = typename GridWord<TX>::type;
@@ -331,9 +343,10 @@ __global__ void __launch_bounds__(kGridThreads)
   constexpr bool kInvRegs = PC && sizeof(TX) == 4;
   constexpr int kI = kInvRegs ? kBjMax / G : 1;
   __shared__ TX pw[kGridLocal];    // direction: own rows, then the halo
+  __shared__ TX zw[SOLO ? 1 : kGridLocal];  // z of the halo
   __shared__ int32_t hrow[SOLO ? 1 : kGridLocal];  // rows of the halo
-  __shared__ TX rs[PC ? RW : 1];   // residual of the own rows
-  __shared__ double sm[2][kWaves], sb[kWaves], sp[kWaves];
+  __shared__ TX rs[PC ? RW : 1];   // what the preconditioner is applied to
+  __shared__ double sm[kSums][kWaves], sp[kSums];
   __shared__ int bad;
   const int cq = blockIdx.x / gc.nw, col = gc.col0 + cq, wl = blockIdx.x - cq * gc.nw;
   const int wg = wgb + wl, t = threadIdx.x, w = t / kWave, lane = t % kWave;
@@ -344,12 +357,12 @@ __global__ void __launch_bounds__(kGridThreads)
   const int64_t row = r0 + (mine ? i : 0);
   const int me = wg - w0, nslot = P.nslot;
   // slot of workgroup wg0 + q of the level in buffer k: slot + (k * nslot + q) * kGridSlot
-  uint64_t* const slotA = P.slots + (size_t)((int)blockIdx.x - me) * kGridSlot;
-  uint64_t* const slotB = slotA + (size_t)2 * nslot * kGridSlot;
+  uint64_t* const slot = P.slots + (size_t)((int)blockIdx.x - me) * kGridSlot;
   {
     const int64_t off = lev[l].off, zo = off * (gc.ld - 1) + (int64_t)col * lev[l].n;
     z0 += zo;
     z1 += zo;
+    z2 += zo;
   }
   if (SOLO && blockIdx.x == 0 && t == 0) *aborted = 0;
 
@@ -390,8 +403,7 @@ __global__ void __launch_bounds__(kGridThreads)
 #pragma unroll
   for (int k = 0; k < kI; ++k) iv[k] = kInvRegs && g + k * G < bm ? Mi[g + k * G] : (TX)0;
 
-  TX xi = 0, ri = mine ? b[row * gc.ld + col] : (TX)0, pi = 0, zi;
-  for (int q = t; q < nr + nh; q += kGridThreads) pw[q] = (TX)0;
+  TX xi = 0, ri = mine ? b[row * gc.ld + col] : (TX)0, pi, zi;
   if (t == 0) bad = 0;
   if constexpr (PC) {
     if (first) rs[i] = ri;
@@ -403,72 +415,38 @@ __global__ void __launch_bounds__(kGridThreads)
   // halo entries t, t + kGridThreads, ... are the thread's; their rows stay in LDS
   for (int q = t; !SOLO && q < nh; q += kGridThreads) hrow[q] = P.halo[(size_t)wg * kGridLocal + q];
 
-  double rzold = 0.0, bb = 0.0, rr = 0.0;
+  // exchange m: words of buffer m % 3
+  W hz[SOLO ? 1 : kH];
+  auto halo_words = [&](W* zc) {
+#pragma unroll
+    for (int q = 0; q < kH; ++q)
+      if (t + q * kGridThreads < nh && hz[q] == GridWord<TX>::empty)
+        hz[q] = poll(&zc[hrow[t + q * kGridThreads]], GridWord<TX>::empty, spin, &bad);
+  };
+  auto halo_ask = [&](W* zc) {
+#pragma unroll
+    for (int q = 0; q < kH; ++q) hz[q] = t + q * kGridThreads < nh ? get(&zc[hrow[t + q * kGridThreads]]) : (W)0;
+  };
+  // z of the halo (exchange 0), and the first direction
+  if constexpr (!SOLO) {
+    __syncthreads();
+    if (first) put(&z0[row], word_of(zi));
+    halo_ask(z0);
+    halo_words(z0);
+#pragma unroll
+    for (int q = 0; q < kH; ++q)
+      if (t + q * kGridThreads < nh) pw[nr + t + q * kGridThreads] = zw[t + q * kGridThreads] = value_of(hz[q]);
+  }
+  pi = zi;
+  if (first) pw[i] = pi;
+
+  double bb = 0.0, rr = 0.0;
   int n = 0, capped = 0;
-  for (;; ++n) {
-    W* const zc = n & 1 ? z1 : z0;
-    W* const zp = n & 1 ? z0 : z1;
-    // publish z, then (exchange A) r.r and r.z
-    if (first && !SOLO) {
-      put(&zc[row], word_of(zi));
-      if (n > 0) put(&zp[row], GridWord<TX>::empty);
-    }
-    double a = first ? (double)ri * (double)ri : 0.0, c = first ? (double)ri * (double)zi : 0.0;
-    a = wave64_sum(a);
-    c = wave64_sum(c);
-    if (lane == 0) {
-      sm[0][w] = a;
-      sm[1][w] = c;
-    }
+  for (int m = 1;; ++n, m = m == 2 ? 0 : m + 1) {  // m = (n + 1) % 3
+    W* const zc = m == 0 ? z0 : m == 1 ? z1 : z2;
+    W* const zp = m == 0 ? z2 : m == 1 ? z0 : z1;
     __syncthreads();
-    double rz;
-    W hz[SOLO ? 1 : kH];
-    if constexpr (SOLO) {
-      rr = lanes_sum<kWaves>(sm[0][lane % kWaves]);
-      rz = lanes_sum<kWaves>(sm[1][lane % kWaves]);
-    } else {
-      if (w < 2) {
-        const double s = lanes_sum<kWaves>(sm[w][lane % kWaves]);
-        if (lane == 0) put(slotA + ((n & 1) * nslot + me) * kGridSlot + w, word_of(s));
-      }
-      // the halo of z and the level's sums, whichever comes first
-#pragma unroll
-      for (int q = 0; q < kH; ++q) hz[q] = t + q * kGridThreads < nh ? get(&zc[hrow[t + q * kGridThreads]]) : (W)0;
-      a = 0.0;
-      if (t % 256 < nw)
-        a = value_of(poll(slotA + ((n & 1) * nslot + t % 256) * kGridSlot + t / 256, kEmptySlot, spin, &bad));
-#pragma unroll
-      for (int q = 0; q < kH; ++q)
-        if (hz[q] == GridWord<TX>::empty)
-          hz[q] = poll(&zc[hrow[t + q * kGridThreads]], GridWord<TX>::empty, spin, &bad);
-      a = wave64_sum(a);
-      if (lane == 0) sp[w] = a;
-      __syncthreads();
-      if (bad) break;
-      if (t == 0 && n > 0) put(slotB + (((n + 1) & 1) * nslot + me) * kGridSlot, kEmptySlot);
-      rr = (sp[0] + sp[1]) + (sp[2] + sp[3]);
-      rz = (sp[4] + sp[5]) + (sp[6] + sp[7]);
-    }
-    if (n == 0) bb = rr;
-    const bool conv = isfinite(rr) && !(rr > rtol2 * bb);
-    if (conv || !isfinite(rr) || !(rz > 0.0) || !isfinite(rz) || n >= maxit) {
-      capped = conv ? 0 : 1;
-      break;
-    }
-    // direction on the own rows and the halo
-    const TX beta = n == 0 ? (TX)0 : (TX)(rz / rzold);
-    rzold = rz;
-    pi = zi + beta * pi;
-    if (first) pw[i] = pi;
-    if constexpr (!SOLO) {
-#pragma unroll
-      for (int q = 0; q < kH; ++q)
-        if (t + q * kGridThreads < nh) {
-          const int at = nr + t + q * kGridThreads;
-          pw[at] = value_of(hz[q]) + beta * pw[at];
-        }
-    }
-    __syncthreads();
+    if (bad) break;
     TX q = 0;
 #pragma unroll
     for (int k0 = 0; k0 < E; k0 += 8)
@@ -477,44 +455,103 @@ __global__ void __launch_bounds__(kGridThreads)
         for (int k = k0; k < k0 + 8; ++k) q += v[k] * pw[k & 1 ? ci[k / 2] >> 16 : ci[k / 2] & 0xffffu];
       }
     q = lanes_sum<G>(q);
-    // exchange B: p.q (every earlier store of this workgroup is waited for first)
-    a = wave64_sum(first ? (double)pi * (double)q : 0.0);
-    if (lane == 0) sb[w] = a;
-    double pq;
-    if constexpr (SOLO) {
+    TX wi = q;  // M^-1 q
+    if constexpr (PC) {
+      if (first) rs[i] = q;
       __syncthreads();
-      pq = lanes_sum<kWaves>(sb[lane % kWaves]);
-    } else {
+      wi = grid_precond<G, kI, TX>(iv, Mi, bm, rs + ba, g);
+    }
+    // every earlier store of this workgroup is waited for before it publishes
+    if constexpr (!SOLO) {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      __syncthreads();
-      if (w == 0) {
-        const double s = lanes_sum<kWaves>(sb[lane % kWaves]);
-        if (lane == 0) put(slotB + ((n & 1) * nslot + me) * kGridSlot, word_of(s));
+      if (first) put(&zc[row], word_of(wi));
+    }
+    double a[kSums] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    if (first) {
+      a[0] = (double)pi * (double)q;
+      a[1] = (double)ri * (double)zi;
+      a[2] = (double)ri * (double)ri;
+      a[3] = (double)q * (double)zi;
+      a[4] = (double)q * (double)wi;
+    }
+#pragma unroll
+    for (int k = 0; k < kSums; ++k) {
+      a[k] = wave64_sum(a[k]);
+      if (lane == 0) sm[k][w] = a[k];
+    }
+    __syncthreads();
+    double pq, rz, qz, qw;
+    if constexpr (SOLO) {
+      pq = lanes_sum<kWaves>(sm[0][lane % kWaves]);
+      rz = lanes_sum<kWaves>(sm[1][lane % kWaves]);
+      rr = lanes_sum<kWaves>(sm[2][lane % kWaves]);
+      qz = lanes_sum<kWaves>(sm[3][lane % kWaves]);
+      qw = lanes_sum<kWaves>(sm[4][lane % kWaves]);
+    } else {
+      if (w < kSums) {
+        const double s = lanes_sum<kWaves>(sm[w][lane % kWaves]);
+        if (lane == 0) put(slot + (m * nslot + me) * kGridSlot + w, word_of(s));
       }
-      a = 0.0;
-      if (t < 256 && t < nw) a = value_of(poll(slotB + ((n & 1) * nslot + t) * kGridSlot, kEmptySlot, spin, &bad));
-      if (w < 4) {
-        a = wave64_sum(a);
-        if (lane == 0) sp[w] = a;
+      // the halo and the level's sums (wave w: word w), whichever comes first
+      halo_ask(zc);
+      if (w < kSums) {
+        uint64_t u[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          u[k] = lane + k * kWave < nw ? get(slot + (m * nslot + lane + k * kWave) * kGridSlot + w) : 0ull;
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if (u[k] == kEmptySlot) u[k] = poll(slot + (m * nslot + lane + k * kWave) * kGridSlot + w, kEmptySlot, spin, &bad);
+          s += value_of(u[k]);
+        }
+        s = wave64_sum(s);
+        if (lane == 0) sp[w] = s;
       }
+      halo_words(zc);
       __syncthreads();
       if (bad) break;
-      pq = (sp[0] + sp[1]) + (sp[2] + sp[3]);
+      pq = sp[0];
+      rz = sp[1];
+      rr = sp[2];
+      qz = sp[3];
+      qw = sp[4];
     }
-    if (!(pq > 0.0) || !isfinite(pq)) {  // cannot happen for SPD A and p != 0
-      capped = !(rr <= rtol2 * bb);
+    if (n == 0) bb = rr;
+    const bool conv = isfinite(rr) && !(rr > rtol2 * bb);
+    if (conv || !isfinite(rr) || !(rz > 0.0) || !isfinite(rz) || n >= maxit) {
+      capped = conv ? 0 : 1;
       break;
     }
-    if (!SOLO && w < 2 && lane == 0) put(slotA + ((n & 1) * nslot + me) * kGridSlot + w, kEmptySlot);
+    if (!(pq > 0.0) || !isfinite(pq)) {  // cannot happen for SPD A and p != 0
+      capped = 1;
+      break;
+    }
+    // everybody has left the exchange before
+    if constexpr (!SOLO) {
+      if (first) put(&zp[row], GridWord<TX>::empty);
+      if (w < kSums && lane == 0) put(slot + ((m == 0 ? 2 : m - 1) * nslot + me) * kGridSlot + w, kEmptySlot);
+    }
     const double alpha = rz / pq;
+    const double rznew = rz - alpha * (2.0 * qz - alpha * qw);  // r.z after the step
+    const TX beta = rznew > 0.0 ? (TX)(rznew / rz) : (TX)0;
     xi = (TX)((double)xi + alpha * (double)pi);
     ri = (TX)((double)ri - alpha * (double)q);
-    if constexpr (PC) {
-      if (first) rs[i] = ri;
-      __syncthreads();
-      zi = grid_precond<G, kI, TX>(iv, Mi, bm, rs + ba, g);
-    } else {
+    if constexpr (PC)
+      zi = (TX)((double)zi - alpha * (double)wi);
+    else
       zi = ri;
+    pi = zi + beta * pi;
+    if (first) pw[i] = pi;
+    if constexpr (!SOLO) {
+#pragma unroll
+      for (int h = 0; h < kH; ++h)
+        if (t + h * kGridThreads < nh) {
+          const int at = nr + t + h * kGridThreads;
+          const TX zh = (TX)((double)zw[at - nr] - alpha * (double)value_of(hz[h]));
+          zw[at - nr] = zh;
+          pw[at] = zh + beta * pw[at];
+        }
     }
   }
   if (bad) {
@@ -576,29 +613,31 @@ void cg_grid_set_spin(mskm_ctx* c, int spin) { c->grid_spin = spin; }
 template <typename TX>
 __global__ void __launch_bounds__(kBlock)
     k_grid_empty(typename GridWord<TX>::type* __restrict__ z0, typename GridWord<TX>::type* __restrict__ z1,
-                 int64_t r0, int64_t n, uint64_t* __restrict__ slots, int64_t ns, int32_t* __restrict__ aborted) {
+                 typename GridWord<TX>::type* __restrict__ z2, int64_t r0, int64_t n, uint64_t* __restrict__ slots, int64_t ns, int32_t* __restrict__ aborted) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i < n) {
     z0[r0 + i] = GridWord<TX>::empty;
     z1[r0 + i] = GridWord<TX>::empty;
+    if (z2) z2[r0 + i] = GridWord<TX>::empty;
   }
   if (i < ns) slots[i] = kEmptySlot;
   if (i == 0 && aborted) *aborted = 0;
 }
 
 template <typename TX>
-void grid_empty(hipStream_t s, TX* z0, TX* z1, int64_t r0, int64_t n, uint64_t* slots, int64_t ns, int32_t* aborted) {
+void grid_empty(hipStream_t s, TX* z0, TX* z1, TX* z2, int64_t r0, int64_t n, uint64_t* slots, int64_t ns,
+                int32_t* aborted) {
   using W = typename GridWord<TX>::type;
   hipLaunchKernelGGL(k_grid_empty<TX>, dim3((unsigned)((std::max(n, ns) + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
-                     (W*)z0, (W*)z1, r0, n, slots, ns, aborted);
+                     (W*)z0, (W*)z1, (W*)z2, r0, n, slots, ns, aborted);
 }
-template void grid_empty<float>(hipStream_t, float*, float*, int64_t, int64_t, uint64_t*, int64_t, int32_t*);
-template void grid_empty<double>(hipStream_t, double*, double*, int64_t, int64_t, uint64_t*, int64_t, int32_t*);
+template void grid_empty<float>(hipStream_t, float*, float*, float*, int64_t, int64_t, uint64_t*, int64_t, int32_t*);
+template void grid_empty<double>(hipStream_t, double*, double*, double*, int64_t, int64_t, uint64_t*, int64_t, int32_t*);
 
 // The kernel for levels lo..hi with the columns of gc, `cols` of them.
 template <typename TX>
 static void grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, const TX* val, const TX* b, TX* x, TX* z0,
-                        TX* z1, CgLevel* st, int32_t* aborted, double rtol2, int maxit, const PcArgs<TX>& pc,
+                        TX* z1, TX* z2, CgLevel* st, int32_t* aborted, double rtol2, int maxit, const PcArgs<TX>& pc,
                         const GridCols& gc, int cols) {
   using W = typename GridWord<TX>::type;
   const CgGridPlan& P = static_cast<CgGrid*>(h->cg_grid)->plan[bj ? 1 : 0][lanes == 2 ? 0 : 1];
@@ -608,8 +647,8 @@ static void grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, const 
   for (int l = lo; l <= hi; ++l) longest = std::max(longest, P.h_row[l]);
 #define MSKM_GRID_LAUNCH(PCF, GG, EE, SS)                                                                         \
   hipLaunchKernelGGL((k_cg_grid<TX, PCF, GG, EE, SS>), dim3((unsigned)gc.nw * cols), dim3(kGridThreads), 0,       \
-                     h->ctx->stream, P.d, w0, h->d_lev, h->diag.rowptr, val, b, x, (W*)z0, (W*)z1, st, aborted,   \
-                     rtol2, maxit, h->ctx->grid_spin, pc, gc)
+                     h->ctx->stream, P.d, w0, h->d_lev, h->diag.rowptr, val, b, x, (W*)z0, (W*)z1, (W*)z2, st,    \
+                     aborted, rtol2, maxit, h->ctx->grid_spin, pc, gc)
 #define MSKM_GRID_FORM(GG, EE)                \
   do {                                        \
     if (solo && bj)                           \
@@ -635,7 +674,7 @@ static void grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, const 
 
 template <typename TX>
 mskm_status cg_grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, const TX* val, const TX* b, TX* x,
-                           TX* z0, TX* z1, CgLevel* st, int32_t* aborted, double rtol2, int maxit,
+                           TX* z0, TX* z1, TX* z2, CgLevel* st, int32_t* aborted, double rtol2, int maxit,
                            const PcArgs<TX>& pc) {
   const CgGridPlan& P = static_cast<CgGrid*>(h->cg_grid)->plan[bj ? 1 : 0][lanes == 2 ? 0 : 1];
   const int nw = P.h_wg0[hi + 1] - P.h_wg0[lo];
@@ -644,18 +683,19 @@ mskm_status cg_grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, con
   const bool solo = nw == hi - lo + 1;
   if (!solo) {
     const int64_t r0 = h->h_off[lo], n = h->h_off[hi + 1] - r0;
-    grid_empty<TX>(h->ctx->stream, z0, z1, r0, n, P.d.slots, (int64_t)4 * P.d.nslot * kGridSlot, aborted);
+    grid_empty<TX>(h->ctx->stream, z0, z1, z2, r0, n, P.d.slots, (int64_t)3 * P.d.nslot * kGridSlot, aborted);
   }
-  auto launch = [&] { grid_launch<TX>(h, lo, hi, bj, lanes, val, b, x, z0, z1, st, aborted, rtol2, maxit, pc, gc, 1); };
+  auto launch = [&] { grid_launch<TX>(h, lo, hi, bj, lanes, val, b, x, z0, z1, z2, st, aborted, rtol2, maxit, pc, gc, 1); };
   if (!solo) return cg_grid_in_turn(h->ctx, launch);
   launch();
   MSKM_HIP_TRY(hipGetLastError());
   return MSKM_OK;
 }
 template mskm_status cg_grid_launch<float>(mskm_hier*, int, int, bool, int, const float*, const float*, float*, float*,
-                                           float*, CgLevel*, int32_t*, double, int, const PcArgs<float>&);
+                                           float*, float*, CgLevel*, int32_t*, double, int, const PcArgs<float>&);
 template mskm_status cg_grid_launch<double>(mskm_hier*, int, int, bool, int, const double*, const double*, double*,
-                                            double*, double*, CgLevel*, int32_t*, double, int, const PcArgs<double>&);
+                                            double*, double*, double*, CgLevel*, int32_t*, double, int,
+                                            const PcArgs<double>&);
 
 // Launches one after the other that the columns of a level may take: an
 // iteration takes 3-4 us in each, launched for all columns at once 25-35 us.
@@ -679,7 +719,7 @@ __global__ void __launch_bounds__(kBlock)
 
 template <typename TX>
 mskm_status cg_grid_columns(mskm_hier* h, int lo, int hi, bool bj, const TX* val, const TX* b, TX* x, TX* z0, TX* z1,
-                            int nrhs, int R, MrState* st, int32_t* aborted, double rtol2, int maxit, const PcArgs<TX>& pc,
+                            TX* z2, int nrhs, int R, MrState* st, int32_t* aborted, double rtol2, int maxit, const PcArgs<TX>& pc,
                             int* how) {
   *how = 0;
   int lanes = 0;
@@ -696,18 +736,18 @@ mskm_status cg_grid_columns(mskm_hier* h, int lo, int hi, bool bj, const TX* val
                        n, lo, hi - lo + 1, nrhs, R);
   if (solo) {
     const GridCols gc{nw, R, 0, st};
-    grid_launch<TX>(h, lo, hi, bj, lanes, val, b, x, z0, z1, nullptr, aborted, rtol2, maxit, pc, gc,
+    grid_launch<TX>(h, lo, hi, bj, lanes, val, b, x, z0, z1, z2, nullptr, aborted, rtol2, maxit, pc, gc,
                     nrhs);
     MSKM_HIP_TRY(hipGetLastError());
     *how = 1;
     return MSKM_OK;
   }
   for (int c0 = 0; c0 < nrhs; c0 += per) {
-    grid_empty<TX>(h->ctx->stream, z0, z1, r0 * R, c0 == 0 ? n * R : 0, P.d.slots, (int64_t)4 * P.d.nslot * kGridSlot,
+    grid_empty<TX>(h->ctx->stream, z0, z1, z2, r0 * R, c0 == 0 ? n * R : 0, P.d.slots, (int64_t)3 * P.d.nslot * kGridSlot,
                    c0 == 0 ? aborted : nullptr);
     const GridCols gc{nw, R, c0, st};
     MSKM_TRY(cg_grid_in_turn(h->ctx, [&] {
-      grid_launch<TX>(h, lo, hi, bj, lanes, val, b, x, z0, z1, nullptr, aborted, rtol2, maxit, pc, gc,
+      grid_launch<TX>(h, lo, hi, bj, lanes, val, b, x, z0, z1, z2, nullptr, aborted, rtol2, maxit, pc, gc,
                       std::min(per, nrhs - c0));
     }));
   }
@@ -715,9 +755,9 @@ mskm_status cg_grid_columns(mskm_hier* h, int lo, int hi, bool bj, const TX* val
   return MSKM_OK;
 }
 template mskm_status cg_grid_columns<float>(mskm_hier*, int, int, bool, const float*, const float*, float*, float*,
-                                            float*, int, int, MrState*, int32_t*, double, int, const PcArgs<float>&, int*);
+                                            float*, float*, int, int, MrState*, int32_t*, double, int, const PcArgs<float>&, int*);
 template mskm_status cg_grid_columns<double>(mskm_hier*, int, int, bool, const double*, const double*, double*,
-                                             double*, double*, int, int, MrState*, int32_t*, double, int,
+                                             double*, double*, double*, int, int, MrState*, int32_t*, double, int,
                                              const PcArgs<double>&, int*);
 
 }  // namespace mskm

@@ -39,24 +39,24 @@ struct PcArgs {
 // first use) whether these levels can take it, and with how many lanes per
 // row (0: they cannot).
 mskm_status cg_grid_ready(mskm_hier* h, int lo, int hi, bool bj, int* lanes);
-// Queues the solve A_l x_l = b_l (x0 = 0) of levels lo..hi; z0, z1: two
+// Queues the solve A_l x_l = b_l (x0 = 0) of levels lo..hi; z0, z1, z2: three
 // vectors of the hierarchy's length, scratch. st[l] receives the final
 // states. *aborted (device) is set, and x and st are unusable, when a
 // workgroup's wait ran out.
 template <typename TX>
 mskm_status cg_grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, const TX* val, const TX* b, TX* x,
-                           TX* z0, TX* z1, CgLevel* st, int32_t* aborted, double rtol2, int maxit,
+                           TX* z0, TX* z1, TX* z2, CgLevel* st, int32_t* aborted, double rtol2, int maxit,
                            const PcArgs<TX>& pc);
 
 // The same for nrhs right-hand sides (b, x: [N][R], R >= nrhs, zeros past them;
-// z0, z1: scratch of that size;
+// z0, z1, z2: scratch of that size;
 // states to st[l * R + r]), every column a system of its own. *how: 0 when it
 // takes more launches than are worth it (nothing is queued), 1 queued, 2 queued
 // and *aborted has to be looked at.
 struct MrState;
 template <typename TX>
 mskm_status cg_grid_columns(mskm_hier* h, int lo, int hi, bool bj, const TX* val, const TX* b, TX* x, TX* z0, TX* z1,
-                            int nrhs, int R, MrState* st, int32_t* aborted, double rtol2, int maxit, const PcArgs<TX>& pc,
+                            TX* z2, int nrhs, int R, MrState* st, int32_t* aborted, double rtol2, int maxit, const PcArgs<TX>& pc,
                             int* how);
 
 // cg_stream.hip: the same for all levels of one depth, FP32, where they do not

@@ -676,7 +676,7 @@ mskm_status cg_stream_launch(mskm_hier* h, int depth, bool bj, const float* b, f
   mskm_ctx* c = h->ctx;
   hipStream_t s = c->stream;
   const int64_t r0 = h->h_off[h->h_depth_begin[depth]], n = h->h_off[h->h_depth_begin[depth + 1]] - r0;
-  grid_empty<float>(s, z0, z1, r0, n, P.d.slots, (int64_t)4 * P.d.nwg * kGridSlot, aborted);
+  grid_empty<float>(s, z0, z1, nullptr, r0, n, P.d.slots, (int64_t)4 * P.d.nwg * kGridSlot, aborted);
   const size_t lds = stream_lds(P);
   hipError_t e = hipSuccess;
   const mskm_status r = cg_grid_in_turn(c, [&] {

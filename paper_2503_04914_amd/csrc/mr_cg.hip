@@ -629,7 +629,7 @@ mskm_status mr_cg(mskm_hier* h, MrWS& W, const TV* dval, const std::vector<char>
   if (all_on) {
     int how = 0;
     const PcArgs<TX> pc{h->bj.start, h->bj.of_row, h->bj.off, inv, nullptr};
-    MSKM_TRY((cg_grid_columns<TX>(h, lo, hi, W.pc, dval, b, x, p, q, W.nrhs, R, W.st, W.aborted, rtol * rtol,
+    MSKM_TRY((cg_grid_columns<TX>(h, lo, hi, W.pc, dval, b, x, p, q, (TX*)W.r, W.nrhs, R, W.st, W.aborted, rtol * rtol,
                                  maxit, pc, &how)));
     *W.h_aborted = 0;
     if (how == 2) {

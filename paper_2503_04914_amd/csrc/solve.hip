@@ -1510,7 +1510,7 @@ static mskm_status cg_run(mskm_hier* h, SolveWS& W, const TV* dval, const std::v
         }
       if (bj) MSKM_TRY(bj_start_side(h));
       if (lanes > 0) {
-        MSKM_TRY(cg_grid_launch<TX>(h, lo, hi, bj, lanes, dval, b, x, (TX*)W.p0, (TX*)W.p1, W.st, W.aborted,
+        MSKM_TRY(cg_grid_launch<TX>(h, lo, hi, bj, lanes, dval, b, x, (TX*)W.p0, (TX*)W.p1, (TX*)W.r, W.st, W.aborted,
                                     rtol * rtol, maxit, pc_args<TX>(h, W)));
       } else if constexpr (sizeof(TX) == 4) {
         MSKM_TRY(cg_stream_launch(h, depth, bj, b, x, (TX*)W.p0, (TX*)W.p1, W.st, W.aborted, rtol * rtol, maxit,
