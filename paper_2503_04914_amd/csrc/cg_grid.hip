@@ -19,7 +19,9 @@
 // uses the predicted value. Against the two exchanges of the textbook order
 // (r.r, r.z and the halo of z, then p.q): 58,000 rows in FP32 380 us a solve
 // (490 before), 22,000 in FP64 without preconditioner 1,021 us (1,333), 1,089
-// rows 462 us (545); coefficients and errors against 64 bits as before.
+// rows 462 us (545); coefficients and errors against 64 bits as before. With the
+// sums taken over 16 lanes and through LDS, and the reads of the preconditioner
+// unconditional: 336, 933 and 437 us.
 //
 // Exchange without a barrier or a cache flush: every workgroup stores its
 // partial sums into a slot of its own with device-coherent (agent scope)
@@ -298,16 +300,20 @@ mskm_status cg_grid_ready(mskm_hier* h, int lo, int hi, bool bj, int* lanes) {
 
 // -------------------------------------------------------------------- solve
 
-// The row's z = M^-1 r from rs: this lane's share of the inverse row, in
-// registers (N of them) or read through the caches (N = 1).
+// The row's entry of M^-1 times the block rb: this lane's share of the inverse
+// row, in registers (N of them, zeros past the block) or read through the caches
+// (N = 1). The reads of rb are unconditional, past the block its last entry: under
+// a bounds check each was waited for by itself, 1,650 cycles for 16 of them
+// instead of 550.
 template <int G, int N, typename TX>
 __device__ __forceinline__ TX grid_precond(const TX (&iv)[N], const TX* Mi, int bm, const TX* rb, int g) {
   TX a = 0;
   if constexpr (N > 1) {
+    const int last = max(bm - 1, 0);
 #pragma unroll
-    for (int k = 0; k < N; ++k)
-      if (g + k * G < bm) a += iv[k] * rb[g + k * G];
+    for (int k = 0; k < N; ++k) a += iv[k] * rb[min(g + k * G, last)];
   } else {
+#pragma unroll 4
     for (int j = g; j < bm; j += G) a += Mi[j] * rb[j];
   }
   return lanes_sum<G>(a);
@@ -340,13 +346,14 @@ __global__ void __launch_bounds__(kGridThreads)
   constexpr int RW = kGridThreads / G;
   constexpr int kWaves = kGridThreads / kWave;
   constexpr int kH = kGridLocal / kGridThreads;  // halo entries per thread
+  constexpr int kParts = kWaves * kWave / 16;    // sums over 16 lanes of a workgroup
   constexpr bool kInvRegs = PC && sizeof(TX) == 4;
   constexpr int kI = kInvRegs ? kBjMax / G : 1;
   __shared__ TX pw[kGridLocal];    // direction: own rows, then the halo
   __shared__ TX zw[SOLO ? 1 : kGridLocal];  // z of the halo
   __shared__ int32_t hrow[SOLO ? 1 : kGridLocal];  // rows of the halo
   __shared__ TX rs[PC ? RW : 1];   // what the preconditioner is applied to
-  __shared__ double sm[kSums][kWaves], sp[kSums];
+  __shared__ double sm[kSums][kParts], sp[kSums];
   __shared__ int bad;
   const int cq = blockIdx.x / gc.nw, col = gc.col0 + cq, wl = blockIdx.x - cq * gc.nw;
   const int wg = wgb + wl, t = threadIdx.x, w = t / kWave, lane = t % kWave;
@@ -419,13 +426,16 @@ __global__ void __launch_bounds__(kGridThreads)
   W hz[SOLO ? 1 : kH];
   auto halo_words = [&](W* zc) {
 #pragma unroll
-    for (int q = 0; q < kH; ++q)
+    for (int q = 0; q < kH; ++q) {
       if (t + q * kGridThreads < nh && hz[q] == GridWord<TX>::empty)
         hz[q] = poll(&zc[hrow[t + q * kGridThreads]], GridWord<TX>::empty, spin, &bad);
+    }
   };
   auto halo_ask = [&](W* zc) {
 #pragma unroll
-    for (int q = 0; q < kH; ++q) hz[q] = t + q * kGridThreads < nh ? get(&zc[hrow[t + q * kGridThreads]]) : (W)0;
+    for (int q = 0; q < kH; ++q) {
+      hz[q] = t + q * kGridThreads < nh ? get(&zc[hrow[t + q * kGridThreads]]) : (W)0;
+    }
   };
   // z of the halo (exchange 0), and the first direction
   if constexpr (!SOLO) {
@@ -440,6 +450,11 @@ __global__ void __launch_bounds__(kGridThreads)
   pi = zi;
   if (first) pw[i] = pi;
 
+  static_assert(kParts == 32, "two sums of 16");
+  auto total = [&](int k) {
+    const double s = lanes_sum<16>(sm[k][lane % kParts]);
+    return readlane_f64(s, 0) + readlane_f64(s, 16);
+  };
   double bb = 0.0, rr = 0.0;
   int n = 0, capped = 0;
   for (int m = 1;; ++n, m = m == 2 ? 0 : m + 1) {  // m = (n + 1) % 3
@@ -476,20 +491,20 @@ __global__ void __launch_bounds__(kGridThreads)
     }
 #pragma unroll
     for (int k = 0; k < kSums; ++k) {
-      a[k] = wave64_sum(a[k]);
-      if (lane == 0) sm[k][w] = a[k];
+      a[k] = lanes_sum<16>(a[k]);
+      if (lane % 16 == 0) sm[k][t / 16] = a[k];
     }
     __syncthreads();
     double pq, rz, qz, qw;
     if constexpr (SOLO) {
-      pq = lanes_sum<kWaves>(sm[0][lane % kWaves]);
-      rz = lanes_sum<kWaves>(sm[1][lane % kWaves]);
-      rr = lanes_sum<kWaves>(sm[2][lane % kWaves]);
-      qz = lanes_sum<kWaves>(sm[3][lane % kWaves]);
-      qw = lanes_sum<kWaves>(sm[4][lane % kWaves]);
+      pq = total(0);
+      rz = total(1);
+      rr = total(2);
+      qz = total(3);
+      qw = total(4);
     } else {
       if (w < kSums) {
-        const double s = lanes_sum<kWaves>(sm[w][lane % kWaves]);
+        const double s = total(w);
         if (lane == 0) put(slot + (m * nslot + me) * kGridSlot + w, word_of(s));
       }
       // the halo and the level's sums (wave w: word w), whichever comes first
@@ -545,13 +560,14 @@ __global__ void __launch_bounds__(kGridThreads)
     if (first) pw[i] = pi;
     if constexpr (!SOLO) {
 #pragma unroll
-      for (int h = 0; h < kH; ++h)
+      for (int h = 0; h < kH; ++h) {
         if (t + h * kGridThreads < nh) {
           const int at = nr + t + h * kGridThreads;
           const TX zh = (TX)((double)zw[at - nr] - alpha * (double)value_of(hz[h]));
           zw[at - nr] = zh;
           pw[at] = zh + beta * pw[at];
         }
+      }
     }
   }
   if (bad) {
