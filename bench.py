@@ -47,10 +47,6 @@ PMC_TRAFFIC = {
     ("halton2d_L8", "k_cg_spmv1_sell<float,float,true>", "level 7"): {
         "fetch_kib": 146135.97, "fetch_scale": 1048576 / 524300.42,
         "write_kib": 4192.75, "write_scale": 1048576 / 1048628.35},
-    # `bench.py --spmv-only --spmv-op mr --spmv-prec fp32 --spmv-rhs 256 --spmv-variant 4064`
-    ("halton2d_L8", "k_mr_cg_spmm_w<1,float,float> R=256", "level 7"): {
-        "fetch_kib": 3607406.5, "fetch_scale": 1048576 / 524300.8,
-        "write_kib": 1081344.0, "write_scale": 1048576 / 1048604.3},
 }
 TARGET = 1e-8
 RTOL_LADDER = [3e-3, 1e-3, 3e-4, 1e-4, 3e-5, 1e-5, 1e-6, 1e-7, 1e-8, 1e-9, 1e-10, 1e-11, 1e-12]
@@ -62,6 +58,14 @@ def pmc_traffic(key):
     if pmc is None:
         return None
     return int(pmc["fetch_kib"] * pmc["fetch_scale"] * 1024 + pmc["write_kib"] * pmc["write_scale"] * 1024)
+
+
+def mr_product_kernel_name(t, nrhs):
+    """Kernel of the many-right-hand-side CG product on a large level."""
+    width = 16 if nrhs <= 16 else (nrhs + 31) // 32 * 32
+    lane = 4 if t == "float" and width % 64 == 0 else 2 if width % 32 == 0 else 1
+    wide = lane > 1 and width % (64 * lane) == 0
+    return f"k_mrt_cg4<{t}, {lane}>" if wide else f"k_mrt_cg<{t}, {lane}>"
 
 
 def log(*a):
@@ -258,10 +262,9 @@ def batched(m, ctx, hd, h, pts_dev, dev, fast_opts, rt_fast, nrhs, count):
         peak = HBM_PEAK_GBS if bound == "hbm" else FP32_PEAK_TFLOPS
         out["multi_rhs"]["roofline"] = {
             "bound": bound, "achieved": round(achieved, 1), "peak": peak, "unit": "GB/s" if bound == "hbm" else "TFLOP/s",
-            "frac": round(achieved / peak, 4), "traffic": pmc_traffic(("halton2d_L8", "k_mr_cg_spmm_w<1,float,float> R=256",
-                                                                         "level 7")) if (nrhs == 256 and h.levels == 8) else None,
-            "kernel": f"k_mr_cg_spmm_w<1,float,float> (CG product Q = A_l P for {nrhs} right-hand sides in chunks "
-                      f"of 64, level {top}: {n_t} rows, {nnz_t} nonzeros, FP32)",
+            "frac": round(achieved / peak, 4), "traffic": None,
+            "kernel": f"{mr_product_kernel_name('float', nrhs)} (CG product Q = A_l P for {nrhs} right-hand sides, "
+                      f"level {top}: {n_t} rows, {nnz_t} nonzeros, FP32)",
             "ms": round(ms_p, 4), "algorithmic_bytes": byt, "flop": flop,
             "tflops": round(flop / (ms_p * 1e-3) / 1e12, 2),
             "gathered_bytes": nnz_t * nrhs * 4}  # the rows of P read through the caches, one per nonzero
@@ -579,7 +582,7 @@ def main():
             n_top = int(h.offsets[top + 1] - h.offsets[top])
             b = m.block_nnz(ctx, hd, top, top) * (sv + 4) + (n_top + 1) * 8 + 2 * n_top * args.spmv_rhs * sv
             tname = "float" if sv == 4 else "double"
-            kname = f"mskm::k_mr_cg_spmm_w<1, {tname}, {tname}> (or the chunk width timed fastest)"
+            kname = f"mskm::{mr_product_kernel_name(tname, args.spmv_rhs)}"
         else:
             nnz = {"diag": st["nnz_diag"], "lower": st["nnz_lower"], "full": st["nnz_diag"] + st["nnz_lower"]}[args.spmv_op]
             sc = diag_col_bytes(code, st) if args.spmv_op == "diag" else 4
