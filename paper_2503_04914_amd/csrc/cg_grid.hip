@@ -625,6 +625,13 @@ mskm_status cg_grid_in_turn(mskm_ctx* c, const std::function<void()>& launch) {
 
 void cg_grid_set_spin(mskm_ctx* c, int spin) { c->grid_spin = spin; }
 
+extern "C" int64_t mskm_test_given_up(const mskm_ctx* c) { return c->given_up; }
+
+extern "C" void mskm_test_limits(mskm_ctx* c, uint64_t hier_bytes, uint64_t scratch_bytes) {
+  c->limit_hier = hier_bytes;
+  c->limit_scratch = scratch_bytes;
+}
+
 // Empties z0, z1 on the rows [r0, r0 + n) and every slot of the plan.
 template <typename TX>
 __global__ void __launch_bounds__(kBlock)

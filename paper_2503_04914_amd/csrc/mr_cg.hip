@@ -636,6 +636,7 @@ mskm_status mr_cg(mskm_hier* h, MrWS& W, const TV* dval, const std::vector<char>
       MSKM_HIP_TRY(hipMemcpyAsync(W.h_aborted, W.aborted, 4, hipMemcpyDeviceToHost, s));
       MSKM_HIP_TRY(hipEventRecord(W.ev[0], s));
       MSKM_HIP_TRY(hipEventSynchronize(W.ev[0]));
+      if (*W.h_aborted) ++h->ctx->given_up;
     }
     if (how > 0 && *W.h_aborted == 0) {
       hipLaunchKernelGGL(k_mr_stats, dim3(nlev), dim3(kBlock), 0, s, lo, W.st, W.on, W.stat, R);

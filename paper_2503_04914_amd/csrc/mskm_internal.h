@@ -196,6 +196,10 @@ struct mskm_ctx {
   int32_t ncu = 0;              // compute units, at most 256 (workgroups of one persistent CG launch)
   int32_t grid_spin = 1 << 15;  // polls before a wait of that kernel is given up (about 30 ms)
   hipEvent_t ev_grid = nullptr; // after this context's last persistent CG launch
+  int64_t given_up = 0;         // persistent launches that gave up and were solved by launched kernels
+  // tests of the ways without them: most bytes of a hierarchy's block, and of a
+  // scratch block, that an allocation still gets (0: no limit)
+  uint64_t limit_hier = 0, limit_scratch = 0;
   // device blocks of destroyed hierarchies, kept for the next allocation of
   // the same size (a hierarchy rebuilt with the same shape reuses all of
   // them without hipMalloc); at most kBlockCacheCap bytes, freed by
@@ -337,6 +341,7 @@ mskm_status halloc(mskm_hier* h, T** p, size_t count) {
   if (count == 0) count = 1;
   const size_t bytes = count * sizeof(T);
   void* q = nullptr;
+  if (h->ctx->limit_hier && bytes > h->ctx->limit_hier) return fail(MSKM_ENOMEM, "the hierarchy's test limit");
   MSKM_TRY(ctx_alloc(h->ctx, bytes, &q));
   *p = static_cast<T*>(q);
   h->allocs.push_back(q);
@@ -409,6 +414,7 @@ inline mskm_status Carve::alloc(mskm_ctx* c, void** base) {
   size_t g = 256;
   while (g * 16 <= bytes) g *= 2;
   bytes = (bytes + g - 1) / g * g;
+  if (c->limit_scratch && bytes > c->limit_scratch) return fail(MSKM_ENOMEM, "the scratch test limit");
   MSKM_TRY(ctx_alloc(c, bytes, base));
   place(static_cast<char*>(*base));
   return MSKM_OK;
@@ -446,6 +452,11 @@ mskm_status bj_wait(mskm_hier* h, int hi);
 mskm_status bj_start_side(mskm_hier* h);
 template <typename TX>
 void launch_bj_apply(mskm_hier* h, int lo, int hi, const TX* r, TX* u);
+
+// For tests: how many persistent launches of the context gave up; limits of
+// allocations (mskm_ctx::limit_hier, limit_scratch).
+extern "C" int64_t mskm_test_given_up(const mskm_ctx* c);
+extern "C" void mskm_test_limits(mskm_ctx* c, uint64_t hier_bytes, uint64_t scratch_bytes);
 
 // cg_grid.hip: no later launch waits for this context's (called before its event goes)
 void cg_grid_forget(mskm_ctx* c);

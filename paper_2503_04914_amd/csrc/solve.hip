@@ -1440,6 +1440,7 @@ static mskm_status flush_deferred(mskm_hier* h, SolveWS& W, CgStats* cs) {
     if (W.h_aborted[l]) {
       W.h_aborted[l] = 0;
       W.grid_failed = true;
+      ++h->ctx->given_up;
     }
     const CgLevel& o = W.h_defer[l];
     cs->iters_total += o.iters;

@@ -1,0 +1,98 @@
+"""The ways without the one-launch CG and without the tiles: a persistent
+launch that gives up is counted and its levels are solved by launched kernels;
+without memory for tiles the many-right-hand-side products go row by row.
+"""
+import ctypes
+
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+SPIN = 1 << 15  # polls of a wait
+
+
+def _hooks(m):
+    spin = getattr(m.lib(), "_ZN4mskm16cg_grid_set_spinEP8mskm_ctxi")
+    spin.argtypes, spin.restype = [ctypes.c_void_p, ctypes.c_int], None
+    given_up, limits = m.lib().mskm_test_given_up, m.lib().mskm_test_limits
+    given_up.argtypes, given_up.restype = [ctypes.c_void_p], ctypes.c_int64
+    limits.argtypes, limits.restype = [ctypes.c_void_p, ctypes.c_uint64, ctypes.c_uint64], None
+    return spin, given_up, limits
+
+
+def _opts(m, mixed, **kw):
+    kw = dict(dict(algorithm=m.MSKM_ALG_SEQUENTIAL, precond=m.MSKM_PRECOND_BLOCK_JACOBI), **kw)
+    return m.solve_opts(precision=m.MSKM_PREC_FP32, cg_rtol=1e-5, target_rel_residual=1e-13, max_refine=20, **kw) \
+        if mixed else m.solve_opts(cg_rtol=1e-13, **kw)
+
+
+def _targets(h, R):
+    return np.ascontiguousarray(np.stack([synth.fourier_target(5100 + r)(h.points) for r in range(R)], axis=1))
+
+
+@pytest.mark.parametrize("R", [1, 3])
+@pytest.mark.parametrize("mixed", [False, True])
+def test_given_up_launches_are_counted(mixed, R):
+    import paper_2503_04914_amd as m
+
+    spin, given_up, _ = _hooks(m)
+    h = synth.halton_hierarchy(sizes=[300, 1200, 4800])
+    F = _targets(h, R)
+    ctx = m.mskm_create(0)
+    hd = m.mskm_hier_create(ctx, h.points, h.offsets, h.delta, fp64=True, fp32=mixed)
+    try:
+        a, b = np.zeros_like(F), np.zeros_like(F)
+        assert m.mskm_solve(ctx, hd, F, a, _opts(m, mixed), nrhs=R).status == m.MSKM_OK
+        assert given_up(ctx) == 0
+        print("[ways back] spin limit 0", flush=True)
+        spin(ctx, 0)
+        assert m.mskm_solve(ctx, hd, F, b, _opts(m, mixed), nrhs=R).status == m.MSKM_OK
+        assert given_up(ctx) > 0
+        spin(ctx, SPIN)
+        n = given_up(ctx)
+        assert m.mskm_solve(ctx, hd, F, b, _opts(m, mixed), nrhs=R).status == m.MSKM_OK
+        assert given_up(ctx) == n
+        assert np.array_equal(a, b)
+    finally:
+        m.mskm_hier_destroy(hd)
+        m.mskm_destroy(ctx)
+
+
+def _tiles_and_rows(mixed, R, sizes):
+    """Solutions and residuals on the tiles and, on a second hierarchy without memory for them, row by row."""
+    import paper_2503_04914_amd as m
+
+    _, _, limits = _hooks(m)
+    h = synth.halton_hierarchy(sizes=sizes)
+    F = _targets(h, R)
+    ctx = m.mskm_create(0)
+    out = []
+    try:
+        for rows in (False, True):
+            hd = m.mskm_hier_create(ctx, h.points, h.offsets, h.delta, fp64=not mixed, fp32=mixed)
+            A, one = np.zeros_like(F), np.zeros(len(F))
+            # one right-hand side first: the preconditioner and the plans of the one-launch CG
+            assert m.mskm_solve(ctx, hd, np.ascontiguousarray(F[:, 0]), one, _opts(m, mixed)).status == m.MSKM_OK
+            print(f"[tiles] rows={rows} R={R} mixed={mixed}", flush=True)
+            if rows:
+                limits(ctx, 1, 0)
+            assert m.mskm_solve(ctx, hd, F, A, _opts(m, mixed), nrhs=R).status == m.MSKM_OK
+            res = m.mskm_residual(ctx, hd, A, F, nrhs=R)
+            limits(ctx, 0, 0)
+            m.mskm_hier_destroy(hd)
+            out.append((A, res))
+    finally:
+        m.mskm_destroy(ctx)
+    return out
+
+
+@pytest.mark.parametrize("R", [2, 17, 64])
+@pytest.mark.parametrize("mixed", [False, True])
+def test_row_by_row_products(mixed, R):
+    """The repository's bars for two results of one system: 1e-10 each in FP64, 1e-8 refined mixed."""
+    (A, ra), (B, rb) = _tiles_and_rows(mixed, R, [60, 301, 1204, 20011])
+    assert ra.max() <= 1e-12 and rb.max() <= 1e-12
+    assert np.linalg.norm(A - B) <= (2e-8 if mixed else 2e-10) * np.linalg.norm(A)
