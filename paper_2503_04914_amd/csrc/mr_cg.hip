@@ -284,8 +284,9 @@ __global__ void __launch_bounds__(kBlock)
 // The same with z = M^-1 r over workgroups of whole preconditioner blocks
 // (partials r.r and r.z): wave w takes blocks w, w + 4, ... of its group. A
 // block's rows of r sit in the lanes as the matrix instruction's second
-// operand, element i of step s in the row that accumulator element i of the
-// product will have, so r and z meet in the same lane. Bound by the four vectors
+// operand, lane (n, k) holding rows k + 4 s of the 16 of step s: a row of the inverse
+// is added in the order of its entries. The rows of the inverse are spread over
+// the first operand so that lane (n, k) gets the same rows of z as it has of r. Bound by the four vectors
 // it streams: 262,144 rows with 256 right-hand sides in FP32 take 191 us, 5.6
 // TB/s. It took 315 us with rows loaded one by one under their bounds check and
 // sixteen waves on the ten or so blocks of a group.
@@ -325,7 +326,7 @@ __global__ void __launch_bounds__(kUpdThreads, 3)
       if (16 * kt < m) {
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-          const size_t e = (size_t)(a + min(16 * kt + Mma<TX>::row(k4, s), m - 1)) * ldr + c;
+          const size_t e = (size_t)(a + min(16 * kt + k4 + 4 * s, m - 1)) * ldr + c;
           load_nt<NT>(rb + e, rv[kt][s]);
           if constexpr (!INIT) load_nt<NT>(q + e, qv[kt][s]);
         }
@@ -337,13 +338,13 @@ __global__ void __launch_bounds__(kUpdThreads, 3)
         if (16 * mt < m && 16 * kt < m) {
 #pragma unroll
           for (int s = 0; s < 4; ++s)
-            mv[mt][kt][s] = Mb[min(16 * mt + n, m - 1) * m + min(16 * kt + Mma<TX>::row(k4, s), m - 1)];
+            mv[mt][kt][s] = Mb[min(16 * mt + Mma<TX>::spread(n), m - 1) * m + min(16 * kt + k4 + 4 * s, m - 1)];
         }
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
-        const int row = 16 * kt + Mma<TX>::row(k4, s);
+        const int row = 16 * kt + k4 + 4 * s;
         if (row < m) {
           const size_t e = (size_t)(a + row) * ldr + c;
           if constexpr (INIT) {
@@ -376,7 +377,7 @@ __global__ void __launch_bounds__(kUpdThreads, 3)
         if (16 * kt >= m) continue;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-          const bool in = 16 * mt + n < m && 16 * kt + Mma<TX>::row(k4, s) < m;
+          const bool in = 16 * mt + Mma<TX>::spread(n) < m && 16 * kt + k4 + 4 * s < m;
           const TX av = in ? mv[mt][kt][s] : (TX)0;
 #pragma unroll
           for (int u = 0; u < NT; ++u) d[u] = Mma<TX>::mul(av, rv[kt][s][u], d[u]);
@@ -384,7 +385,7 @@ __global__ void __launch_bounds__(kUpdThreads, 3)
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int row = 16 * mt + Mma<TX>::row(k4, i);
+        const int row = 16 * mt + k4 + 4 * i;
         if (row < m) {
           TX zv[NT];
 #pragma unroll

@@ -15,16 +15,16 @@ constexpr int kTileSeg = 64;
 
 // One CSR matrix in tiles of 16 rows: tile 4 b + w holds rows 16 w .. of block
 // b of the 64-row SpMV work table. A tile lists the distinct columns of its
-// rows, ascending, padded to a multiple of 16 with its last column; its
-// entries are grouped by segments of 64 listed columns, each with its row and
-// position in the list.
+// rows, ascending (but for their places within 16, tile_place), padded to a
+// multiple of 16 with its last column; its entries are grouped by segments of 64
+// listed columns, each with its row and place in the list.
 struct MrTiles {
   int64_t ntile = 0, nseg = 0, ncol = 0, nnz = 0;
   int64_t* cptr = nullptr;   // [ntile + 1] first listed column
   int32_t* cols = nullptr;   // [ncol]
   int64_t* sptr = nullptr;   // [ntile + 1] first segment
   int64_t* eptr = nullptr;   // [nseg + 1] first entry of each segment
-  uint16_t* code = nullptr;  // [nnz] row << 7 | position % 128
+  uint16_t* code = nullptr;  // [nnz] row << 7 | place % 128
   double* val = nullptr;     // [nnz] values in tile order, as stored by the hierarchy
   float* val32 = nullptr;
   float* lo = nullptr;
@@ -88,6 +88,8 @@ struct Mma<float> {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
   }
   static __device__ __forceinline__ int row(int k, int i) { return 4 * k + i; }  // of accumulator element i
+  // operand row n for which element i of lane (., k) becomes row k + 4 i
+  static __device__ __forceinline__ int spread(int n) { return n / 4 + 4 * (n % 4); }
 };
 template <>
 struct Mma<double> {
@@ -97,6 +99,7 @@ struct Mma<double> {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
   }
   static __device__ __forceinline__ int row(int k, int i) { return k + 4 * i; }
+  static __device__ __forceinline__ int spread(int n) { return n; }
 };
 
 template <typename T, int NT>

@@ -12,10 +12,10 @@
 // accumulation in the operator's precision.
 //
 // Layout. Lane (n, k) = (lane % 16, lane / 16). In one step of 16 listed
-// columns, lane (n, k) reads entries A[n][4 k .. 4 k + 3] of the tile (LDS) and
+// columns, lane (n, k) reads places 4 k .. 4 k + 3 of row n of the tile (LDS) and
 // NT consecutive right-hand sides NT n .. of the four rows of X that belong to
-// columns 4 k .. 4 k + 3 (one vector load each, 256 contiguous bytes per 16
-// lanes): 4 NT matrix instructions, the j-th on columns {4 k + j}, right-hand
+// the columns there (one vector load each, 256 contiguous bytes per 16
+// lanes): 4 NT matrix instructions, the j-th on places {4 k + j}, right-hand
 // sides {NT n + q}. The tile is built in LDS by its own wave (zeroed, the
 // segment's entries scattered), 128 columns at a time in FP32 and 64 in FP64
 // (8.4 KB a wave, 16 waves a CU); the rows of X for the next step are in
@@ -35,6 +35,15 @@ namespace mskm {
 constexpr int kWinWords = 2048;            // bitmap window of 65536 columns
 constexpr int kTileMaxCols = 65536;        // listed columns of one tile (at most)
 constexpr int kTileMaxSegs = kTileMaxCols / kTileSeg;
+
+// Place of listed column pos: within 16 listed columns, column 4 j + k goes to
+// place 4 k + j, so that the matrix instruction j of a step, which takes places j,
+// 4 + j, 8 + j and 12 + j, multiplies columns 4 j .. 4 j + 3. These are added in
+// order, each with one rounding (checked against a chain of fused multiply-adds: no
+// difference in 512,000 FP32 results), and the zeros of the tile add nothing: a
+// row's products are summed in the order of its entries, as the row-by-row
+// kernels of solve_mr.hip sum them, and a level's CG rounds as it does with those.
+__device__ __forceinline__ int tile_place(int pos) { return (pos & ~15) | (pos & 3) << 2 | (pos >> 2 & 3); }
 
 // Rows of tile t: [r0, r1) (empty past the end of its block).
 __device__ __forceinline__ void tile_rows(const WorkTable& wt, int64_t t, int64_t& r0, int64_t& r1) {
@@ -142,9 +151,9 @@ __global__ void __launch_bounds__(kBlock)
   const int n = tile_windows(e0, e1, col, bits, rank, red, [&](int base, int listed) {
     for (int w = t; w < kWinWords; w += kBlock) {
       uint32_t m = bits[w];
-      int64_t at = c0 + listed + rank[w];
+      int at = listed + (int)rank[w];
       while (m) {
-        T.cols[at++] = base + 32 * w + __ffs(m) - 1;
+        T.cols[c0 + tile_place(at++)] = base + 32 * w + __ffs(m) - 1;
         m &= m - 1;
       }
     }
@@ -166,7 +175,7 @@ __global__ void __launch_bounds__(kBlock)
   }
   __threadfence_block();
   __syncthreads();
-  for (int q = n + t; q < nc; q += kBlock) T.cols[c0 + q] = T.cols[c0 + n - 1];
+  for (int q = n + t; q < nc; q += kBlock) T.cols[c0 + tile_place(q)] = T.cols[c0 + tile_place(n - 1)];
   tile_windows(e0, e1, col, bits, rank, red, [&](int base, int listed) {
     for (int64_t k = e0 + t; k < e1; k += kBlock) {
       int pos;
@@ -175,7 +184,7 @@ __global__ void __launch_bounds__(kBlock)
       for (int b = kTileRows / 2; b > 0; b >>= 1)
         if (r0 + row + b < r1 && rp[r0 + row + b] <= k) row += b;
       const int64_t at = e0 + atomicAdd(&hist[pos / kTileSeg], 1);
-      T.code[at] = (uint16_t)(row << 7 | (pos & 127));
+      T.code[at] = (uint16_t)(row << 7 | (tile_place(pos) & 127));
       if (T.val) T.val[at] = val[k];
       if (T.val32) T.val32[at] = val32[k];
       if (T.lo) T.lo[at] = lo32[k];
