@@ -1,27 +1,42 @@
-// CG on one or more middle-sized levels in one launch (x0 = 0): textbook
-// conjugate gradients (Theorem cg), plain or with the cell block-Jacobi
-// preconditioner, with every workgroup of the levels on the GPU at once and
-// every matrix entry, inverse entry and vector of its rows held on its CU.
+// CG on one or more middle-sized levels in one launch (x0 = 0; Theorem cg), plain
+// or with the cell block-Jacobi preconditioner, with every workgroup of the
+// levels on the GPU at once and every matrix entry, inverse entry and vector of its
+// rows held on its CU.
 //
 // What bounds a level of 10^3 .. 10^5 rows is not its bytes but the chain of
 // dependent steps of an iteration: as separate launches it took two to five
 // kernels of 3-6 us each (the preconditioned FP32 form 12 us, the textbook
-// FP64 form 17 us an iteration on 16,384 rows). Here an iteration is one
-// exchange between the level's workgroups, about 1.5 us, plus the work on rows
-// that never leave the CU.
+// FP64 form 17 us an iteration on 16,384 rows). Here an iteration is one or two
+// exchanges between the level's workgroups, about 1.5 us each, plus the work on
+// rows that never leave the CU.
 //
-// One exchange an iteration: with q = A p and w = M^-1 q in hand, a workgroup
-// publishes p.q, r.z, r.r, q.z, q.w of its rows, and w. The sums give the step
-// alpha = r.z / p.q, the stopping test on r.r, and r.z after the step, r.z - 2
-// alpha q.z + alpha^2 q.w, so that the next direction needs nothing more: the
-// halo's z and direction are carried along by every workgroup that reads them,
-// z -= alpha w. r.z and r.r themselves are summed anew every time, only beta
-// uses the predicted value. Against the two exchanges of the textbook order
-// (r.r, r.z and the halo of z, then p.q): 58,000 rows in FP32 380 us a solve
-// (490 before), 22,000 in FP64 without preconditioner 1,021 us (1,333), 1,089
-// rows 462 us (545); coefficients and errors against 64 bits as before. With the
-// sums taken over 16 lanes and through LDS, and the reads of the preconditioner
-// unconditional: 336, 933 and 437 us.
+// Three forms. FP32 and preconditioned solves take the single-reduction form of
+// the launched kernels (kFormOneRed): z = M^-1 r anew in every iteration, exchanged
+// for the halo, then q = A z and the sums z.q, r.z, r.r. Their FP32 arithmetic is
+// the launched kernels' element by element, the order within a row included
+// (GridSum): only the FP64 sums are added in another order, so a mixed solve
+// leaves the coefficients that the launched kernels leave. (Carrying z along by
+// z -= alpha M^-1 q instead saves the halo's exchange, 336 against 371 us for 58,000
+// FP32 rows, but z then keeps the rounding of its first, large values: FP32 solves
+// broke off at 1e-6 of the right-hand side, or ran to their cap, and FP64 ones at
+// 1e-14.)
+//
+// FP64 without preconditioner (kFormPred) has one exchange an iteration: with q =
+// A p in hand, a workgroup publishes p.q, r.r, q.r, q.q of its rows, and q. The sums
+// give the step alpha = r.r / p.q, the stopping test on r.r, and r.r after the
+// step, r.r - 2 alpha q.r + alpha^2 q.q, so that the next direction needs nothing
+// more: the halo's r and direction are carried along by every workgroup that reads
+// them, by the same operations as their owner's. r.r itself is summed anew every
+// time, only beta uses the predicted value. Against the two exchanges of the textbook
+// order: 22,000 rows 881 us a solve (1,333 before), 1,089 rows 399 us (545).
+// Coefficients against 64 bits, 12 to 24 point sets of each of six sizes from 1,600 to
+// 80,000 points: 0.95 to 1.05 times the launched kernels' error in the geometric mean
+// of a size, 0.3 to 2.1 times in single cases (where the last iteration happens to
+// stop).
+//
+// Columns of many right-hand sides, FP32 or preconditioned, take the textbook form
+// of their launched kernels (kFormText), again in their order: r.r, r.z and the
+// halo's z in one exchange, p.q in the other.
 //
 // Exchange without a barrier or a cache flush: every workgroup stores its
 // partial sums into a slot of its own with device-coherent (agent scope)
@@ -35,12 +50,19 @@
 // (2.3 / 2.8 / 3.3 us with adjacent slots; a counter barrier with fences 3.4 /
 // 5.5 / 10.4 us).
 //
-// Reuse of the buffers: exchange m uses buffer m % 3 (exchange 0 has the halo's
-// first z only). A workgroup empties its words of exchange m - 1 once it has
-// received exchange m, which everybody published after leaving m - 1. All
-// stores of a workgroup are waited for before it publishes m + 1, so whoever has
-// received m + 1 sees the emptied words, and polls that buffer again only then,
-// for m + 2.
+// Reuse of the buffers. kFormPred: exchange m uses buffer m % 3 (exchange 0 has the
+// halo's first r only). A workgroup empties its words of exchange m - 1 once it has
+// received exchange m, which everybody published after leaving m - 1. All stores of
+// a workgroup are waited for before it publishes m + 1, so whoever has received m +
+// 1 sees the emptied words, and polls that buffer again only then, for m + 2.
+// kFormOneRed: iteration n's z is in buffer n % 2, its sums in n % 3. Everybody
+// publishes the sums after receiving z, and the sums after leaving the sums before:
+// with the sums of n received, a workgroup empties its z of n and its sums of n - 1,
+// waits for these stores before it publishes the sums of n + 1, and the words are
+// polled again for z of n + 2 and the sums of n + 2, both after the sums of n + 1.
+// kFormText: the sums with z (A) and p.q (B) of iteration n are in buffer n % 2; A
+// and z of n are emptied after B of n, B of n - 1 after A of n, the stores waited
+// for before B of n + 1 or n, and polled again after that.
 //
 // Waiting: every poll loop ends after `spin` polls. A workgroup that gives up
 // sets *aborted and leaves, the others then give up the same way, and the
@@ -74,7 +96,7 @@ struct CgGridDev {
   int32_t* nrow = nullptr;          // [nwg]
   int32_t* nhalo = nullptr;         // [nwg]
   int32_t* halo = nullptr;          // [nwg][kGridLocal] rows of the halo, ascending
-  uint16_t* lidx = nullptr;         // [nwg][kGridE][kGridThreads] position of each entry's column
+  uint16_t* lidx = nullptr;         // [nwg][entry of the row][row] position of each entry's column, kGridE kGridThreads
   int32_t* stats = nullptr;         // [2 L] h_local, h_row
   int32_t nslot = 0;                // workgroups of one launch (at most)
   uint64_t* slots = nullptr;        // [3][nslot][kGridSlot]: three buffers
@@ -97,8 +119,7 @@ static void cg_grid_free(void* p) { delete static_cast<CgGrid*>(p); }
 
 // One workgroup per planned workgroup: its halo (columns of
 // its rows outside its rows, ascending) by a bitmap over the level, and each
-// entry's position in the workgroup's direction vector (own rows first, then
-// the halo), laid out by the registers that will hold the entries.
+// entry's position in the workgroup's vector (own rows first, then the halo).
 __global__ void __launch_bounds__(kGridThreads)
     k_grid_plan(const CgGridDev P, int L, int lanes, int per, const DevLevel* __restrict__ lev, const WorkTable wt,
                 const int64_t* __restrict__ rp, const int32_t* __restrict__ col) {
@@ -171,7 +192,8 @@ __global__ void __launch_bounds__(kGridThreads)
         const int64_t d = c - off;
         p = nr + (int)(rank[d >> 5] + __popc(bits[d >> 5] & ((1u << (d & 31)) - 1u)));
       }
-      P.lidx[((size_t)wg * kGridE + k) * kGridThreads + t] = (uint16_t)min(p, kGridLocal - 1);
+      P.lidx[(size_t)wg * kGridE * kGridThreads + (g + k * lanes) * (kGridThreads / lanes) + i] =
+          (uint16_t)min(p, kGridLocal - 1);
     }
   }
   atomicMax(&maxlen, len);
@@ -248,7 +270,7 @@ static int plan_workgroups(const mskm_hier* h, const CgGridPlan& P, int lanes, i
   return n <= h->ctx->ncu ? n : 0;
 }
 
-mskm_status cg_grid_ready(mskm_hier* h, int lo, int hi, bool bj, int* lanes) {
+mskm_status cg_grid_ready(mskm_hier* h, int lo, int hi, bool bj, int* lanes, int most_lanes) {
   *lanes = 0;
   if (h->N >= INT32_MAX) return MSKM_OK;
   for (int l = lo; l <= hi; ++l)
@@ -262,8 +284,8 @@ mskm_status cg_grid_ready(mskm_hier* h, int lo, int hi, bool bj, int* lanes) {
   CgGrid& g = *static_cast<CgGrid*>(h->cg_grid);
   // 256 rows per workgroup, two lanes a row, as long as the workgroups are at
   // most one per CU; else 512 rows, one lane a row. The latter first for levels
-  // of up to 512 rows that it solves with one workgroup each: a solve of 341 rows
-  // takes 87 us without exchanges, one of 1,365 rows in five workgroups 157 us
+  // of up to 512 rows that it solves with one workgroup each: a solve of 342 rows
+  // takes 74 us without exchanges, one of 1,366 rows in five workgroups 137 us
   // (k_cg_level_wg, which reads the matrix in every iteration: 259 us for 341).
   int64_t most = 0;
   for (int l = lo; l <= hi; ++l) most = std::max<int64_t>(most, h->h_lev[l].n);
@@ -291,7 +313,7 @@ mskm_status cg_grid_ready(mskm_hier* h, int lo, int hi, bool bj, int* lanes) {
       return MSKM_OK;
     }
   }
-  for (int ln = 2; ln >= 1 && *lanes == 0; --ln) {
+  for (int ln = most_lanes; ln >= 1 && *lanes == 0; --ln) {
     MSKM_TRY(fits(ln, &nw));
     if (nw > 0) *lanes = ln;
   }
@@ -300,23 +322,24 @@ mskm_status cg_grid_ready(mskm_hier* h, int lo, int hi, bool bj, int* lanes) {
 
 // -------------------------------------------------------------------- solve
 
-// The row's entry of M^-1 times the block rb: this lane's share of the inverse
-// row, in registers (N of them, zeros past the block) or read through the caches
-// (N = 1). The reads of rb are unconditional, past the block its last entry: under
-// a bounds check each was waited for by itself, 1,650 cycles for 16 of them
+// The row's entry of M^-1 times the block rb, in the block's order as the
+// launched kernels add it; every lane of a row has it. The inverse row is in
+// registers (N of them, zeros past the block) or read through the caches (N =
+// 1). The reads of rb are unconditional, past the block its last entry: under a
+// bounds check each was waited for by itself, 1,650 cycles for 16 of them
 // instead of 550.
-template <int G, int N, typename TX>
-__device__ __forceinline__ TX grid_precond(const TX (&iv)[N], const TX* Mi, int bm, const TX* rb, int g) {
+template <int N, typename TX>
+__device__ __forceinline__ TX grid_precond(const TX (&iv)[N], const TX* Mi, int bm, const TX* rb) {
   TX a = 0;
   if constexpr (N > 1) {
     const int last = max(bm - 1, 0);
 #pragma unroll
-    for (int k = 0; k < N; ++k) a += iv[k] * rb[min(g + k * G, last)];
+    for (int k = 0; k < N; ++k) a += iv[k] * rb[min(k, last)];
   } else {
 #pragma unroll 4
-    for (int j = g; j < bm; j += G) a += Mi[j] * rb[j];
+    for (int j = 0; j < bm; ++j) a += Mi[j] * rb[j];
   }
-  return lanes_sum<G>(a);
+  return a;
 }
 
 // Right-hand sides of one launch: column col0 + q of b and x (ld words a row)
@@ -327,30 +350,50 @@ struct GridCols {
   MrState* st;  // [L][ld], instead of the per-level states
 };
 
-constexpr int kSums = 5;  // p.q, r.z, r.r, q.z, q.M^-1 q
+// Order in which a row's products are added, that of the product which the
+// launched kernels take for the same levels: an FP32 solve then rounds as they
+// do, element by element. Entry order; the two halves of the two-waves-per-slice
+// product (every other group of four); 4, 8 or 16 lanes' shares, lane i's being
+// entries i, i + 4, ....
+enum GridSum { kSumRow = 0, kSumHalves = 1, kSumLanes4 = 4, kSumLanes8 = 8, kSumLanes16 = 16 };
+
+// Forms of the iteration. kFormPred: textbook with one exchange an iteration
+// (FP64 without preconditioner). kFormOneRed: single reduction (FP32, or
+// preconditioned). kFormText: textbook (columns of many right-hand sides, FP32 or
+// preconditioned).
+enum GridForm { kFormPred, kFormOneRed, kFormText };
+
+constexpr int kSums = 4;  // kFormPred: p.q, r.r, q.r, q.q
 
 // G lanes per row, 512 / G rows per workgroup, at most E matrix entries per
-// lane. Thread t holds entries g, g + G, ... of row t / G (g = t % G) and the
-// row's share of its block inverse; all G lanes of a row hold its x, r, p, z.
-// SOLO: every level has one workgroup, which exchanges nothing and takes the
-// sums from LDS.
-template <typename TX, bool PC, int G, int E, bool SOLO>
+// lane. Thread t holds a share of row t / G's entries (grid_entry) and the
+// row's part of its block inverse; all G lanes of a row hold its vectors'
+// entries. SOLO: every level has one workgroup, which exchanges nothing and takes
+// the sums from LDS.
+template <int G>
+__device__ __forceinline__ int grid_entry(int sum, int k, int g) {  // the lane's k-th entry of the row
+  return G == 2 && sum == kSumHalves ? (k >> 2) * 8 + 4 * g + (k & 3) : g + k * G;
+}
+
+template <typename TX, bool PC, int G, int E, bool SOLO, int FORM>
 __global__ void __launch_bounds__(kGridThreads)
-    k_cg_grid(const CgGridDev P, int wgb, const DevLevel* __restrict__ lev, const int64_t* __restrict__ rp,
+    k_cg_grid(const CgGridDev P, int wgb, int sum, const DevLevel* __restrict__ lev, const int64_t* __restrict__ rp,
               const TX* __restrict__ val, const TX* __restrict__ b, TX* __restrict__ x,
               typename GridWord<TX>::type* z0, typename GridWord<TX>::type* z1, typename GridWord<TX>::type* z2,
               CgLevel* __restrict__ st,
               int32_t* aborted, double rtol2, int maxit, int spin, const PcArgs<TX> pc,
               const GridCols gc) {
+  static_assert(FORM != kFormPred || !PC, "z is r");
   using W = typename GridWord<TX>::type;
   constexpr int RW = kGridThreads / G;
   constexpr int kWaves = kGridThreads / kWave;
   constexpr int kH = kGridLocal / kGridThreads;  // halo entries per thread
   constexpr int kParts = kWaves * kWave / 16;    // sums over 16 lanes of a workgroup
   constexpr bool kInvRegs = PC && sizeof(TX) == 4;
-  constexpr int kI = kInvRegs ? kBjMax / G : 1;
-  __shared__ TX pw[kGridLocal];    // direction: own rows, then the halo
-  __shared__ TX zw[SOLO ? 1 : kGridLocal];  // z of the halo
+  constexpr int kI = kInvRegs ? kBjMax : 1;
+  constexpr bool kHaloZ = !SOLO && FORM == kFormPred;
+  __shared__ TX pw[kGridLocal];    // what A multiplies (p, or z in kFormOneRed): own rows, then the halo
+  __shared__ TX zw[kHaloZ ? kGridLocal : 1];  // z of the halo
   __shared__ int32_t hrow[SOLO ? 1 : kGridLocal];  // rows of the halo
   __shared__ TX rs[PC ? RW : 1];   // what the preconditioner is applied to
   __shared__ double sm[kSums][kParts], sp[kSums];
@@ -382,19 +425,65 @@ __global__ void __launch_bounds__(kGridThreads)
     len = mine ? (int)(e - s) : 0;
 #pragma unroll
     for (int k = 0; k < E; ++k) {
-      const int q = g + k * G;
+      const int q = grid_entry<G>(sum, k, g);
       v[k] = q < len ? val[s + q] : (TX)0;
-      const uint32_t c = q < len ? P.lidx[((size_t)wg * kGridE + k) * kGridThreads + t] : 0u;
+      const uint32_t c = q < len ? P.lidx[(size_t)wg * kGridE * kGridThreads + q * RW + i] : 0u;
       if (k & 1)
         ci[k / 2] |= c << 16;
       else
         ci[k / 2] = c;
     }
   }
-  int kmax = (len + G - 1) / G;  // entries per lane of the wave's longest row
+  // entries per lane of the wave's longest row
+  int kmax = G == 2 && sum == kSumHalves ? (len + 7) / 8 * 4 : (len + G - 1) / G;
   for (int o = 32; o > 0; o >>= 1) kmax = max(kmax, __shfl_xor(kmax, o, kWave));
   kmax = __builtin_amdgcn_readfirstlane(kmax);
-  // block inverse: entries g, g + G, ... of the row
+  // the lane's products in NA accumulators, these added in halves
+  auto dot = [&](auto na, auto by_four) {
+    constexpr int NA = decltype(na)::value;
+    TX a[NA];
+#pragma unroll
+    for (int u = 0; u < NA; ++u) a[u] = 0;
+#pragma unroll
+    for (int k0 = 0; k0 < E; k0 += 8)
+      if (k0 < kmax) {
+#pragma unroll
+        for (int k = k0; k < k0 + 8; ++k)
+          a[(decltype(by_four)::value ? k >> 2 : k) & (NA - 1)] +=
+              v[k] * pw[k & 1 ? ci[k / 2] >> 16 : ci[k / 2] & 0xffffu];
+      }
+#pragma unroll
+    for (int o = NA / 2; o > 0; o /= 2)
+#pragma unroll
+      for (int u = 0; u < o; ++u) a[u] += a[u + o];
+    return a[0];
+  };
+  using std::bool_constant;
+  using std::integral_constant;
+  auto product = [&]() -> TX {
+    TX q;
+    if constexpr (FORM == kFormPred) {
+      q = dot(integral_constant<int, 1>{}, bool_constant<false>{});
+    } else if constexpr (G == 2) {
+      if (sum == kSumLanes4)
+        q = dot(integral_constant<int, 2>{}, bool_constant<false>{});
+      else if (sum == kSumLanes8)
+        q = dot(integral_constant<int, 4>{}, bool_constant<false>{});
+      else if (sum == kSumLanes16)
+        q = dot(integral_constant<int, 8>{}, bool_constant<false>{});
+      else
+        q = dot(integral_constant<int, 1>{}, bool_constant<false>{});
+    } else {
+      if (sum == kSumRow)
+        q = dot(integral_constant<int, 1>{}, bool_constant<false>{});
+      else if (sum == kSumHalves)
+        q = dot(integral_constant<int, 2>{}, bool_constant<true>{});
+      else
+        q = dot(integral_constant<int, 8>{}, bool_constant<false>{});
+    }
+    return lanes_sum<G>(q);
+  };
+  // block inverse: the row's entries
   int ba = 0, bm = 0;
   const TX* Mi = nullptr;
   TX iv[kI];
@@ -408,21 +497,24 @@ __global__ void __launch_bounds__(kGridThreads)
     }
   }
 #pragma unroll
-  for (int k = 0; k < kI; ++k) iv[k] = kInvRegs && g + k * G < bm ? Mi[g + k * G] : (TX)0;
+  for (int k = 0; k < kI; ++k) iv[k] = kInvRegs && k < bm ? Mi[k] : (TX)0;
 
-  TX xi = 0, ri = mine ? b[row * gc.ld + col] : (TX)0, pi, zi;
+  TX xi = 0, ri = mine ? b[row * gc.ld + col] : (TX)0, pi = 0, zi;
   if (t == 0) bad = 0;
-  if constexpr (PC) {
-    if (first) rs[i] = ri;
-    __syncthreads();
-    zi = grid_precond<G, kI, TX>(iv, Mi, bm, rs + ba, g);
-  } else {
-    zi = ri;
-  }
+  auto precondition = [&] {  // z = M^-1 r
+    if constexpr (PC) {
+      if (first) rs[i] = ri;
+      __syncthreads();
+      zi = grid_precond<kI, TX>(iv, Mi, bm, rs + ba);
+    } else {
+      zi = ri;
+    }
+  };
+  precondition();
   // halo entries t, t + kGridThreads, ... are the thread's; their rows stay in LDS
   for (int q = t; !SOLO && q < nh; q += kGridThreads) hrow[q] = P.halo[(size_t)wg * kGridLocal + q];
 
-  // exchange m: words of buffer m % 3
+  // words of the halo
   W hz[SOLO ? 1 : kH];
   auto halo_words = [&](W* zc) {
 #pragma unroll
@@ -437,139 +529,275 @@ __global__ void __launch_bounds__(kGridThreads)
       hz[q] = t + q * kGridThreads < nh ? get(&zc[hrow[t + q * kGridThreads]]) : (W)0;
     }
   };
-  // z of the halo (exchange 0), and the first direction
-  if constexpr (!SOLO) {
-    __syncthreads();
-    if (first) put(&z0[row], word_of(zi));
-    halo_ask(z0);
-    halo_words(z0);
-#pragma unroll
-    for (int q = 0; q < kH; ++q)
-      if (t + q * kGridThreads < nh) pw[nr + t + q * kGridThreads] = zw[t + q * kGridThreads] = value_of(hz[q]);
-  }
-  pi = zi;
-  if (first) pw[i] = pi;
-
   static_assert(kParts == 32, "two sums of 16");
   auto total = [&](int k) {
     const double s = lanes_sum<16>(sm[k][lane % kParts]);
     return readlane_f64(s, 0) + readlane_f64(s, 16);
   };
+  auto parts = [&](int k, double a) {
+    a = lanes_sum<16>(a);
+    if (lane % 16 == 0) sm[k][t / 16] = a;
+  };
+  // wave w's sum over the level's workgroups: word w of buffer m
+  auto level_sum = [&](int m, int word) {
+    uint64_t u[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      u[k] = lane + k * kWave < nw ? get(slot + (m * nslot + lane + k * kWave) * kGridSlot + word) : 0ull;
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (u[k] == kEmptySlot)
+        u[k] = poll(slot + (m * nslot + lane + k * kWave) * kGridSlot + word, kEmptySlot, spin, &bad);
+      s += value_of(u[k]);
+    }
+    s = wave64_sum(s);
+    if (lane == 0) sp[word] = s;
+  };
   double bb = 0.0, rr = 0.0;
   int n = 0, capped = 0;
-  for (int m = 1;; ++n, m = m == 2 ? 0 : m + 1) {  // m = (n + 1) % 3
-    W* const zc = m == 0 ? z0 : m == 1 ? z1 : z2;
-    W* const zp = m == 0 ? z2 : m == 1 ? z0 : z1;
+  if constexpr (!SOLO) {
     __syncthreads();
-    if (bad) break;
-    TX q = 0;
-#pragma unroll
-    for (int k0 = 0; k0 < E; k0 += 8)
-      if (k0 < kmax) {
-#pragma unroll
-        for (int k = k0; k < k0 + 8; ++k) q += v[k] * pw[k & 1 ? ci[k / 2] >> 16 : ci[k / 2] & 0xffffu];
-      }
-    q = lanes_sum<G>(q);
-    TX wi = q;  // M^-1 q
-    if constexpr (PC) {
-      if (first) rs[i] = q;
-      __syncthreads();
-      wi = grid_precond<G, kI, TX>(iv, Mi, bm, rs + ba, g);
-    }
-    // every earlier store of this workgroup is waited for before it publishes
+    if (first) put(&z0[row], word_of(zi));
+  }
+
+  if constexpr (FORM == kFormPred) {
+    // z of the halo (exchange 0), and the first direction
     if constexpr (!SOLO) {
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      if (first) put(&zc[row], word_of(wi));
-    }
-    double a[kSums] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    if (first) {
-      a[0] = (double)pi * (double)q;
-      a[1] = (double)ri * (double)zi;
-      a[2] = (double)ri * (double)ri;
-      a[3] = (double)q * (double)zi;
-      a[4] = (double)q * (double)wi;
-    }
+      halo_ask(z0);
+      halo_words(z0);
 #pragma unroll
-    for (int k = 0; k < kSums; ++k) {
-      a[k] = lanes_sum<16>(a[k]);
-      if (lane % 16 == 0) sm[k][t / 16] = a[k];
+      for (int q = 0; q < kH; ++q)
+        if (t + q * kGridThreads < nh) pw[nr + t + q * kGridThreads] = zw[t + q * kGridThreads] = value_of(hz[q]);
     }
-    __syncthreads();
-    double pq, rz, qz, qw;
-    if constexpr (SOLO) {
-      pq = total(0);
-      rz = total(1);
-      rr = total(2);
-      qz = total(3);
-      qw = total(4);
-    } else {
-      if (w < kSums) {
-        const double s = total(w);
-        if (lane == 0) put(slot + (m * nslot + me) * kGridSlot + w, word_of(s));
-      }
-      // the halo and the level's sums (wave w: word w), whichever comes first
-      halo_ask(zc);
-      if (w < kSums) {
-        uint64_t u[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-          u[k] = lane + k * kWave < nw ? get(slot + (m * nslot + lane + k * kWave) * kGridSlot + w) : 0ull;
-        double s = 0.0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          if (u[k] == kEmptySlot) u[k] = poll(slot + (m * nslot + lane + k * kWave) * kGridSlot + w, kEmptySlot, spin, &bad);
-          s += value_of(u[k]);
-        }
-        s = wave64_sum(s);
-        if (lane == 0) sp[w] = s;
-      }
-      halo_words(zc);
+    pi = zi;
+    if (first) pw[i] = pi;
+    for (int m = 1;; ++n, m = m == 2 ? 0 : m + 1) {  // m = (n + 1) % 3
+      W* const zc = m == 0 ? z0 : m == 1 ? z1 : z2;
+      W* const zp = m == 0 ? z2 : m == 1 ? z0 : z1;
       __syncthreads();
       if (bad) break;
-      pq = sp[0];
-      rz = sp[1];
-      rr = sp[2];
-      qz = sp[3];
-      qw = sp[4];
-    }
-    if (n == 0) bb = rr;
-    const bool conv = isfinite(rr) && !(rr > rtol2 * bb);
-    if (conv || !isfinite(rr) || !(rz > 0.0) || !isfinite(rz) || n >= maxit) {
-      capped = conv ? 0 : 1;
-      break;
-    }
-    if (!(pq > 0.0) || !isfinite(pq)) {  // cannot happen for SPD A and p != 0
-      capped = 1;
-      break;
-    }
-    // everybody has left the exchange before
-    if constexpr (!SOLO) {
-      if (first) put(&zp[row], GridWord<TX>::empty);
-      if (w < kSums && lane == 0) put(slot + ((m == 0 ? 2 : m - 1) * nslot + me) * kGridSlot + w, kEmptySlot);
-    }
-    const double alpha = rz / pq;
-    const double rznew = rz - alpha * (2.0 * qz - alpha * qw);  // r.z after the step
-    const TX beta = rznew > 0.0 ? (TX)(rznew / rz) : (TX)0;
-    xi = (TX)((double)xi + alpha * (double)pi);
-    ri = (TX)((double)ri - alpha * (double)q);
-    if constexpr (PC)
-      zi = (TX)((double)zi - alpha * (double)wi);
-    else
-      zi = ri;
-    pi = zi + beta * pi;
-    if (first) pw[i] = pi;
-    if constexpr (!SOLO) {
+      const TX q = product();
+      // every earlier store of this workgroup is waited for before it publishes
+      if constexpr (!SOLO) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (first) put(&zc[row], word_of(q));
+      }
+      parts(0, first ? (double)pi * (double)q : 0.0);
+      parts(1, first ? (double)ri * (double)ri : 0.0);
+      parts(2, first ? (double)q * (double)ri : 0.0);
+      parts(3, first ? (double)q * (double)q : 0.0);
+      __syncthreads();
+      double pq, qr, qq;
+      if constexpr (SOLO) {
+        pq = total(0);
+        rr = total(1);
+        qr = total(2);
+        qq = total(3);
+      } else {
+        if (w < 4) {
+          const double s = total(w);
+          if (lane == 0) put(slot + (m * nslot + me) * kGridSlot + w, word_of(s));
+        }
+        // the halo and the level's sums, whichever comes first
+        halo_ask(zc);
+        if (w < 4) level_sum(m, w);
+        halo_words(zc);
+        __syncthreads();
+        if (bad) break;
+        pq = sp[0];
+        rr = sp[1];
+        qr = sp[2];
+        qq = sp[3];
+      }
+      if (n == 0) bb = rr;
+      const bool conv = isfinite(rr) && !(rr > rtol2 * bb);
+      if (conv || !isfinite(rr) || n >= maxit) {
+        capped = conv ? 0 : 1;
+        break;
+      }
+      if (!(pq > 0.0) || !isfinite(pq)) {  // cannot happen for SPD A and p != 0
+        capped = 1;
+        break;
+      }
+      // everybody has left the exchange before
+      if constexpr (!SOLO) {
+        if (first) put(&zp[row], GridWord<TX>::empty);
+        if (w < 4 && lane == 0) put(slot + ((m == 0 ? 2 : m - 1) * nslot + me) * kGridSlot + w, kEmptySlot);
+      }
+      const double alpha = rr / pq;
+      const double rrnew = rr - alpha * (2.0 * qr - alpha * qq);  // r.r after the step
+      const TX beta = rrnew > 0.0 ? (TX)(rrnew / rr) : (TX)0;
+      xi = (TX)((double)xi + alpha * (double)pi);
+      ri = (TX)((double)ri - alpha * (double)q);
+      pi = ri + beta * pi;
+      if (first) pw[i] = pi;
+      if constexpr (!SOLO) {
 #pragma unroll
-      for (int h = 0; h < kH; ++h) {
-        if (t + h * kGridThreads < nh) {
-          const int at = nr + t + h * kGridThreads;
-          const TX zh = (TX)((double)zw[at - nr] - alpha * (double)value_of(hz[h]));
-          zw[at - nr] = zh;
-          pw[at] = zh + beta * pw[at];
+        for (int h = 0; h < kH; ++h) {
+          if (t + h * kGridThreads < nh) {
+            const int at = nr + t + h * kGridThreads;
+            const TX zh = (TX)((double)zw[at - nr] - alpha * (double)value_of(hz[h]));
+            zw[at - nr] = zh;
+            pw[at] = zh + beta * pw[at];
+          }
         }
       }
     }
   }
+
+  if constexpr (FORM == kFormOneRed) {
+    TX si = 0;  // A p
+    CgLevel S{};
+    S.rtol2 = rtol2;
+    S.maxit = maxit;
+    if (first) pw[i] = zi;
+    for (int m = 0;; ++n, m = m == 2 ? 0 : m + 1) {  // m = n % 3
+      W* const zc = n & 1 ? z1 : z0;
+      W* const zn = n & 1 ? z0 : z1;
+      if constexpr (!SOLO) {
+        halo_ask(zc);
+        halo_words(zc);
+#pragma unroll
+        for (int q = 0; q < kH; ++q)
+          if (t + q * kGridThreads < nh) pw[nr + t + q * kGridThreads] = value_of(hz[q]);
+      }
+      __syncthreads();
+      if (bad) break;
+      const TX q = product();
+      parts(0, first ? (double)zi * (double)q : 0.0);
+      parts(1, first ? (double)zi * (double)ri : 0.0);
+      if constexpr (PC) parts(2, first ? (double)ri * (double)ri : 0.0);
+      constexpr int kWords = PC ? 3 : 2;
+      // every earlier store of this workgroup is waited for before it publishes
+      if constexpr (!SOLO) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      double delta, gamma;
+      if constexpr (SOLO) {
+        delta = total(0);
+        gamma = total(1);
+        rr = PC ? total(2) : gamma;
+      } else {
+        if (w < kWords) {
+          const double s = total(w);
+          if (lane == 0) put(slot + (m * nslot + me) * kGridSlot + w, word_of(s));
+          level_sum(m, w);
+        }
+        __syncthreads();
+        if (bad) break;
+        delta = sp[0];
+        gamma = sp[1];
+        rr = PC ? sp[2] : gamma;
+      }
+      if (n == 0) S.bb = bb = rr;
+      if (!cg1_decide(S, gamma, delta, rr)) {
+        capped = S.capped;
+        break;
+      }
+      if constexpr (!SOLO) {
+        // everybody has this iteration's z, and has left the sums before
+        if (first) put(&zc[row], GridWord<TX>::empty);
+        if (w < kWords && lane == 0) put(slot + ((m == 0 ? 2 : m - 1) * nslot + me) * kGridSlot + w, kEmptySlot);
+      }
+      const TX beta = (TX)S.beta;
+      pi = zi + beta * pi;
+      si = q + beta * si;
+      xi = (TX)((double)xi + S.alpha * (double)pi);
+      ri = (TX)((double)ri - S.alpha * (double)si);
+      precondition();
+      if (first) {
+        pw[i] = zi;
+        if constexpr (!SOLO) put(&zn[row], word_of(zi));
+      }
+    }
+  }
+
+  if constexpr (FORM == kFormText) {
+    if (first) pw[i] = (TX)0;
+    for (int q = t; !SOLO && q < nh; q += kGridThreads) pw[nr + q] = (TX)0;
+    double rzold = 0.0;
+    for (;; ++n) {
+      W* const zc = n & 1 ? z1 : z0;
+      W* const zn = n & 1 ? z0 : z1;
+      const int m = n & 1;
+      // exchange A: r.r, r.z and z of the halo
+      parts(0, first ? (double)ri * (double)ri : 0.0);
+      parts(1, first ? (double)ri * (double)zi : 0.0);
+      __syncthreads();
+      double rz;
+      if constexpr (SOLO) {
+        rr = total(0);
+        rz = total(1);
+      } else {
+        if (w < 2) {
+          const double s = total(w);
+          if (lane == 0) put(slot + (m * nslot + me) * kGridSlot + w, word_of(s));
+        }
+        halo_ask(zc);
+        if (w < 2) level_sum(m, w);
+        halo_words(zc);
+        __syncthreads();
+        if (bad) break;
+        rr = sp[0];
+        rz = sp[1];
+      }
+      if (n == 0) bb = rr;
+      const bool conv = isfinite(rr) && !(rr > rtol2 * bb);
+      if (conv || !isfinite(rr) || (n > 0 && !isfinite(rz)) || n >= maxit) {
+        capped = conv ? 0 : 1;
+        break;
+      }
+      // everybody has left the sum p.q before
+      if constexpr (!SOLO)
+        if (n > 0 && t == 0) put(slot + ((m ^ 1) * nslot + me) * kGridSlot + 2, kEmptySlot);
+      const TX beta = n == 0 ? (TX)0 : (TX)(rz / rzold);
+      rzold = rz;
+      pi = zi + beta * pi;
+      if (first) pw[i] = pi;
+      if constexpr (!SOLO) {
+#pragma unroll
+        for (int h = 0; h < kH; ++h)
+          if (t + h * kGridThreads < nh) {
+            const int at = nr + t + h * kGridThreads;
+            pw[at] = value_of(hz[h]) + beta * pw[at];
+          }
+      }
+      __syncthreads();
+      const TX q = product();
+      // exchange B: p.q (every earlier store of this workgroup is waited for first)
+      parts(2, first ? (double)pi * (double)q : 0.0);
+      if constexpr (!SOLO) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      double pq;
+      if constexpr (SOLO) {
+        pq = total(2);
+      } else {
+        if (w == 0) {
+          const double s = total(2);
+          if (lane == 0) put(slot + (m * nslot + me) * kGridSlot + 2, word_of(s));
+          level_sum(m, 2);
+        }
+        __syncthreads();
+        if (bad) break;
+        pq = sp[2];
+      }
+      if (!(pq > 0.0) || !isfinite(pq)) {  // cannot happen for SPD A and p != 0
+        capped = !(rr <= rtol2 * bb);
+        break;
+      }
+      if constexpr (!SOLO) {  // everybody has this iteration's z and sums
+        if (first) put(&zc[row], GridWord<TX>::empty);
+        if (w < 2 && lane == 0) put(slot + (m * nslot + me) * kGridSlot + w, kEmptySlot);
+      }
+      const double alpha = rz / pq;
+      xi = (TX)((double)xi + alpha * (double)pi);
+      ri = (TX)((double)ri - alpha * (double)q);
+      precondition();
+      if constexpr (!SOLO)
+        if (first) put(&zn[row], word_of(zi));
+    }
+  }
+
   if (bad) {
     if (t == 0) atomicOr(aborted, 1);
     return;
@@ -657,8 +885,25 @@ void grid_empty(hipStream_t s, TX* z0, TX* z1, TX* z2, int64_t r0, int64_t n, ui
 template void grid_empty<float>(hipStream_t, float*, float*, float*, int64_t, int64_t, uint64_t*, int64_t, int32_t*);
 template void grid_empty<double>(hipStream_t, double*, double*, double*, int64_t, int64_t, uint64_t*, int64_t, int32_t*);
 
+// The sum that the launched kernels of these levels make of a row's products
+// (FP32; FP64 results do not depend on it to the accuracy asked for).
+static int grid_sum(const mskm_hier* h, int lo, int hi, int lanes, bool fp32) {
+  int64_t most = 0;
+  for (int l = lo; l <= hi; ++l) most = std::max<int64_t>(most, h->h_lev[l].n);
+  const int code = h->spmv_g[MSKM_OP_DIAG][fp32 ? 1 : 0];
+  int sum = kSumLanes8;  // the CSR product in 8 lanes; others differ in rounding
+  if (most <= kWgSolveRows)
+    sum = most <= 64 ? kSumLanes16 : most <= 256 ? kSumLanes4 : kSumLanes8;
+  else if (code == kSellCode && h->sell.col16)
+    sum = h->h_off[hi + 1] - h->h_off[lo] <= kSplitProductRows ? kSumHalves : kSumRow;
+  else if (code == kSellCode || code == kSell32Code)
+    sum = kSumRow;
+  if (lanes == 2) return sum == kSumRow ? kSumHalves : sum;
+  return sum == kSumRow || sum == kSumHalves ? sum : kSumLanes8;
+}
+
 // The kernel for levels lo..hi with the columns of gc, `cols` of them.
-template <typename TX>
+template <typename TX, int FORM>
 static void grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, const TX* val, const TX* b, TX* x, TX* z0,
                         TX* z1, TX* z2, CgLevel* st, int32_t* aborted, double rtol2, int maxit, const PcArgs<TX>& pc,
                         const GridCols& gc, int cols) {
@@ -666,32 +911,46 @@ static void grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, const 
   const CgGridPlan& P = static_cast<CgGrid*>(h->cg_grid)->plan[bj ? 1 : 0][lanes == 2 ? 0 : 1];
   const int w0 = P.h_wg0[lo];
   const bool solo = gc.nw == hi - lo + 1;
+  const int sum = FORM == kFormOneRed ? grid_sum(h, lo, hi, lanes, sizeof(TX) == 4) : kSumRow;
   int longest = 0;
   for (int l = lo; l <= hi; ++l) longest = std::max(longest, P.h_row[l]);
-#define MSKM_GRID_LAUNCH(PCF, GG, EE, SS)                                                                         \
-  hipLaunchKernelGGL((k_cg_grid<TX, PCF, GG, EE, SS>), dim3((unsigned)gc.nw * cols), dim3(kGridThreads), 0,       \
-                     h->ctx->stream, P.d, w0, h->d_lev, h->diag.rowptr, val, b, x, (W*)z0, (W*)z1, (W*)z2, st,    \
+#define MSKM_GRID_LAUNCH(PCF, GG, EE, SS)                                                                           \
+  hipLaunchKernelGGL((k_cg_grid<TX, PCF, GG, EE, SS, FORM>), dim3((unsigned)gc.nw * cols), dim3(kGridThreads), 0,   \
+                     h->ctx->stream, P.d, w0, sum, h->d_lev, h->diag.rowptr, val, b, x, (W*)z0, (W*)z1, (W*)z2, st, \
                      aborted, rtol2, maxit, h->ctx->grid_spin, pc, gc)
-#define MSKM_GRID_FORM(GG, EE)                \
-  do {                                        \
-    if (solo && bj)                           \
-      MSKM_GRID_LAUNCH(true, GG, EE, true);   \
-    else if (solo)                            \
-      MSKM_GRID_LAUNCH(false, GG, EE, true);  \
-    else if (bj)                              \
-      MSKM_GRID_LAUNCH(true, GG, EE, false);  \
-    else                                      \
-      MSKM_GRID_LAUNCH(false, GG, EE, false); \
+#define MSKM_GRID_SOLO(PCF, GG, EE)          \
+  do {                                       \
+    if (solo)                                \
+      MSKM_GRID_LAUNCH(PCF, GG, EE, true);   \
+    else                                     \
+      MSKM_GRID_LAUNCH(PCF, GG, EE, false);  \
   } while (0)
-  if (lanes == 2 && longest <= 64)
-    MSKM_GRID_FORM(2, 32);
-  else if (lanes == 2)
-    MSKM_GRID_FORM(2, 64);
-  else if (longest <= 48)
+#define MSKM_GRID_FORM(GG, EE)                                  \
+  do {                                                          \
+    if constexpr (FORM != kFormPred) {                          \
+      if (bj) {                                                 \
+        MSKM_GRID_SOLO(true, GG, EE);                           \
+        return;                                                 \
+      }                                                         \
+    }                                                           \
+    if constexpr (FORM == kFormPred || sizeof(TX) == 4)         \
+      MSKM_GRID_SOLO(false, GG, EE);                            \
+  } while (0)
+  if constexpr (FORM != kFormText) {  // whose rows are one lane's
+    if (lanes == 2) {
+      if (longest <= 64)
+        MSKM_GRID_FORM(2, 32);
+      else
+        MSKM_GRID_FORM(2, 64);
+      return;
+    }
+  }
+  if (longest <= 48)
     MSKM_GRID_FORM(1, 48);
   else
     MSKM_GRID_FORM(1, 64);
 #undef MSKM_GRID_FORM
+#undef MSKM_GRID_SOLO
 #undef MSKM_GRID_LAUNCH
 }
 
@@ -708,7 +967,14 @@ mskm_status cg_grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, con
     const int64_t r0 = h->h_off[lo], n = h->h_off[hi + 1] - r0;
     grid_empty<TX>(h->ctx->stream, z0, z1, z2, r0, n, P.d.slots, (int64_t)3 * P.d.nslot * kGridSlot, aborted);
   }
-  auto launch = [&] { grid_launch<TX>(h, lo, hi, bj, lanes, val, b, x, z0, z1, z2, st, aborted, rtol2, maxit, pc, gc, 1); };
+  auto launch = [&] {
+    if constexpr (sizeof(TX) == 8)
+      if (!bj) {
+        grid_launch<TX, kFormPred>(h, lo, hi, bj, lanes, val, b, x, z0, z1, z2, st, aborted, rtol2, maxit, pc, gc, 1);
+        return;
+      }
+    grid_launch<TX, kFormOneRed>(h, lo, hi, bj, lanes, val, b, x, z0, z1, z2, st, aborted, rtol2, maxit, pc, gc, 1);
+  };
   if (!solo) return cg_grid_in_turn(h->ctx, launch);
   launch();
   MSKM_HIP_TRY(hipGetLastError());
@@ -721,9 +987,10 @@ template mskm_status cg_grid_launch<double>(mskm_hier*, int, int, bool, int, con
                                             const PcArgs<double>&);
 
 // Launches one after the other that the columns of a level may take: an
-// iteration takes 3-4 us in each, launched for all columns at once 25-35 us.
-// Measured for 21 right-hand sides: 5,461 rows in two launches 0.48 ms (launched
-// 1.5 ms), 21,845 rows in seven 2.7 ms (2.6 ms).
+// iteration takes 4-5 us in each, launched for all columns at once 25-35 us.
+// Measured for 21 right-hand sides: 4,096 rows in one launch 0.25 ms, 16,384 rows in
+// four 1.4 ms; three solves of a hierarchy of 87,000 points and their residuals 19.9 ms
+// (31.0 ms with every level launched).
 constexpr int kGridRounds = 4;
 
 // Columns past the right-hand sides: zero solutions, nothing done.
@@ -745,8 +1012,11 @@ mskm_status cg_grid_columns(mskm_hier* h, int lo, int hi, bool bj, const TX* val
                             TX* z2, int nrhs, int R, MrState* st, int32_t* aborted, double rtol2, int maxit, const PcArgs<TX>& pc,
                             int* how) {
   *how = 0;
+  // the textbook form as the launched kernels have it, whose rows are added in
+  // entry order (one lane a row); FP64 without preconditioner as in cg_grid_launch
+  const bool text = bj || sizeof(TX) == 4;
   int lanes = 0;
-  MSKM_TRY(cg_grid_ready(h, lo, hi, bj, &lanes));
+  MSKM_TRY(cg_grid_ready(h, lo, hi, bj, &lanes, text ? 1 : 2));
   if (lanes == 0) return MSKM_OK;
   const CgGridPlan& P = static_cast<CgGrid*>(h->cg_grid)->plan[bj ? 1 : 0][lanes == 2 ? 0 : 1];
   const int nw = P.h_wg0[hi + 1] - P.h_wg0[lo], ncu = h->ctx->ncu;
@@ -757,10 +1027,18 @@ mskm_status cg_grid_columns(mskm_hier* h, int lo, int hi, bool bj, const TX* val
   if (nrhs < R)
     hipLaunchKernelGGL(k_grid_pad<TX>, dim3(mr_nblk(n * (R - nrhs), kBlock)), dim3(kBlock), 0, h->ctx->stream, x, st, r0,
                        n, lo, hi - lo + 1, nrhs, R);
+  auto launch = [&](const GridCols& gc, int cols) {
+    if constexpr (sizeof(TX) == 8)
+      if (!text) {
+        grid_launch<TX, kFormPred>(h, lo, hi, bj, lanes, val, b, x, z0, z1, z2, nullptr, aborted, rtol2, maxit, pc, gc,
+                                   cols);
+        return;
+      }
+    grid_launch<TX, kFormText>(h, lo, hi, bj, lanes, val, b, x, z0, z1, z2, nullptr, aborted, rtol2, maxit, pc, gc,
+                               cols);
+  };
   if (solo) {
-    const GridCols gc{nw, R, 0, st};
-    grid_launch<TX>(h, lo, hi, bj, lanes, val, b, x, z0, z1, z2, nullptr, aborted, rtol2, maxit, pc, gc,
-                    nrhs);
+    launch(GridCols{nw, R, 0, st}, nrhs);
     MSKM_HIP_TRY(hipGetLastError());
     *how = 1;
     return MSKM_OK;
@@ -769,10 +1047,7 @@ mskm_status cg_grid_columns(mskm_hier* h, int lo, int hi, bool bj, const TX* val
     grid_empty<TX>(h->ctx->stream, z0, z1, z2, r0 * R, c0 == 0 ? n * R : 0, P.d.slots, (int64_t)3 * P.d.nslot * kGridSlot,
                    c0 == 0 ? aborted : nullptr);
     const GridCols gc{nw, R, c0, st};
-    MSKM_TRY(cg_grid_in_turn(h->ctx, [&] {
-      grid_launch<TX>(h, lo, hi, bj, lanes, val, b, x, z0, z1, z2, nullptr, aborted, rtol2, maxit, pc, gc,
-                      std::min(per, nrhs - c0));
-    }));
+    MSKM_TRY(cg_grid_in_turn(h->ctx, [&] { launch(gc, std::min(per, nrhs - c0)); }));
   }
   *how = 2;
   return MSKM_OK;

@@ -24,6 +24,41 @@ struct CgLevel {
   double alpha_prev;
 };
 
+// Single-reduction step decision on the level's sums: gamma = r.z (z = r, or
+// M^-1 r when preconditioned), delta = z.A z, rr = r.r. Stops on rr before
+// the update; else beta = gamma / gamma_prev, alpha = gamma / (delta - beta
+// gamma / alpha_prev). Returns true when the update is to be applied.
+__device__ __forceinline__ bool cg1_decide(CgLevel& S, double gamma, double delta, double rr) {
+  S.rr = rr;
+  const bool finite = isfinite(rr) && isfinite(gamma) && isfinite(delta);
+  if (finite && !(rr > S.rtol2 * S.bb)) {
+    S.done = 1;
+    return false;
+  }
+  if (!finite || S.iters >= S.maxit) {
+    S.done = 1;
+    S.capped = 1;
+    return false;
+  }
+  const double beta = S.iters == 0 ? 0.0 : gamma / S.rr_prev;
+  const double den = S.iters == 0 ? delta : delta - beta * gamma / S.alpha_prev;
+  if (!(den > 0.0) || !isfinite(den) || !(gamma > 0.0)) {  // cannot happen for SPD A (and M) and r != 0
+    S.done = 1;
+    S.capped = 1;
+    return false;
+  }
+  S.beta = beta;
+  S.alpha = gamma / den;
+  S.rr_prev = gamma;
+  S.alpha_prev = S.alpha;
+  S.iters += 1;
+  return true;
+}
+
+constexpr int kWgSolveRows = 1024;  // largest level solved by one workgroup (k_cg_level_wg)
+// Levels of at most this many rows together take the two-waves-per-slice product.
+constexpr int64_t kSplitProductRows = 65536;
+
 // Preconditioner arguments (block-Jacobi forms).
 template <typename TX>
 struct PcArgs {
@@ -37,8 +72,8 @@ struct PcArgs {
 // cg_grid.hip: the whole CG of levels lo..hi in one launch, their workgroups
 // all on the GPU at once. cg_grid_ready decides (building the plan at its
 // first use) whether these levels can take it, and with how many lanes per
-// row (0: they cannot).
-mskm_status cg_grid_ready(mskm_hier* h, int lo, int hi, bool bj, int* lanes);
+// row (at most most_lanes; 0: they cannot).
+mskm_status cg_grid_ready(mskm_hier* h, int lo, int hi, bool bj, int* lanes, int most_lanes = 2);
 // Queues the solve A_l x_l = b_l (x0 = 0) of levels lo..hi; z0, z1, z2: three
 // vectors of the hierarchy's length, scratch. st[l] receives the final
 // states. *aborted (device) is set, and x and st are unusable, when a

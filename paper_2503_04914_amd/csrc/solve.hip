@@ -805,37 +805,6 @@ __global__ void __launch_bounds__(kRedBlock) k_cg_red_b(int lev0, const int32_t*
   }
 }
 
-// Single-reduction step decision on the level's sums: gamma = r.z (z = r, or
-// M^-1 r when preconditioned), delta = z.A z, rr = r.r. Stops on rr before
-// the update; else beta = gamma / gamma_prev, alpha = gamma / (delta - beta
-// gamma / alpha_prev). Returns true when the update is to be applied.
-__device__ __forceinline__ bool cg1_decide(CgLevel& S, double gamma, double delta, double rr) {
-  S.rr = rr;
-  const bool finite = isfinite(rr) && isfinite(gamma) && isfinite(delta);
-  if (finite && !(rr > S.rtol2 * S.bb)) {
-    S.done = 1;
-    return false;
-  }
-  if (!finite || S.iters >= S.maxit) {
-    S.done = 1;
-    S.capped = 1;
-    return false;
-  }
-  const double beta = S.iters == 0 ? 0.0 : gamma / S.rr_prev;
-  const double den = S.iters == 0 ? delta : delta - beta * gamma / S.alpha_prev;
-  if (!(den > 0.0) || !isfinite(den) || !(gamma > 0.0)) {  // cannot happen for SPD A (and M) and r != 0
-    S.done = 1;
-    S.capped = 1;
-    return false;
-  }
-  S.beta = beta;
-  S.alpha = gamma / den;
-  S.rr_prev = gamma;
-  S.alpha_prev = S.alpha;
-  S.iters += 1;
-  return true;
-}
-
 // Single-reduction form, one block per level: the sums of the product's
 // partials (dq: z.A z, gp: r.z, rp: r.r, null when z = r) and the decision.
 __global__ void __launch_bounds__(kRedBlock) k_cg1_red(int lev0, const int32_t* __restrict__ lev_begin,
@@ -939,7 +908,6 @@ __global__ void __launch_bounds__(kBlock)
 // row bounds and preconditioner block of each row are read once, so an
 // iteration reads from memory only the matrix entries and the inverse rows.
 // x0 = 0; the final state goes to st[l], the solution to x.
-constexpr int kWgSolveRows = 1024;  // largest level solved by one workgroup
 constexpr int kWgThreads = 1024;
 
 // G lanes per row in the product, R rows per group of G lanes (R kWgThreads / G >= n).
@@ -1308,8 +1276,6 @@ static PcArgs<TX> pc_args(mskm_hier* h, SolveWS& W) {
 // table (the sliced copy's for variants kSellCode / kSell32Code, else the
 // CSR table), with the per-block partials v.q into W.part_s and, when given,
 // v.rv (v.v without rv) into pp and rv.rv into p3.
-// Levels of at most this many rows take the two-waves-per-slice product.
-constexpr int64_t kSplitProductRows = 65536;
 
 template <typename TV, typename TX>
 static void launch_cg_product(mskm_hier* h, SolveWS& W, const TV* dval, int G, int qb0, int qbn, const TX* v, TX* q,

@@ -73,3 +73,116 @@ def test_tiles_round_as_rows(R):
     finally:
         m.mskm_destroy(ctx)
     _same_rounding(*out)
+
+
+def _one_launch_and_launched(h, R, opts, sell=True, **store):
+    import paper_2503_04914_amd as m
+
+    spin, given_up, _ = _hooks(m)
+    F = _targets(h, R)
+    ctx = m.mskm_create(0)
+    hd = m.mskm_hier_create(ctx, h.points, h.offsets, h.delta, **store)
+    if sell:
+        for prec in [p for p, k in ((m.MSKM_PREC_FP32, "fp32"), (m.MSKM_PREC_FP64, "fp64")) if store.get(k)]:
+            m.mskm_set_spmv_width(hd, m.MSKM_OP_DIAG, prec, m.SELL_CODE)
+    out = []
+    try:
+        for k in (SPIN, 0):
+            print(f"[rounding] N={len(F)} R={R} spin limit {k}", flush=True)
+            spin(ctx, k)
+            A = np.zeros_like(F)
+            r = m.mskm_solve(ctx, hd, F, A, opts(m), nrhs=R)
+            out.append((A, r.report, r.status))
+            assert (given_up(ctx) > 0) == (k == 0)
+    finally:
+        m.mskm_hier_destroy(hd)
+        m.mskm_destroy(ctx)
+    return out
+
+
+# levels of one workgroup in every group of lanes, of two lanes and one lane a row, and past one sum a row (65,536 rows)
+SIZES = {"one workgroup": [50, 250, 500, 1000], "two lanes a row": [257, 1030, 17001], "one lane a row": [4003, 64001],
+         "entry order": [900, 90003]}
+
+
+@pytest.mark.parametrize("bj", [True, False])
+@pytest.mark.parametrize("sizes", list(SIZES))
+def test_one_launch_rounds_as_launched(sizes, bj):
+    import paper_2503_04914_amd as m
+
+    h = synth.halton_hierarchy(sizes=SIZES[sizes])
+    pc = m.MSKM_PRECOND_BLOCK_JACOBI if bj else m.MSKM_PRECOND_NONE
+    (a, _, _), (b, _, _) = _one_launch_and_launched(h, 1, lambda m: _early(m, precond=pc), fp64=False, fp32=True)
+    _same_rounding(a, b)
+
+
+@pytest.mark.parametrize("bj", [True, False])
+def test_columns_round_as_launched(bj):
+    import paper_2503_04914_amd as m
+
+    h = synth.halton_hierarchy(sizes=[257, 1030, 5003])
+    pc = m.MSKM_PRECOND_BLOCK_JACOBI if bj else m.MSKM_PRECOND_NONE
+    (a, _, _), (b, _, _) = _one_launch_and_launched(h, 21, lambda m: _early(m, precond=pc), fp64=False, fp32=True)
+    _same_rounding(a, b)
+
+
+def _level(n, nu=synth.NU_2D_40):
+    return synth.halton_hierarchy(sizes=[n], nu=nu)
+
+
+@pytest.mark.parametrize("R", [1, 3])
+@pytest.mark.parametrize("rtol", [1e-7, 1e-12])
+@pytest.mark.parametrize("n", [1365, 16385, 58000])
+def test_fp32_preconditioned_tolerance(n, rtol, R):
+    """One FP32 solve with block-Jacobi to tolerances below 1e-6, the default among them: as many iterations as
+    the launched kernels need, give or take one (the stopping test on sums in another order)."""
+    import paper_2503_04914_amd as m
+
+    opts = lambda m: _mixed(m, cg_rtol=rtol, target_rel_residual=1e-3)  # noqa: E731  met after one round
+    (_, ra, sa), (_, rb, sb) = _one_launch_and_launched(_level(n), R, opts, fp64=False, fp32=True)
+    assert sa == sb == m.MSKM_OK
+    assert ra["refine_steps"] == rb["refine_steps"] == 1
+    assert abs(ra["cg_iters_total"] - rb["cg_iters_total"]) <= R, (ra, rb)
+    assert ra["cg_iters_total"] < 1000 * R
+
+
+@pytest.mark.parametrize("rtol", [1e-7, 1e-12])
+@pytest.mark.parametrize("n", [65, 300])
+def test_fp32_preconditioned_tolerance_one_workgroup(n, rtol):
+    """Levels of one workgroup, which never give up: CG ends within as many iterations as unknowns, and the 1,365
+    rows of the test above need about 120 to 1e-12."""
+    import paper_2503_04914_amd as m
+
+    ctx = m.mskm_create(0)
+    h = _level(n)
+    f = _targets(h, 1)
+    hd = m.mskm_hier_create(ctx, h.points, h.offsets, h.delta, fp64=False, fp32=True)
+    try:
+        r = m.mskm_solve(ctx, hd, f, np.zeros_like(f), _mixed(m, cg_rtol=rtol, target_rel_residual=1e-3))
+        assert r.status == m.MSKM_OK and r.report["refine_steps"] == 1
+        assert r.report["cg_iters_total"] <= 200
+    finally:
+        m.mskm_hier_destroy(hd)
+        m.mskm_destroy(ctx)
+
+
+@pytest.mark.parametrize("R", [1, 2])
+@pytest.mark.parametrize("nu,rtol", [(synth.NU_2D_40, 1e-15), (synth.NU_2D_40 * 1.22, 1e-14), (5.4, 1e-14)])
+@pytest.mark.parametrize("n", [341, 1025, 4225, 20000])
+def test_fp64_preconditioned_tolerance(n, nu, rtol, R):
+    """FP64 with block-Jacobi on rows of about 40, 60 and 92 entries, to where the launched kernels still stop by
+    themselves (a level that breaks off or runs to its cap is reported as not converged)."""
+    import paper_2503_04914_amd as m
+
+    ctx = m.mskm_create(0)
+    h = _level(n, nu)
+    F = _targets(h, R)
+    hd = m.mskm_hier_create(ctx, h.points, h.offsets, h.delta, fp64=True, fp32=False)
+    try:
+        r = m.mskm_solve(ctx, hd, F, np.zeros_like(F),
+                         m.solve_opts(cg_rtol=rtol, algorithm=m.MSKM_ALG_SEQUENTIAL,
+                                      precond=m.MSKM_PRECOND_BLOCK_JACOBI), nrhs=R)
+        assert r.status == m.MSKM_OK, r.report
+    finally:
+        m.mskm_hier_destroy(hd)
+        m.mskm_destroy(ctx)
