@@ -1,18 +1,19 @@
-// FP32 CG on a depth of large levels in one launch (x0 = 0): the method and the
-// exchange of cg_grid.hip for levels whose matrix does not fit the registers.
+// FP32 CG on a depth of large levels in one launch (x0 = 0): the single-reduction
+// form and the exchange of cg_grid.hip (kFormOneRed; its buffers and their reuse) for
+// levels whose matrix does not fit the registers.
 //
 // One workgroup per CU owns up to 1,504 consecutive rows (three slots of 512). x,
-// r, the direction on the columns its rows reach, the place of every row's block
-// inverse and, where they fit, the inverses stay in LDS over the whole solve; the
-// matrix of the first RES slots stays in registers, that of the rest in the LDS
-// left over and, past it, is read once an iteration from L2.
+// r, z on the columns its rows reach, the place of every row's block
+// inverse and, where they fit, the inverses stay in LDS over the whole solve, the
+// direction and A p in registers; the matrix of the first RES slots stays in
+// registers, that of the rest in the LDS left over and, past it, is read once an
+// iteration from L2.
 //
-// Bound: two exchanges between 256 workgroups an iteration (2 us each) and the
-// LDS reads of the product, one word an entry. A solve of 262,144 rows with 45
-// entries a row in 55 iterations takes 1.02 ms (launched: 27 us an iteration,
-// 1.5 ms); one step of sixteen series fell from 39.8 to 19.6 ms, a 3-D state of
-// 300,000 sites (levels of up to 100 entries a row, one resident slot) from 41
-// to 30 ms.
+// Bound: the sums' exchange between 256 workgroups (2 us) and the halo's z an
+// iteration, and the LDS reads of the product, one word an entry. A solve of
+// 262,144 rows with 45 entries a row in 55 iterations takes 0.87 ms (launched: 27
+// us an iteration, 1.5 ms; the textbook form, which waits for two sums, 1.02 ms);
+// a 3-D one of up to 100 entries a row, one resident slot, 3.3 ms (4.2 ms).
 //
 // The window is kept in runs of 64 columns, and only the runs that are used: in
 // Morton order a workgroup's columns span up to 60,000 places of which it uses
@@ -61,7 +62,7 @@ struct CgStreamDev {
   uint32_t* chunk = nullptr;      // [nwg][kStreamChunks] those: place << 16 | run
   float* val = nullptr;           // entries in groups of four per row, as in the sliced copy
   uint16_t* idx = nullptr;        // position of each entry's column in the kept runs
-  uint64_t* slots = nullptr;      // [4][nwg][kGridSlot]
+  uint64_t* slots = nullptr;      // [3][nwg][kGridSlot]
   int32_t* stats = nullptr;       // [6] widest slice, longest window, most rows, inverse words, kept runs, halo runs
 };
 
@@ -291,7 +292,7 @@ mskm_status build_stream(mskm_hier* h, CgStreamPlan& P, int depth, bool bj) {
   MSKM_TRY(halloc(h, &D.flags, nwg * kStreamFlagWords));
   MSKM_TRY(halloc(h, &D.chunk, nwg * kStreamChunks));
   MSKM_TRY(halloc(h, &D.rank, nwg * kStreamChunks));
-  MSKM_TRY(halloc(h, &D.slots, 4 * nwg * kGridSlot));
+  MSKM_TRY(halloc(h, &D.slots, 3 * nwg * kGridSlot));
   MSKM_TRY(halloc(h, &D.stats, 6));
   D.nwg = (int32_t)nwg;
   void* part = nullptr;
@@ -342,31 +343,34 @@ typedef float st_f4 __attribute__((ext_vector_type(4)));
 typedef unsigned short st_u4 __attribute__((ext_vector_type(4)));
 
 // kStreamRt slots of 512 rows, the first RES of them in registers (rows of at
-// most E entries). Thread t holds row 512 j + t in slot j.
-template <bool PC, int RES, int E>
+// most E entries). Thread t holds row 512 j + t in slot j. The single-reduction
+// form and the order of the launched kernels, so that a solve rounds as theirs
+// does, element by element: a row's products are added in entry order, or
+// (HALVES, where these take the two-waves-per-slice product) in two sums over
+// every other group of four entries.
+template <bool PC, int RES, int E, bool HALVES>
 __global__ void __launch_bounds__(kGridThreads)
     k_cg_stream(const CgStreamDev P, int window, int rows, int ninv, int nl, int width, const float* __restrict__ b,
                 float* __restrict__ x, uint32_t* z0, uint32_t* z1, CgLevel* __restrict__ st, int32_t* aborted,
                 double rtol2, int maxit, int spin, const PcArgs<float> pc) {
   constexpr int RT = kStreamRt;
   extern __shared__ __align__(16) char lds[];
-  float* const pw = reinterpret_cast<float*>(lds);                 // direction on the kept runs of the window
-  float* const rs = pw + (window + 3) / 4 * 4;                     // r, x of the own rows
+  float* const zw = reinterpret_cast<float*>(lds);                 // z on the kept runs of the window
+  float* const rs = zw + (window + 3) / 4 * 4;                     // r, x of the own rows
   float* const xs = rs + (rows + 3) / 4 * 4;
   int2* const bi = reinterpret_cast<int2*>(xs + (rows + 3) / 4 * 4);  // inverse offset, block start << 8 | size
   float* const li = reinterpret_cast<float*>(bi + (rows + 3) / 4 * 4);  // block inverses
   float* const lv = li + ninv;                                     // slices kept here: values, positions
   uint16_t* const lx = reinterpret_cast<uint16_t*>(lv + nl * width * kWave);
   uint32_t* const chunk = reinterpret_cast<uint32_t*>(lx + nl * width * kWave);
-  __shared__ double sm[2][kStreamWaves], sp[kStreamWaves];
+  __shared__ double sm[3][kStreamWaves], sp[kStreamWaves], sq[4];
   __shared__ int bad;
   const int wg = blockIdx.x, t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t / kWave), lane = t % kWave;
   const int l = P.lev[wg], nw = P.nw[wg], me = P.part[wg], nslot = P.nwg;
   const int r0 = P.row0[wg], nr = P.nrow[wg], base = P.wbase[wg], wlen = P.wlen[wg], own0 = r0 - base;
   const int own = P.rank[(int64_t)wg * kStreamChunks + (own0 >> 6)] * kWave + (own0 & 63);  // own rows in the kept runs
   const int nchunk = P.nchunk[wg];
-  uint64_t* const slotA = P.slots + (size_t)P.wg0[wg] * kGridSlot;
-  uint64_t* const slotB = slotA + (size_t)2 * nslot * kGridSlot;
+  uint64_t* const slot = P.slots + (size_t)P.wg0[wg] * kGridSlot;
   const int64_t* const so = P.soff + ((int64_t)wg * kStreamWaves + w) * RT;
 
   // resident entries
@@ -410,7 +414,7 @@ __global__ void __launch_bounds__(kGridThreads)
     }
   }
   for (int k = t; k < nchunk; k += kGridThreads) chunk[k] = P.chunk[(int64_t)wg * kStreamChunks + k];
-  for (int k = t; k < window; k += kGridThreads) pw[k] = 0.0f;
+  for (int k = t; k < window; k += kGridThreads) zw[k] = 0.0f;
   for (int q = w; q < nl; q += kStreamWaves) {  // streamed slice q: slot RES + q / 8 of wave q % 8
     const int64_t o = so[RES + q / kStreamWaves], e = so[RES + q / kStreamWaves + 1];
     for (int64_t d = o + 4 * lane; d < e; d += 4 * kWave) {
@@ -425,20 +429,17 @@ __global__ void __launch_bounds__(kGridThreads)
   if (t == 0) bad = 0;
   __syncthreads();
 
-  float z[RT];
+  float p[RT], s[RT];  // direction and A p of the own rows
+#pragma unroll
+  for (int j = 0; j < RT; ++j) p[j] = s[j] = 0.0f;
   // z = M^-1 r of the own rows (the inverses are symmetric: lane i of a block
-  // reads column i, consecutive lanes consecutive words), published in zc and
-  // emptied in zp, with the sums of r.r and r.z
-  double a = 0.0, c = 0.0;
-  auto residuals = [&](uint32_t* zc, uint32_t* zp, bool clear) {
-    a = c = 0.0;
+  // reads column i, consecutive lanes consecutive words), published in zc
+  auto precondition = [&](uint32_t* zc) {
 #pragma unroll
     for (int j = 0; j < RT; ++j) {
       const int i = j * kGridThreads + t;
-      z[j] = 0.0f;
       if (i < nr) {
-        const float ri = rs[i];
-        float zi = ri;
+        float zi = rs[i];
         if constexpr (PC) {
           const int2 q = bi[i];
           const int m = q.y & 255, ba = q.y >> 8;
@@ -454,36 +455,23 @@ __global__ void __launch_bounds__(kGridThreads)
             for (int k = 0; k < m; ++k) zi += Mc[k * m] * rb[k];
           }
         }
-        z[j] = zi;
+        zw[own + i] = zi;
         put(&zc[r0 + i], word_of(zi));
-        if (clear) put(&zp[r0 + i], kEmptyWord);
-        a += (double)ri * (double)ri;
-        c += (double)ri * (double)zi;
       }
     }
   };
+  precondition(z0);
 
-  double rzold = 0.0, bb = 0.0, rr = 0.0;
-  int n = 0, capped = 0;
-  residuals(z0, z1, false);
-  for (;; ++n) {
+  CgLevel S{};
+  S.rtol2 = rtol2;
+  S.maxit = maxit;
+  int n = 0;
+  for (int m = 0;; ++n, m = m == 2 ? 0 : m + 1) {  // m = n % 3
     uint32_t* const zc = n & 1 ? z1 : z0;
-    // exchange A: r.r and r.z
-    a = wave64_sum(a);
-    c = wave64_sum(c);
-    if (lane == 0) {
-      sm[0][w] = a;
-      sm[1][w] = c;
-    }
-    __syncthreads();
-    if (w < 2) {
-      const double s = lanes_sum<kStreamWaves>(sm[w][lane % kStreamWaves]);
-      if (lane == 0) put(slotA + ((n & 1) * nslot + me) * kGridSlot + w, word_of(s));
-    }
-    // the wave's first halo runs are on their way while the sums are waited for
-    uint32_t hz[kStreamHalo];
-    int he[kStreamHalo];
-    auto ask = [&](int q0) {
+    // z of the halo, four runs of a wave at a time
+    for (int q0 = 0; q0 < nchunk; q0 += kStreamHalo * kStreamWaves) {
+      uint32_t hz[kStreamHalo];
+      int he[kStreamHalo], at[kStreamHalo];
 #pragma unroll
       for (int q = 0; q < kStreamHalo; ++q) {
         const int k = q0 + q * kStreamWaves + w;
@@ -492,137 +480,138 @@ __global__ void __launch_bounds__(kGridThreads)
           const uint32_t ck = chunk[k];
           const int e = (int)(ck & 0xffffu) * kWave + lane;
           if (e < wlen && (e < own0 || e >= own0 + nr)) {
-            he[q] = (int)(ck >> 16) * kWave + lane;
+            he[q] = e;
+            at[q] = (int)(ck >> 16) * kWave + lane;
             hz[q] = get(&zc[base + e]);
           }
         }
       }
-    };
-    ask(0);
-    double s = 0.0;
-    if (t % 256 < nw) s = value_of(poll(slotA + ((n & 1) * nslot + t % 256) * kGridSlot + t / 256, kEmptySlot, spin, &bad));
-    s = wave64_sum(s);
-    if (lane == 0) sp[w] = s;
-    __syncthreads();
-    rr = (sp[0] + sp[1]) + (sp[2] + sp[3]);
-    const double rz = (sp[4] + sp[5]) + (sp[6] + sp[7]);
-    if (n == 0) bb = rr;
-    const float beta = n == 0 ? 0.0f : (float)(rz / rzold);
-    const int hspin = bad ? 0 : spin;
-    // direction on the halo and the own rows
-    for (int q0 = 0; q0 < nchunk; q0 += kStreamHalo * kStreamWaves) {
-      if (q0 > 0) ask(q0);
 #pragma unroll
       for (int q = 0; q < kStreamHalo; ++q)
         if (he[q] >= 0) {
-          uint32_t u = hz[q];
-          if (u == kEmptyWord)
-            u = poll(&zc[base + (int)(chunk[q0 + q * kStreamWaves + w] & 0xffffu) * kWave + lane], kEmptyWord, hspin,
-                     &bad);
-          pw[he[q]] = value_of(u) + beta * pw[he[q]];
+          if (hz[q] == kEmptyWord) hz[q] = poll(&zc[base + he[q]], kEmptyWord, bad ? 0 : spin, &bad);
+          zw[at[q]] = value_of(hz[q]);
         }
-    }
-#pragma unroll
-    for (int j = 0; j < RT; ++j) {
-      const int i = j * kGridThreads + t;
-      if (i < nr) pw[own + i] = z[j] + beta * pw[own + i];
     }
     __syncthreads();
     if (bad) break;
-    const bool conv = isfinite(rr) && !(rr > rtol2 * bb);
-    if (conv || !isfinite(rr) || !(rz > 0.0) || !isfinite(rz) || n >= maxit) {
-      capped = conv ? 0 : 1;
-      break;
-    }
-    rzold = rz;
-    if (t == 0 && n > 0) put(slotB + (((n + 1) & 1) * nslot + me) * kGridSlot, kEmptySlot);
-    // q = A p (the empty asm statements keep the compiler from unpacking the
+    // q = A z (the empty asm statements keep the compiler from unpacking the
     // resident positions once and for all, into twice as many registers, and
     // from having the LDS reads of many groups in flight: both would spill)
     float qv[RT];
-    a = 0.0;
+    double a0 = 0.0, a1 = 0.0, a2 = 0.0;
 #pragma unroll
     for (int j = 0; j < RT; ++j) {
-      float acc = 0.0f;
+      float acc = 0.0f, odd = 0.0f;
       if (j < RES) {
+        auto resident = [&](float& e, float& o) {  // groups of four into e and o in turn
 #pragma unroll
-        for (int k0 = 0; k0 < kE; k0 += 16) {
+          for (int k0 = 0; k0 < kE; k0 += 16) {
 #pragma unroll
-          for (int k = k0 / 2; k < k0 / 2 + 8; ++k) asm volatile("" : "+v"(ci[j < RES ? j : 0][k]));
+            for (int k = k0 / 2; k < k0 / 2 + 8; ++k) asm volatile("" : "+v"(ci[j < RES ? j : 0][k]));
 #pragma unroll
-          for (int k = k0; k < k0 + 16; ++k)
-            acc += v[j < RES ? j : 0][k] *
-                   pw[k & 1 ? ci[j < RES ? j : 0][k / 2] >> 16 : ci[j < RES ? j : 0][k / 2] & 0xffffu];
-          asm volatile("" ::: "memory");
-        }
+            for (int k = k0; k < k0 + 16; ++k) {
+              const uint32_t c = ci[j < RES ? j : 0][k / 2];
+              float& d = k & 4 ? o : e;
+              d += v[j < RES ? j : 0][k] * zw[k & 1 ? c >> 16 : c & 0xffffu];
+            }
+            asm volatile("" ::: "memory");
+          }
+        };
+        resident(acc, HALVES ? odd : acc);
       } else {
         const int q = (j - RES) * kStreamWaves + w;
         const int64_t o = so[j];
         const int len = (int)(so[j + 1] - o);
-        if (q < nl) {  // kept in LDS
-          const float* pv = lv + q * width * kWave + 4 * lane;
-          const uint16_t* px = lx + q * width * kWave + 4 * lane;
-#pragma unroll 4
-          for (int d = 0; d < len; d += 4 * kWave) {
+        const bool here = q < nl;  // kept in LDS
+        auto streamed = [&](const float* pv, const uint16_t* px) {
+          auto group = [&](int d, float& to) {
             const st_f4 f = *reinterpret_cast<const st_f4*>(pv + d);
             const st_u4 u = *reinterpret_cast<const st_u4*>(px + d);
-            acc += f.x * pw[u.x];
-            acc += f.y * pw[u.y];
-            acc += f.z * pw[u.z];
-            acc += f.w * pw[u.w];
-          }
-        } else {
-          const float* pv = P.val + o + 4 * lane;
-          const uint16_t* px = P.idx + o + 4 * lane;
+            to += f.x * zw[u.x];
+            to += f.y * zw[u.y];
+            to += f.z * zw[u.z];
+            to += f.w * zw[u.w];
+          };
+          if constexpr (HALVES) {
+            int d = 0;
+#pragma unroll 2
+            for (; d + 4 * kWave < len; d += 8 * kWave) {
+              group(d, acc);
+              group(d + 4 * kWave, odd);
+            }
+            if (d < len) group(d, acc);
+          } else {
 #pragma unroll 4
-          for (int d = 0; d < len; d += 4 * kWave) {
-            const st_f4 f = *reinterpret_cast<const st_f4*>(pv + d);
-            const st_u4 u = *reinterpret_cast<const st_u4*>(px + d);
-            acc += f.x * pw[u.x];
-            acc += f.y * pw[u.y];
-            acc += f.z * pw[u.z];
-            acc += f.w * pw[u.w];
+            for (int d = 0; d < len; d += 4 * kWave) group(d, acc);
           }
-        }
+        };
+        if (here)
+          streamed(lv + q * width * kWave + 4 * lane, lx + q * width * kWave + 4 * lane);
+        else
+          streamed(P.val + o + 4 * lane, P.idx + o + 4 * lane);
       }
+      if constexpr (HALVES) acc += odd;
       qv[j] = acc;
       const int i = j * kGridThreads + t;
-      if (i < nr) a += (double)pw[own + i] * (double)acc;
+      if (i < nr) {
+        const double zi = (double)zw[own + i], ri = (double)rs[i];
+        a0 += zi * (double)acc;
+        a1 += zi * ri;
+        a2 += ri * ri;
+      }
     }
-    // exchange B: p.q (every earlier store of this workgroup is waited for first)
-    a = wave64_sum(a);
-    if (lane == 0) sm[0][w] = a;
+    // exchange of z.q, r.z and r.r (every earlier store of this workgroup is waited for first)
+    a0 = wave64_sum(a0);
+    a1 = wave64_sum(a1);
+    if constexpr (PC) a2 = wave64_sum(a2);
+    if (lane == 0) {
+      sm[0][w] = a0;
+      sm[1][w] = a1;
+      sm[2][w] = a2;
+    }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (w == 0) {
-      const double q = lanes_sum<kStreamWaves>(sm[0][lane % kStreamWaves]);
-      if (lane == 0) put(slotB + ((n & 1) * nslot + me) * kGridSlot, word_of(q));
+    if (w < (PC ? 3 : 2)) {
+      const double a = lanes_sum<kStreamWaves>(sm[w][lane % kStreamWaves]);
+      if (lane == 0) put(slot + (m * nslot + me) * kGridSlot + w, word_of(a));
     }
-    s = 0.0;
-    if (t < 256 && t < nw) s = value_of(poll(slotB + ((n & 1) * nslot + t) * kGridSlot, kEmptySlot, spin, &bad));
-    if (w < 4) {
-      s = wave64_sum(s);
-      if (lane == 0) sp[w] = s;
+    const uint64_t* const sa = slot + (size_t)(m * nslot) * kGridSlot;
+    uint64_t u = 0, u2 = 0;  // word t / 256, and word 2
+    if (t % 256 < nw) {
+      u = get(sa + t % 256 * kGridSlot + t / 256);
+      if (PC && t < 256) u2 = get(sa + t * kGridSlot + 2);
+      if (u == kEmptySlot) u = poll(sa + t % 256 * kGridSlot + t / 256, kEmptySlot, spin, &bad);
+      if (PC && u2 == kEmptySlot) u2 = poll(sa + t * kGridSlot + 2, kEmptySlot, bad ? 0 : spin, &bad);
+    }
+    const double s01 = wave64_sum(value_of(u));
+    if (lane == 0) sp[w] = s01;
+    if (PC && w < 4) {
+      const double s2 = wave64_sum(value_of(u2));
+      if (lane == 0) sq[w] = s2;
     }
     __syncthreads();
     if (bad) break;
-    const double pq = (sp[0] + sp[1]) + (sp[2] + sp[3]);
-    if (!(pq > 0.0) || !isfinite(pq)) {  // cannot happen for SPD A and p != 0
-      capped = !(rr <= rtol2 * bb);
-      break;
-    }
-    if (w < 2 && lane == 0) put(slotA + ((n & 1) * nslot + me) * kGridSlot + w, kEmptySlot);
-    const double alpha = rz / pq;
+    const double delta = (sp[0] + sp[1]) + (sp[2] + sp[3]), gamma = (sp[4] + sp[5]) + (sp[6] + sp[7]);
+    const double rr = PC ? (sq[0] + sq[1]) + (sq[2] + sq[3]) : gamma;
+    if (n == 0) S.bb = rr;
+    if (!cg1_decide(S, gamma, delta, rr)) break;
+    // everybody has this iteration's z, and has left the sums before
+    if (w < (PC ? 3 : 2) && lane == 0) put(slot + ((m == 0 ? 2 : m - 1) * nslot + me) * kGridSlot + w, kEmptySlot);
+    const float beta = (float)S.beta;
 #pragma unroll
     for (int j = 0; j < RT; ++j) {
       const int i = j * kGridThreads + t;
       if (i < nr) {
-        xs[i] = (float)((double)xs[i] + alpha * (double)pw[own + i]);
-        rs[i] = (float)((double)rs[i] - alpha * (double)qv[j]);
+        p[j] = zw[own + i] + beta * p[j];
+        s[j] = qv[j] + beta * s[j];
+        xs[i] = (float)((double)xs[i] + S.alpha * (double)p[j]);
+        rs[i] = (float)((double)rs[i] - S.alpha * (double)s[j]);
+        put(&zc[r0 + i], kEmptyWord);
       }
     }
     if constexpr (PC) __syncthreads();
-    residuals(n & 1 ? z0 : z1, zc, true);
+    precondition(n & 1 ? z0 : z1);
   }
   if (bad) {
     if (t == 0) atomicOr(aborted, 1);
@@ -630,16 +619,9 @@ __global__ void __launch_bounds__(kGridThreads)
   }
   for (int i = t; i < nr; i += kGridThreads) x[r0 + i] = xs[i];
   if (t == 0 && me == 0) {
-    CgLevel* const o = st + l;
-    o->rtol2 = rtol2;
-    o->bb = bb;
-    o->rr = rr;
-    o->maxit = maxit;
-    o->on = 1;
-    o->iters = n;
-    o->done = 1;
-    o->capped = capped;
-    o->fallback = 0;
+    S.on = 1;
+    S.done = 1;
+    st[l] = S;
   }
 }
 
@@ -648,8 +630,12 @@ mskm_status cg_stream_ready(mskm_hier* h, int lo, int hi, bool bj, int* depth) {
   const int d = h->h_depth[lo];
   if (!h->diag.val32 || h->h_depth[hi] != d || h->h_depth_begin[d] != lo || h->h_depth_begin[d + 1] != hi + 1)
     return MSKM_OK;
-  for (int l = lo; l <= hi; ++l)
+  int64_t most = 0;
+  for (int l = lo; l <= hi; ++l) {
     if (h->h_lev[l].n <= 0) return MSKM_OK;
+    most = std::max<int64_t>(most, h->h_lev[l].n);
+  }
+  if (most <= kWgSolveRows) return MSKM_OK;  // one workgroup each (k_cg_level_wg)
   if (!h->cg_stream) {
     auto* p = new (std::nothrow) CgStream();
     if (!p) return MSKM_OK;
@@ -676,30 +662,38 @@ mskm_status cg_stream_launch(mskm_hier* h, int depth, bool bj, const float* b, f
   mskm_ctx* c = h->ctx;
   hipStream_t s = c->stream;
   const int64_t r0 = h->h_off[h->h_depth_begin[depth]], n = h->h_off[h->h_depth_begin[depth + 1]] - r0;
-  grid_empty<float>(s, z0, z1, nullptr, r0, n, P.d.slots, (int64_t)4 * P.d.nwg * kGridSlot, aborted);
+  grid_empty<float>(s, z0, z1, nullptr, r0, n, P.d.slots, (int64_t)3 * P.d.nwg * kGridSlot, aborted);
   const size_t lds = stream_lds(P);
+  // the launched kernels' product for these levels
+  const bool halves = h->spmv_g[MSKM_OP_DIAG][1] == kSellCode && h->sell.col16 && n <= kSplitProductRows;
   hipError_t e = hipSuccess;
   const mskm_status r = cg_grid_in_turn(c, [&] {
-#define MSKM_STREAM(PCF, RES, EE)                                                                                    \
+#define MSKM_STREAM(PCF, RES, EE, HH)                                                                                \
   do {                                                                                                              \
-    auto* k = k_cg_stream<PCF, RES, EE>;                                                                            \
+    auto* k = k_cg_stream<PCF, RES, EE, HH>;                                                                        \
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
     if (e == hipSuccess)                                                                                            \
       hipLaunchKernelGGL(k, dim3(P.d.nwg), dim3(kGridThreads), lds, s, P.d, P.window, P.rows, P.inv, P.nl, P.width, \
                          b, x, (uint32_t*)z0, (uint32_t*)z1, st, aborted, rtol2, maxit, c->grid_spin, pc);            \
   } while (0)
-#define MSKM_STREAM_RES(PCF)     \
-  if (P.width <= 48)             \
-    MSKM_STREAM(PCF, 2, 48);     \
-  else if (P.width <= 96)        \
-    MSKM_STREAM(PCF, 1, 96);     \
-  else                           \
-    MSKM_STREAM(PCF, 0, 16)
-    if (bj) {
-      MSKM_STREAM_RES(true);
-    } else {
-      MSKM_STREAM_RES(false);
-    }
+// (two sums a row and 96 resident entries spill 100 registers)
+#define MSKM_STREAM_RES(PCF, HH)   \
+  do {                             \
+    if (P.width <= 48)             \
+      MSKM_STREAM(PCF, 2, 48, HH); \
+    else if (P.width <= 96 && !HH) \
+      MSKM_STREAM(PCF, 1, 96, HH); \
+    else                           \
+      MSKM_STREAM(PCF, 0, 16, HH); \
+  } while (0)
+    if (bj && halves)
+      MSKM_STREAM_RES(true, true);
+    else if (bj)
+      MSKM_STREAM_RES(true, false);
+    else if (halves)
+      MSKM_STREAM_RES(false, true);
+    else
+      MSKM_STREAM_RES(false, false);
 #undef MSKM_STREAM_RES
 #undef MSKM_STREAM
   });

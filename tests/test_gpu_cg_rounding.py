@@ -186,3 +186,16 @@ def test_fp64_preconditioned_tolerance(n, nu, rtol, R):
     finally:
         m.mskm_hier_destroy(hd)
         m.mskm_destroy(ctx)
+
+
+@pytest.mark.parametrize("bj", [True, False])
+@pytest.mark.parametrize("case", ["halton", "uniform3d"])
+def test_large_levels_round_as_launched(case, bj):
+    """Levels whose matrix does not fit the registers."""
+    import paper_2503_04914_amd as m
+
+    h = synth.uniform3d_hierarchy(2, n0=20000) if case == "uniform3d" else \
+        synth.halton_hierarchy(sizes=[1000, 256 * 1024 + 77])
+    pc = m.MSKM_PRECOND_BLOCK_JACOBI if bj else m.MSKM_PRECOND_NONE
+    (a, _, _), (b, _, _) = _one_launch_and_launched(h, 1, lambda m: _early(m, precond=pc), fp64=False, fp32=True)
+    _same_rounding(a, b)
