@@ -22,10 +22,9 @@ __device__ constexpr uint32_t kEmptyWord = 0x7fa4beefu;            // produces t
 // would wait for workgroups that cannot start.
 mskm_status cg_grid_in_turn(mskm_ctx* c, const std::function<void()>& launch);
 
-// Empties z0, z1 (and z2) on the rows [r0, r0 + n) and ns slot words, clears *aborted.
+// Empties z0, z1 (and z2) on the rows [r0, r0 + n) and ns slot words.
 template <typename TX>
-void grid_empty(hipStream_t s, TX* z0, TX* z1, TX* z2, int64_t r0, int64_t n, uint64_t* slots, int64_t ns,
-                int32_t* aborted);
+void grid_empty(hipStream_t s, TX* z0, TX* z1, TX* z2, int64_t r0, int64_t n, uint64_t* slots, int64_t ns);
 
 // lane-crossing moves within 16 lanes
 template <int CTRL>
@@ -90,12 +89,16 @@ __device__ __forceinline__ W get(const W* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The word at p once it is there; *bad after `spin` further polls.
+// The word at p once it is there; *bad after `left` further polls, and then none
+// are left for the thread's next waits.
 template <typename W>
-__device__ __forceinline__ W poll(const W* p, W empty, int spin, int* bad) {
+__device__ __forceinline__ W poll(const W* p, W empty, int& left, int* bad) {
   W u = get(p);
-  for (int k = 0; u == empty && k < spin; ++k) u = get(p);
-  if (u == empty) *bad = 1;
+  for (int k = 0; u == empty && k < left; ++k) u = get(p);
+  if (u == empty) {
+    *bad = 1;
+    left = 0;
+  }
   return u;
 }
 

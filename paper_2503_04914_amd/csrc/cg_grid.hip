@@ -64,9 +64,11 @@
 // and z of n are emptied after B of n, B of n - 1 after A of n, the stores waited
 // for before B of n + 1 or n, and polled again after that.
 //
-// Waiting: every poll loop ends after `spin` polls. A workgroup that gives up
-// sets *aborted and leaves, the others then give up the same way, and the
-// caller solves the levels by the launched kernels instead. All workgroups of
+// Waiting: every poll loop ends after `spin` polls, and a thread that has waited
+// that long does not wait again. A workgroup that gives up sets *aborted and
+// leaves, the others then give up the same way, the launches queued behind it
+// give up at once, and the caller solves the levels by the launched kernels
+// instead. All workgroups of
 // a launch must be on the GPU together: at most one per CU is launched, and
 // launches of this kernel from different streams of the process are ordered
 // one after the other (another kernel only delays the start).
@@ -414,7 +416,6 @@ __global__ void __launch_bounds__(kGridThreads)
     z1 += zo;
     z2 += zo;
   }
-  if (SOLO && blockIdx.x == 0 && t == 0) *aborted = 0;
 
   // matrix entries (past the row's end: value 0 at position 0)
   TX v[E];
@@ -500,7 +501,8 @@ __global__ void __launch_bounds__(kGridThreads)
   for (int k = 0; k < kI; ++k) iv[k] = kInvRegs && k < bm ? Mi[k] : (TX)0;
 
   TX xi = 0, ri = mine ? b[row * gc.ld + col] : (TX)0, pi = 0, zi;
-  if (t == 0) bad = 0;
+  if (t == 0) bad = !SOLO && get(aborted) != 0;  // a launch before this one has given up
+  int left = spin;                               // polls that the thread still waits for
   auto precondition = [&] {  // z = M^-1 r
     if constexpr (PC) {
       if (first) rs[i] = ri;
@@ -520,7 +522,7 @@ __global__ void __launch_bounds__(kGridThreads)
 #pragma unroll
     for (int q = 0; q < kH; ++q) {
       if (t + q * kGridThreads < nh && hz[q] == GridWord<TX>::empty)
-        hz[q] = poll(&zc[hrow[t + q * kGridThreads]], GridWord<TX>::empty, spin, &bad);
+        hz[q] = poll(&zc[hrow[t + q * kGridThreads]], GridWord<TX>::empty, left, &bad);
     }
   };
   auto halo_ask = [&](W* zc) {
@@ -548,7 +550,7 @@ __global__ void __launch_bounds__(kGridThreads)
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       if (u[k] == kEmptySlot)
-        u[k] = poll(slot + (m * nslot + lane + k * kWave) * kGridSlot + word, kEmptySlot, spin, &bad);
+        u[k] = poll(slot + (m * nslot + lane + k * kWave) * kGridSlot + word, kEmptySlot, left, &bad);
       s += value_of(u[k]);
     }
     s = wave64_sum(s);
@@ -558,6 +560,7 @@ __global__ void __launch_bounds__(kGridThreads)
   int n = 0, capped = 0;
   if constexpr (!SOLO) {
     __syncthreads();
+    if (bad) left = 0;
     if (first) put(&z0[row], word_of(zi));
   }
 
@@ -851,7 +854,10 @@ mskm_status cg_grid_in_turn(mskm_ctx* c, const std::function<void()>& launch) {
   return MSKM_OK;
 }
 
-void cg_grid_set_spin(mskm_ctx* c, int spin) { c->grid_spin = spin; }
+void cg_grid_set_spin(mskm_ctx* c, int spin) {
+  c->grid_spin = spin;
+  c->grid_rest = 0;
+}
 
 extern "C" int64_t mskm_test_given_up(const mskm_ctx* c) { return c->given_up; }
 
@@ -864,7 +870,8 @@ extern "C" void mskm_test_limits(mskm_ctx* c, uint64_t hier_bytes, uint64_t scra
 template <typename TX>
 __global__ void __launch_bounds__(kBlock)
     k_grid_empty(typename GridWord<TX>::type* __restrict__ z0, typename GridWord<TX>::type* __restrict__ z1,
-                 typename GridWord<TX>::type* __restrict__ z2, int64_t r0, int64_t n, uint64_t* __restrict__ slots, int64_t ns, int32_t* __restrict__ aborted) {
+                 typename GridWord<TX>::type* __restrict__ z2, int64_t r0, int64_t n, uint64_t* __restrict__ slots,
+                 int64_t ns) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i < n) {
     z0[r0 + i] = GridWord<TX>::empty;
@@ -872,18 +879,16 @@ __global__ void __launch_bounds__(kBlock)
     if (z2) z2[r0 + i] = GridWord<TX>::empty;
   }
   if (i < ns) slots[i] = kEmptySlot;
-  if (i == 0 && aborted) *aborted = 0;
 }
 
 template <typename TX>
-void grid_empty(hipStream_t s, TX* z0, TX* z1, TX* z2, int64_t r0, int64_t n, uint64_t* slots, int64_t ns,
-                int32_t* aborted) {
+void grid_empty(hipStream_t s, TX* z0, TX* z1, TX* z2, int64_t r0, int64_t n, uint64_t* slots, int64_t ns) {
   using W = typename GridWord<TX>::type;
   hipLaunchKernelGGL(k_grid_empty<TX>, dim3((unsigned)((std::max(n, ns) + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
-                     (W*)z0, (W*)z1, (W*)z2, r0, n, slots, ns, aborted);
+                     (W*)z0, (W*)z1, (W*)z2, r0, n, slots, ns);
 }
-template void grid_empty<float>(hipStream_t, float*, float*, float*, int64_t, int64_t, uint64_t*, int64_t, int32_t*);
-template void grid_empty<double>(hipStream_t, double*, double*, double*, int64_t, int64_t, uint64_t*, int64_t, int32_t*);
+template void grid_empty<float>(hipStream_t, float*, float*, float*, int64_t, int64_t, uint64_t*, int64_t);
+template void grid_empty<double>(hipStream_t, double*, double*, double*, int64_t, int64_t, uint64_t*, int64_t);
 
 // The sum that the launched kernels of these levels make of a row's products
 // (FP32; FP64 results do not depend on it to the accuracy asked for).
@@ -965,7 +970,7 @@ mskm_status cg_grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, con
   const bool solo = nw == hi - lo + 1;
   if (!solo) {
     const int64_t r0 = h->h_off[lo], n = h->h_off[hi + 1] - r0;
-    grid_empty<TX>(h->ctx->stream, z0, z1, z2, r0, n, P.d.slots, (int64_t)3 * P.d.nslot * kGridSlot, aborted);
+    grid_empty<TX>(h->ctx->stream, z0, z1, z2, r0, n, P.d.slots, (int64_t)3 * P.d.nslot * kGridSlot);
   }
   auto launch = [&] {
     if constexpr (sizeof(TX) == 8)
@@ -1044,8 +1049,7 @@ mskm_status cg_grid_columns(mskm_hier* h, int lo, int hi, bool bj, const TX* val
     return MSKM_OK;
   }
   for (int c0 = 0; c0 < nrhs; c0 += per) {
-    grid_empty<TX>(h->ctx->stream, z0, z1, z2, r0 * R, c0 == 0 ? n * R : 0, P.d.slots, (int64_t)3 * P.d.nslot * kGridSlot,
-                   c0 == 0 ? aborted : nullptr);
+    grid_empty<TX>(h->ctx->stream, z0, z1, z2, r0 * R, c0 == 0 ? n * R : 0, P.d.slots, (int64_t)3 * P.d.nslot * kGridSlot);
     const GridCols gc{nw, R, c0, st};
     MSKM_TRY(cg_grid_in_turn(h->ctx, [&] { launch(gc, std::min(per, nrhs - c0)); }));
   }

@@ -76,8 +76,9 @@ struct PcArgs {
 mskm_status cg_grid_ready(mskm_hier* h, int lo, int hi, bool bj, int* lanes, int most_lanes = 2);
 // Queues the solve A_l x_l = b_l (x0 = 0) of levels lo..hi; z0, z1, z2: three
 // vectors of the hierarchy's length, scratch. st[l] receives the final
-// states. *aborted (device) is set, and x and st are unusable, when a
-// workgroup's wait ran out.
+// states. *aborted (device, cleared by the caller before the first of several
+// launches) is set, and x and st are unusable, when a workgroup's wait ran out;
+// launches that find it set give up at once.
 template <typename TX>
 mskm_status cg_grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, const TX* val, const TX* b, TX* x,
                            TX* z0, TX* z1, TX* z2, CgLevel* st, int32_t* aborted, double rtol2, int maxit,
@@ -87,7 +88,7 @@ mskm_status cg_grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, con
 // z0, z1, z2: scratch of that size;
 // states to st[l * R + r]), every column a system of its own. *how: 0 when it
 // takes more launches than are worth it (nothing is queued), 1 queued, 2 queued
-// and *aborted has to be looked at.
+// and *aborted (cleared by the caller) has to be looked at.
 struct MrState;
 template <typename TX>
 mskm_status cg_grid_columns(mskm_hier* h, int lo, int hi, bool bj, const TX* val, const TX* b, TX* x, TX* z0, TX* z1,

@@ -426,8 +426,9 @@ __global__ void __launch_bounds__(kGridThreads)
     rs[i] = b[r0 + i];
     xs[i] = 0.0f;
   }
-  if (t == 0) bad = 0;
+  if (t == 0) bad = get(aborted) != 0;  // a launch before this one has given up
   __syncthreads();
+  int left = bad ? 0 : spin;            // polls that the thread still waits for
 
   float p[RT], s[RT];  // direction and A p of the own rows
 #pragma unroll
@@ -489,7 +490,7 @@ __global__ void __launch_bounds__(kGridThreads)
 #pragma unroll
       for (int q = 0; q < kStreamHalo; ++q)
         if (he[q] >= 0) {
-          if (hz[q] == kEmptyWord) hz[q] = poll(&zc[base + he[q]], kEmptyWord, bad ? 0 : spin, &bad);
+          if (hz[q] == kEmptyWord) hz[q] = poll(&zc[base + he[q]], kEmptyWord, left, &bad);
           zw[at[q]] = value_of(hz[q]);
         }
     }
@@ -581,8 +582,8 @@ __global__ void __launch_bounds__(kGridThreads)
     if (t % 256 < nw) {
       u = get(sa + t % 256 * kGridSlot + t / 256);
       if (PC && t < 256) u2 = get(sa + t * kGridSlot + 2);
-      if (u == kEmptySlot) u = poll(sa + t % 256 * kGridSlot + t / 256, kEmptySlot, spin, &bad);
-      if (PC && u2 == kEmptySlot) u2 = poll(sa + t * kGridSlot + 2, kEmptySlot, bad ? 0 : spin, &bad);
+      if (u == kEmptySlot) u = poll(sa + t % 256 * kGridSlot + t / 256, kEmptySlot, left, &bad);
+      if (PC && u2 == kEmptySlot) u2 = poll(sa + t * kGridSlot + 2, kEmptySlot, left, &bad);
     }
     const double s01 = wave64_sum(value_of(u));
     if (lane == 0) sp[w] = s01;
@@ -662,7 +663,7 @@ mskm_status cg_stream_launch(mskm_hier* h, int depth, bool bj, const float* b, f
   mskm_ctx* c = h->ctx;
   hipStream_t s = c->stream;
   const int64_t r0 = h->h_off[h->h_depth_begin[depth]], n = h->h_off[h->h_depth_begin[depth + 1]] - r0;
-  grid_empty<float>(s, z0, z1, nullptr, r0, n, P.d.slots, (int64_t)3 * P.d.nwg * kGridSlot, aborted);
+  grid_empty<float>(s, z0, z1, nullptr, r0, n, P.d.slots, (int64_t)3 * P.d.nwg * kGridSlot);
   const size_t lds = stream_lds(P);
   // the launched kernels' product for these levels
   const bool halves = h->spmv_g[MSKM_OP_DIAG][1] == kSellCode && h->sell.col16 && n <= kSplitProductRows;

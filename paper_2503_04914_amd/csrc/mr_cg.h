@@ -48,6 +48,7 @@ struct MrWS {
   int32_t* on = nullptr;       // [L]
   MrLevStat* stat = nullptr;   // [L]
   int32_t* aborted = nullptr;  // the persistent form gave up
+  bool grid_off = false;       // no persistent launches (any more)
   int32_t* h_aborted = nullptr;
   int32_t* h_running[2] = {nullptr, nullptr};  // pinned copies behind the two chunks in flight
   hipEvent_t ev[2] = {nullptr, nullptr};

@@ -432,6 +432,7 @@ mskm_status mr_workspace(mskm_hier* h, int nrhs, int R, int what, bool pc, MrWS&
   W.nrhs = nrhs;
   W.ctx = h->ctx;
   W.pc = pc;
+  W.grid_off = what != 0 && grid_resting(h->ctx);
   int LR = 1;
   while (LR < R && LR < 64) LR <<= 1;
   W.c = MrCfg{R, LR, (R + LR - 1) / LR};
@@ -625,10 +626,11 @@ mskm_status mr_cg(mskm_hier* h, MrWS& W, const TV* dval, const std::vector<char>
   // small levels: every column solved by workgroups of its own in one launch
   // (cg_grid.hip). Launched, an iteration is five launches of 3-9 us however
   // small the level is.
-  bool all_on = dval != nullptr;
+  bool all_on = dval != nullptr && !W.grid_off;
   for (int l = lo; l <= hi; ++l) all_on = all_on && on[l];
   if (all_on) {
     int how = 0;
+    MSKM_HIP_TRY(hipMemsetAsync(W.aborted, 0, 4, s));
     const PcArgs<TX> pc{h->bj.start, h->bj.of_row, h->bj.off, inv, nullptr};
     MSKM_TRY((cg_grid_columns<TX>(h, lo, hi, W.pc, dval, b, x, p, q, (TX*)W.r, W.nrhs, R, W.st, W.aborted, rtol * rtol,
                                  maxit, pc, &how)));
@@ -637,7 +639,11 @@ mskm_status mr_cg(mskm_hier* h, MrWS& W, const TV* dval, const std::vector<char>
       MSKM_HIP_TRY(hipMemcpyAsync(W.h_aborted, W.aborted, 4, hipMemcpyDeviceToHost, s));
       MSKM_HIP_TRY(hipEventRecord(W.ev[0], s));
       MSKM_HIP_TRY(hipEventSynchronize(W.ev[0]));
-      if (*W.h_aborted) ++h->ctx->given_up;
+      if (*W.h_aborted) {
+        ++h->ctx->given_up;
+        h->ctx->grid_rest = kGridRest;
+        W.grid_off = true;
+      }
     }
     if (how > 0 && *W.h_aborted == 0) {
       hipLaunchKernelGGL(k_mr_stats, dim3(nlev), dim3(kBlock), 0, s, lo, W.st, W.on, W.stat, R);

@@ -197,6 +197,7 @@ struct mskm_ctx {
   int32_t grid_spin = 1 << 15;  // polls before a wait of that kernel is given up (about 30 ms)
   hipEvent_t ev_grid = nullptr; // after this context's last persistent CG launch
   int64_t given_up = 0;         // persistent launches that gave up and were solved by launched kernels
+  int32_t grid_rest = 0;        // solves still to be done without such launches after one gave up
   // tests of the ways without them: most bytes of a hierarchy's block, and of a
   // scratch block, that an allocation still gets (0: no limit)
   uint64_t limit_hier = 0, limit_scratch = 0;
@@ -457,6 +458,17 @@ void launch_bj_apply(mskm_hier* h, int lo, int hi, const TX* r, TX* u);
 // allocations (mskm_ctx::limit_hier, limit_scratch).
 extern "C" int64_t mskm_test_given_up(const mskm_ctx* c);
 extern "C" void mskm_test_limits(mskm_ctx* c, uint64_t hier_bytes, uint64_t scratch_bytes);
+
+// Whether a solve that begins now goes without persistent launches: the GPU was too
+// busy for them a few solves ago (another process's kernels, which these waits
+// cannot be ordered with; each costs up to the 30 ms of a wait before the launched
+// kernels take over).
+constexpr int kGridRest = 16;
+inline bool grid_resting(mskm_ctx* c) {
+  if (c->grid_rest <= 0) return false;
+  --c->grid_rest;
+  return true;
+}
 
 // cg_grid.hip: no later launch waits for this context's (called before its event goes)
 void cg_grid_forget(mskm_ctx* c);

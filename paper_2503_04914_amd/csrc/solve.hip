@@ -1140,7 +1140,7 @@ struct SolveWS {
   int32_t* aborted = nullptr;    // device: a persistent CG launch gave up (cg_grid.hip)
   int32_t* h_aborted = nullptr;  // pinned copies of it, one per level (its lowest)
   bool grid_failed = false;      // one of them was set: the solve is run again without these launches
-  bool grid_off = false;         // no persistent launches (that second run)
+  bool grid_off = false;         // no persistent launches (from that second run on, to the end of the solve)
   hipEvent_t ev_defer = nullptr;  // after the last copy into h_defer
   hipEvent_t ev_chk[2] = {nullptr, nullptr};
   hipEvent_t pending = nullptr;  // copy of a speculative chunk still in flight (null: none)
@@ -1393,6 +1393,14 @@ static mskm_status chunk_graph(mskm_hier* h, SolveWS& W, const TV* dval, int lo,
   return MSKM_OK;
 }
 
+// Before the first CG of a pass: nothing has given up, no state is waited for.
+static mskm_status begin_pass(mskm_hier* h, SolveWS& W) {
+  W.grid_failed = false;
+  std::fill(W.deferred.begin(), W.deferred.end(), 0);
+  MSKM_HIP_TRY(hipMemsetAsync(W.aborted, 0, 4, h->ctx->stream));
+  return MSKM_OK;
+}
+
 // Adds the final states of the levels solved in one launch (copied into
 // h_defer behind it) to the statistics; waits for that copy.
 static mskm_status flush_deferred(mskm_hier* h, SolveWS& W, CgStats* cs) {
@@ -1407,6 +1415,7 @@ static mskm_status flush_deferred(mskm_hier* h, SolveWS& W, CgStats* cs) {
       W.h_aborted[l] = 0;
       W.grid_failed = true;
       ++h->ctx->given_up;
+      h->ctx->grid_rest = kGridRest;
     }
     const CgLevel& o = W.h_defer[l];
     cs->iters_total += o.iters;
@@ -1419,7 +1428,8 @@ static mskm_status flush_deferred(mskm_hier* h, SolveWS& W, CgStats* cs) {
 // Per-level CG on A_l x_l = b_l for the levels in `mask` (contiguous bits).
 // x holds x0 if warm, else it is overwritten. Iterations run as replays of a
 // captured chunk of K iterations; the host reads the per-level state after
-// each chunk and stops when every level has stopped.
+// each chunk and stops when every level has stopped. Returns early, with
+// W.grid_failed, once it sees that a persistent launch before has given up.
 template <typename TV, typename TX>
 static mskm_status cg_run(mskm_hier* h, SolveWS& W, const TV* dval, const std::vector<char>& on, const TX* b, TX* x,
                           double rtol, int maxit, bool warm, int K, CgStats* cs, const mskm_mlp* mlp, bool bj,
@@ -1475,6 +1485,7 @@ static mskm_status cg_run(mskm_hier* h, SolveWS& W, const TV* dval, const std::v
           MSKM_TRY(flush_deferred(h, W, cs));
           break;
         }
+      if (W.grid_failed) return MSKM_OK;
       if (bj) MSKM_TRY(bj_start_side(h));
       if (lanes > 0) {
         MSKM_TRY(cg_grid_launch<TX>(h, lo, hi, bj, lanes, dval, b, x, (TX*)W.p0, (TX*)W.p1, (TX*)W.r, W.st, W.aborted,
@@ -1497,6 +1508,7 @@ static mskm_status cg_run(mskm_hier* h, SolveWS& W, const TV* dval, const std::v
         MSKM_TRY(flush_deferred(h, W, cs));
         break;
       }
+    if (W.grid_failed) return MSKM_OK;
     const PcArgs<TX> pc = pc_args<TX>(h, W);
     int nmax = 0;
     for (int l = lo; l <= hi; ++l) nmax = std::max(nmax, (int)h->h_lev[l].n);
@@ -1531,6 +1543,7 @@ static mskm_status cg_run(mskm_hier* h, SolveWS& W, const TV* dval, const std::v
       MSKM_TRY(flush_deferred(h, W, cs));
       break;
     }
+  if (W.grid_failed) return MSKM_OK;
   // the first chunked level starts the side-stream inversion of the finest
   // depth's blocks (its few-block launches leave most of the GPU free)
   if (bj) MSKM_TRY(bj_start_side(h));
@@ -1615,9 +1628,11 @@ static mskm_status cg_run(mskm_hier* h, SolveWS& W, const TV* dval, const std::v
     ++checked;
     bool any = false;
     for (int l = lo; l <= hi; ++l) any |= c[l].done == 0;
-    if (!any) break;
+    if (checked == 1) MSKM_TRY(flush_deferred(h, W, cs));  // persistent launches before: done, nothing is waited for
+    if (!any || W.grid_failed) break;
   }
   if (launched > checked) W.pending = W.ev_chk[(launched - 1) & 1];
+  if (W.grid_failed) return MSKM_OK;
   const CgLevel* fin = W.h_chk[(checked - 1) & 1];
   MSKM_HIP_TRY(hipGetLastError());
   for (int l = lo; l <= hi; ++l) {
@@ -1951,6 +1966,7 @@ static mskm_status solve_pass(mskm_hier* h, SolveWS& W, const TV* dval, const TV
   int K = o->check_every > 0 ? o->check_every : 8;
   K += K & 1;  // even chunk length
   std::vector<char> on(L, 0);
+  MSKM_TRY(begin_pass(h, W));
   if (o->algorithm == MSKM_ALG_SEQUENTIAL) {
     // block forward substitution, depth by depth (every group's level of
     // that depth in the same launches): rhs_l = f_l - sum_{k<l} B_{l,k} alpha_k
@@ -1970,6 +1986,7 @@ static mskm_status solve_pass(mskm_hier* h, SolveWS& W, const TV* dval, const TV
       else
         MSKM_TRY((cg_run<TV, TX>(h, W, dval, on, beta, alpha, o->cg_rtol, maxit, false, K, cs, mlp, bj,
                                  d + 1 < D ? &next : nullptr)));
+      if (W.grid_failed) return MSKM_OK;
     }
     *sweeps_done = 0;
     return flush_deferred(h, W, cs);
@@ -1983,6 +2000,7 @@ static mskm_status solve_pass(mskm_hier* h, SolveWS& W, const TV* dval, const TV
   for (int l = 0; l < L; ++l) on[l] = h->h_next[l] >= 0;  // every level below its hierarchy's top
   for (int sw = 0; sw < S && Lmax > 1; ++sw) {
     MSKM_TRY((cg_run<TV, TX>(h, W, dval, on, beta, t, o->cg_rtol, maxit, prev && sw > 0, K, cs, nullptr, bj)));
+    if (W.grid_failed) return MSKM_OK;
     lower_update<TV, TX>(h, lval, t, f, beta, 0, N);
     *sweeps_done = sw + 1;
   }
@@ -1993,19 +2011,17 @@ static mskm_status solve_pass(mskm_hier* h, SolveWS& W, const TV* dval, const TV
 }
 
 // The same, run again with launched kernels only when a persistent launch
-// gave up (its workgroups did not all get onto the GPU in time).
+// gave up (its workgroups did not all get onto the GPU in time), as is the rest
+// of the solve.
 template <typename TV, typename TX>
 static mskm_status solve_internal(mskm_hier* h, SolveWS& W, const TV* dval, const TV* lval, const TX* f, TX* alpha,
                                   const mskm_solve_opts* o, int* sweeps_done, CgStats* cs) {
   const CgStats before = *cs;
   MSKM_TRY((solve_pass<TV, TX>(h, W, dval, lval, f, alpha, o, sweeps_done, cs)));
   if (!W.grid_failed) return MSKM_OK;
-  W.grid_failed = false;
   W.grid_off = true;
   *cs = before;
-  const mskm_status st = solve_pass<TV, TX>(h, W, dval, lval, f, alpha, o, sweeps_done, cs);
-  W.grid_off = false;
-  return st;
+  return solve_pass<TV, TX>(h, W, dval, lval, f, alpha, o, sweeps_done, cs);
 }
 
 // ------------------------------------------------------------- residual
@@ -2627,6 +2643,7 @@ mskm_status solve(mskm_hier* h, const double* f_in, int nrhs, const mskm_solve_o
   SolveWS* Wp = nullptr;
   MSKM_TRY(get_ws(h, &Wp));
   SolveWS& W = *Wp;
+  W.grid_off = grid_resting(h->ctx);
   double* fi = W.fi;
   double* ai = W.ai;
   CgStats cs;
@@ -2713,6 +2730,7 @@ mskm_status trunc_solve(mskm_hier* h, const Csr& X, const double* f_in, const ms
   SolveWS* Wp = nullptr;
   MSKM_TRY(get_ws(h, &Wp));
   SolveWS& W = *Wp;
+  W.grid_off = grid_resting(h->ctx);
   int Lmax = 0;
   for (int g = 0; g < h->ngroups; ++g) Lmax = std::max(Lmax, (int)h->h_group_levels[g]);
   const int S = o->sweeps > 0 ? o->sweeps : Lmax - 1;
@@ -2740,16 +2758,14 @@ mskm_status trunc_solve(mskm_hier* h, const Csr& X, const double* f_in, const ms
     double rtol = o->cg_rtol;
     if (refine_on && rounds > 0) rtol = std::min(0.1, std::max(o->cg_rtol, 0.5 * o->target_rel_residual / rel));
     const CgStats before = cs;
+    MSKM_TRY(begin_pass(h, W));
     MSKM_TRY((cg_run<double, double>(h, W, h->diag.val, on, b, nb, rtol, maxit, false, K, &cs, nullptr, bj)));
     MSKM_TRY(flush_deferred(h, W, &cs));
-    if (W.grid_failed) {  // a persistent launch gave up: the launched kernels instead
-      W.grid_failed = false;
+    if (W.grid_failed) {  // a persistent launch gave up: the launched kernels instead, here and in later rounds
+      MSKM_TRY(begin_pass(h, W));
       W.grid_off = true;
       cs = before;
-      const mskm_status again =
-          cg_run<double, double>(h, W, h->diag.val, on, b, nb, rtol, maxit, false, K, &cs, nullptr, bj);
-      W.grid_off = false;
-      MSKM_TRY(again);
+      MSKM_TRY((cg_run<double, double>(h, W, h->diag.val, on, b, nb, rtol, maxit, false, K, &cs, nullptr, bj)));
       MSKM_TRY(flush_deferred(h, W, &cs));
     }
     hipLaunchKernelGGL(k_axpy64, dim3(nblk(N)), dim3(kBlock), 0, s, (const double*)nb, W.ai, N);
@@ -2788,6 +2804,7 @@ mskm_status train_pairs(mskm_hier* h, const double* f, int nrhs, bool io_dev, do
   MSKM_TRY(stage_in(s, f, (size_t)N * nrhs, io_dev, F));
   SolveWS* Wp = nullptr;
   MSKM_TRY(get_ws(h, &Wp));
+  Wp->grid_off = grid_resting(h->ctx);
   mskm_solve_opts o;
   mskm_solve_opts_default(&o);
   o.algorithm = MSKM_ALG_SEQUENTIAL;

@@ -96,3 +96,42 @@ def test_row_by_row_products(mixed, R):
     (A, ra), (B, rb) = _tiles_and_rows(mixed, R, [60, 301, 1204, 20011])
     assert ra.max() <= 1e-12 and rb.max() <= 1e-12
     assert np.linalg.norm(A - B) <= (2e-8 if mixed else 2e-10) * np.linalg.norm(A)
+
+
+@pytest.mark.parametrize("R", [1, 3])
+def test_a_give_up_is_remembered(R):
+    """A launch that gives up is tried once: the launches behind it, the rounds of that solve and the next solves
+    go without (their count stays), and the results are those of the launched kernels."""
+    import paper_2503_04914_amd as m
+
+    spin, given_up, _ = _hooks(m)
+    h = synth.halton_hierarchy(sizes=[300, 1200, 4800, 140001])  # 4 depths, one past the registers and one launch
+    F = _targets(h, R)
+    ctx = m.mskm_create(0)
+    hd = m.mskm_hier_create(ctx, h.points, h.offsets, h.delta, fp64=True, fp32=True)
+    out = []
+    try:
+        for mixed in (True, False):
+            print(f"[ways back] remembered, R={R} mixed={mixed}", flush=True)
+            spin(ctx, 0)
+            n = given_up(ctx)
+            a, b, c = np.zeros_like(F), np.zeros_like(F), np.zeros_like(F)
+            r = m.mskm_solve(ctx, hd, F, a, _opts(m, mixed), nrhs=R)
+            assert r.status == m.MSKM_OK
+            if mixed:
+                assert r.report["refine_steps"] > 1
+            assert n < given_up(ctx) <= n + h.levels
+            n = given_up(ctx)
+            assert m.mskm_solve(ctx, hd, F, b, _opts(m, mixed), nrhs=R).status == m.MSKM_OK
+            assert given_up(ctx) == n
+            if R == 1:  # (of several, levels of one workgroup, which cannot give up, were solved in one launch in a)
+                assert np.array_equal(a, b)
+            spin(ctx, SPIN)
+            assert m.mskm_solve(ctx, hd, F, c, _opts(m, mixed), nrhs=R).status == m.MSKM_OK
+            assert given_up(ctx) == n
+            out.append((a, c))
+    finally:
+        m.mskm_hier_destroy(hd)
+        m.mskm_destroy(ctx)
+    for (a, c), bar in zip(out, (2e-8, 2e-10)):  # two results within the repository's bars, 1e-8 mixed and 1e-10 FP64
+        assert np.linalg.norm(a - c) <= bar * np.linalg.norm(c)
