@@ -511,7 +511,9 @@ mskm_status solve_multi(mskm_hier* h, const double* f_in, int nrhs, const mskm_s
 // each with two permutations and a host wait). The tiles cost about as much
 // as 16 such passes to build, so fewer right-hand sides use them only when a
 // solve has left them. *done stays false where this form does not apply (no
-// tiles, no room for the vectors).
+// tiles, no room for the vectors), and where a residual is not finite: the zeros
+// of a tile times an infinite coefficient are NaN in rows that do not touch it, so
+// an infinite residual is told from an undefined one by the products row by row.
 mskm_status residual_multi(mskm_hier* h, const double* alpha, const double* f, int nrhs, double* rel_out, bool* done) {
   *done = false;
   constexpr int kBuildAt = 16, kSlab = 64 * kMaxRPerLane;
@@ -533,6 +535,8 @@ mskm_status residual_multi(mskm_hier* h, const double* alpha, const double* f, i
                        R);
     std::vector<double> rel;
     MSKM_TRY(mr_residual(h, W, W.ai, W.fi, nullptr, rel));
+    for (size_t i = 0; i < (size_t)cnt * h->ngroups; ++i)
+      if (!std::isfinite(rel[i])) return MSKM_OK;
     std::memcpy(rel_out + (size_t)r0 * h->ngroups, rel.data(), (size_t)cnt * h->ngroups * sizeof(double));
   }
   *done = true;
