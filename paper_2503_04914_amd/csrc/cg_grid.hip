@@ -861,6 +861,8 @@ void cg_grid_set_spin(mskm_ctx* c, int spin) {
 
 extern "C" int64_t mskm_test_given_up(const mskm_ctx* c) { return c->given_up; }
 
+extern "C" void mskm_test_spin(mskm_ctx* c, int spin) { cg_grid_set_spin(c, spin); }
+
 extern "C" void mskm_test_limits(mskm_ctx* c, uint64_t hier_bytes, uint64_t scratch_bytes) {
   c->limit_hier = hier_bytes;
   c->limit_scratch = scratch_bytes;

@@ -454,9 +454,10 @@ mskm_status bj_start_side(mskm_hier* h);
 template <typename TX>
 void launch_bj_apply(mskm_hier* h, int lo, int hi, const TX* r, TX* u);
 
-// For tests: how many persistent launches of the context gave up; limits of
-// allocations (mskm_ctx::limit_hier, limit_scratch).
+// For tests: how many persistent launches of the context gave up; the polls of their
+// waits (cg_grid_set_spin); limits of allocations (mskm_ctx::limit_hier, limit_scratch).
 extern "C" int64_t mskm_test_given_up(const mskm_ctx* c);
+extern "C" void mskm_test_spin(mskm_ctx* c, int spin);
 extern "C" void mskm_test_limits(mskm_ctx* c, uint64_t hier_bytes, uint64_t scratch_bytes);
 
 // Whether a solve that begins now goes without persistent launches: the GPU was too

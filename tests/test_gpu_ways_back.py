@@ -15,7 +15,7 @@ SPIN = 1 << 15  # polls of a wait
 
 
 def _hooks(m):
-    spin = getattr(m.lib(), "_ZN4mskm16cg_grid_set_spinEP8mskm_ctxi")
+    spin = m.lib().mskm_test_spin
     spin.argtypes, spin.restype = [ctypes.c_void_p, ctypes.c_int], None
     given_up, limits = m.lib().mskm_test_given_up, m.lib().mskm_test_limits
     given_up.argtypes, given_up.restype = [ctypes.c_void_p], ctypes.c_int64
