@@ -2629,7 +2629,10 @@ mskm_status apply_op(mskm_hier* h, int op, int prec, const double* x_in, int nrh
 
 mskm_status solve(mskm_hier* h, const double* f_in, int nrhs, const mskm_solve_opts* o, double* alpha_out,
                   mskm_report* rep) {
-  if (nrhs > 1 && mr_supported(nrhs)) return solve_multi(h, f_in, nrhs, o, alpha_out, rep);
+  if (nrhs > 1 && mr_supported(nrhs)) {
+    const mskm_status st = solve_multi(h, f_in, nrhs, o, alpha_out, rep);
+    if (st != MSKM_ENOMEM) return st;  // no room for the padded vectors: one after the other
+  }
   hipStream_t s = h->ctx->stream;
   const int64_t N = h->N;
   const bool io_dev = (o->flags & MSKM_IO_DEVICE) != 0;
@@ -2888,7 +2891,7 @@ mskm_status evaluate(mskm_hier* h, const double* alpha, int nrhs, const double* 
   MSKM_TRY(stage_in(s, query, (size_t)nq * h->dim, io_dev, Q));
   MSKM_TRY(stage_out_alloc(out, (size_t)nq * nrhs, io_dev, O));
   // internal-order coefficients of up to four right-hand sides at a time
-  const int NR = nrhs == 1 ? 1 : nrhs == 2 ? 2 : 4;
+  int NR = nrhs == 1 ? 1 : nrhs == 2 ? 2 : 4;
   double* ai = nullptr;
   int32_t *key = nullptr, *order = nullptr;
   int64_t *count = nullptr, *next = nullptr, *part = nullptr;
@@ -2909,8 +2912,21 @@ mskm_status evaluate(mskm_hier* h, const double* alpha, int nrhs, const double* 
     cv.add(&part, (size_t)scan_parts(bins));
   }
   void* base = nullptr;
-  MSKM_TRY(cv.alloc(h->ctx, &base));
+  const mskm_status room = cv.alloc(h->ctx, &base);
+  if (room < 0 && room != MSKM_ENOMEM) return room;
   CtxScratch scratch{h->ctx, base, cv.bytes};
+  DevBuf own;
+  if (room == MSKM_ENOMEM) {  // one right-hand side at a time in the order given, on the solver's vector if there is one
+    NR = 1;
+    level = -1;
+    if (h->solve_ws) {
+      ai = static_cast<SolveWS*>(h->solve_ws)->ai;
+    } else {
+      MSKM_TRY(dalloc(&own.p, N));
+      own.own = true;
+      ai = own.p;
+    }
+  }
   if (level >= 0) {
     MSKM_HIP_TRY(hipMemsetAsync(count, 0, (size_t)bins * 8, s));
     hipLaunchKernelGGL(k_eval_keys, dim3(nblk(nq)), dim3(kBlock), 0, s, h->dim, h->d_lev, level, Q.p, nq, key, count);

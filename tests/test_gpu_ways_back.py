@@ -135,3 +135,39 @@ def test_a_give_up_is_remembered(R):
         m.mskm_destroy(ctx)
     for (a, c), bar in zip(out, (2e-8, 2e-10)):  # two results within the repository's bars, 1e-8 mixed and 1e-10 FP64
         assert np.linalg.norm(a - c) <= bar * np.linalg.norm(c)
+
+
+def test_no_scratch_memory():
+    """Without memory for their scratch blocks, an evaluation goes one right-hand side at a time (with and without
+    the solver's vectors) and a solve of several right-hand sides one after the other."""
+    import paper_2503_04914_amd as m
+
+    _, _, limits = _hooks(m)
+    h = synth.halton_hierarchy(sizes=[300, 5003, 140001])
+    F = _targets(h, 5)
+    q = synth.uniform01(5200, 0, 2 * 40000).reshape(-1, 2)  # as many as are sorted otherwise
+    ctx = m.mskm_create(0)
+    hd = m.mskm_hier_create(ctx, h.points, h.offsets, h.delta, fp64=True, fp32=True)
+    o = _opts(m, True)
+    try:
+        for solved in (False, True):
+            for R in (1, 2, 5):
+                x = np.ascontiguousarray(F[:, :R])
+                v, w = np.zeros((len(q), R)), np.zeros((len(q), R))
+                m.mskm_evaluate(ctx, hd, x, q, v, nrhs=R)
+                limits(ctx, 0, 1)
+                m.mskm_evaluate(ctx, hd, x, q, w, nrhs=R)
+                limits(ctx, 0, 0)
+                # sums of about 150 terms in FP64
+                assert np.abs(v - w).max() <= 1e-12 * np.abs(v).max()
+            a, b = np.zeros((len(F), 2)), np.zeros(len(F))
+            limits(ctx, 0, 1)
+            r = m.mskm_solve(ctx, hd, np.ascontiguousarray(F[:, :2]), a, o, nrhs=2)
+            limits(ctx, 0, 0)
+            assert r.status == m.MSKM_OK
+            for c in range(2):
+                assert m.mskm_solve(ctx, hd, np.ascontiguousarray(F[:, c]), b, o).status == m.MSKM_OK
+                assert np.array_equal(a[:, c], b)
+    finally:
+        m.mskm_hier_destroy(hd)
+        m.mskm_destroy(ctx)
