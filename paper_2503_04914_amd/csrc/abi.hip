@@ -34,15 +34,27 @@ using mskm::fail;
 
 namespace mskm {
 
-constexpr size_t kBlockCacheCap = (size_t)32 << 30;
+// Size class of a block: up to a multiple of an eighth of the next lower power of
+// two, so that blocks of similar sizes serve each other through the context's cache;
+// from kClassBytes on the size itself. Point sets of one size differ a little in
+// their entries: with exact sizes each pass on a new one allocated and freed all its
+// blocks once the cache was full, 4 to 85 ms a hierarchy of 250,000 points.
+constexpr size_t kClassBytes = (size_t)256 << 20;
+static size_t size_class(size_t bytes) {
+  if (bytes >= kClassBytes) return bytes;
+  size_t g = 256;
+  while (g * 16 <= bytes) g *= 2;
+  return (bytes + g - 1) / g * g;
+}
 
 mskm_status ctx_alloc(mskm_ctx* c, size_t bytes, void** out) {
   *out = nullptr;
+  bytes = size_class(bytes);
   if (c) {
     std::lock_guard<std::mutex> lock(c->cache_mu);
     auto it = c->cache.find(bytes);
     if (it != c->cache.end()) {
-      *out = it->second;
+      *out = it->second.p;
       c->cache_bytes -= bytes;
       c->cache.erase(it);
       return MSKM_OK;
@@ -64,21 +76,36 @@ mskm_status ctx_alloc(mskm_ctx* c, size_t bytes, void** out) {
 
 void ctx_release(mskm_ctx* c, void* p, size_t bytes) {
   if (!p) return;
-  if (c) {
+  bytes = size_class(bytes);
+  if (!c || bytes > c->cache_cap) {
+    (void)hipFree(p);
+    return;
+  }
+  std::vector<void*> old;
+  {
     std::lock_guard<std::mutex> lock(c->cache_mu);
-    if (c->cache_bytes + bytes <= kBlockCacheCap) {
-      c->cache.emplace(bytes, p);
-      c->cache_bytes += bytes;
-      return;
+    c->cache.emplace(bytes, mskm_ctx::Cached{p, ++c->cache_stamp});
+    c->cache_bytes += bytes;
+    while (c->cache_bytes > c->cache_cap) {
+      auto o = std::min_element(c->cache.begin(), c->cache.end(),
+                                [](const auto& a, const auto& b) { return a.second.stamp < b.second.stamp; });
+      old.push_back(o->second.p);
+      c->cache_bytes -= o->first;
+      c->cache.erase(o);
     }
   }
-  (void)hipFree(p);
+  for (void* q : old) (void)hipFree(q);
+}
+
+extern "C" uint64_t mskm_test_cache(mskm_ctx* c, uint64_t cap) {
+  if (cap) c->cache_cap = cap;
+  return c->cache_bytes;
 }
 
 void ctx_trim(mskm_ctx* c) {
   if (!c) return;
   std::lock_guard<std::mutex> lock(c->cache_mu);
-  for (auto& kv : c->cache) (void)hipFree(kv.second);
+  for (auto& kv : c->cache) (void)hipFree(kv.second.p);
   c->cache.clear();
   c->cache_bytes = 0;
   for (auto& kv : c->host_cache) (void)hipHostFree(kv.second);

@@ -237,16 +237,18 @@ static mskm_status build_plan(mskm_hier* h, CgGridPlan& P, bool bj, int lanes) {
   P.h_wg0[L] = (int32_t)lev.size();
   const size_t n = lev.size();
   if (n == 0) return MSKM_OK;
-  MSKM_TRY(halloc(h, &D.wg0, (size_t)L + 1));
-  MSKM_TRY(halloc(h, &D.lev, n));
-  MSKM_TRY(halloc(h, &D.row0, n));
-  MSKM_TRY(halloc(h, &D.nrow, n));
-  MSKM_TRY(halloc(h, &D.nhalo, n));
-  MSKM_TRY(halloc(h, &D.halo, n * kGridLocal));
-  MSKM_TRY(halloc(h, &D.lidx, n * kGridE * kGridThreads));
-  MSKM_TRY(halloc(h, &D.stats, 2 * (size_t)L));
   D.nslot = h->ctx->ncu;
-  MSKM_TRY(halloc(h, &D.slots, 3 * (size_t)D.nslot * kGridSlot));
+  Carve cv;
+  cv.add(&D.wg0, (size_t)L + 1);
+  cv.add(&D.lev, n);
+  cv.add(&D.row0, n);
+  cv.add(&D.nrow, n);
+  cv.add(&D.nhalo, n);
+  cv.add(&D.halo, n * kGridLocal);
+  cv.add(&D.lidx, n * kGridE * kGridThreads);
+  cv.add(&D.stats, 2 * (size_t)L);
+  cv.add(&D.slots, 3 * (size_t)D.nslot * kGridSlot);
+  MSKM_TRY(cv.alloc(h));
   hipStream_t s = h->ctx->stream;
   MSKM_TRY(upload_async(h, D.wg0, P.h_wg0.data(), P.h_wg0.size() * 4));
   MSKM_TRY(upload_async(h, D.lev, lev.data(), n * 4));

@@ -282,18 +282,17 @@ mskm_status build_stream(mskm_hier* h, CgStreamPlan& P, int depth, bool bj) {
   if (nwg == 0) return MSKM_OK;
   hipStream_t s = h->ctx->stream;
   int32_t** dst[4] = {&D.lev, &D.part, &D.wg0, &D.nw};
-  for (int k = 0; k < 4; ++k) {
-    MSKM_TRY(halloc(h, dst[k], nwg));
-    MSKM_TRY(upload_async(h, *dst[k], tab[k].data(), nwg * 4));
-  }
-  for (int32_t** v : {&D.row0, &D.nrow, &D.wbase, &D.wlen, &D.nchunk}) MSKM_TRY(halloc(h, v, nwg));
-  MSKM_TRY(halloc(h, &D.size, ns + 1));
-  MSKM_TRY(halloc(h, &D.soff, ns + 1));
-  MSKM_TRY(halloc(h, &D.flags, nwg * kStreamFlagWords));
-  MSKM_TRY(halloc(h, &D.chunk, nwg * kStreamChunks));
-  MSKM_TRY(halloc(h, &D.rank, nwg * kStreamChunks));
-  MSKM_TRY(halloc(h, &D.slots, 3 * nwg * kGridSlot));
-  MSKM_TRY(halloc(h, &D.stats, 6));
+  Carve cv;
+  for (int32_t** v : {&D.lev, &D.part, &D.wg0, &D.nw, &D.row0, &D.nrow, &D.wbase, &D.wlen, &D.nchunk}) cv.add(v, nwg);
+  cv.add(&D.size, ns + 1);
+  cv.add(&D.soff, ns + 1);
+  cv.add(&D.flags, nwg * kStreamFlagWords);
+  cv.add(&D.chunk, nwg * kStreamChunks);
+  cv.add(&D.rank, nwg * kStreamChunks);
+  cv.add(&D.slots, 3 * nwg * kGridSlot);
+  cv.add(&D.stats, 6);
+  MSKM_TRY(cv.alloc(h));
+  for (int k = 0; k < 4; ++k) MSKM_TRY(upload_async(h, *dst[k], tab[k].data(), nwg * 4));
   D.nwg = (int32_t)nwg;
   void* part = nullptr;
   const size_t part_bytes = (size_t)scan_parts((int64_t)ns + 1) * 8;
@@ -314,8 +313,10 @@ mskm_status build_stream(mskm_hier* h, CgStreamPlan& P, int depth, bool bj) {
   if (st[1] > kStreamWindow || st[2] > kStreamRt * kGridThreads) return MSKM_OK;
   hipLaunchKernelGGL(k_stream_flags, dim3((unsigned)ns), dim3(kBlock), 0, s, D, h->diag.rowptr, h->diag.col);
   hipLaunchKernelGGL(k_stream_chunks, dim3(D.nwg), dim3(kWave), 0, s, D);
-  MSKM_TRY(halloc(h, &D.val, (size_t)total));
-  MSKM_TRY(halloc(h, &D.idx, (size_t)total));
+  Carve entries;
+  entries.add(&D.val, (size_t)total);
+  entries.add(&D.idx, (size_t)total);
+  MSKM_TRY(entries.alloc(h));
   hipLaunchKernelGGL(k_stream_fill, dim3((unsigned)ns), dim3(kBlock), 0, s, D, h->diag.rowptr, h->diag.col,
                      h->diag.val32);
   MSKM_HIP_TRY(hipMemcpyAsync(st, D.stats, 24, hipMemcpyDeviceToHost, s));

@@ -229,12 +229,14 @@ mskm_status build_tiles(mskm_hier* h, const Csr& A, MrTiles& T, bool* ok) {
   MSKM_HIP_TRY(hipMemcpyAsync(&over, most, 4, hipMemcpyDeviceToHost, s));
   MSKM_HIP_TRY(hipStreamSynchronize(s));
   if (over) return MSKM_OK;
-  MSKM_TRY(halloc(h, &T.cols, (size_t)T.ncol));
-  MSKM_TRY(halloc(h, &T.eptr, (size_t)T.nseg + 1));
-  MSKM_TRY(halloc(h, &T.code, (size_t)T.nnz));
-  if (A.val) MSKM_TRY(halloc(h, &T.val, (size_t)T.nnz));
-  if (A.val32) MSKM_TRY(halloc(h, &T.val32, (size_t)T.nnz));
-  if (A.val32lo) MSKM_TRY(halloc(h, &T.lo, (size_t)T.nnz));
+  Carve tiles;
+  tiles.add(&T.cols, (size_t)T.ncol);
+  tiles.add(&T.eptr, (size_t)T.nseg + 1);
+  tiles.add(&T.code, (size_t)T.nnz);
+  if (A.val) tiles.add(&T.val, (size_t)T.nnz);
+  if (A.val32) tiles.add(&T.val32, (size_t)T.nnz);
+  if (A.val32lo) tiles.add(&T.lo, (size_t)T.nnz);
+  MSKM_TRY(tiles.alloc(h));
   hipLaunchKernelGGL(k_tile_fill, dim3((unsigned)T.ntile), dim3(kBlock), 0, s, wt, A.rowptr, A.col, A.val, A.val32,
                      A.val32lo, T);
   MSKM_HIP_TRY(hipGetLastError());

@@ -203,11 +203,17 @@ struct mskm_ctx {
   uint64_t limit_hier = 0, limit_scratch = 0;
   // device blocks of destroyed hierarchies, kept for the next allocation of
   // the same size (a hierarchy rebuilt with the same shape reuses all of
-  // them without hipMalloc); at most kBlockCacheCap bytes, freed by
-  // mskm_destroy or when an allocation would otherwise fail
+  // them without hipMalloc); at most cache_cap bytes, of which the longest
+  // unused go first; freed by mskm_destroy or when an allocation would
+  // otherwise fail
+  struct Cached {
+    void* p;
+    uint64_t stamp;  // when it was given back
+  };
   std::mutex cache_mu;
-  std::multimap<size_t, void*> cache;
-  size_t cache_bytes = 0;
+  std::multimap<size_t, Cached> cache;
+  size_t cache_bytes = 0, cache_cap = (size_t)32 << 30;
+  uint64_t cache_stamp = 0;
   std::multimap<size_t, void*> host_cache;  // pinned host blocks, likewise (solver workspaces)
 };
 
@@ -319,10 +325,11 @@ mskm_status fail(mskm_status st, const std::string& msg);
     if (_s < 0) return _s;          \
   } while (0)
 
-// Context block cache (abi.hip): a block of exactly `bytes` from the cache,
-// else hipMalloc (after emptying the cache if the first attempt fails).
+// Context block cache (abi.hip): a block of the size class of `bytes` from the
+// cache, else hipMalloc (after emptying the cache if the first attempt fails).
 mskm_status ctx_alloc(mskm_ctx* c, size_t bytes, void** out);
-// Gives a block back to the cache (hipFree beyond the cap or without a context).
+// Gives a block back to the cache, which frees the longest unused ones past its cap
+// (hipFree at once for a block beyond the cap, or without a context).
 void ctx_release(mskm_ctx* c, void* p, size_t bytes);
 // Frees every cached block.
 void ctx_trim(mskm_ctx* c);
@@ -391,6 +398,8 @@ struct Carve {
   }
   // one block from the context's cache for all pieces (given back by the caller)
   mskm_status alloc(mskm_ctx* c, void** base);
+  // one block of the hierarchy's for all pieces
+  mskm_status alloc(mskm_hier* h);
   void place(char* b) {
     size_t o = 0;
     for (auto& w : want) {
@@ -409,12 +418,13 @@ struct CtxScratch {
   size_t bytes;
   ~CtxScratch();
 };
+inline mskm_status Carve::alloc(mskm_hier* h) {
+  char* base = nullptr;
+  MSKM_TRY(halloc(h, &base, bytes));
+  place(base);
+  return MSKM_OK;
+}
 inline mskm_status Carve::alloc(mskm_ctx* c, void** base) {
-  // up to a multiple of an eighth of the next lower power of two, so that
-  // calls of similar sizes find each other's blocks
-  size_t g = 256;
-  while (g * 16 <= bytes) g *= 2;
-  bytes = (bytes + g - 1) / g * g;
   if (c->limit_scratch && bytes > c->limit_scratch) return fail(MSKM_ENOMEM, "the scratch test limit");
   MSKM_TRY(ctx_alloc(c, bytes, base));
   place(static_cast<char*>(*base));
@@ -459,6 +469,8 @@ void launch_bj_apply(mskm_hier* h, int lo, int hi, const TX* r, TX* u);
 extern "C" int64_t mskm_test_given_up(const mskm_ctx* c);
 extern "C" void mskm_test_spin(mskm_ctx* c, int spin);
 extern "C" void mskm_test_limits(mskm_ctx* c, uint64_t hier_bytes, uint64_t scratch_bytes);
+// Sets the cap of the context's block cache (0: as it is); returns the bytes it holds.
+extern "C" uint64_t mskm_test_cache(mskm_ctx* c, uint64_t cap);
 
 // Whether a solve that begins now goes without persistent launches: the GPU was too
 // busy for them a few solves ago (another process's kernels, which these waits

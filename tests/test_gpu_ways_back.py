@@ -171,3 +171,32 @@ def test_no_scratch_memory():
     finally:
         m.mskm_hier_destroy(hd)
         m.mskm_destroy(ctx)
+
+
+@pytest.mark.parametrize("cap", [1, 8 << 20, 32 << 30])
+def test_block_cache(cap):
+    """Hierarchies of changing sizes on a block cache of nothing, of less than one of them, and of the ordinary
+    size: the same coefficients, and no more bytes held than the cap."""
+    import paper_2503_04914_amd as m
+
+    cache = m.lib().mskm_test_cache
+    cache.argtypes, cache.restype = [ctypes.c_void_p, ctypes.c_uint64], ctypes.c_uint64
+    ctx = m.mskm_create(0)
+    first = {}
+    try:
+        cache(ctx, cap)
+        for n in (5000, 20011, 5000, 20480, 5003, 20011):
+            h = synth.halton_hierarchy(sizes=[n // 16, n // 4, n])
+            F = _targets(h, 2)
+            a, A = np.zeros(len(F)), np.zeros_like(F)
+            hd = m.mskm_hier_create(ctx, h.points, h.offsets, h.delta, fp64=False, fp32=True, sliced_lower=True)
+            assert m.mskm_solve(ctx, hd, np.ascontiguousarray(F[:, 0]), a, _opts(m, True)).status == m.MSKM_OK
+            assert m.mskm_solve(ctx, hd, F, A, _opts(m, True), nrhs=2).status == m.MSKM_OK
+            m.mskm_hier_destroy(hd)
+            held = cache(ctx, 0)
+            assert held <= cap and (held > 0 or cap == 1)
+            if n in first:
+                assert np.array_equal(a, first[n][0]) and np.array_equal(A, first[n][1])
+            first[n] = a, A
+    finally:
+        m.mskm_destroy(ctx)
