@@ -22,6 +22,19 @@ __device__ constexpr uint32_t kEmptyWord = 0x7fa4beefu;            // produces t
 // would wait for workgroups that cannot start.
 mskm_status cg_grid_in_turn(mskm_ctx* c, const std::function<void()>& launch);
 
+// Order in which a row's products are added, that of the product which the
+// launched kernels take for the same levels: an FP32 solve then rounds as they
+// do, element by element. Entry order; the two halves of the two-waves-per-slice
+// product (every other group of four); 4, 8 or 16 lanes' shares, lane i's being
+// entries i, i + 4, ....
+enum GridSum { kSumRow = 0, kSumHalves = 1, kSumLanes4 = 4, kSumLanes8 = 8, kSumLanes16 = 16 };
+
+// The order of the launched kernels for levels lo..hi (FP32; FP64 results do not
+// depend on it to the accuracy asked for). The products of the CSR copy with
+// other widths than its default of 8 lanes, which only an autotuned or chosen
+// product has, are taken for that one and differ in rounding.
+int launched_sum(const mskm_hier* h, int lo, int hi, bool fp32);
+
 // Empties z0, z1 (and z2) on the rows [r0, r0 + n) and ns slot words.
 template <typename TX>
 void grid_empty(hipStream_t s, TX* z0, TX* z1, TX* z2, int64_t r0, int64_t n, uint64_t* slots, int64_t ns);

@@ -354,13 +354,6 @@ struct GridCols {
   MrState* st;  // [L][ld], instead of the per-level states
 };
 
-// Order in which a row's products are added, that of the product which the
-// launched kernels take for the same levels: an FP32 solve then rounds as they
-// do, element by element. Entry order; the two halves of the two-waves-per-slice
-// product (every other group of four); 4, 8 or 16 lanes' shares, lane i's being
-// entries i, i + 4, ....
-enum GridSum { kSumRow = 0, kSumHalves = 1, kSumLanes4 = 4, kSumLanes8 = 8, kSumLanes16 = 16 };
-
 // Forms of the iteration. kFormPred: textbook with one exchange an iteration
 // (FP64 without preconditioner). kFormOneRed: single reduction (FP32, or
 // preconditioned). kFormText: textbook (columns of many right-hand sides, FP32 or
@@ -837,6 +830,17 @@ constexpr int kGridDevices = 64;
 GridOrder g_order[kGridDevices];
 }  // namespace
 
+int launched_sum(const mskm_hier* h, int lo, int hi, bool fp32) {
+  int64_t most = 0;
+  for (int l = lo; l <= hi; ++l) most = std::max<int64_t>(most, h->h_lev[l].n);
+  if (most <= kWgSolveRows) return most <= 64 ? kSumLanes16 : most <= 256 ? kSumLanes4 : kSumLanes8;
+  const int code = h->spmv_g[MSKM_OP_DIAG][fp32 ? 1 : 0];
+  if (code == kSellCode && h->sell.col16)
+    return h->h_off[hi + 1] - h->h_off[lo] <= kSplitProductRows ? kSumHalves : kSumRow;
+  if (code == kSellCode || code == kSell32Code) return kSumRow;
+  return kSumLanes8;
+}
+
 void cg_grid_forget(mskm_ctx* c) {
   if (c->device < 0 || c->device >= kGridDevices) return;
   GridOrder& o = g_order[c->device];
@@ -894,19 +898,9 @@ void grid_empty(hipStream_t s, TX* z0, TX* z1, TX* z2, int64_t r0, int64_t n, ui
 template void grid_empty<float>(hipStream_t, float*, float*, float*, int64_t, int64_t, uint64_t*, int64_t);
 template void grid_empty<double>(hipStream_t, double*, double*, double*, int64_t, int64_t, uint64_t*, int64_t);
 
-// The sum that the launched kernels of these levels make of a row's products
-// (FP32; FP64 results do not depend on it to the accuracy asked for).
+// The order that a form with `lanes` lanes a row has for these levels.
 static int grid_sum(const mskm_hier* h, int lo, int hi, int lanes, bool fp32) {
-  int64_t most = 0;
-  for (int l = lo; l <= hi; ++l) most = std::max<int64_t>(most, h->h_lev[l].n);
-  const int code = h->spmv_g[MSKM_OP_DIAG][fp32 ? 1 : 0];
-  int sum = kSumLanes8;  // the CSR product in 8 lanes; others differ in rounding
-  if (most <= kWgSolveRows)
-    sum = most <= 64 ? kSumLanes16 : most <= 256 ? kSumLanes4 : kSumLanes8;
-  else if (code == kSellCode && h->sell.col16)
-    sum = h->h_off[hi + 1] - h->h_off[lo] <= kSplitProductRows ? kSumHalves : kSumRow;
-  else if (code == kSellCode || code == kSell32Code)
-    sum = kSumRow;
+  const int sum = launched_sum(h, lo, hi, fp32);
   if (lanes == 2) return sum == kSumRow ? kSumHalves : sum;
   return sum == kSumRow || sum == kSumHalves ? sum : kSumLanes8;
 }

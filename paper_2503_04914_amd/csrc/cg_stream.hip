@@ -346,15 +346,14 @@ typedef unsigned short st_u4 __attribute__((ext_vector_type(4)));
 // kStreamRt slots of 512 rows, the first RES of them in registers (rows of at
 // most E entries). Thread t holds row 512 j + t in slot j. The single-reduction
 // form and the order of the launched kernels, so that a solve rounds as theirs
-// does, element by element: a row's products are added in entry order, or
-// (HALVES, where these take the two-waves-per-slice product) in two sums over
-// every other group of four entries.
-template <bool PC, int RES, int E, bool HALVES>
+// does, element by element: SUM is the order of a row's products (kSumRow,
+// kSumHalves or kSumLanes8), NA sums added in halves.
+template <bool PC, int RES, int E, int SUM>
 __global__ void __launch_bounds__(kGridThreads)
     k_cg_stream(const CgStreamDev P, int window, int rows, int ninv, int nl, int width, const float* __restrict__ b,
                 float* __restrict__ x, uint32_t* z0, uint32_t* z1, CgLevel* __restrict__ st, int32_t* aborted,
                 double rtol2, int maxit, int spin, const PcArgs<float> pc) {
-  constexpr int RT = kStreamRt;
+  constexpr int RT = kStreamRt, NA = SUM == kSumRow ? 1 : SUM == kSumHalves ? 2 : 8;
   extern __shared__ __align__(16) char lds[];
   float* const zw = reinterpret_cast<float*>(lds);                 // z on the kept runs of the window
   float* const rs = zw + (window + 3) / 4 * 4;                     // r, x of the own rows
@@ -504,48 +503,48 @@ __global__ void __launch_bounds__(kGridThreads)
     double a0 = 0.0, a1 = 0.0, a2 = 0.0;
 #pragma unroll
     for (int j = 0; j < RT; ++j) {
-      float acc = 0.0f, odd = 0.0f;
+      float acc[NA];  // entry k in number k % 8, (k / 4) % 2 or 0
+#pragma unroll
+      for (int u = 0; u < NA; ++u) acc[u] = 0.0f;
       if (j < RES) {
-        auto resident = [&](float& e, float& o) {  // groups of four into e and o in turn
 #pragma unroll
-          for (int k0 = 0; k0 < kE; k0 += 16) {
+        for (int k0 = 0; k0 < kE; k0 += 16) {
 #pragma unroll
-            for (int k = k0 / 2; k < k0 / 2 + 8; ++k) asm volatile("" : "+v"(ci[j < RES ? j : 0][k]));
+          for (int k = k0 / 2; k < k0 / 2 + 8; ++k) asm volatile("" : "+v"(ci[j < RES ? j : 0][k]));
 #pragma unroll
-            for (int k = k0; k < k0 + 16; ++k) {
-              const uint32_t c = ci[j < RES ? j : 0][k / 2];
-              float& d = k & 4 ? o : e;
-              d += v[j < RES ? j : 0][k] * zw[k & 1 ? c >> 16 : c & 0xffffu];
-            }
-            asm volatile("" ::: "memory");
+          for (int k = k0; k < k0 + 16; ++k) {
+            const uint32_t c = ci[j < RES ? j : 0][k / 2];
+            acc[NA == 8 ? k & 7 : NA == 2 ? (k >> 2) & 1 : 0] +=
+                v[j < RES ? j : 0][k] * zw[k & 1 ? c >> 16 : c & 0xffffu];
           }
-        };
-        resident(acc, HALVES ? odd : acc);
+          asm volatile("" ::: "memory");
+        }
       } else {
         const int q = (j - RES) * kStreamWaves + w;
         const int64_t o = so[j];
         const int len = (int)(so[j + 1] - o);
         const bool here = q < nl;  // kept in LDS
         auto streamed = [&](const float* pv, const uint16_t* px) {
-          auto group = [&](int d, float& to) {
+          auto group = [&](int d, auto odd) {
+            constexpr int o = decltype(odd)::value ? NA / 2 : 0, s = NA == 8 ? 1 : 0;
             const st_f4 f = *reinterpret_cast<const st_f4*>(pv + d);
             const st_u4 u = *reinterpret_cast<const st_u4*>(px + d);
-            to += f.x * zw[u.x];
-            to += f.y * zw[u.y];
-            to += f.z * zw[u.z];
-            to += f.w * zw[u.w];
+            acc[o] += f.x * zw[u.x];
+            acc[o + s] += f.y * zw[u.y];
+            acc[o + 2 * s] += f.z * zw[u.z];
+            acc[o + 3 * s] += f.w * zw[u.w];
           };
-          if constexpr (HALVES) {
-            int d = 0;
-#pragma unroll 2
+          if constexpr (NA > 1) {  // unrolled twice the preconditioned form takes 61 ms where it takes 42, the
+            int d = 0;             // other one 45 where once takes 53 (70,001 rows of 180 entries, 3,000 and 4,250 iterations)
+#pragma unroll (PC ? 1 : 2)
             for (; d + 4 * kWave < len; d += 8 * kWave) {
-              group(d, acc);
-              group(d + 4 * kWave, odd);
+              group(d, std::false_type{});
+              group(d + 4 * kWave, std::true_type{});
             }
-            if (d < len) group(d, acc);
+            if (d < len) group(d, std::false_type{});
           } else {
 #pragma unroll 4
-            for (int d = 0; d < len; d += 4 * kWave) group(d, acc);
+            for (int d = 0; d < len; d += 4 * kWave) group(d, std::false_type{});
           }
         };
         if (here)
@@ -553,12 +552,15 @@ __global__ void __launch_bounds__(kGridThreads)
         else
           streamed(P.val + o + 4 * lane, P.idx + o + 4 * lane);
       }
-      if constexpr (HALVES) acc += odd;
-      qv[j] = acc;
+#pragma unroll
+      for (int o = NA / 2; o > 0; o /= 2)
+#pragma unroll
+        for (int u = 0; u < o; ++u) acc[u] += acc[u + o];
+      qv[j] = acc[0];
       const int i = j * kGridThreads + t;
       if (i < nr) {
         const double zi = (double)zw[own + i], ri = (double)rs[i];
-        a0 += zi * (double)acc;
+        a0 += zi * (double)acc[0];
         a1 += zi * ri;
         a2 += ri * ri;
       }
@@ -666,36 +668,41 @@ mskm_status cg_stream_launch(mskm_hier* h, int depth, bool bj, const float* b, f
   const int64_t r0 = h->h_off[h->h_depth_begin[depth]], n = h->h_off[h->h_depth_begin[depth + 1]] - r0;
   grid_empty<float>(s, z0, z1, nullptr, r0, n, P.d.slots, (int64_t)3 * P.d.nwg * kGridSlot);
   const size_t lds = stream_lds(P);
-  // the launched kernels' product for these levels
-  const bool halves = h->spmv_g[MSKM_OP_DIAG][1] == kSellCode && h->sell.col16 && n <= kSplitProductRows;
+  const int sum = launched_sum(h, h->h_depth_begin[depth], h->h_depth_begin[depth + 1] - 1, true);
   hipError_t e = hipSuccess;
   const mskm_status r = cg_grid_in_turn(c, [&] {
-#define MSKM_STREAM(PCF, RES, EE, HH)                                                                                \
+#define MSKM_STREAM(PCF, RES, EE, SS)                                                                                \
   do {                                                                                                              \
-    auto* k = k_cg_stream<PCF, RES, EE, HH>;                                                                        \
+    auto* k = k_cg_stream<PCF, RES, EE, SS>;                                                                        \
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
     if (e == hipSuccess)                                                                                            \
       hipLaunchKernelGGL(k, dim3(P.d.nwg), dim3(kGridThreads), lds, s, P.d, P.window, P.rows, P.inv, P.nl, P.width, \
                          b, x, (uint32_t*)z0, (uint32_t*)z1, st, aborted, rtol2, maxit, c->grid_spin, pc);            \
   } while (0)
-// (two sums a row and 96 resident entries spill 100 registers)
-#define MSKM_STREAM_RES(PCF, HH)   \
-  do {                             \
-    if (P.width <= 48)             \
-      MSKM_STREAM(PCF, 2, 48, HH); \
-    else if (P.width <= 96 && !HH) \
-      MSKM_STREAM(PCF, 1, 96, HH); \
-    else                           \
-      MSKM_STREAM(PCF, 0, 16, HH); \
+// (two sums a row in turn and 96 resident entries spill 100 registers)
+#define MSKM_STREAM_RES(PCF, SS)                \
+  do {                                          \
+    if (P.width <= 48)                          \
+      MSKM_STREAM(PCF, 2, 48, SS);              \
+    else if (P.width <= 96 && SS != kSumHalves) \
+      MSKM_STREAM(PCF, 1, 96, SS);              \
+    else                                        \
+      MSKM_STREAM(PCF, 0, 16, SS);              \
   } while (0)
-    if (bj && halves)
-      MSKM_STREAM_RES(true, true);
-    else if (bj)
-      MSKM_STREAM_RES(true, false);
-    else if (halves)
-      MSKM_STREAM_RES(false, true);
+#define MSKM_STREAM_SUM(PCF)                   \
+  do {                                         \
+    if (sum == kSumRow)                        \
+      MSKM_STREAM_RES(PCF, kSumRow);           \
+    else if (sum == kSumHalves)                \
+      MSKM_STREAM_RES(PCF, kSumHalves);        \
+    else                                       \
+      MSKM_STREAM_RES(PCF, kSumLanes8);        \
+  } while (0)
+    if (bj)
+      MSKM_STREAM_SUM(true);
     else
-      MSKM_STREAM_RES(false, false);
+      MSKM_STREAM_SUM(false);
+#undef MSKM_STREAM_SUM
 #undef MSKM_STREAM_RES
 #undef MSKM_STREAM
   });

@@ -105,14 +105,15 @@ SIZES = {"one workgroup": [50, 250, 500, 1000], "two lanes a row": [257, 1030, 1
          "entry order": [900, 90003]}
 
 
+@pytest.mark.parametrize("sell", [True, False])  # the sliced product, or the default one of 8 lanes a row
 @pytest.mark.parametrize("bj", [True, False])
 @pytest.mark.parametrize("sizes", list(SIZES))
-def test_one_launch_rounds_as_launched(sizes, bj):
+def test_one_launch_rounds_as_launched(sizes, bj, sell):
     import paper_2503_04914_amd as m
 
     h = synth.halton_hierarchy(sizes=SIZES[sizes])
     pc = m.MSKM_PRECOND_BLOCK_JACOBI if bj else m.MSKM_PRECOND_NONE
-    (a, _, _), (b, _, _) = _one_launch_and_launched(h, 1, lambda m: _early(m, precond=pc), fp64=False, fp32=True)
+    (a, _, _), (b, _, _) = _one_launch_and_launched(h, 1, lambda m: _early(m, precond=pc), sell, fp64=False, fp32=True)
     _same_rounding(a, b)
 
 
@@ -188,14 +189,18 @@ def test_fp64_preconditioned_tolerance(n, nu, rtol, R):
         m.mskm_destroy(ctx)
 
 
+@pytest.mark.parametrize("sell", [True, False])
 @pytest.mark.parametrize("bj", [True, False])
-@pytest.mark.parametrize("case", ["halton", "uniform3d"])
-def test_large_levels_round_as_launched(case, bj):
-    """Levels whose matrix does not fit the registers."""
+@pytest.mark.parametrize("case", ["halton", "uniform3d", "wide rows", "few wide rows"])
+def test_large_levels_round_as_launched(case, bj, sell):
+    """Levels whose matrix does not fit the registers: many rows, and rows of about 180 entries on levels past and
+    below the rows (65,536) that the launched kernels split a row's sum in two for."""
     import paper_2503_04914_amd as m
 
-    h = synth.uniform3d_hierarchy(2, n0=20000) if case == "uniform3d" else \
-        synth.halton_hierarchy(sizes=[1000, 256 * 1024 + 77])
+    h = {"halton": lambda: synth.halton_hierarchy(sizes=[1000, 256 * 1024 + 77]),
+         "uniform3d": lambda: synth.uniform3d_hierarchy(2, n0=20000),
+         "wide rows": lambda: synth.halton_hierarchy(sizes=[5003, 70001], nu=7.5),
+         "few wide rows": lambda: synth.halton_hierarchy(sizes=[1025, 9001], nu=7.5)}[case]()
     pc = m.MSKM_PRECOND_BLOCK_JACOBI if bj else m.MSKM_PRECOND_NONE
-    (a, _, _), (b, _, _) = _one_launch_and_launched(h, 1, lambda m: _early(m, precond=pc), fp64=False, fp32=True)
+    (a, _, _), (b, _, _) = _one_launch_and_launched(h, 1, lambda m: _early(m, precond=pc), sell, fp64=False, fp32=True)
     _same_rounding(a, b)
