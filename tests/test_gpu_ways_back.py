@@ -143,9 +143,9 @@ def test_no_scratch_memory():
     import paper_2503_04914_amd as m
 
     _, _, limits = _hooks(m)
-    h = synth.halton_hierarchy(sizes=[300, 5003, 140001])
+    h = synth.halton_hierarchy(sizes=[300, 5003, 200001])
     F = _targets(h, 5)
-    q = synth.uniform01(5200, 0, 2 * 40000).reshape(-1, 2)  # as many as are sorted otherwise
+    q = synth.uniform01(5200, 0, 2 * 140001).reshape(-1, 2)  # as many points and queries as are sorted otherwise
     ctx = m.mskm_create(0)
     hd = m.mskm_hier_create(ctx, h.points, h.offsets, h.delta, fp64=True, fp32=True)
     o = _opts(m, True)
