@@ -368,8 +368,13 @@ constexpr int kSums = 4;  // kFormPred: p.q, r.r, q.r, q.q
 // entries. SOLO: every level has one workgroup, which exchanges nothing and takes
 // the sums from LDS.
 template <int G>
-__device__ __forceinline__ int grid_entry(int sum, int k, int g) {  // the lane's k-th entry of the row
-  return G == 2 && sum == kSumHalves ? (k >> 2) * 8 + 4 * g + (k & 3) : g + k * G;
+__device__ __forceinline__ int grid_entry(int sum, int k, int g, int len) {  // the lane's k-th entry of the row
+  if (G == 2 && sum == kSumHalves) return (k >> 2) * 8 + 4 * g + (k & 3);
+  if (G == 2 && sum == kSumRow) {  // the row's first half, the rest
+    const int h = (len + 1) / 2;
+    return g == 0 ? (k < h ? k : INT32_MAX) : h + k;
+  }
+  return g + k * G;
 }
 
 template <typename TX, bool PC, int G, int E, bool SOLO, int FORM>
@@ -421,7 +426,7 @@ __global__ void __launch_bounds__(kGridThreads)
     len = mine ? (int)(e - s) : 0;
 #pragma unroll
     for (int k = 0; k < E; ++k) {
-      const int q = grid_entry<G>(sum, k, g);
+      const int q = grid_entry<G>(sum, k, g, len);
       v[k] = q < len ? val[s + q] : (TX)0;
       const uint32_t c = q < len ? P.lidx[(size_t)wg * kGridE * kGridThreads + q * RW + i] : 0u;
       if (k & 1)
@@ -434,12 +439,12 @@ __global__ void __launch_bounds__(kGridThreads)
   int kmax = G == 2 && sum == kSumHalves ? (len + 7) / 8 * 4 : (len + G - 1) / G;
   for (int o = 32; o > 0; o >>= 1) kmax = max(kmax, __shfl_xor(kmax, o, kWave));
   kmax = __builtin_amdgcn_readfirstlane(kmax);
-  // the lane's products in NA accumulators, these added in halves
-  auto dot = [&](auto na, auto by_four) {
+  // the lane's products added to `from` in NA accumulators, these added in halves
+  auto dot = [&](auto na, auto by_four, TX from = 0) {
     constexpr int NA = decltype(na)::value;
     TX a[NA];
 #pragma unroll
-    for (int u = 0; u < NA; ++u) a[u] = 0;
+    for (int u = 0; u < NA; ++u) a[u] = u == 0 ? from : (TX)0;
 #pragma unroll
     for (int k0 = 0; k0 < E; k0 += 8)
       if (k0 < kmax) {
@@ -469,6 +474,11 @@ __global__ void __launch_bounds__(kGridThreads)
         q = dot(integral_constant<int, 8>{}, bool_constant<false>{});
       else
         q = dot(integral_constant<int, 1>{}, bool_constant<false>{});
+      if (sum == kSumRow) {  // the second lane goes on from the first one's sum
+        q = dot(integral_constant<int, 1>{}, bool_constant<false>{}, dpp<kDppXor1>(q));
+        const TX o = dpp<kDppXor1>(q);
+        return g ? q : o;
+      }
     } else {
       if (sum == kSumRow)
         q = dot(integral_constant<int, 1>{}, bool_constant<false>{});
@@ -901,7 +911,7 @@ template void grid_empty<double>(hipStream_t, double*, double*, double*, int64_t
 // The order that a form with `lanes` lanes a row has for these levels.
 static int grid_sum(const mskm_hier* h, int lo, int hi, int lanes, bool fp32) {
   const int sum = launched_sum(h, lo, hi, fp32);
-  if (lanes == 2) return sum == kSumRow ? kSumHalves : sum;
+  if (lanes == 2) return sum;
   return sum == kSumRow || sum == kSumHalves ? sum : kSumLanes8;
 }
 
@@ -914,7 +924,9 @@ static void grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, const 
   const CgGridPlan& P = static_cast<CgGrid*>(h->cg_grid)->plan[bj ? 1 : 0][lanes == 2 ? 0 : 1];
   const int w0 = P.h_wg0[lo];
   const bool solo = gc.nw == hi - lo + 1;
-  const int sum = FORM == kFormOneRed ? grid_sum(h, lo, hi, lanes, sizeof(TX) == 4) : kSumRow;
+  const int sum = FORM == kFormOneRed ? grid_sum(h, lo, hi, lanes, sizeof(TX) == 4)
+                  : FORM == kFormText ? kSumRow
+                                      : kSumLanes8;  // kFormPred: any
   int longest = 0;
   for (int l = lo; l <= hi; ++l) longest = std::max(longest, P.h_row[l]);
 #define MSKM_GRID_LAUNCH(PCF, GG, EE, SS)                                                                           \
@@ -939,14 +951,12 @@ static void grid_launch(mskm_hier* h, int lo, int hi, bool bj, int lanes, const 
     if constexpr (FORM == kFormPred || sizeof(TX) == 4)         \
       MSKM_GRID_SOLO(false, GG, EE);                            \
   } while (0)
-  if constexpr (FORM != kFormText) {  // whose rows are one lane's
-    if (lanes == 2) {
-      if (longest <= 64)
-        MSKM_GRID_FORM(2, 32);
-      else
-        MSKM_GRID_FORM(2, 64);
-      return;
-    }
+  if (lanes == 2) {
+    if (longest <= 64)
+      MSKM_GRID_FORM(2, 32);
+    else
+      MSKM_GRID_FORM(2, 64);
+    return;
   }
   if (longest <= 48)
     MSKM_GRID_FORM(1, 48);
@@ -1016,10 +1026,12 @@ mskm_status cg_grid_columns(mskm_hier* h, int lo, int hi, bool bj, const TX* val
                             int* how) {
   *how = 0;
   // the textbook form as the launched kernels have it, whose rows are added in
-  // entry order (one lane a row); FP64 without preconditioner as in cg_grid_launch
+  // entry order: one lane a row, or two, one after the other, for rows past 64
+  // entries; FP64 without preconditioner as in cg_grid_launch
   const bool text = bj || sizeof(TX) == 4;
   int lanes = 0;
   MSKM_TRY(cg_grid_ready(h, lo, hi, bj, &lanes, text ? 1 : 2));
+  if (text && lanes == 0) MSKM_TRY(cg_grid_ready(h, lo, hi, bj, &lanes));
   if (lanes == 0) return MSKM_OK;
   const CgGridPlan& P = static_cast<CgGrid*>(h->cg_grid)->plan[bj ? 1 : 0][lanes == 2 ? 0 : 1];
   const int nw = P.h_wg0[hi + 1] - P.h_wg0[lo], ncu = h->ctx->ncu;

@@ -639,7 +639,7 @@ mskm_status cg_stream_ready(mskm_hier* h, int lo, int hi, bool bj, int* depth) {
     if (h->h_lev[l].n <= 0) return MSKM_OK;
     most = std::max<int64_t>(most, h->h_lev[l].n);
   }
-  if (most <= kWgSolveRows) return MSKM_OK;  // one workgroup each (k_cg_level_wg)
+  if (most <= 256) return MSKM_OK;  // one workgroup each (k_cg_level_wg), whose order there this kernel does not have
   if (!h->cg_stream) {
     auto* p = new (std::nothrow) CgStream();
     if (!p) return MSKM_OK;

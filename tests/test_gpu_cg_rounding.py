@@ -118,10 +118,11 @@ def test_one_launch_rounds_as_launched(sizes, bj, sell):
 
 
 @pytest.mark.parametrize("bj", [True, False])
-def test_columns_round_as_launched(bj):
+@pytest.mark.parametrize("nu", [synth.NU_2D_40, 5.4])  # rows of about 40 and of 92 entries: one lane a row, two
+def test_columns_round_as_launched(nu, bj):
     import paper_2503_04914_amd as m
 
-    h = synth.halton_hierarchy(sizes=[257, 1030, 5003])
+    h = synth.halton_hierarchy(sizes=[257, 1030, 5003], nu=nu)
     pc = m.MSKM_PRECOND_BLOCK_JACOBI if bj else m.MSKM_PRECOND_NONE
     (a, _, _), (b, _, _) = _one_launch_and_launched(h, 21, lambda m: _early(m, precond=pc), fp64=False, fp32=True)
     _same_rounding(a, b)
@@ -191,16 +192,18 @@ def test_fp64_preconditioned_tolerance(n, nu, rtol, R):
 
 @pytest.mark.parametrize("sell", [True, False])
 @pytest.mark.parametrize("bj", [True, False])
-@pytest.mark.parametrize("case", ["halton", "uniform3d", "wide rows", "few wide rows"])
+@pytest.mark.parametrize("case", ["halton", "uniform3d", "wide rows", "few wide rows", "small wide levels"])
 def test_large_levels_round_as_launched(case, bj, sell):
     """Levels whose matrix does not fit the registers: many rows, and rows of about 180 entries on levels past and
-    below the rows (65,536) that the launched kernels split a row's sum in two for."""
+    below the rows (65,536) that the launched kernels split a row's sum in two for, and the rows (1,024) that they
+    solve in one workgroup."""
     import paper_2503_04914_amd as m
 
     h = {"halton": lambda: synth.halton_hierarchy(sizes=[1000, 256 * 1024 + 77]),
          "uniform3d": lambda: synth.uniform3d_hierarchy(2, n0=20000),
          "wide rows": lambda: synth.halton_hierarchy(sizes=[5003, 70001], nu=7.5),
-         "few wide rows": lambda: synth.halton_hierarchy(sizes=[1025, 9001], nu=7.5)}[case]()
+         "few wide rows": lambda: synth.halton_hierarchy(sizes=[1025, 9001], nu=7.5),
+         "small wide levels": lambda: synth.halton_hierarchy(sizes=[300, 900], nu=7.5)}[case]()
     pc = m.MSKM_PRECOND_BLOCK_JACOBI if bj else m.MSKM_PRECOND_NONE
     (a, _, _), (b, _, _) = _one_launch_and_launched(h, 1, lambda m: _early(m, precond=pc), sell, fp64=False, fp32=True)
     _same_rounding(a, b)
